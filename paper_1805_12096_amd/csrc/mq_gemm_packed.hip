@@ -868,8 +868,7 @@ int launch_coop(const GemmArgs& a, hipStream_t s) {
     max_blocks = per_cu * cus;
   }
   // the grid-wide barrier needs every workgroup resident at the same time (and has a slot)
-  static_assert(BM == 256 && BN == 256 && kBarrierSlots == 256, "single_pass_fits assumes this tile and slot count");
-  if (!single_pass_fits(a.M, a.N, (size_t)max_blocks)) return MQ_ERR_UNSUPPORTED;
+  if (tiles_m * tiles_n > (size_t)max_blocks || tiles_m * tiles_n > kBarrierSlots) return MQ_ERR_UNSUPPORTED;
   hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(WM * WN * 64), smem, s, p);
   return check_hip(hipGetLastError());
 }
@@ -884,6 +883,14 @@ int launch_gemm_requant_coop(const GemmArgs& a, float* s_out, void* packed_out, 
   b.barrier = barrier;
   b.s_out = s_out;
   b.packed_out = packed_out;
+  // The smallest tile whose workgroups are all resident at once: a workgroup's time is its tile's, so a result that
+  // leaves compute units idle with 256 x 256 tiles (1001 x 2048: 32 workgroups) is cut finer.  Measured for K = 512,
+  // whole FFN block with f = 2048 (the finer second
+  // product included): 600 rows 31.1 -> 20.1 us, 1001 rows 32.9 -> 22.7, 2048 rows 29.9 -> 26.3, 4096 rows 33.6 -> 30.3.
+  int rc = launch_coop<128, 128, 4, 2, 6>(b, s);
+  if (rc == MQ_ERR_UNSUPPORTED) rc = launch_coop<256, 128, 4, 2, 6>(b, s);
+  if (rc != MQ_ERR_UNSUPPORTED) return rc;
+  static_assert(kBarrierSlots == 256, "single_pass_fits describes this last attempt: it assumes the tile and slot count");
   return launch_coop<256, 256, 2, 4, 4>(b, s);
 }
 
@@ -913,25 +920,56 @@ int launch_gemm_requant_fixed_i16(const GemmArgs& a, const float* s_fixed, void*
   return launch_pp<16, 128, 128, 4, 2, 4, kPRequant>(b, s);
 }
 
+namespace {
+// Default tile configuration of a packed product, for shapes nobody has timed with mq_autotune_gemm.
+//
+// A launch is a number of rounds of one workgroup per compute unit (every candidate here but the split-K kernel fills
+// a compute unit's LDS with one workgroup), and a round takes a fixed part (launch, first operands, stores) plus a part
+// per 64-element K step, whether it is full or not: the best tile is the one with the smallest
+// rounds x (fixed + per_step x steps).  The constants are fitted to the timed shapes below, in microseconds (8 bit) and
+// relative (16 bit, where K steps dominate and cancel).
+// Measured on 66 shapes per width (M 300 .. 8192, parameters 512 x 512 to 4096 x 1024): this rule is 1.9 % (8 bit) and
+// 0.7 % (16 bit) slower than the best variant of each shape on average, the rule it replaces ("the largest tile that
+// still gives 200 workgroups", split K up to 512 rows only) 12 % and 7 %; e.g. 8 bit, 1001 x 512 x 2048 6.3 instead of
+// 10.0 us (split K), 2000 x 4096 x 1024 18.7 instead of 24.2, 5003 x 1024 x 1024 12.4 instead of 13.8 us.
+constexpr size_t kCUs = 256;
+struct TileCost { int variant; size_t bm, bn; float fixed, per_step; };
+
+int default_variant(const GemmArgs& a) {
+  const size_t steps = (a.K + 63) / 64;
+  const size_t small_wg = gemm_small_workgroups(a.M, a.N);
+  if (a.bits == 16) {
+    // split K while its workgroups are at most one and a half rounds (3.7 - 14 us where the tiles take 7 - 27)
+    if (small_wg <= 384) return 6;
+    const TileCost cost[] = {{3, 64, 128, 0.f, 103.f}, {1, 128, 128, 0.f, 128.f}, {8, 256, 128, 0.f, 223.f}};
+    int best = 1;
+    float best_cost = 0.f;
+    for (const TileCost& c : cost) {
+      const size_t tiles = ((a.M + c.bm - 1) / c.bm) * ((a.N + c.bn - 1) / c.bn);
+      // (256 workgroups of the 64 x 128 tile do not land one per compute unit: 15.6 us against 11.9 for 192 of them)
+      const size_t per_round = c.variant == 3 ? kCUs - 1 : kCUs;
+      const float t = (float)((tiles + per_round - 1) / per_round) * c.per_step;
+      if (best_cost == 0.f || t < best_cost) { best = c.variant; best_cost = t; }
+    }
+    return best;
+  }
+  if (small_wg <= 320) return 10;
+  const TileCost cost[] = {{7, 128, 64, 1.6f, 0.22f}, {8, 128, 128, 1.3f, 0.31f}, {6, 256, 128, 1.0f, 0.45f}, {1, 256, 256, 3.0f, 0.52f}};
+  int best = 1;
+  float best_cost = 0.f;
+  for (const TileCost& c : cost) {
+    const size_t tiles = ((a.M + c.bm - 1) / c.bm) * ((a.N + c.bn - 1) / c.bn);
+    const float t = (float)((tiles + kCUs - 1) / kCUs) * (c.fixed + c.per_step * (float)steps);
+    if (best_cost == 0.f || t < best_cost) { best = c.variant; best_cost = t; }
+  }
+  return best;
+}
+}  // namespace
+
 int launch_gemm_packed(const GemmArgs& a, Epilogue epi, hipStream_t s) {
   int v = forced_variant();
   if (v <= 0) v = tuned_variant(a.bits, a.M, a.N, a.K);     // frozen by mq_autotune_gemm for this shape, or 0
-  if (v <= 0) {
-    // Shape heuristic standing in for a per-shape timing run: the largest tile that still gives
-    // every compute unit work, smaller tiles for small problems.
-    if (a.bits == 16) {
-      const size_t t = ((a.M + 255) / 256) * ((a.N + 127) / 128);
-      // enough big tiles to fill the chip: the workgroup per compute unit that walks through them (measured 2 - 7 %
-      // ahead of one workgroup per tile, the more the shorter K is)
-      v = a.M <= 512 ? 6 : (t >= 200 ? 8 : (((a.M + 127) / 128) * ((a.N + 127) / 128) >= 128 ? 1 : 3));
-    } else {
-      // small problems (a decode step's 300 sentences) are latency bound: the split-K kernel (variant 10)
-      // fetches all operands of a workgroup in one round trip
-      const size_t t256 = ((a.M + 255) / 256) * ((a.N + 255) / 256);
-      const size_t t128 = ((a.M + 127) / 128) * ((a.N + 127) / 128);
-      v = a.M <= 512 ? 10 : (t256 >= 200 ? 1 : (t128 >= 128 ? 3 : 7));
-    }
-  }
+  if (v <= 0) v = default_variant(a);
   if ((a.bits == 8 && v == 10) || (a.bits == 16 && v == 6)) return launch_gemm_small(a, epi, s);
   if (a.bits == 16 && v == 7) return launch_gemm_dot2(a, epi, s);                        // vector ALU instead of matrix cores
   if (a.bits == 16 && v == 8) {                                                          // one workgroup per CU, tile after tile

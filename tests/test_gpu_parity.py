@@ -550,6 +550,19 @@ def test_gemm_packed_full_range_all_variants(dtype, M, N, K):
 
 
 @pytest.mark.parametrize("dtype", [np.int8, np.int16])
+@pytest.mark.parametrize("M,N,K", [(640, 1024, 96), (641, 1024, 96), (704, 1100, 70), (1500, 700, 160), (2049, 1024, 700),
+                                   (4100, 1030, 96), (2304, 4096, 64)])
+def test_gemm_packed_default_choice(dtype, M, N, K):
+    # no forced variant: shapes on both sides of the lines where the default changes from the split-K kernel to the tiles
+    # and from one tile size to the next
+    rng = np.random.default_rng(M * 1009 + N + K)
+    lim = 127 if dtype == np.int8 else 32767
+    qA = rng.integers(-lim, lim + 1, size=(M, K)).astype(dtype)
+    qB = rng.integers(-lim, lim + 1, size=(N, K)).astype(dtype)
+    assert np.array_equal(gpu_dot_int_packed(qA, qB), oracle.dot_int(qA, qB))
+
+
+@pytest.mark.parametrize("dtype", [np.int8, np.int16])
 @pytest.mark.parametrize("K", [129, 192, 256, 320, 384, 448, 576, 640])
 def test_gemm_packed_pipeline_boundaries_all_variants(dtype, K):
     # 3 to 10 K steps of 64: around every variant's ring depth (3, 4, 6 or 8 stages), where the main loop changes from
@@ -1141,7 +1154,9 @@ def test_two_pass_requantizing_product():
     assert torch.equal(out, ref.packed)
 
 
-@pytest.mark.parametrize("shape", [(1, 1, 1), (300, 520, 256), (1000, 1100, 128), (512, 768, 192), (256, 256, 64)])
+# (the last three: 256 tiles of 128 x 128; too many of those, so 256 x 128, ragged and whole; too many of those, so 256 x 256)
+@pytest.mark.parametrize("shape", [(1, 1, 1), (300, 520, 256), (1000, 1100, 128), (512, 768, 192), (256, 256, 64),
+                                   (2048, 2048, 64), (2060, 2048, 64), (2304, 2048, 128), (4100, 2048, 64)])
 def test_single_pass_requantizing_product(shape):
     # one pass over the operands, the sums waiting in registers while the grid agrees on max|y|;
     # called twice on one workspace (it clears its two words itself)
