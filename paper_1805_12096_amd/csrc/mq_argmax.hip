@@ -82,6 +82,24 @@ __device__ __forceinline__ size_t operand16_uniform_offset(const PackedDims& d, 
   return d.frag_offset(unit / 2, 2 * g) + (unit % 2) * 256;
 }
 
+// top = the BEAM largest of two descending lists, descending: the pairwise maxima of one list with the reversed other
+// are the largest BEAM in bitonic order, which half-cleaners sort (a third of the comparisons of inserting one by one).
+template <int BEAM>
+__device__ __forceinline__ void merge_sorted(unsigned long long (&top)[BEAM], const unsigned long long (&other)[BEAM]) {
+  static_assert(BEAM == 2 || BEAM == 4, "list lengths in use");
+#pragma unroll
+  for (int j = 0; j < BEAM; ++j) top[j] = top[j] > other[BEAM - 1 - j] ? top[j] : other[BEAM - 1 - j];
+#pragma unroll
+  for (int half = BEAM / 2; half >= 1; half /= 2)
+#pragma unroll
+    for (int j = 0; j < BEAM; ++j)
+      if ((j & half) == 0) {
+        const unsigned long long a = top[j], b = top[j + half];
+        top[j] = a > b ? a : b;
+        top[j + half] = a > b ? b : a;
+      }
+}
+
 // TPW: 16-sentence tiles per wave (8 * TPW * 16 >= M).
 // GATHER: candidates are the rows listed in p.shortlist (the lexical shortlist of Section 4.1: the
 // output product restricted to a subset of the vocabulary).  A unit is then 16 consecutive shortlist
@@ -89,8 +107,19 @@ __device__ __forceinline__ size_t operand16_uniform_offset(const PackedDims& d, 
 // rows costs nothing extra.  Indices are candidate positions; the reduce kernel maps them back.
 
 // BEAM > 1 (beam search, Table 2's b = 2 and b = 4 rows): every accumulator register keeps its BEAM best
-// keys instead of one (sorted insertion: BEAM max / min pairs per candidate), and every sentence tile keeps
-// a running (max, sum) of 2^(logit log2 e) so that the k best words come with normalised log-probabilities.
+// keys instead of one, and every sentence tile keeps a running (reference, sum) of 2^(logit log2 e - reference) so
+// that the k best words come with normalised log-probabilities.  This is bound by vector instructions (1200 rows
+// x 36 000 words are 675 000 wave-wide candidates), so a candidate costs as few as possible:
+//   * sorted insertion is one maximum and BEAM - 1 median-of-three instructions (the new second of a >= b with k
+//     arriving is med3(a, b, k), and so on down the list) instead of BEAM maximum / minimum pairs;
+//   * the reference of the sum moves only when a logit exceeds it by more than kNormSlack (a wave-uniform branch that
+//     is hardly ever taken after the first unit), so a candidate is one conversion, one multiply-add, one exponential
+//     and one addition, without rescaling the sum every four candidates;
+//   * every candidate of the stage before is worked off between two groups of matrix instructions of its own.
+// 1200 rows, k = 4, 36 000 words, with the quantizer and the reduce kernel: 84.7 us with maximum / minimum pairs, a
+// rescaled sum and every chunk of 256 rows spread over all compute units; 52.3 us with the above and the chunks sharing
+// them (launch_topk_stream); 48.3 us with sorted lists merged instead of inserted one by one at the end.  240 rows:
+// 29.1 -> 26.2 us.  What is left per unit: 0.27 us of LDS reads and waits, 0.13 of matrix instructions, 0.21 of these.
 template <int TPW, bool GATHER, int BEAM = 1>
 __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParams p_in) {
   ArgmaxParams p = p_in;
@@ -186,13 +215,13 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
   constexpr int kNone = (int)0x80000000;
   int best[TPW][4];
   int more_best[BEAM > 1 ? TPW : 1][4][BEAM > 1 ? BEAM - 1 : 1];     // places 2 .. BEAM of each register's list
-  float run_max[TPW], run_sum[TPW];                                    // softmax normaliser, base 2 (BEAM > 1)
+  float norm_ref[TPW], norm_sum[TPW];                                  // softmax normaliser, base 2 (BEAM > 1)
   float u2 = 0.f;
   if constexpr (BEAM > 1) u2 = __fmul_rn(__fdiv_rn(1.0f, __fmul_rn(*p.sA, *p.sW)), 1.44269504088896340736f);
 #pragma unroll
   for (int i = 0; i < TPW; ++i) {
-    run_max[i] = -INFINITY;
-    run_sum[i] = 0.f;
+    norm_ref[i] = -INFINITY;
+    norm_sum[i] = 0.f;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       best[i][r] = kNone;
@@ -201,31 +230,40 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
         for (int j = 0; j < BEAM - 1; ++j) more_best[i][r][j] = kNone;
     }
   }
-  // one sentence tile's four new sums (one stage): keys into the sorted lists, logits into the normaliser;
-  // valid[r] = false leaves candidate r out (padding past the last candidate)
-  auto beam_update = [&](int i, const v4i& sums, int tag, bool v0, bool v1, bool v2, bool v3) {
-    const bool valid[4] = {v0, v1, v2, v3};
-    float f[4];
+  auto med3 = [](int x, int y, int z) -> int { return max(min(x, y), min(max(x, y), z)); };    // v_med3_i32
+  // one candidate's key into the sorted list of its register
+  auto beam_insert = [&](int i, int r, int key) {
+    if constexpr (BEAM > 1) {
+#pragma unroll
+      for (int j = BEAM - 2; j > 0; --j) more_best[i][r][j] = med3(more_best[i][r][j - 1], more_best[i][r][j], key);
+      more_best[i][r][0] = med3(best[i][r], more_best[i][r][0], key);
+      best[i][r] = max(best[i][r], key);
+    }
+  };
+  // exponents (relative to the reference) of one sentence tile's four new sums; moves the reference first, in the
+  // lanes where one of them exceeds it by more than kNormSlack (and at the first unit, whose reference is -inf).
+  // valid: bit r clear leaves candidate r out (padding past the last candidate).
+  constexpr float kNormSlack = 16.0f;
+  auto beam_exponents = [&](int i, const v4i& sums, unsigned valid, float (&t)[4]) {
+    float c[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      int key = valid[r] ? ((sums[r] << 8) | (tag & 255)) : kNone;
-      const int t0 = max(best[i][r], key);
-      key = min(best[i][r], key);
-      best[i][r] = t0;
-#pragma unroll
-      for (int j = 0; j < BEAM - 1; ++j) {
-        const int t = max(more_best[i][r][j], key);
-        key = min(more_best[i][r][j], key);
-        more_best[i][r][j] = t;
-      }
-      f[r] = valid[r] ? __fmul_rn((float)sums[r], u2) : -INFINITY;
+      c[r] = (float)sums[r];
+      t[r] = (valid >> r) & 1u ? fmaf(c[r], u2, -norm_ref[i]) : -INFINITY;
     }
-    const float mnew = fmaxf(fmaxf(run_max[i], fmaxf(f[0], f[1])), fmaxf(f[2], f[3]));
-    if (mnew > -INFINITY) {          // (no valid candidate so far: nothing to add, and inf - inf is avoided)
-      run_sum[i] = run_sum[i] * __builtin_amdgcn_exp2f(run_max[i] - mnew) + __builtin_amdgcn_exp2f(f[0] - mnew) +
-                   __builtin_amdgcn_exp2f(f[1] - mnew) + __builtin_amdgcn_exp2f(f[2] - mnew) +
-                   __builtin_amdgcn_exp2f(f[3] - mnew);
-      run_max[i] = mnew;
+    float top = fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3]));
+    if (__any(top > kNormSlack)) {
+      if (top > kNormSlack) {
+        float ref = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if ((valid >> r) & 1u) ref = fmaxf(ref, __fmul_rn(c[r], u2));
+        norm_sum[i] *= __builtin_amdgcn_exp2f(norm_ref[i] - ref);      // 0 * 2^-inf at the first unit
+        norm_ref[i] = ref;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if ((valid >> r) & 1u) t[r] = fmaf(c[r], u2, -ref);
+      }
     }
   };
 
@@ -249,9 +287,11 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
   // maxima are updated from `prev` (the sums of the stage before) and the next unit is read from LDS
   // into `enext`.  The update's VALU work is cut into slices that sit between the MFMA groups, so it
   // runs while the matrix pipeline is busy instead of after it; the scheduling fences keep that order.
-  auto stage = [&](auto nt_tag, auto refill_tag, int newest, unsigned s, v4i (&cur)[TPW], const v4i (&prev)[TPW],
-                   const v4i (&e)[KG], v4i (&enext)[KG]) {
+  // first_tag: stage 0, which has no stage before it.
+  auto stage = [&](auto nt_tag, auto refill_tag, auto first_tag, int newest, unsigned s, v4i (&cur)[TPW],
+                   const v4i (&prev)[TPW], const v4i (&e)[KG], v4i (&enext)[KG]) {
     constexpr int NT = decltype(nt_tag)::value;
+    constexpr bool FIRST = decltype(first_tag)::value;
     land(newest);
     // everybody is past stage s - 1 (and has its copy of stage s in registers), so slot s - 1 can be refilled
     if constexpr (decltype(refill_tag)::value) issue(s + S - 1);
@@ -262,6 +302,7 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
     const int prev_tag = 256 - (int)s;          // 255 - (s - 1); unused garbage for s == 0 (prev holds "none")
     constexpr int ITEMS = NT * 4, PER = (ITEMS + KG - 1) / KG;
     const v4i zero = {0, 0, 0, 0};
+    float expo[TPW][4];      // beam search: exponents of the stage before, formed in the first group
 #pragma unroll
     for (int g = 0; g < KG; ++g) {
       enext[g] = as_v4i(*reinterpret_cast<const u4*>(nx + g * kFragBytes));
@@ -272,9 +313,16 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
 #pragma unroll
         for (int j = g * PER; j < (g + 1) * PER && j < ITEMS; ++j)
           best[j / 4][j % 4] = max(best[j / 4][j % 4], (prev[j / 4][j % 4] << 8) | (prev_tag & 255));
-      } else {
-        // one sentence tile of the stage before per MFMA group (stage 0 has no stage before it)
-        if (g < NT && s > 0) beam_update(g < TPW ? g : 0, prev[g < TPW ? g : 0], prev_tag, true, true, true, true);
+      } else if constexpr (!FIRST) {
+        if (g == 0) {
+#pragma unroll
+          for (int i = 0; i < NT; ++i) beam_exponents(i, prev[i], 15u, expo[i]);
+        }
+#pragma unroll
+        for (int j = g * PER; j < (g + 1) * PER && j < ITEMS; ++j) {
+          beam_insert(j / 4, j % 4, (prev[j / 4][j % 4] << 8) | (prev_tag & 255));
+          norm_sum[j / 4] += __builtin_amdgcn_exp2f(expo[j / 4][j % 4]);
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -314,13 +362,15 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
       for (int s = 0; s < S - 1; ++s) {
         if ((unsigned)s >= nlocal) break;
         const int newest = S - 3 - s > 0 ? S - 3 - s : 0;
-        if (s % 2 == 0) stage(nt_tag, std::false_type{}, newest, (unsigned)s, acc0, acc1, e0, e1);
-        else stage(nt_tag, std::false_type{}, newest, (unsigned)s, acc1, acc0, e1, e0);
+        if (s == 0) stage(nt_tag, std::false_type{}, std::true_type{}, newest, 0u, acc0, acc1, e0, e1);
+        else if (s % 2 == 0) stage(nt_tag, std::false_type{}, std::false_type{}, newest, (unsigned)s, acc0, acc1, e0, e1);
+        else stage(nt_tag, std::false_type{}, std::false_type{}, newest, (unsigned)s, acc1, acc0, e1, e0);
       }
     } else {
-      for (unsigned s = 0; s < nlocal; s += 2) {
-        stage(nt_tag, std::true_type{}, S - 3, s, acc0, acc1, e0, e1);
-        if (s + 1 < nlocal) stage(nt_tag, std::true_type{}, S - 3, s + 1, acc1, acc0, e1, e0);
+      stage(nt_tag, std::true_type{}, std::true_type{}, S - 3, 0u, acc0, acc1, e0, e1);
+      for (unsigned s = 1; s < nlocal; s += 2) {
+        stage(nt_tag, std::true_type{}, std::false_type{}, S - 3, s, acc1, acc0, e1, e0);
+        if (s + 1 < nlocal) stage(nt_tag, std::true_type{}, std::false_type{}, S - 3, s + 1, acc0, acc1, e0, e1);
       }
     }
   };
@@ -343,57 +393,66 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
           if (unit0 + r < p.L) best[i][r] = max(best[i][r], (v << 8) | tag);
         }
       } else {
-        if (i < ntl)
-          beam_update(i, (sl % 2 == 0) ? acc0[i] : acc1[i], tag, unit0 + 0 < p.L, unit0 + 1 < p.L, unit0 + 2 < p.L,
-                      unit0 + 3 < p.L);
+        if (i < ntl) {
+          unsigned valid = 0;
+          v4i sums;
+          float t[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            sums[r] = (sl % 2 == 0) ? acc0[i][r] : acc1[i][r];
+            valid |= unit0 + r < p.L ? 1u << r : 0u;
+          }
+          beam_exponents(i, sums, valid, t);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            beam_insert(i, r, (valid >> r) & 1u ? (sums[r] << 8) | tag : kNone);
+            norm_sum[i] += __builtin_amdgcn_exp2f(t[r]);
+          }
+        }
       }
     }
   }
 
   if constexpr (BEAM > 1) {
-    // Per sentence tile: decode the 4 x BEAM register keys into (sum, lowest index) keys, keep the BEAM best,
-    // merge with the three other lane groups that hold candidates of the same sentence, and write the list
-    // and the normaliser's (max, sum) pair.
-    auto decode = [&](int k32) -> unsigned long long {
+    // Per sentence tile: merge the four registers' sorted lists, still as (32-bit key, 3 - register) pairs (equal sums of
+    // one unit: the smaller register is the smaller index), decode the BEAM that are left into (sum, lowest index) keys,
+    // merge with the three other lane groups that hold candidates of the same sentence, and write the list and the
+    // normaliser's (reference, sum) pair.
+    auto decode = [&](unsigned long long k) -> unsigned long long {
+      const int k32 = (int)((unsigned)(k >> 32) ^ 0x80000000u);
       const int sum = k32 >> 8;
       if (sum == -8388608) return 0ull;
       const unsigned st = 255u - (unsigned)(k32 & 255);
-      const unsigned n = (first + st * stride) * 16 + 4 * (lane / 16);
+      const unsigned n = (first + st * stride) * 16 + 4 * (lane / 16) + (3u - (unsigned)k);
       return ((unsigned long long)((unsigned)sum ^ 0x80000000u) << 32) | (unsigned long long)(0xFFFFFFFFu - n);
-    };
-    auto insert = [&](unsigned long long (&top)[BEAM], unsigned long long k) {
-#pragma unroll
-      for (int j = 0; j < BEAM; ++j) {
-        const unsigned long long hi = top[j] > k ? top[j] : k;
-        k = top[j] > k ? k : top[j];
-        top[j] = hi;
-      }
     };
 #pragma unroll
     for (int i = 0; i < TPW; ++i) {
       unsigned long long top[BEAM];
 #pragma unroll
-      for (int j = 0; j < BEAM; ++j) top[j] = 0ull;
-#pragma unroll
       for (int r = 0; r < 4; ++r) {
-        unsigned long long k = decode(best[i][r]);
-        if (k != 0ull) k -= (unsigned)r;                       // candidate index 4 (l / 16) + r: larger index, smaller key
-        insert(top, k);
+        unsigned long long list[BEAM];
 #pragma unroll
-        for (int j = 0; j < BEAM - 1; ++j) {
-          unsigned long long k2 = decode(more_best[i][r][j]);
-          if (k2 != 0ull) k2 -= (unsigned)r;
-          insert(top, k2);
+        for (int j = 0; j < BEAM; ++j) {
+          const unsigned k32 = (unsigned)(j == 0 ? best[i][r] : more_best[i][r][j - 1]) ^ 0x80000000u;
+          list[j] = ((unsigned long long)k32 << 32) | (unsigned long long)(3 - r);
+        }
+        if (r == 0) {
+#pragma unroll
+          for (int j = 0; j < BEAM; ++j) top[j] = list[j];
+        } else {
+          merge_sorted(top, list);
         }
       }
-      float mx = run_max[i], sm = run_sum[i];
+#pragma unroll
+      for (int j = 0; j < BEAM; ++j) top[j] = decode(top[j]);
+      float mx = norm_ref[i], sm = norm_sum[i];
 #pragma unroll
       for (int off = 16; off <= 32; off *= 2) {
         unsigned long long other[BEAM];
 #pragma unroll
         for (int j = 0; j < BEAM; ++j) other[j] = __shfl_xor(top[j], off, 64);
-#pragma unroll
-        for (int j = 0; j < BEAM; ++j) insert(top, other[j]);
+        merge_sorted(top, other);
         const float omx = __shfl_xor(mx, off, 64), osm = __shfl_xor(sm, off, 64);
         const float m2 = fmaxf(mx, omx);
         if (m2 > -INFINITY) {
@@ -477,8 +536,15 @@ __global__ __launch_bounds__(256) void k_argmax_reduce(const unsigned long long*
   }
 }
 
-// Beam search: one wave per row.  Merges the per-workgroup lists into the k best (sum, lowest index) keys
-// and the per-workgroup (max, sum) pairs into log sum exp; writes tok [M x k] and logprob [M x k].
+// The value of another lane of the same row of 16 lanes, by a data-parallel-primitive move.
+template <int CTRL>
+__device__ __forceinline__ unsigned dpp16(unsigned x) {
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
+}
+
+// Beam search: 16 lanes per row, each takes every 16th workgroup's list and (reference, sum) pair; the lanes' lists are
+// merged inside their row of 16 lanes without LDS traffic (a whole wave per row spent 2.4 us in k rounds of six 64-bit
+// cross-lane exchanges).  Writes tok [M x k] and logprob [M x k].
 template <int BEAM>
 __global__ __launch_bounds__(256) void k_topk_reduce(const unsigned long long* __restrict__ partial,
                                                      const float2* __restrict__ norm, unsigned cols, unsigned M,
@@ -486,63 +552,64 @@ __global__ __launch_bounds__(256) void k_topk_reduce(const unsigned long long* _
                                                      const float* __restrict__ sW, int32_t* __restrict__ tok,
                                                      float* __restrict__ logprob,
                                                      const int32_t* __restrict__ shortlist) {
-  const int lane = threadIdx.x % 64;
-  const unsigned m = blockIdx.x * 4 + threadIdx.x / 64;
-  if (m >= M) return;
+  const unsigned sub = threadIdx.x % 16;
+  const unsigned row = blockIdx.x * 16 + threadIdx.x / 16;
+  const unsigned m = row < M ? row : M - 1;         // lanes past the end repeat the last row and write nothing
+  const float u = __fdiv_rn(1.0f, __fmul_rn(*sA, *sW));
   unsigned long long top[BEAM];
 #pragma unroll
   for (int j = 0; j < BEAM; ++j) top[j] = 0ull;
   float mx = -INFINITY, sm = 0.f;
-  for (unsigned g = lane; g < cols; g += 64) {
-    const size_t at = (size_t)m * cols + g;
-#pragma unroll
-    for (int j = 0; j < BEAM; ++j) {
-      unsigned long long key = partial[at * BEAM + j];
-#pragma unroll
-      for (int q = 0; q < BEAM; ++q) {
-        const unsigned long long hi = top[q] > key ? top[q] : key;
-        key = top[q] > key ? key : top[q];
-        top[q] = hi;
-      }
-    }
-    const float2 nm = norm[at];
-    const float m2 = fmaxf(mx, nm.x);
-    if (m2 > -INFINITY) {
-      sm = sm * __builtin_amdgcn_exp2f(mx - m2) + nm.y * __builtin_amdgcn_exp2f(nm.x - m2);
-      mx = m2;
-    }
-  }
-  // normaliser over the wave
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const float omx = __shfl_xor(mx, off, 64), osm = __shfl_xor(sm, off, 64);
+  auto join = [&](float omx, float osm) {
     const float m2 = fmaxf(mx, omx);
     if (m2 > -INFINITY) {
       sm = sm * __builtin_amdgcn_exp2f(mx - m2) + osm * __builtin_amdgcn_exp2f(omx - m2);
       mx = m2;
     }
+  };
+  for (unsigned g0 = sub; g0 < cols; g0 += 64) {
+    // up to four workgroups' lists in flight per lane (a slot past the end reads a valid list again, which adds nothing)
+    unsigned long long list[4][BEAM];
+    float2 nm[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const unsigned g = g0 + 16 * t < cols ? g0 + 16 * t : g0;
+      const size_t at = (size_t)m * cols + g;
+#pragma unroll
+      for (int j = 0; j < BEAM; ++j) list[t][j] = partial[at * BEAM + j];
+      nm[t] = norm[at];
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      if (g0 + 16 * t < cols) {
+        merge_sorted(top, list[t]);
+        join(nm[t].x, nm[t].y);
+      }
   }
-  const float u = __fdiv_rn(1.0f, __fmul_rn(*sA, *sW));
-  const float lse = (mx + __builtin_amdgcn_logf(sm)) * 0.693147180559945309417f;     // log2 -> natural log
-  // k rounds: the wave's best key wins, the lane that held it moves its list up
-  for (unsigned j = 0; j < k; ++j) {
+  auto exchange = [&](auto ctrl) {
+    constexpr int C = decltype(ctrl)::value;
+    unsigned long long other[BEAM];
+#pragma unroll
+    for (int j = 0; j < BEAM; ++j)
+      other[j] = ((unsigned long long)dpp16<C>((unsigned)(top[j] >> 32)) << 32) | dpp16<C>((unsigned)top[j]);
+    const float omx = __uint_as_float(dpp16<C>(__float_as_uint(mx))), osm = __uint_as_float(dpp16<C>(__float_as_uint(sm)));
+    merge_sorted(top, other);
+    join(omx, osm);
+  };
+  exchange(std::integral_constant<int, 0xB1>{});     // quad_perm [1,0,3,2]
+  exchange(std::integral_constant<int, 0x4E>{});     // quad_perm [2,3,0,1]
+  exchange(std::integral_constant<int, 0x141>{});    // row_half_mirror
+  exchange(std::integral_constant<int, 0x140>{});    // row_mirror
+  if (sub < k && row < M) {
+    const float lse = (mx + __builtin_amdgcn_logf(sm)) * 0.693147180559945309417f;     // log2 -> natural log
     unsigned long long w = top[0];
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      const unsigned long long o = __shfl_xor(w, off, 64);
-      if (o > w) w = o;
-    }
-    if (top[0] == w && w != 0ull) {      // keys are unique (the index is part of the key)
-#pragma unroll
-      for (int q = 0; q + 1 < BEAM; ++q) top[q] = top[q + 1];
-      top[BEAM - 1] = 0ull;
-    }
-    if (lane == 0) {
-      const int sum = (int)((unsigned)(w >> 32) ^ 0x80000000u);
-      const unsigned pos = 0xFFFFFFFFu - (unsigned)(w & 0xFFFFFFFFull);
-      tok[(size_t)m * k + j] = shortlist != nullptr ? shortlist[pos] : (int32_t)pos;
-      logprob[(size_t)m * k + j] = __fmul_rn((float)sum, u) - lse;
-    }
+    for (int j = 1; j < BEAM; ++j)
+      if (sub == (unsigned)j) w = top[j];
+    const int sum = (int)((unsigned)(w >> 32) ^ 0x80000000u);
+    const unsigned pos = 0xFFFFFFFFu - (unsigned)(w & 0xFFFFFFFFull);
+    tok[(size_t)m * k + sub] = shortlist != nullptr ? shortlist[pos] : (int32_t)pos;
+    logprob[(size_t)m * k + sub] = __fmul_rn((float)sum, u) - lse;
   }
 }
 
@@ -693,19 +760,24 @@ int launch_topk_stream(const void* packedA, const void* packedW, size_t M, size_
       cus = v;
   }
   const size_t units = shortlist != nullptr ? (shortlist_len + 15) / 16 : dW.nblocks * 2;
-  unsigned grid = (unsigned)(units < (size_t)cus ? units : (size_t)cus);
-  if (grid > 256u) grid = 256u;
-  if ((units + grid - 1) / grid > 255) return MQ_ERR_UNSUPPORTED;
   const int beam = k <= 2 ? 2 : 4;
   unsigned long long* keys = static_cast<unsigned long long*>(ws);
   float2* norm = reinterpret_cast<float2*>(static_cast<uint8_t*>(ws) +
                                            round_up((size_t)256 * M * beam * sizeof(unsigned long long), 256));
   // Rows go 256 to a workgroup (two sentence tiles per wave); all chunks run in ONE launch, the grid's y index picking
   // the chunk, and one reduce launch follows for all rows: a launch per chunk (ten for 1200 rows) cost more than the
-  // chunks' work.
+  // chunks' work.  The chunks share the compute units: a workgroup fills one (LDS), so with n chunks every chunk's
+  // vocabulary is cut over a n-th of them and a workgroup starts (hidden states into registers) and ends (lists merged
+  // and written) once instead of n times; at most 255 units each (the stage's place in a key).
   constexpr unsigned kChunkRows = 256;
   const unsigned nchunks = (unsigned)((M + kChunkRows - 1) / kChunkRows);
   if (nchunks > 65535u) return MQ_ERR_UNSUPPORTED;
+  const size_t share = (size_t)cus / nchunks > 0 ? (size_t)cus / nchunks : 1, least = (units + 254) / 255;
+  size_t columns = share > least ? share : least;
+  if (columns < 2) columns = 2;             // both units that can reach past N are then some workgroup's last
+  if (columns > 256) columns = 256;
+  const unsigned grid = (unsigned)(units < columns ? units : columns);
+  if ((units + grid - 1) / grid > 255) return MQ_ERR_UNSUPPORTED;
   ArgmaxParams p{};
   p.packedA = static_cast<const uint8_t*>(packedA);
   p.packedW = static_cast<const uint8_t*>(packedW);
@@ -726,10 +798,10 @@ int launch_topk_stream(const void* packedA, const void* packedW, size_t M, size_
   }
   if (rc != MQ_OK) return rc;
   if (beam == 2)
-    hipLaunchKernelGGL((k_topk_reduce<2>), dim3((unsigned)((M + 3) / 4)), dim3(256), 0, s, keys, norm, grid, (unsigned)M,
+    hipLaunchKernelGGL((k_topk_reduce<2>), dim3((unsigned)((M + 15) / 16)), dim3(256), 0, s, keys, norm, grid, (unsigned)M,
                        (unsigned)k, sA, sW, tok, logprob, shortlist);
   else
-    hipLaunchKernelGGL((k_topk_reduce<4>), dim3((unsigned)((M + 3) / 4)), dim3(256), 0, s, keys, norm, grid, (unsigned)M,
+    hipLaunchKernelGGL((k_topk_reduce<4>), dim3((unsigned)((M + 15) / 16)), dim3(256), 0, s, keys, norm, grid, (unsigned)M,
                        (unsigned)k, sA, sW, tok, logprob, shortlist);
   return check_hip(hipGetLastError());
 }

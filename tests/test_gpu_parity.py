@@ -1475,6 +1475,20 @@ def test_beam_output_layer_ties_and_crowded_lanes():
 
 
 @pytest.mark.parametrize("k", [2, 4])
+@pytest.mark.parametrize("M,V", [(520, 20000), (40, 9000)])
+def test_beam_output_layer_growing_logits(M, V, k):
+    # Embedding rows that grow with their index: later words exceed the running reference of the softmax normaliser
+    # again and again (by more than its slack of 2^16), in chunks of rows that share the compute units and alone.
+    # Logits reach about 60: one binary32 rounding of such a logit is 4e-6, a sum of V terms stays below 1e-4.
+    c = workloads.config3(M=M, V=V, d=64, seed_extra=31 + k)
+    E = np.ascontiguousarray(c["E"] * (30.0 * np.arange(V) / V)[:, None]).astype(np.float32)
+    o = oracle.topk_log_softmax(c["Hd"], E, k)
+    tok, lp = gpu_topk(c["Hd"], E, k)
+    assert np.array_equal(tok, o["tok"])
+    assert np.allclose(lp, o["logprob"], rtol=0, atol=1e-4)
+
+
+@pytest.mark.parametrize("k", [2, 4])
 @pytest.mark.parametrize("V,L", [(9000, 1234), (120000, 60000)])     # the longer list refills the ring's slots
 def test_beam_output_layer_with_shortlist(k, V, L):
     c = workloads.config3(M=64, V=V, d=128 if V < 10000 else 32, seed_extra=77)
