@@ -340,8 +340,8 @@ int mq_gemm_argmax(const void* qA, const void* packedW, size_t M, size_t N, size
 /* The same with the hidden states packed by mq_quantize_pack_f32 (8 bit): the
  * decode-step kernel.  The hidden states sit in registers, the embedding
  * streams through LDS exactly once, each block reports one candidate per
- * sentence and a second small kernel picks the winners.  Rows are processed
- * 384 at a time (the embedding streams once per pass).  Serves K <= 512
+ * sentence and a second small kernel picks the winners.  Rows go up to 384 to
+ * a chunk (the embedding streams once per chunk).  Serves K <= 512
  * (MQ_ERR_UNSUPPORTED beyond; use mq_gemm_argmax there).  Same results, same
  * workspace query. */
 int mq_gemm_argmax_packed(const void* packedA, const void* packedW, size_t M, size_t N, size_t K,

@@ -507,7 +507,8 @@ int mq_gemm_argmax_packed(const void* packedA, const void* packedW, size_t M, si
     return MQ_ERR_ALIGN;
   if (ws_bytes < mq_argmax_ws_bytes(M, N)) return MQ_ERR_WORKSPACE;
   if (!argmax_stream_supported(M, N, K)) return MQ_ERR_UNSUPPORTED;
-  return launch_argmax_stream(packedA, packedW, M, N, K, sA, sW, tok, maxlogit, ws, nullptr, 0, as_stream(stream));
+  return launch_argmax_stream(packedA, packedW, M, N, K, sA, sW, tok, maxlogit, ws, mq_argmax_ws_bytes(M, N), nullptr, 0,
+                              as_stream(stream));
 }
 
 int mq_gemm_argmax_packed_static(const void* packedA, const void* packedW, size_t M, size_t N, size_t K,
@@ -536,8 +537,8 @@ int mq_gemm_argmax_shortlist(const void* packedA, const void* packedW, const int
     return MQ_ERR_ALIGN;
   if (ws_bytes < mq_argmax_ws_bytes(M, N)) return MQ_ERR_WORKSPACE;
   if (!argmax_stream_supported(M, N, K)) return MQ_ERR_UNSUPPORTED;
-  return launch_argmax_stream(packedA, packedW, M, N, K, sA, sW, tok, maxlogit, ws, shortlist, shortlist_len,
-                              as_stream(stream));
+  return launch_argmax_stream(packedA, packedW, M, N, K, sA, sW, tok, maxlogit, ws, mq_argmax_ws_bytes(M, N), shortlist,
+                              shortlist_len, as_stream(stream));
 }
 
 size_t mq_topk_ws_bytes(size_t M, size_t N, int k) {
@@ -574,6 +575,9 @@ int mq_gemm_argmax(const void* qA, const void* packedW, size_t M, size_t N, size
     return MQ_ERR_ALIGN;
   if (ws_bytes < mq_argmax_ws_bytes(M, N)) return MQ_ERR_WORKSPACE;
   hipStream_t s = as_stream(stream);
+  // widths up to 1024 in whole 16-byte pieces: the streaming kernel (two launches, no atomics), see mq_argmax.hip
+  if (argmax_stream_rows_supported(N, K))
+    return launch_argmax_stream_rows(qA, packedW, M, N, K, sA, sW, tok, maxlogit, ws, mq_argmax_ws_bytes(M, N), s);
   unsigned long long* keys = static_cast<unsigned long long*>(ws);
   rc = launch_argmax_init(keys, M, s);
   if (rc != MQ_OK) return rc;

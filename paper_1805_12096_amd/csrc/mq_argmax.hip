@@ -13,15 +13,17 @@
 //     candidate words for ONE sentence (l % 16), so the running maxima are
 //     plain per-lane registers and nothing crosses lanes until the very end;
 //   * the quantized hidden states (M x K, a few 100 KB) are loaded once per
-//     workgroup into REGISTERS as operand fragments, split over the four waves
-//     by 16-sentence tile;
+//     workgroup into REGISTERS as operand fragments, split over the eight waves
+//     by 16-sentence tile; more sentences than that go in chunks (the grid's y
+//     index) that share the compute units;
 //   * the packed embedding streams through LDS with direct-to-LDS loads: each
 //     load instruction gathers, for one 64-element K group, the 16 rows of the
 //     unit out of two 32-row fragments, so that LDS receives exactly the
 //     operand image (lane l at byte 16 l); many stages are in flight;
 //   * sums of 8-bit products over K <= 512 stay below 2^23, so (sum << 8 |
 //     255 - stage) is a 32-bit key whose integer maximum is the arg-max with
-//     the earliest stage winning ties: two VALU operations per candidate;
+//     the earliest stage winning ties: two VALU operations per candidate
+//     (K <= 1024: below 2^24, one bit less for the stage);
 //   * every workgroup writes one 64-bit (sum, index) key per sentence, its own
 //     run of consecutive keys; a second small kernel reduces them and decodes.
 //     No atomics, no initialisation.  (Folding that reduction into this kernel
@@ -41,7 +43,14 @@ namespace {
 
 constexpr int kWaves = 8;             // two per SIMD: one wave's waits hide behind the other's MFMAs
 constexpr int kKG = 8;                // 64-element K groups per unit (K <= 512)
-constexpr int kStages = 10;           // 80 KB of LDS, 8 stages in flight
+constexpr int kWideKG = 16;           // the same for K <= 1024
+constexpr int kMaxTPW = 3;            // 16-sentence tiles per wave that fit the registers at K <= 512
+constexpr int kWideTPW = 2;           // and at K <= 1024
+constexpr int kBeamTPW = 2;           // and in beam search
+constexpr int stages_of(int kg) { return kg == kKG ? 10 : 18; }            // ring slots of 8 KB: all but two in flight
+// key of a candidate: sum << shift | (mask - stage)
+constexpr int shift_of(int kg) { return kg == kKG ? 8 : 7; }
+constexpr unsigned max_units_of(int kg) { return (1u << shift_of(kg)) - 1; }  // units per workgroup
 constexpr int kMaxBlocks = 1024;      // upper bound on workgroups (columns of the partials array)
 
 __device__ __forceinline__ void wait_vmcnt_n(int n) {
@@ -55,7 +64,7 @@ __device__ __forceinline__ void wait_vmcnt_n(int n) {
 }
 
 struct ArgmaxParams {
-  const uint8_t* packedA;   // hidden states, packed 8 bit [M x K]
+  const uint8_t* packedA;   // hidden states, packed 8 bit [M x K] (or, ROWM, plain rows of K bytes)
   const uint8_t* packedW;   // embedding, packed 8 bit [N x K]
   unsigned M, N, K;
   unsigned long long* partial;   // BEAM == 1: [gridDim.x][Mpad], Mpad = M rounded up to 16; beam search: [M][gridDim.x][BEAM]
@@ -66,9 +75,9 @@ struct ArgmaxParams {
   float2* norm;
   const float* sA;
   const float* sW;
-  // beam search with more rows than one workgroup's registers hold: the grid's y index picks a chunk of chunk_rows
-  // rows out of Mtotal (M, packedA, partial and norm above then describe the whole problem); 0 = M is the chunk
-  unsigned chunk_rows, Mtotal;
+  // more rows than one workgroup's registers hold: the grid's y index picks a chunk of chunk_rows rows (a multiple of
+  // 16) out of M; everything above describes all rows of the launch
+  unsigned chunk_rows;
 };
 
 // What lane l feeds to the 16x16x64 MFMA for rows 16 u .. 16 u + 15 of a packed
@@ -120,35 +129,35 @@ __device__ __forceinline__ void merge_sorted(unsigned long long (&top)[BEAM], co
 // rescaled sum and every chunk of 256 rows spread over all compute units; 52.3 us with the above and the chunks sharing
 // them (launch_topk_stream); 48.3 us with sorted lists merged instead of inserted one by one at the end.  240 rows:
 // 29.1 -> 26.2 us.  What is left per unit: 0.27 us of LDS reads and waits, 0.13 of matrix instructions, 0.21 of these.
-template <int TPW, bool GATHER, int BEAM = 1>
-__global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParams p_in) {
-  ArgmaxParams p = p_in;
-  if (BEAM > 1 && p_in.chunk_rows != 0) {
-    // this workgroup's chunk of rows: the keys and normalisers are laid out by row, so a chunk's share starts at its
-    // first row, and so do its packed hidden states (chunks are whole 32-row blocks)
-    const unsigned row0 = blockIdx.y * p_in.chunk_rows;
-    p.M = p_in.Mtotal - row0 < p_in.chunk_rows ? p_in.Mtotal - row0 : p_in.chunk_rows;
-    p.packedA = p_in.packedA + PackedDims(8, p_in.Mtotal, p_in.K).frag_offset(row0 / 32, 0);
-    p.partial = p_in.partial + (size_t)row0 * gridDim.x * BEAM;
-    p.norm = p_in.norm + (size_t)row0 * gridDim.x;
-  }
-  constexpr int KG = kKG, S = kStages;
-  constexpr int STAGE = KG * kFragBytes;
-  static_assert(KG == kWaves, "one direct-to-LDS load per wave and stage");
+// Greedy, 36 000 words, kernels of a captured step (quantizer included): 300 sentences of width 512 17.6 -> 16.9 us (the
+// 19th of 24 tile slots' operands no longer fetched for nothing, reduce kernel), 600 sentences against 50 000 words 34.8
+// -> 24.9 us (chunks that share the compute units instead of one launch pair after the other), 300 sentences of width
+// 1024 41.9 -> 31.3 us (the tiled kernel's arg-max epilogue took 32.7 us of them, this one 20).
+// KG: 64-element K groups held (8: K <= 512, 16: K <= 1024).  ROWM: the hidden states are plain rows (K a multiple of
+// 16) instead of packed ones; only the addresses of the operand loads differ.
+template <int TPW, bool GATHER, int BEAM = 1, int KG = kKG, bool ROWM = false>
+__global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParams p) {
+  constexpr int S = stages_of(KG);
+  constexpr int NH = KG / kKG;                        // stages per unit: 512 elements of K each
+  constexpr int STAGE = kKG * kFragBytes;
+  constexpr int SHIFT = shift_of(KG), TAGS = (1 << SHIFT) - 1;
+  static_assert(kKG == kWaves, "one direct-to-LDS load per wave and stage");
+  static_assert(KG % kKG == 0 && (NH == 1 || S % NH == 0), "stages of a unit");
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
 
   const int lane = threadIdx.x % 64;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const unsigned row0 = blockIdx.y * p.chunk_rows;    // this workgroup's rows: row0 .. row0 + rows - 1
+  const unsigned rows = p.M - row0 < p.chunk_rows ? p.M - row0 : p.chunk_rows;
   const PackedDims dA(8, p.M, p.K), dW(8, p.N, p.K);
   const unsigned kgroups = (unsigned)(dW.kfrags / 2);          // real K groups (<= KG)
   const unsigned nunits = GATHER ? (p.L + 15) / 16 : (unsigned)(dW.nblocks * 2);   // 16-candidate units
   const unsigned first = blockIdx.x, stride = gridDim.x;
-  const unsigned nlocal = first < nunits ? (nunits - first + stride - 1) / stride : 0;
+  const unsigned nlocal = (nunits - first + stride - 1) / stride;      // the grid has at most nunits columns: at least 1
   const unsigned lane_off = operand16_lane_offset(lane);
 
-  // stage s of the pipeline = this workgroup's s-th unit, all of K; wave w copies K group w
-  // (K shorter than 512: a real group is copied again and its products are zeroed through `hid`)
-  const unsigned my_group = (unsigned)wave < kgroups ? (unsigned)wave : kgroups - 1;
+  // stage s of the pipeline = 512 elements of K (part s % NH) of this workgroup's (s / NH)-th unit; wave w copies the
+  // part's K group w (K shorter than 64 KG: a real group is copied again and its products are zeroed through `hid`)
   const uint8_t* src_lane = p.packedW + lane_off;
   // GATHER: this workgroup's candidate rows, 16 per stage, are fetched into LDS once, before any
   // direct-to-LDS load is in flight (later ordinary loads would have to drain the pipeline)
@@ -167,16 +176,17 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
   // per-wave slot behind the stages that nobody reads: every stage then issues exactly one load, the number of loads
   // in flight at a given point is a constant, and the waits need neither a branch nor a table.  Needs nlocal > 0.
   auto issue = [&](unsigned s_any) {
-    const bool real = s_any < nlocal;
+    const bool real = s_any < nlocal * NH;
     const unsigned s = real ? s_any : 0;
+    const unsigned unit = s / NH, g = (s % NH) * kKG + wave, my_group = g < kgroups ? g : kgroups - 1;
     uint8_t* dst = real ? smem + (s % S) * STAGE + wave * kFragBytes : smem + S * STAGE + wave * kFragBytes;
     const uint8_t* src;
     if (GATHER) {
-      const unsigned r = (unsigned)rows_lds[s * 16 + lane % 16];
+      const unsigned r = (unsigned)rows_lds[unit * 16 + lane % 16];
       src = p.packedW + dW.frag_offset(r / 32, 2 * my_group + lane / 32) +
             (size_t)((r % 32) + 32 * ((lane / 16) % 2)) * 16;
     } else {
-      src = src_lane + operand16_uniform_offset(dW, (size_t)first + (size_t)s * stride, my_group);
+      src = src_lane + operand16_uniform_offset(dW, (size_t)first + (size_t)unit * stride, my_group);
     }
     __builtin_amdgcn_global_load_lds(
         (const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
@@ -185,37 +195,21 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
   // hidden-state operands of this wave's sentence tiles (tile t = wave + 8 i covers sentences 16 t ..
   // 16 t + 15; they come from L2, every workgroup reads the same ones), then the remaining stages.  The
   // memory counter retires loads in order, so waiting for "all but the newest n" later covers stages 0
-  // and 1 and the operands while the newer stages are still on their way.  The operand loads are written
-  // as instructions so that the waiting is ours: the compiler would wait for ALL outstanding loads, the
-  // whole pipeline included, at the first use.
+  // and 1 and the operands while the newer stages are still on their way.
   constexpr int kEarly = 2;
 #pragma unroll
-  for (int s = 0; s < kEarly; ++s)
-    if (nlocal > 0) issue(s);
-  v4i hid[TPW][KG];
-  const size_t tiles_avail = dA.nblocks * 2;
-  // 16-sentence tiles this wave really owns (a slot beyond them would only repeat a tile): TPW or TPW - 1
-  const int ntl = (size_t)wave < tiles_avail ? (int)((tiles_avail - 1 - wave) / kWaves) + 1 : 0;
-#pragma unroll
-  for (int i = 0; i < TPW; ++i) {
-    size_t t = (size_t)wave + kWaves * i;
-    if (t >= tiles_avail) t = tiles_avail - 1;   // slot past the end: a copy, never multiplied, never written out
-#pragma unroll
-    for (int g = 0; g < KG; ++g) {
-      const uint8_t* src = p.packedA + lane_off + operand16_uniform_offset(dA, t, (unsigned)g < kgroups ? g : 0);
-      asm volatile("global_load_dwordx4 %0, %1, off" : "=&v"(hid[i][g]) : "v"(src) : "memory");
-    }
-  }
-#pragma unroll
-  for (int s = kEarly; s < S - 1; ++s)
-    if (nlocal > 0) issue(s);
+  for (int s = 0; s < kEarly; ++s) issue(s);
+  // 16-sentence tiles this wave owns
+  const unsigned tiles_avail = (rows + 15) / 16;
+  const int ntl = (unsigned)wave < tiles_avail ? (int)((tiles_avail - 1 - wave) / kWaves) + 1 : 0;
 
-  // running maxima, one per accumulator register: (sum << 8) | (255 - stage).  Real sums exceed
-  // -2^23, so a key whose sum field is -2^23 means "no candidate yet".
+  // running maxima, one per accumulator register: (sum << SHIFT) | (TAGS - stage).  Real sums exceed
+  // -2^(31 - SHIFT), so a key whose sum field is that means "no candidate yet".
   constexpr int kNone = (int)0x80000000;
+  constexpr int kNoSum = -(1 << (31 - SHIFT));
   int best[TPW][4];
   int more_best[BEAM > 1 ? TPW : 1][4][BEAM > 1 ? BEAM - 1 : 1];     // places 2 .. BEAM of each register's list
-  float norm_ref[TPW], norm_sum[TPW];                                  // softmax normaliser, base 2 (BEAM > 1)
+  float norm_ref[TPW], norm_sum[TPW], norm_expo[TPW][4];               // softmax normaliser, base 2 (BEAM > 1)
   float u2 = 0.f;
   if constexpr (BEAM > 1) u2 = __fmul_rn(__fdiv_rn(1.0f, __fmul_rn(*p.sA, *p.sW)), 1.44269504088896340736f);
 #pragma unroll
@@ -229,6 +223,12 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
 #pragma unroll
         for (int j = 0; j < BEAM - 1; ++j) more_best[i][r][j] = kNone;
     }
+  }
+  v4i acc0[TPW], acc1[TPW];             // sums of even and odd units
+#pragma unroll
+  for (int i = 0; i < TPW; ++i) {
+    acc0[i] = v4i{kNoSum, kNoSum, kNoSum, kNoSum};
+    acc1[i] = v4i{kNoSum, kNoSum, kNoSum, kNoSum};           // "none" for unit 0's update
   }
   auto med3 = [](int x, int y, int z) -> int { return max(min(x, y), min(max(x, y), z)); };    // v_med3_i32
   // one candidate's key into the sorted list of its register
@@ -271,126 +271,165 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
   // registers while s is multiplied): of the loads issued so far the oldest s + 2 are needed, `newest` may be
   // outstanding.  With a load in every stage S - 1 + s have been issued (newest = S - 3); without, S - 1
   // (newest = S - 3 - s).
+  // This wave's LDS reads of stage s have returned, too: the compiler would otherwise wait for ALL outstanding reads,
+  // the first ones of stage s + 1 included, before the stage's first matrix instructions.
   auto land = [&](int newest) {
     wait_vmcnt_n(newest);
+    __builtin_amdgcn_s_waitcnt(0xC07F);                // lgkmcnt(0)
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
-  auto read_stage = [&](unsigned s, v4i (&e)[KG]) {
-    const uint8_t* st = smem + (s % S) * STAGE + lane * 16;
-#pragma unroll
-    for (int g = 0; g < KG; ++g) e[g] = as_v4i(*reinterpret_cast<const u4*>(st + g * kFragBytes));
-  };
 
-  // One stage: the unit's K groups (in `e`) against this wave's NT sentence tiles into `cur`, while the
-  // maxima are updated from `prev` (the sums of the stage before) and the next unit is read from LDS
-  // into `enext`.  The update's VALU work is cut into slices that sit between the MFMA groups, so it
-  // runs while the matrix pipeline is busy instead of after it; the scheduling fences keep that order.
-  // first_tag: stage 0, which has no stage before it.
-  auto stage = [&](auto nt_tag, auto refill_tag, auto first_tag, int newest, unsigned s, v4i (&cur)[TPW],
-                   const v4i (&prev)[TPW], const v4i (&e)[KG], v4i (&enext)[KG]) {
+  // Everything from the operand loads to the last stage, for a wave with NT sentence tiles.  The operand loads are
+  // written as instructions so that the waiting is ours: the compiler would wait for ALL outstanding loads, the whole
+  // pipeline included, at the first use.  It takes their results for there at once, so between the loads and the wait
+  // there must be nothing that makes it move them: no branch that joins one value of an operand with another (which is
+  // why the number of tiles is a constant here and not a condition around the loads).
+  using T = std::true_type;
+  using F = std::false_type;
+  using P0 = std::integral_constant<int, 0>;
+  using P1 = std::integral_constant<int, 1>;
+  auto body = [&](auto nt_tag) {
     constexpr int NT = decltype(nt_tag)::value;
-    constexpr bool FIRST = decltype(first_tag)::value;
-    land(newest);
-    // everybody is past stage s - 1 (and has its copy of stage s in registers), so slot s - 1 can be refilled
-    if constexpr (decltype(refill_tag)::value) issue(s + S - 1);
-    // the next unit's LDS reads are spread between the MFMA groups: eight reads in a row would fill the
-    // LDS queue (all eight waves read at the same time) and hold this wave's MFMAs back behind them
-    // (after the last unit they read a finished slot again and the result is unused)
-    const uint8_t* nx = smem + ((s + 1) % S) * STAGE + lane * 16;
-    const int prev_tag = 256 - (int)s;          // 255 - (s - 1); unused garbage for s == 0 (prev holds "none")
-    constexpr int ITEMS = NT * 4, PER = (ITEMS + KG - 1) / KG;
-    const v4i zero = {0, 0, 0, 0};
-    float expo[TPW][4];      // beam search: exponents of the stage before, formed in the first group
+    v4i hid[NT > 0 ? NT : 1][KG];
 #pragma unroll
-    for (int g = 0; g < KG; ++g) {
-      enext[g] = as_v4i(*reinterpret_cast<const u4*>(nx + g * kFragBytes));
-#pragma unroll
-      for (int i = 0; i < NT; ++i)
-        cur[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(e[g], hid[i][g], g == 0 ? zero : cur[i], 0, 0, 0);
-      if constexpr (BEAM == 1) {
-#pragma unroll
-        for (int j = g * PER; j < (g + 1) * PER && j < ITEMS; ++j)
-          best[j / 4][j % 4] = max(best[j / 4][j % 4], (prev[j / 4][j % 4] << 8) | (prev_tag & 255));
-      } else if constexpr (!FIRST) {
-        if (g == 0) {
-#pragma unroll
-          for (int i = 0; i < NT; ++i) beam_exponents(i, prev[i], 15u, expo[i]);
-        }
-#pragma unroll
-        for (int j = g * PER; j < (g + 1) * PER && j < ITEMS; ++j) {
-          beam_insert(j / 4, j % 4, (prev[j / 4][j % 4] << 8) | (prev_tag & 255));
-          norm_sum[j / 4] += __builtin_amdgcn_exp2f(expo[j / 4][j % 4]);
-        }
+    for (int i = 0; i < NT; ++i) {
+      unsigned t = (unsigned)wave + kWaves * i;
+      if (t >= tiles_avail) t = tiles_avail - 1;     // a chunk of few rows: a tile again, never written out
+      t += row0 / 16;
+      // one 32-bit lane offset per tile and a wave-uniform base per K group (a launch's rows are below 2^32 bytes)
+      unsigned voff = lane_off, voff_last = lane_off;
+      if constexpr (ROWM) {
+        // this lane's sentence (past the end: the last one again), 16 bytes at K quarter lane / 16; a quarter past the
+        // end of the row, which only the last group can have, reads quarter 0: it meets the embedding's zero padding
+        const unsigned m = t * 16 + lane % 16, quarter = (unsigned)(lane / 16) * 16;
+        voff_last = (m < p.M ? m : p.M - 1) * p.K;
+        voff = voff_last + quarter;
+        voff_last = (kgroups - 1) * 64 + quarter < p.K ? voff : voff_last;
       }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-
-  // two stages per trip so the two accumulator sets and the two unit buffers swap roles without copies
-  v4i acc0[TPW], acc1[TPW], e0[KG], e1[KG];
 #pragma unroll
-  for (int i = 0; i < TPW; ++i) {
-    acc0[i] = v4i{-8388608, -8388608, -8388608, -8388608};
-    acc1[i] = v4i{-8388608, -8388608, -8388608, -8388608};   // "none" for stage 0's update
-  }
-  if (nlocal > 0) {
+      for (int g = 0; g < KG; ++g) {
+        const unsigned gr = (unsigned)g < kgroups ? (unsigned)g : 0u;         // groups past the end are zeroed below
+        const uint8_t* base = p.packedA + (ROWM ? (size_t)gr * 64 : operand16_uniform_offset(dA, t, gr));
+        const unsigned off = ROWM && gr == kgroups - 1 ? voff_last : voff;
+        asm volatile("global_load_dwordx4 %0, %1, %2" : "=&v"(hid[i][g]) : "v"(off), "s"(base) : "memory");
+      }
+    }
+#pragma unroll
+    for (int s = kEarly; s < S - 1; ++s) issue(s);
     // stage 0 has to be in registers before the loop, and so have the operands: everything but the
     // stages issued after the operands may still be outstanding
+    v4i e0[kKG], e1[kKG];                   // two stages per trip, so that the buffers swap roles without copies
     wait_vmcnt_n(S - 1 - kEarly);
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    read_stage(0, e0);
-  } else {
-    wait_vmcnt_n(0);
-  }
-  // the operands are older than every stage, so they are there now; K groups past the end of K are zeroed
 #pragma unroll
-  for (int i = 0; i < TPW; ++i)
+    for (int g = 0; g < kKG; ++g) e0[g] = as_v4i(*reinterpret_cast<const u4*>(smem + lane * 16 + g * kFragBytes));
+    // the operands are older than every stage, so they are there now; K groups past the end of K are zeroed
 #pragma unroll
-    for (int g = 0; g < KG; ++g) {
-      asm volatile("" : "+v"(hid[i][g]));
-      if ((unsigned)g >= kgroups) hid[i][g] = v4i{0, 0, 0, 0};
-    }
-  auto run = [&](auto nt_tag) {
-    if (nlocal <= (unsigned)(S - 1)) {
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int g = 0; g < KG; ++g) {
+        asm volatile("" : "+v"(hid[i][g]));
+        if ((unsigned)g >= kgroups) hid[i][g] = v4i{0, 0, 0, 0};
+      }
+
+    // One stage: 512 elements of K of a unit (in `e`) against this wave's NT sentence tiles into `cur`, while the
+    // maxima are updated from `prev` (the sums of the unit before) and the next stage is read from LDS into `enext`.
+    // The update's VALU work is cut into slices that sit between the MFMA groups, so it runs while the matrix pipeline
+    // is busy instead of after it; the scheduling fences keep that order.
+    // refill_tag: the freed slot takes a new load; first_tag: unit 0, which has no unit before it; part_tag: s % NH.
+    auto stage = [&](auto refill_tag, auto first_tag, auto part_tag, int newest, unsigned s, v4i (&cur)[TPW],
+                     const v4i (&prev)[TPW], const v4i (&e)[kKG], v4i (&enext)[kKG]) {
+      constexpr int PART = decltype(part_tag)::value;
+      constexpr bool FIRST = decltype(first_tag)::value;
+      land(newest);
+      // everybody is past stage s - 1 (and has its copy of stage s in registers), so slot s - 1 can be refilled
+      if constexpr (decltype(refill_tag)::value) issue(s + S - 1);
+      // the next stage's LDS reads go two at a time between the first MFMA groups: eight in a row would fill the LDS
+      // queue (all eight waves read at the same time) and hold this wave's MFMAs back behind them, and they should be
+      // back before the next barrier (after the last stage they read a finished slot again and the result is unused)
+      const uint8_t* nx = smem + ((s + 1) % S) * STAGE + lane * 16;
+      const int prev_tag = TAGS + 1 - (int)(s / NH);     // TAGS - (unit - 1); unused garbage for unit 0 (prev holds "none")
+      constexpr int ITEMS = NT * 4, PER = (ITEMS + KG - 1) / KG;
+      const v4i zero = {0, 0, 0, 0};
+#pragma unroll
+      for (int g = 0; g < kKG; ++g) {
+        if (g < kKG / 2) {
+          enext[2 * g] = as_v4i(*reinterpret_cast<const u4*>(nx + (2 * g) * kFragBytes));
+          enext[2 * g + 1] = as_v4i(*reinterpret_cast<const u4*>(nx + (2 * g + 1) * kFragBytes));
+        }
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+          cur[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(e[g], hid[i][PART * kKG + g], PART == 0 && g == 0 ? zero : cur[i], 0, 0, 0);
+        constexpr int J0 = PART * kKG;
+        if constexpr (BEAM == 1) {
+#pragma unroll
+          for (int j = (J0 + g) * PER; j < (J0 + g + 1) * PER && j < ITEMS; ++j)
+            best[j / 4][j % 4] = max(best[j / 4][j % 4], (prev[j / 4][j % 4] << SHIFT) | (prev_tag & TAGS));
+        } else if constexpr (!FIRST) {
+          // exponents of the unit before (norm_expo) are formed in the first group
+          if (g == 0) {
+#pragma unroll
+            for (int i = 0; i < NT; ++i) beam_exponents(i, prev[i], 15u, norm_expo[i]);
+          }
+#pragma unroll
+          for (int j = (J0 + g) * PER; j < (J0 + g + 1) * PER && j < ITEMS; ++j) {
+            beam_insert(j / 4, j % 4, (prev[j / 4][j % 4] << SHIFT) | (prev_tag & TAGS));
+            norm_sum[j / 4] += __builtin_amdgcn_exp2f(norm_expo[j / 4][j % 4]);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+
+    if (NH == 1 && nlocal <= (unsigned)(S - 1)) {
       // The usual case (36 000 rows over 256 workgroups are 9 units each): the prologue has issued everything.
       // Unrolled, so that each stage waits with its own constant and nothing is issued inside the loop.
 #pragma unroll
       for (int s = 0; s < S - 1; ++s) {
         if ((unsigned)s >= nlocal) break;
         const int newest = S - 3 - s > 0 ? S - 3 - s : 0;
-        if (s == 0) stage(nt_tag, std::false_type{}, std::true_type{}, newest, 0u, acc0, acc1, e0, e1);
-        else if (s % 2 == 0) stage(nt_tag, std::false_type{}, std::false_type{}, newest, (unsigned)s, acc0, acc1, e0, e1);
-        else stage(nt_tag, std::false_type{}, std::false_type{}, newest, (unsigned)s, acc1, acc0, e1, e0);
+        if (s == 0) stage(F{}, T{}, P0{}, newest, 0u, acc0, acc1, e0, e1);
+        else if (s % 2 == 0) stage(F{}, F{}, P0{}, newest, (unsigned)s, acc0, acc1, e0, e1);
+        else stage(F{}, F{}, P0{}, newest, (unsigned)s, acc1, acc0, e1, e0);
+      }
+    } else if constexpr (NH == 1) {
+      stage(T{}, T{}, P0{}, S - 3, 0u, acc0, acc1, e0, e1);
+      for (unsigned s = 1; s < nlocal; s += 2) {
+        stage(T{}, F{}, P0{}, S - 3, s, acc1, acc0, e1, e0);
+        if (s + 1 < nlocal) stage(T{}, F{}, P0{}, S - 3, s + 1, acc0, acc1, e0, e1);
       }
     } else {
-      stage(nt_tag, std::true_type{}, std::true_type{}, S - 3, 0u, acc0, acc1, e0, e1);
-      for (unsigned s = 1; s < nlocal; s += 2) {
-        stage(nt_tag, std::true_type{}, std::false_type{}, S - 3, s, acc1, acc0, e1, e0);
-        if (s + 1 < nlocal) stage(nt_tag, std::true_type{}, std::false_type{}, S - 3, s + 1, acc0, acc1, e0, e1);
+      for (unsigned n = 0; n < nlocal; n += 2) {
+        stage(T{}, F{}, P0{}, S - 3, 2 * n, acc0, acc1, e0, e1);
+        stage(T{}, F{}, P1{}, S - 3, 2 * n + 1, acc0, acc1, e1, e0);
+        if (n + 1 < nlocal) {
+          stage(T{}, F{}, P0{}, S - 3, 2 * n + 2, acc1, acc0, e0, e1);
+          stage(T{}, F{}, P1{}, S - 3, 2 * n + 3, acc1, acc0, e1, e0);
+        }
       }
     }
+    wait_vmcnt_n(0);      // the refills past the last unit are still landing in their slots
   };
-  if (ntl == TPW) run(std::integral_constant<int, TPW>{});
-  else run(std::integral_constant<int, TPW - 1>{});
-  wait_vmcnt_n(0);      // the refills past the last unit are still landing in their slots
+  if (ntl == TPW) body(std::integral_constant<int, TPW>{});
+  else body(std::integral_constant<int, TPW - 1>{});
   // the last stage's sums are still pending; only a workgroup's last unit can reach past N, where
   // the rows are padding and must not compete (needs at least two workgroups, which the launcher
   // guarantees whenever there is more than one unit)
-  if (nlocal > 0) {
+  {
     const unsigned sl = nlocal - 1;
     const unsigned unit0 = (first + sl * stride) * 16 + 4 * (lane / 16);
-    const int tag = 255 - (int)sl;
+    const int tag = TAGS - (int)sl;
 #pragma unroll
     for (int i = 0; i < TPW; ++i) {
       if constexpr (BEAM == 1) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int v = (sl % 2 == 0) ? acc0[i][r] : acc1[i][r];
-          if (unit0 + r < p.L) best[i][r] = max(best[i][r], (v << 8) | tag);
+          if (unit0 + r < p.L) best[i][r] = max(best[i][r], (v << SHIFT) | tag);
         }
       } else {
         if (i < ntl) {
@@ -405,7 +444,7 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
           beam_exponents(i, sums, valid, t);
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            beam_insert(i, r, (valid >> r) & 1u ? (sums[r] << 8) | tag : kNone);
+            beam_insert(i, r, (valid >> r) & 1u ? (sums[r] << SHIFT) | tag : kNone);
             norm_sum[i] += __builtin_amdgcn_exp2f(t[r]);
           }
         }
@@ -420,9 +459,9 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
     // normaliser's (reference, sum) pair.
     auto decode = [&](unsigned long long k) -> unsigned long long {
       const int k32 = (int)((unsigned)(k >> 32) ^ 0x80000000u);
-      const int sum = k32 >> 8;
-      if (sum == -8388608) return 0ull;
-      const unsigned st = 255u - (unsigned)(k32 & 255);
+      const int sum = k32 >> SHIFT;
+      if (sum == kNoSum) return 0ull;
+      const unsigned st = (unsigned)TAGS - (unsigned)(k32 & TAGS);
       const unsigned n = (first + st * stride) * 16 + 4 * (lane / 16) + (3u - (unsigned)k);
       return ((unsigned long long)((unsigned)sum ^ 0x80000000u) << 32) | (unsigned long long)(0xFFFFFFFFu - n);
     };
@@ -461,8 +500,8 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
         }
       }
       const unsigned m = (wave + kWaves * i) * 16 + lane % 16;
-      if (lane < 16 && m < p.M && i < ntl) {
-        const size_t at = (size_t)m * gridDim.x + blockIdx.x;
+      if (lane < 16 && m < rows && i < ntl) {
+        const size_t at = (size_t)(row0 + m) * gridDim.x + blockIdx.x;
 #pragma unroll
         for (int j = 0; j < BEAM; ++j) p.partial[at * BEAM + j] = top[j];
         p.norm[at] = make_float2(mx, sm);
@@ -477,9 +516,9 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
     unsigned long long key = 0ull;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int sum = best[i][r] >> 8;
-      if (sum != -8388608) {
-        const unsigned s = 255u - (unsigned)(best[i][r] & 255);
+      const int sum = best[i][r] >> SHIFT;
+      if (sum != kNoSum) {
+        const unsigned s = (unsigned)TAGS - (unsigned)(best[i][r] & TAGS);
         const unsigned n = (first + s * stride) * 16 + 4 * (lane / 16) + r;
         const unsigned long long k =
             ((unsigned long long)((unsigned)sum ^ 0x80000000u) << 32) | (unsigned long long)(0xFFFFFFFFu - n);
@@ -492,12 +531,14 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
     if (o > key) key = o;
     const unsigned m = (wave + kWaves * i) * 16 + lane % 16;
     // this workgroup's keys are consecutive in memory: the 16 lanes of a sentence tile fill one 128-byte line
-    if (lane < 16 && m < p.M) p.partial[(size_t)blockIdx.x * (((size_t)p.M + 15) / 16 * 16) + m] = key;
+    if (lane < 16 && m < rows) p.partial[(size_t)blockIdx.x * (((size_t)p.M + 15) / 16 * 16) + row0 + m] = key;
   }
 }
 
 // One workgroup per tile of 16 sentences: 16 groups of 16 lanes each take every 16th workgroup's keys of the tile (one
-// 128-byte line per group and load), the groups' maxima meet in LDS, and 16 lanes decode.
+// 128-byte line per group and load), the groups' maxima meet in LDS, and 16 lanes decode.  Bound by the round trip to
+// keys that other dies' workgroups have just written: a lane's loads (16 for 256 workgroups) all go out before the first
+// is looked at (four at a time the output layer took 0.7 us longer for 300 and for 61 sentences).
 __global__ __launch_bounds__(256) void k_argmax_reduce(const unsigned long long* __restrict__ partial, unsigned cols,
                                                        unsigned M, const float* __restrict__ sA,
                                                        const float* __restrict__ sW, int32_t* __restrict__ tok,
@@ -510,16 +551,17 @@ __global__ __launch_bounds__(256) void k_argmax_reduce(const unsigned long long*
   unsigned long long key = 0ull;
   if (m < M) {
     const unsigned long long* col = partial + m;
-    unsigned g = gs;
-    for (; g + 48 < cols; g += 64) {              // four independent loads in flight per lane
-      const unsigned long long k0 = col[(size_t)g * Mpad], k1 = col[(size_t)(g + 16) * Mpad];
-      const unsigned long long k2 = col[(size_t)(g + 32) * Mpad], k3 = col[(size_t)(g + 48) * Mpad];
-      const unsigned long long a = k0 > k1 ? k0 : k1, b = k2 > k3 ? k2 : k3, c = a > b ? a : b;
-      if (c > key) key = c;
+    unsigned long long k[16];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {                // (a slot past the end reads a valid key again, which changes nothing)
+      const unsigned g = gs + 16 * t < cols ? gs + 16 * t : gs % cols;
+      k[t] = col[(size_t)g * Mpad];
     }
-    for (; g < cols; g += 16) {
-      const unsigned long long k = col[(size_t)g * Mpad];
-      if (k > key) key = k;
+#pragma unroll
+    for (int t = 0; t < 16; ++t) key = k[t] > key ? k[t] : key;
+    for (unsigned g = gs + 256; g < cols; g += 16) {
+      const unsigned long long v = col[(size_t)g * Mpad];
+      if (v > key) key = v;
     }
   }
   red[gs][mi] = key;
@@ -542,18 +584,19 @@ __device__ __forceinline__ unsigned dpp16(unsigned x) {
   return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
 }
 
-// Beam search: 16 lanes per row, each takes every 16th workgroup's list and (reference, sum) pair; the lanes' lists are
-// merged inside their row of 16 lanes without LDS traffic (a whole wave per row spent 2.4 us in k rounds of six 64-bit
-// cross-lane exchanges).  Writes tok [M x k] and logprob [M x k].
-template <int BEAM>
+// Beam search: LANES = 16 or 64 lanes per row, each takes every LANES-th workgroup's list and (reference, sum) pair, up to
+// four of them in flight (so 64 lanes where there are more than 64 workgroups to a row); the lanes' lists are merged
+// inside rows of 16 lanes without LDS traffic (a wave per row spent 2.4 us in k rounds of six 64-bit cross-lane
+// exchanges).  Writes tok [M x k] and logprob [M x k].
+template <int BEAM, int LANES>
 __global__ __launch_bounds__(256) void k_topk_reduce(const unsigned long long* __restrict__ partial,
                                                      const float2* __restrict__ norm, unsigned cols, unsigned M,
                                                      unsigned k, const float* __restrict__ sA,
                                                      const float* __restrict__ sW, int32_t* __restrict__ tok,
                                                      float* __restrict__ logprob,
                                                      const int32_t* __restrict__ shortlist) {
-  const unsigned sub = threadIdx.x % 16;
-  const unsigned row = blockIdx.x * 16 + threadIdx.x / 16;
+  const unsigned sub = threadIdx.x % LANES;
+  const unsigned row = blockIdx.x * (256 / LANES) + threadIdx.x / LANES;
   const unsigned m = row < M ? row : M - 1;         // lanes past the end repeat the last row and write nothing
   const float u = __fdiv_rn(1.0f, __fmul_rn(*sA, *sW));
   unsigned long long top[BEAM];
@@ -567,13 +610,13 @@ __global__ __launch_bounds__(256) void k_topk_reduce(const unsigned long long* _
       mx = m2;
     }
   };
-  for (unsigned g0 = sub; g0 < cols; g0 += 64) {
-    // up to four workgroups' lists in flight per lane (a slot past the end reads a valid list again, which adds nothing)
+  for (unsigned g0 = sub; g0 < cols; g0 += 4 * LANES) {
+    // (a slot past the end reads a valid list again, which adds nothing)
     unsigned long long list[4][BEAM];
     float2 nm[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      const unsigned g = g0 + 16 * t < cols ? g0 + 16 * t : g0;
+      const unsigned g = g0 + LANES * t < cols ? g0 + LANES * t : g0;
       const size_t at = (size_t)m * cols + g;
 #pragma unroll
       for (int j = 0; j < BEAM; ++j) list[t][j] = partial[at * BEAM + j];
@@ -581,7 +624,7 @@ __global__ __launch_bounds__(256) void k_topk_reduce(const unsigned long long* _
     }
 #pragma unroll
     for (int t = 0; t < 4; ++t)
-      if (g0 + 16 * t < cols) {
+      if (g0 + LANES * t < cols) {
         merge_sorted(top, list[t]);
         join(nm[t].x, nm[t].y);
       }
@@ -600,6 +643,17 @@ __global__ __launch_bounds__(256) void k_topk_reduce(const unsigned long long* _
   exchange(std::integral_constant<int, 0x4E>{});     // quad_perm [2,3,0,1]
   exchange(std::integral_constant<int, 0x141>{});    // row_half_mirror
   exchange(std::integral_constant<int, 0x140>{});    // row_mirror
+  if constexpr (LANES == 64) {
+#pragma unroll
+    for (int off = 16; off <= 32; off *= 2) {
+      unsigned long long other[BEAM];
+#pragma unroll
+      for (int j = 0; j < BEAM; ++j) other[j] = __shfl_xor(top[j], off, 64);
+      const float omx = __shfl_xor(mx, off, 64), osm = __shfl_xor(sm, off, 64);
+      merge_sorted(top, other);
+      join(omx, osm);
+    }
+  }
   if (sub < k && row < M) {
     const float lse = (mx + __builtin_amdgcn_logf(sm)) * 0.693147180559945309417f;     // log2 -> natural log
     unsigned long long w = top[0];
@@ -613,10 +667,12 @@ __global__ __launch_bounds__(256) void k_topk_reduce(const unsigned long long* _
   }
 }
 
-template <int TPW, bool GATHER, int BEAM = 1>
+template <int TPW, bool GATHER, int BEAM = 1, int KG = kKG, bool ROWM = false>
 int launch_stream(const ArgmaxParams& p, unsigned grid, hipStream_t s, unsigned ny = 1) {
-  constexpr size_t smem = (size_t)(kStages + 1) * kKG * kFragBytes + (GATHER ? 255 * 16 * sizeof(int32_t) : 0);
-  auto kern = k_argmax_stream<TPW, GATHER, BEAM>;
+  constexpr size_t smem = (size_t)stages_of(KG) * kKG * kFragBytes + (size_t)kWaves * kFragBytes +
+                          (GATHER ? max_units_of(KG) * 16 * sizeof(int32_t) : 0);
+  static_assert(smem <= 160 * 1024, "LDS budget");
+  auto kern = k_argmax_stream<TPW, GATHER, BEAM, KG, ROWM>;
   static bool attr_done = false;
   if (!attr_done) {
     int rc = check_hip(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -628,78 +684,124 @@ int launch_stream(const ArgmaxParams& p, unsigned grid, hipStream_t s, unsigned 
   return check_hip(hipGetLastError());
 }
 
-}  // namespace
-
-// one pass's keys: a run of (rows of the pass, rounded up to 16) keys per workgroup
-size_t argmax_stream_ws_bytes(size_t M) {
-  const size_t rows = M < (size_t)kWaves * 3 * 16 ? M : (size_t)kWaves * 3 * 16;
-  return (size_t)kMaxBlocks * round_up(rows, 16) * sizeof(unsigned long long);
-}
-
-// Limits: sums must fit 24 bits (127^2 K < 2^23); at most 255 stages per workgroup.  Any number of rows: 384 per pass.
-bool argmax_stream_supported(size_t M, size_t N, size_t K) {
-  (void)M;
-  return K <= 64 * kKG && N <= (size_t)255 * 256 * 16;
-}
-
-int launch_argmax_stream(const void* packedA, const void* packedW, size_t M, size_t N, size_t K, const float* sA,
-                         const float* sW, int32_t* tok, float* maxlogit, void* ws, const int32_t* shortlist,
-                         size_t shortlist_len, hipStream_t s, unsigned max_grid) {
-  if (!argmax_stream_supported(M, N, K)) return MQ_ERR_UNSUPPORTED;
-  const PackedDims dW(8, N, K), dAll(8, M, K);
-  static int cus = 0;               // compute units of the device, asked once
+unsigned compute_units() {
+  static unsigned cus = 0;          // of the device, asked once
   if (cus == 0) {
     int dev = 0, v = 0;
     cus = 256;
     if (hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
-      cus = v;
+      cus = (unsigned)v;
   }
+  return cus;
+}
+
+// How a launch cuts its rows and its vocabulary.  A workgroup holds up to rows_max rows and fills a compute unit (LDS),
+// so n chunks of rows share the compute units: every chunk's vocabulary is cut over an n-th of them and a workgroup
+// starts (hidden states into registers) and ends (winners merged and written) once.  At most max_units units of 16
+// words each (the stage's place in a key), at least two columns (both units that can reach past N are then some
+// workgroup's last).
+struct StreamCut {
+  unsigned chunks, chunk_rows, columns;
+};
+StreamCut cut_stream(size_t M, size_t units, size_t rows_max, size_t max_units) {
+  StreamCut c;
+  c.chunks = (unsigned)((M + rows_max - 1) / rows_max);
+  c.chunk_rows = (unsigned)round_up((M + c.chunks - 1) / c.chunks, 16);
+  const size_t share = compute_units() / c.chunks, least = (units + max_units - 1) / max_units;
+  size_t columns = share > least ? share : least;
+  columns = columns < 2 ? 2 : (columns > 256 ? 256 : columns);
+  c.columns = (unsigned)(units < columns ? units : columns);
+  return c;
+}
+
+}  // namespace
+
+// one launch's keys: a run of (rows of the launch, rounded up to 16) keys per workgroup column
+size_t argmax_stream_ws_bytes(size_t M) {
+  const size_t rows = M < (size_t)kWaves * 3 * 16 ? M : (size_t)kWaves * 3 * 16;
+  return (size_t)kMaxBlocks * round_up(rows, 16) * sizeof(unsigned long long);
+}
+
+// Limits: sums must fit 24 bits (127^2 K < 2^23); at most 255 units per workgroup.  Any number of rows.
+bool argmax_stream_supported(size_t M, size_t N, size_t K) {
+  (void)M;
+  return K <= 64 * kKG && N <= (size_t)max_units_of(kKG) * 256 * 16;
+}
+
+// The same on plain row-major hidden states, K up to 1024 in whole 16-byte pieces.
+bool argmax_stream_rows_supported(size_t N, size_t K) {
+  return K % 16 == 0 && K <= 64 * kWideKG && N <= (size_t)max_units_of(K <= 64 * kKG ? kKG : kWideKG) * 256 * 16;
+}
+
+// hidden: packed, or (row_major) plain rows.  ws_keys: keys the partials array at ws holds.
+static int launch_argmax_any(const uint8_t* hidden, bool row_major, const void* packedW, size_t M, size_t N, size_t K,
+                             const float* sA, const float* sW, int32_t* tok, float* maxlogit, void* ws, size_t ws_keys,
+                             const int32_t* shortlist, size_t shortlist_len, hipStream_t s) {
+  const bool wide = K > 64 * kKG;
+  const PackedDims dW(8, N, K), dAll(8, M, K);
   const size_t units = shortlist != nullptr ? (shortlist_len + 15) / 16 : dW.nblocks * 2;
-  unsigned grid = (unsigned)(units < (size_t)cus ? units : (size_t)cus);
-  if (grid > (unsigned)kMaxBlocks) grid = kMaxBlocks;
-  if (max_grid != 0 && grid > max_grid) grid = max_grid;       // the caller's partials array has that many columns
-  if ((units + grid - 1) / grid > 255) return MQ_ERR_UNSUPPORTED;
-  // rows beyond what one workgroup's registers hold (3 tiles of 16 sentences per wave) go in further passes
-  constexpr size_t kChunk = (size_t)kWaves * 3 * 16;
-  for (size_t row0 = 0; row0 < M; row0 += kChunk) {
-    const size_t rows = M - row0 < kChunk ? M - row0 : kChunk;
+  const size_t rows_max = (size_t)kWaves * 16 * (wide ? kWideTPW : kMaxTPW), max_units = max_units_of(wide ? kWideKG : kKG);
+  // as many chunks of rows per launch as the partials array serves (and the compute units: more only queue up)
+  for (size_t row0 = 0; row0 < M;) {
+    size_t nrows = M - row0;
+    StreamCut c = cut_stream(nrows, units, rows_max, max_units);
+    while (nrows > rows_max && (c.chunks > 16 || (size_t)c.columns * round_up(nrows, 16) > ws_keys)) {
+      const size_t fewer = (c.chunks > 16 ? 16 : c.chunks - 1) * rows_max;
+      nrows = fewer < nrows ? fewer : nrows - 16;
+      c = cut_stream(nrows, units, rows_max, max_units);
+    }
+    while (c.columns > 2 && (size_t)c.columns * round_up(nrows, 16) > ws_keys) --c.columns;
+    if ((units + c.columns - 1) / c.columns > max_units) return MQ_ERR_UNSUPPORTED;
     ArgmaxParams p{};
-    p.packedA = static_cast<const uint8_t*>(packedA) + dAll.frag_offset(row0 / 32, 0);
+    p.packedA = row_major ? hidden + row0 * K : hidden + dAll.frag_offset(row0 / 32, 0);   // (row0: whole 32-row blocks)
     p.packedW = static_cast<const uint8_t*>(packedW);
-    p.M = (unsigned)rows; p.N = (unsigned)N; p.K = (unsigned)K;
+    p.M = (unsigned)nrows; p.N = (unsigned)N; p.K = (unsigned)K;
     p.partial = static_cast<unsigned long long*>(ws);
     p.shortlist = shortlist;
     p.L = shortlist != nullptr ? (unsigned)shortlist_len : (unsigned)N;
-    p.norm = nullptr; p.sA = sA; p.sW = sW;
-    const size_t tiles = (rows + 15) / 16;
-    const int tpw = (int)((tiles + kWaves - 1) / kWaves);
+    p.sA = sA; p.sW = sW;
+    p.chunk_rows = c.chunk_rows;
+    const int tpw = (int)((c.chunk_rows / 16 + kWaves - 1) / kWaves);
+    const unsigned g = c.columns, ny = c.chunks;
     int rc;
-    if (shortlist != nullptr) {
-      switch (tpw) {
-        case 1: rc = launch_stream<1, true>(p, grid, s); break;
-        case 2: rc = launch_stream<2, true>(p, grid, s); break;
-        default: rc = launch_stream<3, true>(p, grid, s); break;
-      }
-    } else {
-      switch (tpw) {
-        case 1: rc = launch_stream<1, false>(p, grid, s); break;
-        case 2: rc = launch_stream<2, false>(p, grid, s); break;
-        default: rc = launch_stream<3, false>(p, grid, s); break;
-      }
-    }
+    if (shortlist != nullptr)
+      rc = tpw == 1 ? launch_stream<1, true>(p, g, s, ny) : tpw == 2 ? launch_stream<2, true>(p, g, s, ny) : launch_stream<3, true>(p, g, s, ny);
+    else if (!row_major)
+      rc = tpw == 1 ? launch_stream<1, false>(p, g, s, ny) : tpw == 2 ? launch_stream<2, false>(p, g, s, ny) : launch_stream<3, false>(p, g, s, ny);
+    else if (wide)
+      rc = tpw == 1 ? launch_stream<1, false, 1, kWideKG, true>(p, g, s, ny) : launch_stream<2, false, 1, kWideKG, true>(p, g, s, ny);
+    else
+      rc = tpw == 1 ? launch_stream<1, false, 1, kKG, true>(p, g, s, ny)
+                    : tpw == 2 ? launch_stream<2, false, 1, kKG, true>(p, g, s, ny) : launch_stream<3, false, 1, kKG, true>(p, g, s, ny);
     if (rc != MQ_OK) return rc;
-    hipLaunchKernelGGL(k_argmax_reduce, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, s, p.partial, grid,
-                       (unsigned)rows, sA, sW, tok + row0, maxlogit + row0, shortlist);
+    hipLaunchKernelGGL(k_argmax_reduce, dim3((unsigned)((nrows + 15) / 16)), dim3(256), 0, s, p.partial, g,
+                       (unsigned)nrows, sA, sW, tok + row0, maxlogit + row0, shortlist);
     rc = check_hip(hipGetLastError());
     if (rc != MQ_OK) return rc;
+    row0 += nrows;
   }
   return MQ_OK;
 }
 
+int launch_argmax_stream(const void* packedA, const void* packedW, size_t M, size_t N, size_t K, const float* sA,
+                         const float* sW, int32_t* tok, float* maxlogit, void* ws, size_t ws_bytes, const int32_t* shortlist,
+                         size_t shortlist_len, hipStream_t s) {
+  if (!argmax_stream_supported(M, N, K)) return MQ_ERR_UNSUPPORTED;
+  return launch_argmax_any(static_cast<const uint8_t*>(packedA), false, packedW, M, N, K, sA, sW, tok, maxlogit, ws,
+                           ws_bytes / sizeof(unsigned long long), shortlist, shortlist_len, s);
+}
+
+int launch_argmax_stream_rows(const void* qA, const void* packedW, size_t M, size_t N, size_t K, const float* sA,
+                              const float* sW, int32_t* tok, float* maxlogit, void* ws, size_t ws_bytes, hipStream_t s) {
+  if (!argmax_stream_rows_supported(N, K)) return MQ_ERR_UNSUPPORTED;
+  return launch_argmax_any(static_cast<const uint8_t*>(qA), true, packedW, M, N, K, sA, sW, tok, maxlogit, ws,
+                           ws_bytes / sizeof(unsigned long long), nullptr, 0, s);
+}
+
 // ---- the same output layer for callers that cannot allocate: partial winners in a static device array ----
-// One pass of kStaticRows sentences against at most kStaticCols workgroups' candidates: 768 KiB per device, held
-// until the process ends.  Further passes (more rows) reuse it one after the other on the stream.
+// kStaticRows x kStaticCols keys, 768 KiB per device, held until the process ends.  Rows that need more go in further
+// launches that reuse it one after the other on the stream.
 namespace {
 constexpr size_t kStaticRows = (size_t)kWaves * 3 * 16;     // rows of one pass of the streaming kernel (384)
 constexpr unsigned kStaticCols = 256;
@@ -729,7 +831,8 @@ int launch_argmax_stream_static(const void* packedA, const void* packedW, size_t
     ptr = g_scratch_ptr[dev];
   }
   // every key the reduce kernel reads was written by this call's streaming kernel: nothing has to start at zero
-  return launch_argmax_stream(packedA, packedW, M, N, K, sA, sW, tok, maxlogit, ptr, nullptr, 0, s, kStaticCols);
+  return launch_argmax_stream(packedA, packedW, M, N, K, sA, sW, tok, maxlogit, ptr, sizeof(unsigned long long) * kStaticRows * kStaticCols,
+                              nullptr, 0, s);
 }
 
 size_t topk_stream_ws_bytes(size_t M, int k) {
@@ -740,7 +843,7 @@ size_t topk_stream_ws_bytes(size_t M, int k) {
 
 bool topk_stream_supported(size_t M, size_t N, size_t K, int k) {
   (void)M;
-  return k >= 1 && k <= 4 && (size_t)k <= N && K <= 64 * kKG && N <= (size_t)255 * 256 * 16;
+  return k >= 1 && k <= 4 && (size_t)k <= N && K <= 64 * kKG && N <= (size_t)max_units_of(kKG) * 256 * 16;
 }
 
 // Beam-search output layer: the k <= 4 best words of every row with log-probabilities.  Rows are processed in
@@ -751,58 +854,45 @@ int launch_topk_stream(const void* packedA, const void* packedW, size_t M, size_
   if (!topk_stream_supported(M, N, K, k)) return MQ_ERR_UNSUPPORTED;
   if (shortlist != nullptr && (size_t)k > shortlist_len) return MQ_ERR_SHAPE;
   const PackedDims dW(8, N, K);
-  static int cus = 0;
-  if (cus == 0) {
-    int dev = 0, v = 0;
-    cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
-      cus = v;
-  }
   const size_t units = shortlist != nullptr ? (shortlist_len + 15) / 16 : dW.nblocks * 2;
   const int beam = k <= 2 ? 2 : 4;
   unsigned long long* keys = static_cast<unsigned long long*>(ws);
   float2* norm = reinterpret_cast<float2*>(static_cast<uint8_t*>(ws) +
                                            round_up((size_t)256 * M * beam * sizeof(unsigned long long), 256));
-  // Rows go 256 to a workgroup (two sentence tiles per wave); all chunks run in ONE launch, the grid's y index picking
-  // the chunk, and one reduce launch follows for all rows: a launch per chunk (ten for 1200 rows) cost more than the
-  // chunks' work.  The chunks share the compute units: a workgroup fills one (LDS), so with n chunks every chunk's
-  // vocabulary is cut over a n-th of them and a workgroup starts (hidden states into registers) and ends (lists merged
-  // and written) once instead of n times; at most 255 units each (the stage's place in a key).
-  constexpr unsigned kChunkRows = 256;
-  const unsigned nchunks = (unsigned)((M + kChunkRows - 1) / kChunkRows);
-  if (nchunks > 65535u) return MQ_ERR_UNSUPPORTED;
-  const size_t share = (size_t)cus / nchunks > 0 ? (size_t)cus / nchunks : 1, least = (units + 254) / 255;
-  size_t columns = share > least ? share : least;
-  if (columns < 2) columns = 2;             // both units that can reach past N are then some workgroup's last
-  if (columns > 256) columns = 256;
-  const unsigned grid = (unsigned)(units < columns ? units : columns);
-  if ((units + grid - 1) / grid > 255) return MQ_ERR_UNSUPPORTED;
+  // Rows go up to 256 (two sentence tiles per wave) to a workgroup; all chunks run in ONE launch that shares the compute units (cut_stream), and one
+  // reduce launch follows for all rows: a launch per chunk (ten for 1200 rows) cost more than the chunks' work.
+  const StreamCut c = cut_stream(M, units, (size_t)kWaves * 16 * kBeamTPW, max_units_of(kKG));
+  if (c.chunks > 65535u || (units + c.columns - 1) / c.columns > max_units_of(kKG)) return MQ_ERR_UNSUPPORTED;
   ArgmaxParams p{};
   p.packedA = static_cast<const uint8_t*>(packedA);
   p.packedW = static_cast<const uint8_t*>(packedW);
-  p.M = (unsigned)(M < kChunkRows ? M : kChunkRows); p.N = (unsigned)N; p.K = (unsigned)K;
+  p.M = (unsigned)M; p.N = (unsigned)N; p.K = (unsigned)K;
   p.partial = keys; p.norm = norm; p.sA = sA; p.sW = sW;
   p.shortlist = shortlist;
   p.L = shortlist != nullptr ? (unsigned)shortlist_len : (unsigned)N;
-  p.chunk_rows = nchunks > 1 ? kChunkRows : 0u;
-  p.Mtotal = (unsigned)M;
-  const int tpw = (int)(((size_t)(p.M + 15) / 16 + kWaves - 1) / kWaves);
+  p.chunk_rows = c.chunk_rows;
+  const int tpw = (int)((c.chunk_rows / 16 + kWaves - 1) / kWaves);
+  const unsigned grid = c.columns, ny = c.chunks;
+  auto go = [&](auto gather, auto beam_tag) -> int {
+    constexpr bool G = decltype(gather)::value;
+    constexpr int B = decltype(beam_tag)::value;
+    return tpw == 1 ? launch_stream<1, G, B>(p, grid, s, ny) : launch_stream<kBeamTPW, G, B>(p, grid, s, ny);
+  };
+  using B2 = std::integral_constant<int, 2>;
+  using B4 = std::integral_constant<int, 4>;
   int rc;
-  if (shortlist != nullptr) {
-    if (beam == 2) rc = tpw == 1 ? launch_stream<1, true, 2>(p, grid, s, nchunks) : launch_stream<2, true, 2>(p, grid, s, nchunks);
-    else rc = tpw == 1 ? launch_stream<1, true, 4>(p, grid, s, nchunks) : launch_stream<2, true, 4>(p, grid, s, nchunks);
-  } else {
-    if (beam == 2) rc = tpw == 1 ? launch_stream<1, false, 2>(p, grid, s, nchunks) : launch_stream<2, false, 2>(p, grid, s, nchunks);
-    else rc = tpw == 1 ? launch_stream<1, false, 4>(p, grid, s, nchunks) : launch_stream<2, false, 4>(p, grid, s, nchunks);
-  }
+  if (shortlist != nullptr) rc = beam == 2 ? go(std::true_type{}, B2{}) : go(std::true_type{}, B4{});
+  else rc = beam == 2 ? go(std::false_type{}, B2{}) : go(std::false_type{}, B4{});
   if (rc != MQ_OK) return rc;
-  if (beam == 2)
-    hipLaunchKernelGGL((k_topk_reduce<2>), dim3((unsigned)((M + 15) / 16)), dim3(256), 0, s, keys, norm, grid, (unsigned)M,
-                       (unsigned)k, sA, sW, tok, logprob, shortlist);
-  else
-    hipLaunchKernelGGL((k_topk_reduce<4>), dim3((unsigned)((M + 15) / 16)), dim3(256), 0, s, keys, norm, grid, (unsigned)M,
-                       (unsigned)k, sA, sW, tok, logprob, shortlist);
+  auto reduce = [&](auto beam_tag, auto lanes_tag) {
+    constexpr int B = decltype(beam_tag)::value, LN = decltype(lanes_tag)::value;
+    hipLaunchKernelGGL((k_topk_reduce<B, LN>), dim3((unsigned)((M + 256 / LN - 1) / (256 / LN))), dim3(256), 0, s, keys, norm, grid,
+                       (unsigned)M, (unsigned)k, sA, sW, tok, logprob, shortlist);
+  };
+  using L16 = std::integral_constant<int, 16>;
+  using L64 = std::integral_constant<int, 64>;
+  if (beam == 2) grid > 64 ? reduce(B2{}, L64{}) : reduce(B2{}, L16{});
+  else grid > 64 ? reduce(B4{}, L64{}) : reduce(B4{}, L16{});
   return check_hip(hipGetLastError());
 }
 

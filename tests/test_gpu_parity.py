@@ -351,6 +351,35 @@ def test_greedy_output_layer_small(M, V, d):
     assert np.array_equal(val, o["maxlogit"])
 
 
+# Row-major hidden states: widths around the streaming kernel's two sizes (512, 1024), with and without a last group of
+# less than 64, beyond it (the tiled kernel), fewer and more sentences than a workgroup's chunk, more units than stages.
+@pytest.mark.parametrize("M,V,d", [(1, 40, 16), (300, 3000, 1024), (257, 5000, 1008), (17, 777, 528), (600, 9000, 1024),
+                                   (3, 70000, 544), (400, 2000, 496), (700, 1500, 512), (300, 3000, 1040), (33, 2000, 1023)])
+def test_greedy_output_layer_row_major_widths(M, V, d):
+    c = workloads.config3(M=M, V=V, d=d, seed_extra=M + V + d)
+    o = oracle.greedy_output_layer(c["Hd"], c["E"])
+    tok, val = gpu_greedy(c["Hd"], c["E"])
+    assert np.array_equal(tok, o["tok"])
+    assert np.array_equal(val, o["maxlogit"])
+
+
+@pytest.mark.parametrize("d", [512, 1024])
+def test_greedy_output_layer_extreme_sums(d):
+    # sums of +-127 * 127 * d, the ends of the range a key's sum field holds, and ties between them
+    M, V = 20, 600
+    Hd = np.ones((M, d), dtype=np.float32)
+    Hd[1::2] = -1
+    E = np.full((V, d), -1, dtype=np.float32)
+    o = oracle.greedy_output_layer(Hd, E)
+    tok, val = gpu_greedy(Hd, E)
+    assert np.array_equal(tok, o["tok"]) and np.array_equal(val, o["maxlogit"])
+    E[[77, 78, 400]] = 1
+    o = oracle.greedy_output_layer(Hd, E)
+    assert o["tok"][0] == 77 and o["tok"][1] == 0 and o["acc"].max() == 127 * 127 * d
+    tok, val = gpu_greedy(Hd, E)
+    assert np.array_equal(tok, o["tok"]) and np.array_equal(val, o["maxlogit"])
+
+
 def test_greedy_planted_winner_and_ties():
     c = workloads.config3(M=40, V=2085, d=128, seed_extra=9)
     Hd, E = c["Hd"].copy(), c["E"].copy()
