@@ -13,6 +13,7 @@
 // Both operands are in fragment order; a fragment is one coalesced 1 KB read
 // straight into the registers the matrix instruction takes.
 #include "mq_gemm_common.h"
+#include "mq_grid_max.h"
 
 namespace mq {
 
@@ -61,6 +62,27 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small(const Params p, const in
     if (p.bias != nullptr && n_ok) bias = p.bias[n];
   }
 
+  // The partial sums meet in vectors of V rows, the widest that leaves every thread one: vector i of a thread holds rows
+  // row_of(i) .. + V - 1 of column n.  16 bit: their sums and the column's are asked for here as well.
+  constexpr int V = TMW * 1024 / (KS * 64) >= 4 ? 4 : TMW * 1024 / (KS * 64), NV = TMW * 1024 / (KS * 64) / V;
+  static_assert(V >= 1 && NV * V * KS * 64 == TMW * 1024, "elements must divide over the threads");
+  typedef uint32_t Vec __attribute__((ext_vector_type(V)));
+  auto row_of = [&](int i) -> unsigned {
+    const int g = (tid + i * KS * 64) / 64 * V, mt = g / 16, r = g % 16;
+    return (tile_m * TMW + mt) * 32 + 8 * (r / 4) + 4 * lh + r % 4;
+  };
+  uint32_t rs[BITS == 16 ? NV : 1][V];
+  uint32_t corr = 0;
+  if constexpr (BITS == 16) {
+    const uint32_t* rowsum = reinterpret_cast<const uint32_t*>(p.qA + dA.plane_bytes());
+    const uint32_t* colsum = reinterpret_cast<const uint32_t*>(p.packedW + dW.plane_bytes());
+    corr = 128u * (n_ok ? colsum[n] : 0u) - 16384u * p.K;
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+#pragma unroll
+      for (int t = 0; t < V; ++t) rs[i][t] = row_of(i) + t < p.M ? rowsum[row_of(i) + t] : 0u;
+  }
+
   v16i acc[TMW][NACC];
 #pragma unroll
   for (int mt = 0; mt < TMW; ++mt)
@@ -101,42 +123,45 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small(const Params p, const in
     }
   }
 
-  // partial sums of this wave: element e = (mt * 16 + r) * 64 + lane
-  int* mine = part + wave * (TMW * 1024);
+  // partial sums of this wave, V consecutive rows at a time: vector e = group * 64 + lane, group = (mt * 16 + r) / V
+  Vec* mine = reinterpret_cast<Vec*>(part) + wave * (TMW * 1024 / V);
 #pragma unroll
   for (int mt = 0; mt < TMW; ++mt)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      unsigned v = (unsigned)acc[mt][0][r];
-      if constexpr (BITS == 16) v = (v << 16) + ((unsigned)acc[mt][1][r] << 8) + (unsigned)acc[mt][2][r];
-      mine[(mt * 16 + r) * 64 + lane] = (int)v;
+    for (int r = 0; r < 16; r += V) {
+      Vec v;
+#pragma unroll
+      for (int t = 0; t < V; ++t) {
+        v[t] = (unsigned)acc[mt][0][r + t];
+        if constexpr (BITS == 16) v[t] = (v[t] << 16) + ((unsigned)acc[mt][1][r + t] << 8) + (unsigned)acc[mt][2][r + t];
+      }
+      mine[(mt * 16 + r) / V * 64 + lane] = v;
     }
   __syncthreads();
 
-  // Every thread adds up KS partial sums for TMW * 1024 / (KS * 64) elements.
-  constexpr int PER_THREAD = TMW * 1024 / (KS * 64);
-  static_assert(PER_THREAD >= 1 && PER_THREAD * KS * 64 == TMW * 1024, "elements must divide over the threads");
+  // Every thread adds up the KS partial sums of NV vectors.
 #pragma unroll
-  for (int i = 0; i < PER_THREAD; ++i) {
-    const int e = tid + i * KS * 64;
-    unsigned v = 0;
+  for (int i = 0; i < NV; ++i) {
+    Vec v;
 #pragma unroll
-    for (int w = 0; w < KS; ++w) v += (unsigned)part[w * (TMW * 1024) + e];      // mod 2^32
-    const int mt = e / 1024, r = (e / 64) % 16;
-    const unsigned m = (tile_m * TMW + mt) * 32 + 8 * (r / 4) + 4 * lh + r % 4;
-    if (n_ok && m < p.M) {
-      if constexpr (BITS == 16) {
-        const int32_t* rowsum = reinterpret_cast<const int32_t*>(p.qA + dA.plane_bytes());
-        const int32_t* colsum = reinterpret_cast<const int32_t*>(p.packedW + dW.plane_bytes());
-        v += 128u * ((unsigned)rowsum[m] + (unsigned)colsum[n]) - 16384u * p.K;
-      }
-      if (dequant) {
-        float y = fmaf((float)(int)v, u, bias);
-        if (p.relu) y = (y > 0.0f) ? y : 0.0f;
-        p.Y[(size_t)m * p.N + n] = y;
-        local_amax = fmaxf(local_amax, fabsf(y));
-      } else {
-        p.C[(size_t)m * p.N + n] = (int)v;
+    for (int t = 0; t < V; ++t) v[t] = 0u;
+#pragma unroll
+    for (int w = 0; w < KS; ++w) v += reinterpret_cast<const Vec*>(part)[w * (TMW * 1024 / V) + tid + i * KS * 64];      // mod 2^32
+    const unsigned m0 = row_of(i);
+#pragma unroll
+    for (int t = 0; t < V; ++t) {
+      const unsigned m = m0 + t;
+      if (n_ok && m < p.M) {
+        unsigned sum = v[t];
+        if constexpr (BITS == 16) sum += 128u * rs[i][t] + corr;
+        if (dequant) {
+          float y = fmaf((float)(int)sum, u, bias);
+          if (p.relu) y = (y > 0.0f) ? y : 0.0f;
+          p.Y[(size_t)m * p.N + n] = y;
+          local_amax = fmaxf(local_amax, fabsf(y));
+        } else {
+          p.C[(size_t)m * p.N + n] = (int)sum;
+        }
       }
     }
   }
@@ -145,8 +170,7 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small(const Params p, const in
     // them), and/or raised into *p.out_amax with at most one atomic per block; the running maximum only
     // grows, so a block that cannot raise it skips the atomic
     __shared__ float wave_amax[KS];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) local_amax = fmaxf(local_amax, __shfl_xor(local_amax, off, 64));
+    local_amax = __uint_as_float(wave_max_u32(__float_as_uint(local_amax)));      // non-negative: ordered like its bits
     if (lane == 0) wave_amax[wave] = local_amax;
     __syncthreads();
     if (tid == 0) {
@@ -216,14 +240,19 @@ struct SmallF32Params {
   float* partial_out;        // optional: max|y| of every workgroup
 };
 
+// Four elements of quant_int as bytes.  CLAMP = false: the multiplier is 127 / max over a set these elements belong to,
+// rounded, so |x s| <= 127 (1 + 2^-23) rounds to at most 127 and no clamp can act (an infinite max gives s = 0, products
+// 0 or NaN, and NaN converts to 0 either way).
+template <bool CLAMP>
 __device__ __forceinline__ uint32_t quant_pack4(float4 v, float s) {
   auto q = [&](float x) -> uint32_t {
     const float r = rintf(__fmul_rn(x, s));
     int i;
     asm("v_cvt_i32_f32 %0, %1" : "=v"(i) : "v"(r));      // saturates, NaN -> 0
-    return (uint32_t)(min(max(i, -127), 127) & 0xFF);
+    return (uint32_t)(CLAMP ? min(max(i, -127), 127) : i);
   };
-  return q(v.x) | (q(v.y) << 8) | (q(v.z) << 16) | (q(v.w) << 24);
+  // bytes 0 of four words: two byte permutes and an or (0x0c selects zero)
+  return __builtin_amdgcn_perm(q(v.y), q(v.x), 0x0c0c0400u) | __builtin_amdgcn_perm(q(v.w), q(v.z), 0x04000c0cu);
 }
 
 // TNW: 32-column blocks per workgroup; KS waves split K; a round is 4 fragments (128 elements of K).
@@ -231,7 +260,14 @@ __device__ __forceinline__ uint32_t quant_pack4(float4 v, float s) {
 // instruction), converts, and turns the bytes into operand fragments through a private piece of LDS:
 // fragment f of a round sits at f * kPitch, K half h of a row at h * kHalf inside it (the paddings
 // spread the 4-byte writes of a row over the banks), 16 bytes per row.
-template <int TNW, int KS>
+// Where its time goes (300 x 2048 x 512, wall clock inside the kernel before the conversion was shortened): 1.6 us until
+// all loads are issued (64 KB of fp32 rows and 32 KB of parameter per workgroup through the 64 bytes per clock of a compute
+// unit's address path), 1.2 until they and the partial maxima are there, 1.3 for conversion and products, 0.3 for the
+// exchange, 1.2 for results and their maximum.  Without clamps where none can act, byte permutes for packing, 16-byte
+// exchange through LDS and lane moves for the maxima: this product with its abs-max 9.15 -> 8.3 us, a decoder layer of 300
+// sentences 74.1 -> 70.1 us.
+// GIVEN: the multiplier is given (elements may exceed it and are clamped); otherwise it comes from partial maxima.
+template <int TNW, int KS, bool GIVEN>
 __global__ __launch_bounds__(KS * 64) void k_gemm_small_f32(const SmallF32Params p) {
   constexpr int KW = 4;
   constexpr int kHalf = 512 + 16, kPitch = 2 * kHalf;
@@ -300,12 +336,11 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small_f32(const SmallF32Params
   if (kb_begin < kb_end) fetch(kb_begin);        // the first round is on its way while the multiplier is formed
 
   float s;
-  if (p.npartial != 0) {
+  if constexpr (!GIVEN) {
     float m = 0.f;
     for (unsigned i = tid; i < p.npartial; i += KS * 64) m = fmaxf(m, p.scale[i]);
     for (unsigned i = tid; i < p.npartial2; i += KS * 64) m = fmaxf(m, p.scale2[i]);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+    m = __uint_as_float(wave_max_u32(__float_as_uint(m)));
     if (lane == 0) red[wave] = m;
     __syncthreads();
     float amax = red[0];
@@ -325,7 +360,7 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small_f32(const SmallF32Params
   for (unsigned kb0 = kb_begin; kb0 < kb_end; kb0 += KW) {
     if (kb0 != kb_begin) fetch(kb0);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) *reinterpret_cast<uint32_t*>(st_dst + i * 32) = quant_pack4(fa[i], s);
+    for (int i = 0; i < 16; ++i) *reinterpret_cast<uint32_t*>(st_dst + i * 32) = quant_pack4<GIVEN>(fa[i], s);
     // The wave reads back what it wrote itself: LDS operations of one wave complete in order, so the
     // hardware needs no wait.  The compiler does: words are written and 16-byte vectors read, types it may
     // take for non-aliasing, so both sides are fenced against compile-time motion.
@@ -344,39 +379,52 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small_f32(const SmallF32Params
     }
   }
 
-  int* mine = part + wave * (TNW * 1024);
+  // the partial sums meet in vectors of V rows, see k_gemm_small
+  constexpr int V = TNW * 1024 / (KS * 64) >= 4 ? 4 : TNW * 1024 / (KS * 64), NV = TNW * 1024 / (KS * 64) / V;
+  static_assert(V >= 1 && NV * V * KS * 64 == TNW * 1024, "elements must divide over the threads");
+  typedef uint32_t Vec __attribute__((ext_vector_type(V)));
+  Vec* mine = reinterpret_cast<Vec*>(part) + wave * (TNW * 1024 / V);
 #pragma unroll
   for (int c = 0; c < TNW; ++c)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) mine[(c * 16 + r) * 64 + lane] = acc[c][r];
+    for (int r = 0; r < 16; r += V) {
+      Vec v;
+#pragma unroll
+      for (int t = 0; t < V; ++t) v[t] = (unsigned)acc[c][r + t];
+      mine[(c * 16 + r) / V * 64 + lane] = v;
+    }
   __syncthreads();
 
   const float u = __fdiv_rn(1.0f, __fmul_rn(s, sW_pre));
   float local_amax = 0.f;
-  constexpr int PER_THREAD = TNW * 1024 / (KS * 64);
-  static_assert(1024 % (KS * 64) == 0, "a thread's i-th element lies in a column block known at compile time");
-  static_assert(PER_THREAD >= 1 && PER_THREAD * KS * 64 == TNW * 1024, "elements must divide over the threads");
 #pragma unroll
-  for (int i = 0; i < PER_THREAD; ++i) {
-    const int e = tid + i * KS * 64;
-    unsigned v = 0;
+  for (int i = 0; i < NV; ++i) {
+    Vec v;
 #pragma unroll
-    for (int w = 0; w < KS; ++w) v += (unsigned)part[w * (TNW * 1024) + e];      // mod 2^32
-    const int c = e / 1024, r = (e / 64) % 16;
+    for (int t = 0; t < V; ++t) v[t] = 0u;
+#pragma unroll
+    for (int w = 0; w < KS; ++w) v += reinterpret_cast<const Vec*>(part)[w * (TNW * 1024 / V) + tid + i * KS * 64];      // mod 2^32
+    constexpr int kPerBlock = 16 / V;                                 // groups of a column block
+    const int c = (wave + i * KS) / kPerBlock, r = (wave + i * KS) % kPerBlock * V;      // wave-uniform
+    float bias = bias_pre[0];
+#pragma unroll
+    for (int cc = 1; cc < TNW; ++cc)
+      if (cc == c) bias = bias_pre[cc];
     const unsigned n = (tile_n * TNW + c) * 32 + lj;
-    const unsigned m = tile_m * 32 + 8 * (r / 4) + 4 * lh + r % 4;
-    if (n < p.N && m < p.M) {
-      float y = fmaf((float)(int)v, u, bias_pre[(i * KS * 64) / 1024]);
-      if (p.relu) y = (y > 0.0f) ? y : 0.0f;
-      p.Y[(size_t)m * p.N + n] = y;
-      local_amax = fmaxf(local_amax, fabsf(y));
-    }
+    const unsigned m0 = tile_m * 32 + 8 * (r / 4) + 4 * lh + r % 4;
+#pragma unroll
+    for (int t = 0; t < V; ++t)
+      if (n < p.N && m0 + t < p.M) {
+        float y = fmaf((float)(int)v[t], u, bias);
+        if (p.relu) y = (y > 0.0f) ? y : 0.0f;
+        p.Y[(size_t)(m0 + t) * p.N + n] = y;
+        local_amax = fmaxf(local_amax, fabsf(y));
+      }
   }
   if (p.out_amax != nullptr || p.partial_out != nullptr) {
     // as in k_gemm_small: one maximum per workgroup, without atomics, and/or the raised word
     __shared__ float wave_amax[KS];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) local_amax = fmaxf(local_amax, __shfl_xor(local_amax, off, 64));
+    local_amax = __uint_as_float(wave_max_u32(__float_as_uint(local_amax)));      // non-negative: ordered like its bits
     if (lane == 0) wave_amax[wave] = local_amax;
     __syncthreads();
     if (tid == 0) {
@@ -393,14 +441,14 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small_f32(const SmallF32Params
   }
 }
 
-template <int TNW, int KS>
-int launch_small_f32(SmallF32Params p, hipStream_t s) {
+template <int TNW, int KS, bool GIVEN>
+int launch_small_f32_one(SmallF32Params p, hipStream_t s) {
   constexpr size_t smem = (size_t)KS * TNW * 1024 * sizeof(int) + (size_t)KS * 4 * 2 * (512 + 16);
   const PackedDims dW(8, p.N, p.K);
   const size_t tiles_m = (p.M + 31) / 32, tiles_n = (dW.nblocks + TNW - 1) / TNW;
   p.tiles_n = (unsigned)tiles_n;
   if (tiles_m * tiles_n > 0x7FFFFFFFull) return MQ_ERR_SHAPE;
-  auto kern = k_gemm_small_f32<TNW, KS>;
+  auto kern = k_gemm_small_f32<TNW, KS, GIVEN>;
   static bool attr_done = false;
   if (!attr_done) {
     int rc = check_hip(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -410,6 +458,11 @@ int launch_small_f32(SmallF32Params p, hipStream_t s) {
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(KS * 64), smem, s, p);
   return check_hip(hipGetLastError());
+}
+
+template <int TNW, int KS>
+int launch_small_f32(const SmallF32Params& p, hipStream_t s) {
+  return p.npartial != 0 ? launch_small_f32_one<TNW, KS, false>(p, s) : launch_small_f32_one<TNW, KS, true>(p, s);
 }
 
 template <int BITS, int TMW>
