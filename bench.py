@@ -344,7 +344,7 @@ def main():
             "note_on_wrapping": "with 32767/max|x| multipliers part of the 32-bit sums wrap (fractions in "
                                 "cpu_baseline.parity.config4); the paper's fixed 2^10 avoids that: next entry",
             "paper_scheme_fixed_multiplier_2^10": {
-                "path": "mq_ffn_i16_fixed_f32 (4 launches, H written once as packed int16, no abs-max pass, no wrapped sum)",
+                "path": "mq_ffn_i16_fixed_f32 (3 launches, H written once as packed int16, no abs-max pass, no wrapped sum)",
                 "us_per_step": round(usf16, 1), "us_per_step_median": round(usf16_med, 1),
                 "TOPS_useful": round(w4.ops / usf16 / 1e6, 1),
                 "pct_int8_mfma_peak_issued": round(100 * 4 * w4.ops / usf16 / 1e6 / PEAK_INT8_TOPS, 2)},

@@ -460,7 +460,7 @@ int mq_ffn_i16_f32(const float* A, size_t M, size_t d, size_t f, const void* pac
 /* The 16-bit block with multipliers fixed in advance, the paper's own 16-bit scheme (Section 4.2: every tensor
  * times 2^10, sums in 32 bits, so that no sum can wrap for the model's value range): quant_int(A, sA[0]), product +
  * b1 + ReLU re-quantized with sH[0] in the producing epilogue (saturating at +-32767; the intermediate goes to
- * memory once, as packed 16-bit values, never as floats), product + b2.  No abs-max pass anywhere.  Four launches.
+ * memory once, as packed 16-bit values, never as floats), product + b2.  No abs-max pass anywhere.  Three launches.
  * sA, sH: device float[1] multipliers of the input and of the intermediate; packedW1 / packedW2 prepared with
  * bits = 16 and whatever multipliers sW1 / sW2 say (2^10 in the paper).  Results are those of
  * mq_quantize_pack_f32 + mq_gemm_requant_fixed_packed_i16 + mq_gemm_dequant_packed bit for bit.

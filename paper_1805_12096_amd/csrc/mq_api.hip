@@ -824,14 +824,16 @@ int mq_ffn_i16_fixed_f32(const float* A, size_t M, size_t d, size_t f, const flo
   hipStream_t s = as_stream(stream);
   uint8_t* qA = static_cast<uint8_t*>(ws);
   uint8_t* qH = qA + round_up(PackedDims(16, M, d).total_bytes(), 256);
-  // quant_int(A) with the given multiplier, product + b1 + ReLU re-quantized with the given multiplier in the
-  // epilogue (H goes to memory once, as packed 16-bit values), product + b2
-  int rc = launch_quantize_pack(A, M, d, 16, sA, qA, s);
+  // quant_int(A) with the given multiplier (that kernel also zeroes H's row sums, which the next one accumulates),
+  // product + b1 + ReLU re-quantized with the given multiplier in the epilogue (H goes to memory once, as packed 16-bit
+  // values), product + b2
+  const PackedDims dH(16, M, f);
+  int rc = launch_quantize_pack(A, M, d, 16, sA, qA, s, reinterpret_cast<unsigned*>(qH + dH.plane_bytes()), (unsigned)dH.Np);
   if (rc != MQ_OK) return rc;
   GemmArgs g1{};
   g1.qA = qA; g1.packedW = packedW1; g1.bits = 16; g1.M = M; g1.N = f; g1.K = d;
   g1.sA = sA; g1.sW = sW1; g1.bias = b1; g1.relu = 1;
-  rc = launch_gemm_requant_fixed_i16(g1, sH, qH, s);
+  rc = launch_gemm_requant_fixed_i16(g1, sH, qH, s, true);
   if (rc != MQ_OK) return rc;
   GemmArgs g2{};
   g2.qA = qH; g2.packedW = packedW2; g2.bits = 16; g2.M = M; g2.N = d; g2.K = f;

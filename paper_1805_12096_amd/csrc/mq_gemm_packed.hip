@@ -906,12 +906,15 @@ int launch_gemm_requant_fixed(const GemmArgs& a, const float* s_fixed, void* pac
 }
 
 // 16-bit product re-quantized with a fixed multiplier into packed 16-bit activations (planes + row sums).
-// The row sums are accumulated with atomics: they are zeroed here by a small launch first.
-int launch_gemm_requant_fixed_i16(const GemmArgs& a, const float* s_fixed, void* packed_out, hipStream_t s) {
+// The row sums are accumulated with atomics: they are zeroed here by a small launch first unless that has been done.
+int launch_gemm_requant_fixed_i16(const GemmArgs& a, const float* s_fixed, void* packed_out, hipStream_t s,
+                                  bool sums_cleared) {
   const PackedDims dO(16, a.M, a.N);
-  int rc = launch_clear_words(reinterpret_cast<unsigned*>(static_cast<uint8_t*>(packed_out) + dO.plane_bytes()),
-                              (unsigned)dO.Np, s);
-  if (rc != MQ_OK) return rc;
+  if (!sums_cleared) {
+    const int rc = launch_clear_words(reinterpret_cast<unsigned*>(static_cast<uint8_t*>(packed_out) + dO.plane_bytes()),
+                                      (unsigned)dO.Np, s);
+    if (rc != MQ_OK) return rc;
+  }
   GemmArgs b = a;
   b.s_out = const_cast<float*>(s_fixed);
   b.packed_out = packed_out;

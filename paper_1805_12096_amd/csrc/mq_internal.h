@@ -107,8 +107,9 @@ int launch_gemm_small_f32(const float* A, const float* scale, unsigned npartial,
 // partial maxima of its own (n1, n2 >= 1): the concatenation is never stored.  K1 must be a multiple of 4.
 int launch_gemm_small_f32_pair(const float* A1, size_t K1, const float* part1, unsigned n1, const float* A2,
                                const float* part2, unsigned n2, float* scale_out, const GemmArgs& a, hipStream_t s);
+// clear / nclear (optional): words of a later kernel that this one zeroes.
 int launch_quantize_pack(const float* x, size_t rows, size_t cols, int bits, const float* scale,
-                         void* packed, hipStream_t s);
+                         void* packed, hipStream_t s, unsigned* clear = nullptr, unsigned nclear = 0);
 int launch_argmax_init(unsigned long long* keys, size_t M, hipStream_t s);
 int launch_argmax_finish(const unsigned long long* keys, size_t M, const float* sA, const float* sW,
                          int32_t* tok, float* maxlogit, hipStream_t s);
@@ -166,7 +167,9 @@ int launch_fill_pattern(void* p, size_t bytes, unsigned seed, hipStream_t s);   
 int launch_gemm_requant_coop(const GemmArgs& a, float* s_out, void* packed_out, unsigned* barrier,
                              hipStream_t s);
 int launch_gemm_requant_fixed(const GemmArgs& a, const float* s_fixed, void* packed_out, hipStream_t s);
-int launch_gemm_requant_fixed_i16(const GemmArgs& a, const float* s_fixed, void* packed_out, hipStream_t s);
+// sums_cleared: the row sums inside packed_out are zero already (an earlier kernel on the stream zeroed them).
+int launch_gemm_requant_fixed_i16(const GemmArgs& a, const float* s_fixed, void* packed_out, hipStream_t s,
+                                  bool sums_cleared = false);
 // Tiled 8-bit product with two extra waves per workgroup that only load (mq_gemm_prod.hip); variants 11 .. 13.
 int launch_gemm_prod(const GemmArgs& a, Epilogue epi, int which, hipStream_t s);
 // Variant 14 of the packed 8-bit products (mq_gemm_ks.hip): 128 x 128 tile, K split over two groups of four waves.

@@ -35,7 +35,8 @@ __global__ void k_fill_pattern(uint32_t* p, size_t nwords, uint32_t seed) {
 }
 
 __global__ void k_clear_words(uint32_t* p, unsigned n) {
-  for (unsigned i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0u;
+  const unsigned i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) p[i] = 0u;
 }
 
 // |x| of a non-NaN float orders like its bit pattern, so the grid-wide maximum
@@ -245,6 +246,7 @@ namespace {
 
 // Abs-max without atomics or initialisation: block b writes its maximum to partial[b];
 // the consumer reduces the few hundred values itself (block_max_of_partials).
+constexpr int kAbsmaxFlight = 4;
 __global__ __launch_bounds__(kThreads) void k_absmax_partial(const float* __restrict__ x, size_t n,
                                                              float* __restrict__ partial, unsigned* clear, unsigned nclear) {
   if (clear != nullptr && blockIdx.x == 0)                 // a later kernel's counters
@@ -253,19 +255,18 @@ __global__ __launch_bounds__(kThreads) void k_absmax_partial(const float* __rest
   const size_t nthreads = (size_t)gridDim.x * kThreads;
   const size_t nvec = n / 4;
   const float4* xv = reinterpret_cast<const float4*>(x);
-  float m0 = 0.f, m1 = 0.f;
-  size_t i = tid;
-  for (; i + nthreads < nvec; i += 2 * nthreads) {
-    const float4 a = xv[i], b = xv[i + nthreads];
-    m0 = fmaxf(m0, fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))));
-    m1 = fmaxf(m1, fmaxf(fmaxf(fabsf(b.x), fabsf(b.y)), fmaxf(fabsf(b.z), fabsf(b.w))));
+  float m0 = 0.f;
+  // kAbsmaxFlight loads in flight per thread (past the end: the last vector again, which changes nothing)
+  for (size_t i = tid; i < nvec; i += kAbsmaxFlight * nthreads) {
+    float4 a[kAbsmaxFlight];
+#pragma unroll
+    for (int t = 0; t < kAbsmaxFlight; ++t) a[t] = xv[i + t * nthreads < nvec ? i + t * nthreads : nvec - 1];
+#pragma unroll
+    for (int t = 0; t < kAbsmaxFlight; ++t)
+      m0 = fmaxf(m0, fmaxf(fmaxf(fabsf(a[t].x), fabsf(a[t].y)), fmaxf(fabsf(a[t].z), fabsf(a[t].w))));
   }
-  for (; i < nvec; i += nthreads) {
-    const float4 a = xv[i];
-    m0 = fmaxf(m0, fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))));
-  }
-  for (size_t j = nvec * 4 + tid; j < n; j += nthreads) m1 = fmaxf(m1, fabsf(x[j]));
-  const float m = wave_max(fmaxf(m0, m1));
+  for (size_t j = nvec * 4 + tid; j < n; j += nthreads) m0 = fmaxf(m0, fabsf(x[j]));
+  const float m = __uint_as_float(wave_max_u32(__float_as_uint(m0)));
   __shared__ float part[kThreads / kWave];
   const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
   if (lane == 0) part[w] = m;
@@ -281,8 +282,14 @@ __global__ __launch_bounds__(kThreads) void k_absmax_partial(const float* __rest
 // Maximum of `count` partial maxima, computed redundantly by every block that needs it.
 __device__ __forceinline__ float block_max_of_partials(const float* __restrict__ partial, unsigned count) {
   float m = 0.f;
-  for (unsigned i = threadIdx.x; i < count; i += kThreads) m = fmaxf(m, partial[i]);
-  m = wave_max(m);
+  for (unsigned i0 = 0; i0 < count; i0 += 4 * kThreads) {      // kAbsmaxPartials of them: one trip, four loads in flight
+    float v[4];
+#pragma unroll
+    for (unsigned t = 0; t < 4; ++t) v[t] = partial[min(i0 + t * kThreads + threadIdx.x, count - 1)];
+#pragma unroll
+    for (unsigned t = 0; t < 4; ++t) m = fmaxf(m, v[t]);
+  }
+  m = __uint_as_float(wave_max_u32(__float_as_uint(m)));      // non-negative: ordered like its bits
   __shared__ float red[kThreads / kWave];
   if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = m;
   __syncthreads();
@@ -292,15 +299,84 @@ __device__ __forceinline__ float block_max_of_partials(const float* __restrict__
   return r;
 }
 
+// Four consecutive elements of a row from column k on, always from addresses inside the tensor (what lies past its end is
+// masked after the conversion): a load under a condition is a branch with a wait of its own behind it, which makes the
+// loads of a trip follow one another instead of being in flight together (quantizing kernel of a 5003 x 1024 product 7.4
+// -> 6.4 us = 4.0 TB/s, of 8192 x 4096 to 16 bit 35.7 -> 34.3 us = 5.9 TB/s; one-kernel form, 300 x 512, 4.8 -> 4.6 us).
+template <bool VEC>
+__device__ __forceinline__ float4 load4_clamped(const float* __restrict__ row, unsigned k, unsigned cols) {
+  if constexpr (VEC) {                       // cols is a multiple of 4, rows are 16-byte aligned
+    return *reinterpret_cast<const float4*>(row + min(k, cols - 4));
+  } else {
+    const unsigned last = cols - 1;
+    return make_float4(row[min(k, last)], row[min(k + 1, last)], row[min(k + 2, last)], row[min(k + 3, last)]);
+  }
+}
+// Bit masks that clear the bytes of elements k .. k + 3 that lie past the row's end, or all of them past the last row.
+template <bool VEC>
+__device__ __forceinline__ uint32_t mask4(bool row_ok, unsigned k, unsigned cols) {
+  if constexpr (VEC) {
+    return row_ok && k < cols ? 0xFFFFFFFFu : 0u;
+  } else {
+    const unsigned n = row_ok && k < cols ? min(cols - k, 4u) : 0u;
+    return n == 0 ? 0u : 0xFFFFFFFFu >> (8 * (4 - n));
+  }
+}
+
+// Converts four elements and stores their bytes at dst (16 bit: two planes; q = 256 h + l + 128, high bytes and low
+// bytes with the top bit flipped).  Returns the sum of the four quantized values (16 bit).
+template <int BITS>
+__device__ __forceinline__ int store4(uint8_t* dst, float4 v, float s, float lim, uint32_t mask) {
+  const int q0 = quant1(v.x, s, lim), q1 = quant1(v.y, s, lim), q2 = quant1(v.z, s, lim), q3 = quant1(v.w, s, lim);
+  const uint32_t lo = pack4_i8(q0, q1, q2, q3) & mask;
+  if constexpr (BITS == 8) {
+    *reinterpret_cast<uint32_t*>(dst) = lo;
+    return 0;
+  } else {
+    const uint32_t hi = pack4_i8(q0 >> 8, q1 >> 8, q2 >> 8, q3 >> 8) & mask;
+    *reinterpret_cast<uint32_t*>(dst) = hi;
+    *reinterpret_cast<uint32_t*>(dst + kFragBytes) = lo ^ 0x80808080u;
+    // sum of the values = sum of the low bytes (unsigned) + 256 x sum of the high bytes (signed)
+    return (int)__builtin_amdgcn_udot4(lo, 0x01010101u, 0u, false) + 256 * __builtin_amdgcn_sdot4((int)hi, 0x01010101, 0, false);
+  }
+}
+
 // FROM_PARTIALS: `scale` holds `npartial` partial abs-maxima instead of the multiplier; the
 // multiplier Qmax / max is formed here (one correctly rounded division) and block 0 also
 // publishes it in scale_out[0] for the product kernels that follow.
+// A work item is `per` fragments along K of a group of eight rows, kQuantFlight of them loaded at a time; the first item's
+// first loads go out before the partial maxima are asked for, so that the two round trips to memory are one.
+constexpr int kQuantFlight = 4;
 template <int BITS, bool VEC, bool FROM_PARTIALS>
 __global__ __launch_bounds__(kThreads) void k_quantize_pack(const float* __restrict__ x, size_t rows,
                                                             size_t cols, const float* __restrict__ scale,
                                                             uint8_t* __restrict__ packed, unsigned ksplit,
-                                                            unsigned npartial, float* __restrict__ scale_out) {
+                                                            unsigned npartial, float* __restrict__ scale_out,
+                                                            unsigned* __restrict__ clear, unsigned nclear) {
+  // words a later kernel wants zero (spread over the grid: one workgroup walking through them is a serial tail)
+  for (unsigned i = blockIdx.x * kThreads + threadIdx.x; i < nclear; i += gridDim.x * kThreads) clear[i] = 0u;
   const PackedDims d(BITS, rows, cols);
+  const float lim = BITS == 8 ? 127.0f : 32767.0f;
+  const int lane = threadIdx.x % kWave;
+  const int sub = lane % 8;                       // which 4 floats of a 32-element fragment row
+  // (indexes of fragments, row groups and items fit 32 bits: rows and columns are below 2^31, items below 2^29 x 16)
+  const unsigned kfrags = (unsigned)d.kfrags, row_groups = (unsigned)(d.Np / 8);
+  const unsigned wave = blockIdx.x * (kThreads / kWave) + threadIdx.x / kWave;
+  const unsigned nwaves = gridDim.x * (kThreads / kWave);
+  const unsigned per = (kfrags + ksplit - 1) / ksplit;   // fragments along K per work item
+  // 16 bit, long rows: the workgroup's waves share a row group, each takes its part of K (four times the loads in
+  // flight of one wave per row group, which leaves a chip with a thousand row groups at four waves per compute
+  // unit), and the rows' sums meet in LDS.  ksplit is the number of waves of the workgroup then.
+  const bool shared_rows = BITS == 16 && ksplit > 1;
+  unsigned rg = shared_rows ? blockIdx.x : wave / ksplit, part = shared_rows ? threadIdx.x / kWave : wave % ksplit;
+  const unsigned ncols = (unsigned)cols, nrows = (unsigned)rows;
+  float4 v[kQuantFlight];
+  auto load = [&](unsigned kb0) {
+    const float* xr = x + (size_t)min(rg * 8 + lane / 8, nrows - 1) * cols;
+#pragma unroll
+    for (int j = 0; j < kQuantFlight; ++j) v[j] = load4_clamped<VEC>(xr, (kb0 + j) * kFragK + 4 * sub, ncols);
+  };
+  if (rg < row_groups) load(part * per);
   float s;
   if (FROM_PARTIALS) {
     const float amax = block_max_of_partials(scale, npartial);
@@ -309,54 +385,19 @@ __global__ __launch_bounds__(kThreads) void k_quantize_pack(const float* __restr
   } else {
     s = *scale;
   }
-  const float lim = BITS == 8 ? 127.0f : 32767.0f;
-  const int lane = threadIdx.x % kWave;
-  const int sub = lane % 8;                       // which 4 floats of a 32-element fragment row
-  const size_t wave = (size_t)blockIdx.x * (kThreads / kWave) + threadIdx.x / kWave;
-  const size_t nwaves = (size_t)gridDim.x * (kThreads / kWave);
-  const size_t row_groups = d.Np / 8;
-  const size_t per = (d.kfrags + ksplit - 1) / ksplit;   // fragments along K per work item
-  // fragments [part * per, ...) of row group rg; returns the lane's share of the rows' sums (16 bit)
-  auto convert = [&](size_t rg, size_t part) -> int {
-    const size_t row = rg * 8 + lane / 8;
-    const size_t kb_end = (part + 1) * per < d.kfrags ? (part + 1) * per : d.kfrags;
-    const size_t nb = row / kFragRows;
-    const int slot = (int)(row % kFragRows) + 32 * (sub / 4);
+  // the item (rg, part), whose first loads are in v; returns the lane's share of the rows' sums (16 bit)
+  auto convert = [&]() -> int {
+    const unsigned row = rg * 8 + lane / 8;
+    const unsigned kb_end = (part + 1) * per < kfrags ? (part + 1) * per : kfrags;
+    uint8_t* out = packed + d.frag_offset(row / kFragRows, 0) + (row % kFragRows + 32 * (sub / 4)) * 16 + 4 * (sub % 4);
     int sum = 0;
-    // four fragments per trip: all four loads are issued before the first conversion, so several
-    // 128-byte lines per row are in flight instead of one
-    for (size_t kb0 = part * per; kb0 < kb_end; kb0 += 4) {
-      float4 v[4];
+    for (unsigned kb0 = part * per; kb0 < kb_end; kb0 += kQuantFlight) {
+      if (kb0 != part * per) load(kb0);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const size_t k = (kb0 + j) * kFragK + 4 * sub;
-        v[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (kb0 + j < kb_end && row < rows) {
-          if (VEC) {
-            if (k < cols) v[j] = *reinterpret_cast<const float4*>(x + row * cols + k);
-          } else {
-            const float* xr = x + row * cols;
-            if (k + 0 < cols) v[j].x = xr[k + 0];
-            if (k + 1 < cols) v[j].y = xr[k + 1];
-            if (k + 2 < cols) v[j].z = xr[k + 2];
-            if (k + 3 < cols) v[j].w = xr[k + 3];
-          }
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < kQuantFlight; ++j) {
         if (kb0 + j >= kb_end) break;
-        const int q0 = quant1(v[j].x, s, lim), q1 = quant1(v[j].y, s, lim), q2 = quant1(v[j].z, s, lim),
-                  q3 = quant1(v[j].w, s, lim);
-        uint8_t* dst = packed + d.frag_offset(nb, kb0 + j) + (size_t)slot * 16 + 4 * (sub % 4);
-        if (BITS == 8) {
-          *reinterpret_cast<uint32_t*>(dst) = pack4_i8(q0, q1, q2, q3);
-        } else {
-          sum += q0 + q1 + q2 + q3;
-          // q = 256 h + l + 128: high bytes, and low bytes with the top bit flipped
-          *reinterpret_cast<uint32_t*>(dst) = pack4_i8(q0 >> 8, q1 >> 8, q2 >> 8, q3 >> 8);
-          *reinterpret_cast<uint32_t*>(dst + kFragBytes) = pack4_i8(q0, q1, q2, q3) ^ 0x80808080u;
-        }
+        sum += store4<BITS>(out + (size_t)(kb0 + j) * (kFragBytes * (BITS == 16 ? 2 : 1)), v[j], s, lim,
+                            mask4<VEC>(row < nrows, (kb0 + j) * kFragK + 4 * sub, ncols));
       }
     }
     if (BITS == 16) {
@@ -366,29 +407,30 @@ __global__ __launch_bounds__(kThreads) void k_quantize_pack(const float* __restr
     }
     return sum;
   };
-  if (BITS == 16 && ksplit > 1) {
-    // 16 bit, long rows: the workgroup's waves share a row group, each takes its part of K (four times the loads in
-    // flight of one wave per row group, which leaves a chip with a thousand row groups at four waves per compute
-    // unit), and the rows' sums meet in LDS.  ksplit is the number of waves of the workgroup here.
+  if (shared_rows) {
     __shared__ int s_part[kThreads / kWave][8];
-    const int w = threadIdx.x / kWave;
-    for (size_t rg = blockIdx.x; rg < row_groups; rg += gridDim.x) {
-      const int sum = convert(rg, (size_t)w);
-      if (sub == 0) s_part[w][lane / 8] = sum;
+    for (; rg < row_groups; rg += gridDim.x) {
+      if (rg != blockIdx.x) load(part * per);
+      const int sum = convert();
+      if (sub == 0) s_part[part][lane / 8] = sum;
       __syncthreads();
-      if (w == 0 && sub == 0) {
+      if (part == 0 && sub == 0) {
         int total = 0;
 #pragma unroll
         for (int k = 0; k < kThreads / kWave; ++k) total += s_part[k][lane / 8];
-        reinterpret_cast<int32_t*>(packed + d.plane_bytes())[rg * 8 + lane / 8] = total;
+        reinterpret_cast<int32_t*>(packed + d.plane_bytes())[(size_t)rg * 8 + lane / 8] = total;
       }
       __syncthreads();
     }
     return;
   }
-  for (size_t item = wave; item < row_groups * ksplit; item += nwaves) {
-    const size_t rg = item / ksplit, part = item % ksplit;
-    const int sum = convert(rg, part);
+  for (unsigned item = wave; item < row_groups * ksplit; item += nwaves) {
+    if (item != wave) {
+      rg = item / ksplit;
+      part = item % ksplit;
+      load(part * per);
+    }
+    const int sum = convert();
     // 16 bit here: one wave owns whole rows
     if (BITS == 16 && sub == 0) reinterpret_cast<int32_t*>(packed + d.plane_bytes())[rg * 8 + lane / 8] = sum;
   }
@@ -421,27 +463,16 @@ __global__ __launch_bounds__(512) void k_absmax_quantize_pack(const float* __res
   const size_t row = rg * 8 + lane / 8;
   const size_t kb_begin = part * per;
   const size_t kb_end = (part + 1) * per < d.kfrags ? (part + 1) * per : d.kfrags;
+  // every load from inside the tensor and without a condition around it (see load4_clamped); fragments past this wave's
+  // part and inactive waves read elements that other lanes hold as well, so the maximum needs no mask
+  const unsigned ncols = (unsigned)cols;
+  const float* xr = x + min(row, rows - 1) * cols;
   float4 v[NI][4];
   float m = 0.f;
 #pragma unroll
   for (int t = 0; t < NI; ++t)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const size_t kb = kb_begin + 4 * t + j;
-      const size_t k = kb * kFragK + 4 * sub;
-      v[t][j] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (active && kb < kb_end && row < rows) {
-        if (VEC) {
-          if (k < cols) v[t][j] = *reinterpret_cast<const float4*>(x + row * cols + k);
-        } else {
-          const float* xr = x + row * cols;
-          if (k + 0 < cols) v[t][j].x = xr[k + 0];
-          if (k + 1 < cols) v[t][j].y = xr[k + 1];
-          if (k + 2 < cols) v[t][j].z = xr[k + 2];
-          if (k + 3 < cols) v[t][j].w = xr[k + 3];
-        }
-      }
-    }
+    for (int j = 0; j < 4; ++j) v[t][j] = load4_clamped<VEC>(xr, ((unsigned)kb_begin + 4 * t + j) * kFragK + 4 * sub, ncols);
 #pragma unroll
   for (int t = 0; t < NI; ++t)
 #pragma unroll
@@ -476,19 +507,9 @@ __global__ __launch_bounds__(512) void k_absmax_quantize_pack(const float* __res
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const size_t kb = kb_begin + 4 * t + j;
-        if (kb < kb_end) {
-          const int q0 = quant1(v[t][j].x, s, lim), q1 = quant1(v[t][j].y, s, lim), q2 = quant1(v[t][j].z, s, lim),
-                    q3 = quant1(v[t][j].w, s, lim);
-          uint8_t* dst = packed + d.frag_offset(nb, kb) + (size_t)slot * 16 + 4 * (sub % 4);
-          if (BITS == 8) {
-            *reinterpret_cast<uint32_t*>(dst) = pack4_i8(q0, q1, q2, q3);
-          } else {
-            sum += q0 + q1 + q2 + q3;
-            // q = 256 h + l + 128: high bytes, and low bytes with the top bit flipped
-            *reinterpret_cast<uint32_t*>(dst) = pack4_i8(q0 >> 8, q1 >> 8, q2 >> 8, q3 >> 8);
-            *reinterpret_cast<uint32_t*>(dst + kFragBytes) = pack4_i8(q0, q1, q2, q3) ^ 0x80808080u;
-          }
-        }
+        if (kb < kb_end)
+          sum += store4<BITS>(packed + d.frag_offset(nb, kb) + (size_t)slot * 16 + 4 * (sub % 4), v[t][j], s, lim,
+                              mask4<VEC>(row < rows, (unsigned)kb * kFragK + 4 * sub, ncols));
       }
   }
   if (BITS == 16) {
@@ -526,7 +547,7 @@ __global__ __launch_bounds__(512) void k_absmax_quantize_pack(const float* __res
 }  // namespace
 
 int launch_quantize_pack(const float* x, size_t rows, size_t cols, int bits, const float* scale,
-                         void* packed, hipStream_t s) {
+                         void* packed, hipStream_t s, unsigned* clear, unsigned nclear) {
   const PackedDims d(bits, rows, cols);
   const size_t row_groups = d.Np / 8;
   // 8-bit: split K so that even a 300-row batch fills the chip; 16-bit: rows of 512 elements or more are shared by the
@@ -542,11 +563,11 @@ int launch_quantize_pack(const float* x, size_t rows, size_t cols, int bits, con
   const bool vec = cols % 4 == 0;
   float* none = nullptr;
   if (bits == 8) {
-    if (vec) hipLaunchKernelGGL((k_quantize_pack<8, true, false>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, scale, p, ksplit, 0u, none);
-    else hipLaunchKernelGGL((k_quantize_pack<8, false, false>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, scale, p, ksplit, 0u, none);
+    if (vec) hipLaunchKernelGGL((k_quantize_pack<8, true, false>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, scale, p, ksplit, 0u, none, clear, nclear);
+    else hipLaunchKernelGGL((k_quantize_pack<8, false, false>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, scale, p, ksplit, 0u, none, clear, nclear);
   } else {
-    if (vec) hipLaunchKernelGGL((k_quantize_pack<16, true, false>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, scale, p, ksplit, 0u, none);
-    else hipLaunchKernelGGL((k_quantize_pack<16, false, false>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, scale, p, ksplit, 0u, none);
+    if (vec) hipLaunchKernelGGL((k_quantize_pack<16, true, false>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, scale, p, ksplit, 0u, none, clear, nclear);
+    else hipLaunchKernelGGL((k_quantize_pack<16, false, false>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, scale, p, ksplit, 0u, none, clear, nclear);
   }
   return check_hip(hipGetLastError());
 }
@@ -560,7 +581,8 @@ int launch_fill_pattern(void* p, size_t bytes, unsigned seed, hipStream_t s) {
 }
 
 int launch_clear_words(unsigned* p, unsigned n, hipStream_t s) {
-  hipLaunchKernelGGL(k_clear_words, dim3(1), dim3(256), 0, s, reinterpret_cast<uint32_t*>(p), n);
+  if (n == 0) return MQ_OK;
+  hipLaunchKernelGGL(k_clear_words, dim3((n + 255) / 256), dim3(256), 0, s, reinterpret_cast<uint32_t*>(p), n);
   return check_hip(hipGetLastError());
 }
 
@@ -581,11 +603,11 @@ int launch_quantize_pack_partials(const float* x, size_t rows, size_t cols, int 
   uint8_t* p = static_cast<uint8_t*>(packed);
   const bool vec = cols % 4 == 0;
   if (bits == 8) {
-    if (vec) hipLaunchKernelGGL((k_quantize_pack<8, true, true>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, partials, p, ksplit, g1, scale_out);
-    else hipLaunchKernelGGL((k_quantize_pack<8, false, true>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, partials, p, ksplit, g1, scale_out);
+    if (vec) hipLaunchKernelGGL((k_quantize_pack<8, true, true>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, partials, p, ksplit, g1, scale_out, (unsigned*)nullptr, 0u);
+    else hipLaunchKernelGGL((k_quantize_pack<8, false, true>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, partials, p, ksplit, g1, scale_out, (unsigned*)nullptr, 0u);
   } else {
-    if (vec) hipLaunchKernelGGL((k_quantize_pack<16, true, true>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, partials, p, ksplit, g1, scale_out);
-    else hipLaunchKernelGGL((k_quantize_pack<16, false, true>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, partials, p, ksplit, g1, scale_out);
+    if (vec) hipLaunchKernelGGL((k_quantize_pack<16, true, true>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, partials, p, ksplit, g1, scale_out, (unsigned*)nullptr, 0u);
+    else hipLaunchKernelGGL((k_quantize_pack<16, false, true>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, partials, p, ksplit, g1, scale_out, (unsigned*)nullptr, 0u);
   }
   return check_hip(hipGetLastError());
 }
