@@ -51,16 +51,17 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small(const Params p, const in
   const uint8_t* w_src = p.packedW + dW.frag_offset(tile_n, 0) + lane * 16;
 
   // The epilogue's constants are asked for before the operands: loaded where they are used, they are a memory
-  // round trip that nothing hides.  Every element a thread finishes has e % 64 == lane, so they share the
-  // column n and the bias.
+  // round trip that nothing hides.  They are only looked at after the operands have been asked for as well, and no
+  // load sits under a condition (a branch with a wait behind it): where there is nothing to load, a valid address is
+  // read and the value not used.  Every element a thread finishes has e % 64 == lane, so they share the column n and
+  // the bias.
   const int lj = lane % 32, lh = lane / 32;
   const unsigned n = tile_n * 32 + lj;
   const bool n_ok = n < p.N;
-  float u = 0.f, bias = 0.f, local_amax = 0.f;
-  if (dequant) {
-    u = __fdiv_rn(1.0f, __fmul_rn(*p.sA, *p.sW));
-    if (p.bias != nullptr && n_ok) bias = p.bias[n];
-  }
+  const float* some = reinterpret_cast<const float*>(p.packedW);
+  const bool has_bias = dequant && p.bias != nullptr;
+  const float s_a = *(dequant ? p.sA : some), s_w = *(dequant ? p.sW : some);
+  const float bias_raw = (has_bias ? p.bias : some)[has_bias ? min(n, p.N - 1) : 0u];
 
   // The partial sums meet in vectors of V rows, the widest that leaves every thread one: vector i of a thread holds rows
   // row_of(i) .. + V - 1 of column n.  16 bit: their sums and the column's are asked for here as well.
@@ -72,15 +73,15 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small(const Params p, const in
     return (tile_m * TMW + mt) * 32 + 8 * (r / 4) + 4 * lh + r % 4;
   };
   uint32_t rs[BITS == 16 ? NV : 1][V];
-  uint32_t corr = 0;
+  uint32_t cs = 0;
   if constexpr (BITS == 16) {
     const uint32_t* rowsum = reinterpret_cast<const uint32_t*>(p.qA + dA.plane_bytes());
     const uint32_t* colsum = reinterpret_cast<const uint32_t*>(p.packedW + dW.plane_bytes());
-    corr = 128u * (n_ok ? colsum[n] : 0u) - 16384u * p.K;
+    cs = colsum[n];                                                // (the sums cover the padded rows of both operands)
 #pragma unroll
     for (int i = 0; i < NV; ++i)
 #pragma unroll
-      for (int t = 0; t < V; ++t) rs[i][t] = row_of(i) + t < p.M ? rowsum[row_of(i) + t] : 0u;
+      for (int t = 0; t < V; ++t) rs[i][t] = rowsum[min(row_of(i) + t, (unsigned)dA.Np - 1)];
   }
 
   v16i acc[TMW][NACC];
@@ -123,6 +124,9 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small(const Params p, const in
     }
   }
 
+  const float u = dequant ? __fdiv_rn(1.0f, __fmul_rn(s_a, s_w)) : 0.f, bias = has_bias ? bias_raw : 0.f;
+  const uint32_t corr = 128u * cs - 16384u * p.K;
+  float local_amax = 0.f;
   // partial sums of this wave, V consecutive rows at a time: vector e = group * 64 + lane, group = (mt * 16 + r) / V
   Vec* mine = reinterpret_cast<Vec*>(part) + wave * (TMW * 1024 / V);
 #pragma unroll
@@ -324,22 +328,41 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small_f32(const SmallF32Params
 #pragma unroll
     for (int i = 0; i < 16; ++i) fa[i] = *reinterpret_cast<const float4*>(base + (size_t)a_row[i] * ld);
   };
-  // the epilogue's constants first (see k_gemm_small): a thread's elements lie in column block
-  // c = (i KS 64) / 1024 of the tile, all at column lj of it
+  // The partial maxima and the epilogue's constants first, without conditions around the loads (see k_gemm_small): memory
+  // answers in order, so what the multiplier waits for must not stand behind the operands, nor follow its own first trip.
+  // A trip serves PV maxima per thread, all 1024 that the producers leave at most.
+  constexpr unsigned T = KS * 64, PV = 1024 / T;
+  float pv[GIVEN ? 1 : 2 * PV];
+  if constexpr (!GIVEN) {
+    const unsigned n1 = p.npartial, n2 = p.npartial2;
+#pragma unroll
+    for (unsigned t = 0; t < PV; ++t) pv[t] = p.scale[min(t * T + tid, n1 - 1)];
+    const float* second = n2 != 0 ? p.scale2 : p.scale;          // no second piece: the first one's maxima again
+    const unsigned last2 = (n2 != 0 ? n2 : n1) - 1;
+#pragma unroll
+    for (unsigned t = 0; t < PV; ++t) pv[PV + t] = second[min(t * T + tid, last2)];
+  }
   const float sW_pre = *p.sW;
   float bias_pre[TNW];
+  const bool has_bias = p.bias != nullptr;
 #pragma unroll
   for (int c = 0; c < TNW; ++c) {
     const unsigned n = (tile_n * TNW + c) * 32 + lj;
-    bias_pre[c] = (p.bias != nullptr && n < p.N) ? p.bias[n] : 0.0f;
+    bias_pre[c] = (has_bias ? p.bias : p.sW)[has_bias ? min(n, p.N - 1) : 0u];
   }
-  if (kb_begin < kb_end) fetch(kb_begin);        // the first round is on its way while the multiplier is formed
+  __builtin_amdgcn_sched_barrier(0);
+  // the first round is on its way while the multiplier is formed (a wave without a run of its own fetches the last
+  // fragments again: under a condition, the wait for the maxima could not tell whether these loads stand behind them)
+  fetch(kb_begin);
+  __builtin_amdgcn_sched_barrier(0);
 
   float s;
   if constexpr (!GIVEN) {
     float m = 0.f;
-    for (unsigned i = tid; i < p.npartial; i += KS * 64) m = fmaxf(m, p.scale[i]);
-    for (unsigned i = tid; i < p.npartial2; i += KS * 64) m = fmaxf(m, p.scale2[i]);
+#pragma unroll
+    for (unsigned t = 0; t < 2 * PV; ++t) m = fmaxf(m, pv[t]);
+    for (unsigned i = PV * T + tid; i < p.npartial; i += T) m = fmaxf(m, p.scale[i]);
+    for (unsigned i = PV * T + tid; i < p.npartial2; i += T) m = fmaxf(m, p.scale2[i]);
     m = __uint_as_float(wave_max_u32(__float_as_uint(m)));
     if (lane == 0) red[wave] = m;
     __syncthreads();
@@ -410,6 +433,7 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small_f32(const SmallF32Params
 #pragma unroll
     for (int cc = 1; cc < TNW; ++cc)
       if (cc == c) bias = bias_pre[cc];
+    if (!has_bias) bias = 0.f;
     const unsigned n = (tile_n * TNW + c) * 32 + lj;
     const unsigned m0 = tile_m * 32 + 8 * (r / 4) + 4 * lh + r % 4;
 #pragma unroll
