@@ -1047,8 +1047,8 @@ int mq_aan_layer_f32(const mq_aan_layer* P, const float* x, const float* g_prev,
     if (want_max) { g.out_amax = hword; out_partials = hword; out_np = 1; }
     return launch_gemm_packed(g, kEpiDequant, s);
   };
-  const size_t np_avg = running_average_partials(M * d);
-  int rc = launch_running_average(g_prev, x, M * d, t, g_out, s, gpart, reinterpret_cast<unsigned*>(hmax), 3, xpart);
+  unsigned np_avg = 0;
+  int rc = launch_running_average(g_prev, x, M * d, t, g_out, s, gpart, reinterpret_cast<unsigned*>(hmax), 3, xpart, &np_avg);
   if (rc != MQ_OK) return rc;
   const float* fpath = g_out;
   const float* fpart = gpart;     // partial maxima of |f|
@@ -1069,7 +1069,7 @@ int mq_aan_layer_f32(const mq_aan_layer* P, const float* x, const float* g_prev,
     if (gemm_small_f32_supported(M, 2 * d, 2 * d) && d % 4 == 0 && fpart != nullptr && fnp >= 1) {
       // the gate's input [x, f] is read from its two pieces (with their partial maxima) inside the product
       // kernel: the concatenation is never stored and its launch disappears
-      rc = launch_gemm_small_f32_pair(x, d, xpart, (unsigned)np_avg, fpath, fpart, (unsigned)fnp, sA, gg, s);
+      rc = launch_gemm_small_f32_pair(x, d, xpart, np_avg, fpath, fpart, (unsigned)fnp, sA, gg, s);
       if (rc != MQ_OK) return rc;
     } else {
       if ((rc = launch_concat2(x, d, fpath, d, M, cat, s, gpart)) != MQ_OK) return rc;

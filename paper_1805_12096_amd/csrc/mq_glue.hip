@@ -5,6 +5,7 @@
 // sub-layer ends in residual + layer normalisation).  All tensors are binary32, a decode step has a
 // few hundred rows of model width, so every kernel here is one short pass over a few 100 KB: one
 // workgroup per sentence, the row staged in LDS, reductions inside the workgroup.
+#include "mq_grid_max.h"
 #include "mq_internal.h"
 
 namespace mq {
@@ -67,6 +68,38 @@ __global__ __launch_bounds__(kT) void k_running_average(const float* __restrict_
   if (partial_x != nullptr) block_absmax_out(fabsf(xv), red, partial_x);
 }
 
+// The same, four elements per thread, for 16-byte aligned tensors of a multiple of 4 elements: a quarter of the workgroups
+// and of the partial maxima the next kernel has to read.
+__global__ __launch_bounds__(kT) void k_running_average4(const float4* __restrict__ g_prev, const float4* __restrict__ x,
+                                                         size_t n4, float tm1, float t, float4* __restrict__ g,
+                                                         float* __restrict__ partial, unsigned* __restrict__ clear,
+                                                         unsigned nclear, float* __restrict__ partial_x) {
+  __shared__ float red[2][kT / kWave];
+  const size_t i = (size_t)blockIdx.x * kT + threadIdx.x, ic = i < n4 ? i : n4 - 1;      // past the end: the last one again
+  const float4 xv = x[ic], gv = g_prev[ic];
+  const float4 v = make_float4(__fdiv_rn(__fmaf_rn(tm1, gv.x, xv.x), t), __fdiv_rn(__fmaf_rn(tm1, gv.y, xv.y), t),
+                               __fdiv_rn(__fmaf_rn(tm1, gv.z, xv.z), t), __fdiv_rn(__fmaf_rn(tm1, gv.w, xv.w), t));
+  if (i < n4) g[i] = v;
+  if (clear != nullptr && blockIdx.x == 0 && threadIdx.x < nclear) clear[threadIdx.x] = 0u;
+  if (partial == nullptr) return;
+  // maxima of |g| and |x| (fmaxf drops NaN; non-negative floats order like their bits)
+  const float mg = fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w)));
+  const float mx = fmaxf(fmaxf(fabsf(xv.x), fabsf(xv.y)), fmaxf(fabsf(xv.z), fabsf(xv.w)));
+  const float wg = __uint_as_float(wave_max_u32(__float_as_uint(fmaxf(mg, 0.f))));
+  const float wx = __uint_as_float(wave_max_u32(__float_as_uint(fmaxf(mx, 0.f))));
+  if (threadIdx.x % kWave == 0) {
+    red[0][threadIdx.x / kWave] = wg;
+    red[1][threadIdx.x / kWave] = wx;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2 && (threadIdx.x == 0 || partial_x != nullptr)) {
+    float r = red[threadIdx.x][0];
+#pragma unroll
+    for (int k = 1; k < kT / kWave; ++k) r = fmaxf(r, red[threadIdx.x][k]);
+    (threadIdx.x == 0 ? partial : partial_x)[blockIdx.x] = r;
+  }
+}
+
 __global__ __launch_bounds__(kT) void k_concat2(const float* __restrict__ a, unsigned da, const float* __restrict__ b,
                                                 unsigned db, float* __restrict__ out, float* __restrict__ partial) {
   __shared__ float red[kT / kWave];
@@ -121,6 +154,73 @@ __global__ __launch_bounds__(kT) void k_layer_norm(const float* __restrict__ a, 
     mx = fmaxf(mx, fabsf(v));
   }
   if (partial != nullptr) block_absmax_out(mx, red, partial);
+}
+
+// The same for rows of 256 CH floats (CH <= 4) with 16-byte alignment: one wave per row, the row in registers, everything
+// the row needs asked for at once (gamma and beta included), reductions by lane moves -- no LDS, no barrier, and no
+// second round trip to memory.
+// The two kernels of a decoder layer (300 x 512) together with the averaging above: 65.3 -> 62.1 us per layer.
+template <bool GATED, int CH>
+__global__ __launch_bounds__(kWave) void k_layer_norm_wave(const float* __restrict__ a, const float* __restrict__ f,
+                                                           const float* __restrict__ z, const float* __restrict__ r,
+                                                           const float* __restrict__ gamma,
+                                                           const float* __restrict__ beta, float eps,
+                                                           float* __restrict__ y, float* __restrict__ partial) {
+  constexpr unsigned d = 256u * CH;
+  const size_t m = blockIdx.x;
+  const unsigned lane = threadIdx.x;
+  auto load = [&](const float* base, int c) { return reinterpret_cast<const float4*>(base)[c * 64 + lane]; };
+  float4 av[CH], rv[CH], fv[CH], z1[CH], z2[CH], gv[CH], bv[CH];
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    av[c] = load(a + m * d, c);
+    if constexpr (GATED) {
+      fv[c] = load(f + m * d, c);
+      z1[c] = load(z + m * 2 * d, c);
+      z2[c] = load(z + m * 2 * d + d, c);
+    }
+    rv[c] = load(r + m * d, c);
+  }
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    gv[c] = load(gamma, c);
+    bv[c] = load(beta, c);
+  }
+  float h[CH][4];
+  float s = 0.f;
+#pragma unroll
+  for (int c = 0; c < CH; ++c)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      auto at = [&](const float4& v) { return t == 0 ? v.x : t == 1 ? v.y : t == 2 ? v.z : v.w; };
+      float v = at(av[c]);
+      if constexpr (GATED) v = sigmoidf_(at(z1[c])) * v + sigmoidf_(at(z2[c])) * at(fv[c]);
+      h[c][t] = v + at(rv[c]);
+      s += h[c][t];
+    }
+  const float mu = wave_sum_f(s) / (float)d;
+  float q = 0.f;
+#pragma unroll
+  for (int c = 0; c < CH; ++c)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      h[c][t] -= mu;
+      q += h[c][t] * h[c][t];
+    }
+  const float var = wave_sum_f(q) / (float)d;
+  const float inv = __fdiv_rn(1.0f, sqrtf(var + eps));
+  float mx = 0.f;
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    const float4 v = make_float4(h[c][0] * inv * gv[c].x + bv[c].x, h[c][1] * inv * gv[c].y + bv[c].y,
+                                 h[c][2] * inv * gv[c].z + bv[c].z, h[c][3] * inv * gv[c].w + bv[c].w);
+    reinterpret_cast<float4*>(y + m * d)[c * 64 + lane] = v;
+    mx = fmaxf(mx, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+  }
+  if (partial != nullptr) {
+    mx = __uint_as_float(wave_max_u32(__float_as_uint(mx)));
+    if (lane == 0) partial[m] = mx;
+  }
 }
 
 // One workgroup per sentence.  Scores of all heads and source positions into LDS (one wave per (head,
@@ -337,12 +437,21 @@ __global__ __launch_bounds__(kTA) void k_cross_attention_fast(const float* __res
 // The launchers' optional `partial` receives one max|output| per workgroup (glue_partials(...) of them).
 size_t running_average_partials(size_t n) { return (n + kT - 1) / kT; }
 
+static bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
+
 int launch_running_average(const float* g_prev, const float* x, size_t n, int t, float* g, hipStream_t s, float* partial,
-                           unsigned* clear, unsigned nclear, float* partial_x) {
-  const size_t blocks = (n + kT - 1) / kT;
+                           unsigned* clear, unsigned nclear, float* partial_x, unsigned* npartial) {
+  const bool vec = n % 4 == 0 && aligned16(g_prev) && aligned16(x) && aligned16(g);
+  const size_t blocks = vec ? (n / 4 + kT - 1) / kT : (n + kT - 1) / kT;
   if (blocks > 0x7FFFFFFFull || nclear > (unsigned)kT) return MQ_ERR_SHAPE;
-  hipLaunchKernelGGL(k_running_average, dim3((unsigned)blocks), dim3(kT), 0, s, g_prev, x, n, (float)(t - 1), (float)t, g,
-                     partial, clear, nclear, partial_x);
+  if (npartial != nullptr) *npartial = (unsigned)blocks;
+  if (vec)
+    hipLaunchKernelGGL(k_running_average4, dim3((unsigned)blocks), dim3(kT), 0, s, reinterpret_cast<const float4*>(g_prev),
+                       reinterpret_cast<const float4*>(x), n / 4, (float)(t - 1), (float)t, reinterpret_cast<float4*>(g),
+                       partial, clear, nclear, partial_x);
+  else
+    hipLaunchKernelGGL(k_running_average, dim3((unsigned)blocks), dim3(kT), 0, s, g_prev, x, n, (float)(t - 1), (float)t, g,
+                       partial, clear, nclear, partial_x);
   return check_hip(hipGetLastError());
 }
 
@@ -352,19 +461,38 @@ int launch_concat2(const float* a, size_t da, const float* b, size_t db, size_t 
   return check_hip(hipGetLastError());
 }
 
+// the wave-per-row kernel where the row fits it; false = not launched
+template <bool GATED>
+static bool launch_layer_norm_wave(const float* a, const float* f, const float* z, const float* r, const float* gamma,
+                                   const float* beta, size_t M, size_t d, float eps, float* y, hipStream_t s, float* partial) {
+  if (d % 256 != 0 || d > 1024) return false;
+  if (!aligned16(a) || !aligned16(r) || !aligned16(gamma) || !aligned16(beta) || !aligned16(y)) return false;
+  if (GATED && (!aligned16(f) || !aligned16(z))) return false;
+  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3((unsigned)M), dim3(kWave), 0, s, a, f, z, r, gamma, beta, eps, y, partial); };
+  switch (d / 256) {
+    case 1: go(k_layer_norm_wave<GATED, 1>); break;
+    case 2: go(k_layer_norm_wave<GATED, 2>); break;
+    case 3: go(k_layer_norm_wave<GATED, 3>); break;
+    default: go(k_layer_norm_wave<GATED, 4>); break;
+  }
+  return true;
+}
+
 int launch_add_layer_norm(const float* a, const float* r, const float* gamma, const float* beta, size_t M, size_t d,
                           float eps, float* y, hipStream_t s, float* partial) {
   if (d > (size_t)kMaxRow) return MQ_ERR_UNSUPPORTED;
-  hipLaunchKernelGGL((k_layer_norm<false>), dim3((unsigned)M), dim3(kT), 0, s, a, (const float*)nullptr,
-                     (const float*)nullptr, r, gamma, beta, (unsigned)d, eps, y, partial);
+  if (!launch_layer_norm_wave<false>(a, nullptr, nullptr, r, gamma, beta, M, d, eps, y, s, partial))
+    hipLaunchKernelGGL((k_layer_norm<false>), dim3((unsigned)M), dim3(kT), 0, s, a, (const float*)nullptr,
+                       (const float*)nullptr, r, gamma, beta, (unsigned)d, eps, y, partial);
   return check_hip(hipGetLastError());
 }
 
 int launch_gate_mix_layer_norm(const float* x, const float* f, const float* z, const float* gamma, const float* beta,
                                size_t M, size_t d, float eps, float* y, hipStream_t s, float* partial) {
   if (d > (size_t)kMaxRow) return MQ_ERR_UNSUPPORTED;
-  hipLaunchKernelGGL((k_layer_norm<true>), dim3((unsigned)M), dim3(kT), 0, s, x, f, z, x, gamma, beta, (unsigned)d, eps, y,
-                     partial);
+  if (!launch_layer_norm_wave<true>(x, f, z, x, gamma, beta, M, d, eps, y, s, partial))
+    hipLaunchKernelGGL((k_layer_norm<true>), dim3((unsigned)M), dim3(kT), 0, s, x, f, z, x, gamma, beta, (unsigned)d, eps, y,
+                       partial);
   return check_hip(hipGetLastError());
 }
 

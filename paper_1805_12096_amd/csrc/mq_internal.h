@@ -153,7 +153,8 @@ int launch_topk_stream(const void* packedA, const void* packedW, size_t M, size_
 size_t running_average_partials(size_t n);
 int launch_running_average(const float* g_prev, const float* x, size_t n, int t, float* g, hipStream_t s,
                            float* partial = nullptr, unsigned* clear = nullptr, unsigned nclear = 0,
-                           float* partial_x = nullptr);     // partial_x: the same number of maxima of |x|
+                           float* partial_x = nullptr, unsigned* npartial = nullptr);
+                           // partial_x: the same number of maxima of |x|; *npartial: how many (at most running_average_partials)
 int launch_concat2(const float* a, size_t da, const float* b, size_t db, size_t M, float* out, hipStream_t s,
                    float* partial = nullptr);
 int launch_add_layer_norm(const float* a, const float* r, const float* gamma, const float* beta, size_t M, size_t d,
