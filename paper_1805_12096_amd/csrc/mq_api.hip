@@ -41,6 +41,11 @@ constexpr size_t kMaxElems = (size_t)1 << 40;
 constexpr size_t kMaxDim = (size_t)1 << 31;
 
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
+// whether two arrays of 4-byte elements share memory
+bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t pa = reinterpret_cast<uintptr_t>(a), pb = reinterpret_cast<uintptr_t>(b);
+  return pa < pb + 4 * nb && pb < pa + 4 * na;
+}
 bool bits_ok(int bits) { return bits == 8 || bits == 16; }
 bool dims_ok(size_t M, size_t N, size_t K) {
   if (M == 0 || N == 0 || K == 0) return false;
@@ -869,6 +874,9 @@ int mq_linear_f32(const float* A, size_t M, size_t K, const float* sA_or_null, c
   a.packedW = packedW; a.bits = bits; a.M = M; a.N = N; a.K = K;
   a.sW = sW; a.bias = bias; a.relu = relu != 0; a.Y = Y; a.out_amax = out_amax;
   int rc;
+  // one block of rows: abs-max, quant_int and product in one launch (a forced or tuned variant names a packed product)
+  if (gemm_rows_supported(bits, M, N, K) && forced_variant() == 0 && !overlap(A, M * K, Y, M * N))
+    return launch_gemm_rows(A, sA, a, s);
   if (bits == 8 && gemm_small_f32_supported(M, N, K)) {
     // decode-sized input: quant_int happens inside the product's operand fetch (same arithmetic, same
     // results), one launch with a given multiplier, two with abs-max
@@ -1047,8 +1055,40 @@ int mq_aan_layer_f32(const mq_aan_layer* P, const float* x, const float* g_prev,
     if (want_max) { g.out_amax = hword; out_partials = hword; out_np = 1; }
     return launch_gemm_packed(g, kEpiDequant, s);
   };
+  int rc;
+  if (gemm_rows_glue_supported(M, d) && use_ffn && use_gate && aligned(g_prev, 16) && aligned(P->ln1.gamma, 16) &&
+      aligned(P->ln1.beta, 16) && aligned(P->ln2.gamma, 16) && aligned(P->ln2.beta, 16) && !overlap(g_prev, M * d, g_out, M * d) &&
+      !overlap(x, M * d, g_out, M * d)) {
+    // One block of rows: the running average, the normalisations in front of a product and every quantizer happen in the
+    // operand fetch of the product that follows, and the gate in the epilogue of its own product: nine launches for
+    // fourteen.
+    auto args = [&](const mq_product& W, size_t N, size_t Kdim, int relu, float* Y) {
+      GemmArgs g{};
+      g.packedW = W.packed; g.bits = 8; g.M = M; g.N = N; g.K = Kdim;
+      g.sW = W.scale; g.bias = W.bias; g.relu = relu; g.Y = Y;
+      return g;
+    };
+    // H (with partial maxima, for the form that quantizes in a launch of its own) times the second parameter
+    auto second = [&](size_t width, const mq_product& W, float* Y) {
+      if (gemm_rows_supported(8, M, d, width)) return launch_gemm_rows(hid, nullptr, args(W, d, width, 0, Y), s);
+      return product(hid, width, W, d, 0, Y, hpart, gemm_rows_partials(width), false, nullptr, nullptr);
+    };
+    GemmArgs g1 = args(P->aan_ffn1, aan_ffn, d, 1, hid), g5 = args(P->ffn1, ffn, d, 1, hid);
+    g1.partial = g5.partial = hpart;
+    if (gemm_rows_partials(aan_ffn) > kAbsmaxPartials) g1.partial = nullptr;
+    if (gemm_rows_partials(ffn) > kAbsmaxPartials) g5.partial = nullptr;
+    if ((rc = launch_gemm_rows_average(g_prev, x, t, g_out, g1, s)) != MQ_OK) return rc;
+    if ((rc = second(aan_ffn, P->aan_ffn2, f)) != MQ_OK) return rc;
+    if ((rc = launch_gemm_rows_gate(x, f, args(P->aan_gate, 2 * d, 2 * d, 0, z), s)) != MQ_OK) return rc;
+    if ((rc = launch_gemm_rows_norm(z, x, P->ln1.gamma, P->ln1.beta, eps, y1, args(P->ctx_q, d, d, 0, qv), s)) != MQ_OK) return rc;
+    if ((rc = launch_cross_attention(qv, K, V, M, S, d, heads, ctx, s)) != MQ_OK) return rc;
+    if ((rc = launch_gemm_rows(ctx, nullptr, args(P->ctx_o, d, d, 0, o), s)) != MQ_OK) return rc;
+    if ((rc = launch_gemm_rows_norm(o, y1, P->ln2.gamma, P->ln2.beta, eps, y2, g5, s)) != MQ_OK) return rc;
+    if ((rc = second(ffn, P->ffn2, ff)) != MQ_OK) return rc;
+    return launch_add_layer_norm(ff, y2, P->ln3.gamma, P->ln3.beta, M, d, eps, y, s);
+  }
   unsigned np_avg = 0;
-  int rc = launch_running_average(g_prev, x, M * d, t, g_out, s, gpart, reinterpret_cast<unsigned*>(hmax), 3, xpart, &np_avg);
+  rc = launch_running_average(g_prev, x, M * d, t, g_out, s, gpart, reinterpret_cast<unsigned*>(hmax), 3, xpart, &np_avg);
   if (rc != MQ_OK) return rc;
   const float* fpath = g_out;
   const float* fpart = gpart;     // partial maxima of |f|

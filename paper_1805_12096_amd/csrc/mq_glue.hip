@@ -5,6 +5,7 @@
 // sub-layer ends in residual + layer normalisation).  All tensors are binary32, a decode step has a
 // few hundred rows of model width, so every kernel here is one short pass over a few 100 KB: one
 // workgroup per sentence, the row staged in LDS, reductions inside the workgroup.
+#include "mq_glue.h"
 #include "mq_grid_max.h"
 #include "mq_internal.h"
 
@@ -15,12 +16,6 @@ namespace {
 constexpr int kT = 256;              // threads per workgroup
 constexpr int kMaxRow = 8192;        // floats of a row kept in LDS (32 KB)
 constexpr int kMaxScores = 4096;     // heads x source positions kept in LDS
-
-__device__ __forceinline__ float wave_sum_f(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
-  return v;
-}
 
 // sum over the workgroup; every thread gets the result.  `red` holds kT / 64 floats.
 __device__ __forceinline__ float block_sum(float v, float* red) {
@@ -112,8 +107,6 @@ __global__ __launch_bounds__(kT) void k_concat2(const float* __restrict__ a, uns
   }
   if (partial != nullptr) block_absmax_out(mx, red, partial);
 }
-
-__device__ __forceinline__ float sigmoidf_(float z) { return __fdiv_rn(1.0f, 1.0f + expf(-z)); }
 
 // One workgroup per row: h = GATED ? sigmoid(z[:d]) x + sigmoid(z[d:]) f : a;  y = LN(h + r) gamma + beta with
 // the biased variance, mean and variance as two passes over the row held in LDS.

@@ -107,6 +107,21 @@ int launch_gemm_small_f32(const float* A, const float* scale, unsigned npartial,
 // partial maxima of its own (n1, n2 >= 1): the concatenation is never stored.  K1 must be a multiple of 4.
 int launch_gemm_small_f32_pair(const float* A1, size_t K1, const float* part1, unsigned n1, const float* A2,
                                const float* part2, unsigned n2, float* scale_out, const GemmArgs& a, hipStream_t s);
+// Products of at most 32 rows that read the fp32 input themselves (mq_gemm_rows.hip): every workgroup sees all rows, so
+// the abs-max multiplier (scale == NULL) and the glue in front of the product need no launch of their own.  8 bit, or 16
+// bit for the plain form; K a multiple of 4 up to 2048 (4096 for 8 bit and at most 16 rows), rows 16-byte aligned;
+// a.qA and a.sA are not used.  The result must not overlap the input.  a.partial receives gemm_rows_partials(N) maxima.
+bool gemm_rows_supported(int bits, size_t M, size_t N, size_t K);
+size_t gemm_rows_partials(size_t N);
+int launch_gemm_rows(const float* A, const float* scale, const GemmArgs& a, hipStream_t s);
+// The same with the input formed in the operand fetch, model width d = 256, 512, 768 or 1024, all tensors 16-byte aligned:
+// the running average of (g_prev, x), also written to g; LN(h + r) gamma + beta, also written to y; and the pair [x | f]
+// into a product of 2 d columns whose result is mixed, Y[M x d] = sigmoid(z1) x + sigmoid(z2) f.
+bool gemm_rows_glue_supported(size_t M, size_t d);
+int launch_gemm_rows_average(const float* g_prev, const float* x, int t, float* g, const GemmArgs& a, hipStream_t s);
+int launch_gemm_rows_norm(const float* h, const float* r, const float* gamma, const float* beta, float eps, float* y,
+                          const GemmArgs& a, hipStream_t s);
+int launch_gemm_rows_gate(const float* x, const float* f, const GemmArgs& a, hipStream_t s);
 // clear / nclear (optional): words of a later kernel that this one zeroes.
 int launch_quantize_pack(const float* x, size_t rows, size_t cols, int bits, const float* scale,
                          void* packed, hipStream_t s, unsigned* clear = nullptr, unsigned nclear = 0);

@@ -325,6 +325,39 @@ def test_mq_linear_f32_decode_sizes_special_values():
     assert np.array_equal(host(Y), oracle.linear(B, Wt, 8, bias, False)["Y"])
 
 
+@pytest.mark.parametrize("bits", [8, 16])
+@pytest.mark.parametrize("M,N,K,relu,fixed", [(1, 1, 4, False, False), (8, 33, 60, True, False), (9, 64, 256, False, True),
+                                              (32, 31, 260, True, True), (1, 512, 512, False, False),
+                                              (32, 512, 1024, False, False), (31, 70, 1028, True, False),
+                                              (16, 40, 2048, False, True), (17, 40, 2044, False, False),
+                                              (16, 32, 4096, False, False), (17, 32, 4096, True, False)])
+def test_mq_linear_f32_of_one_row_block(M, N, K, relu, fixed, bits):
+    # one launch up to 32 rows (K a multiple of 4; every edge of its waves, pieces and row counts), with NaN and
+    # infinities (fixed multiplier) or NaN and a lone maximum (abs-max); an in-place call takes the separate quantizer
+    p = workloads.random_problem(M * 5 + N * 3 + K + bits, M, N, K)
+    A = p["A"].copy()
+    A[0, 0], A[-1, -1] = np.nan, 7.25
+    if fixed:
+        A[-1, 1:3] = [np.inf, -np.inf]
+    s0 = None if not fixed else 1024.0 if bits == 16 else 63.5
+    pw = mq.prepare_weight(dev(p["Wt"]), bits)
+    nb = mq.mq_linear_ws_bytes(bits, M, K)
+    ws = torch.full((nb,), 0x5A, dtype=torch.uint8, device=DEV)
+    am = torch.zeros(1, dtype=torch.float32, device=DEV)
+    sA = torch.full((1,), s0, dtype=torch.float32, device=DEV) if fixed else None
+    for bias in (p["bias"], None):
+        want = oracle.linear(A, p["Wt"], bits, bias, relu, sA=s0)["Y"]
+        Y = torch.full((M + 1, N), -3.0, dtype=torch.float32, device=DEV)
+        am.zero_()
+        mq.mq_linear_f32(dev(A), M, K, sA, pw.packed, pw.scale, bits, N, None if bias is None else dev(bias), relu, Y[:M], am, ws, nb)
+        assert np.array_equal(host(Y[:M]), want) and (host(Y[M]) == -3.0).all()
+        assert host(am)[0] == np.abs(want).max()
+    if N == K and bits == 16:
+        B = dev(A)
+        mq.mq_linear_f32(B, M, K, sA, pw.packed, pw.scale, 16, N, None, relu, B, None, ws, nb)
+        assert np.array_equal(host(B), want)
+
+
 # -------------------------------------------------------------------- arg-max
 
 def gpu_greedy(Hd, E, pw=None):
