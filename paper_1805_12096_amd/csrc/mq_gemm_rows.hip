@@ -151,26 +151,25 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_rows(const RowsParams p) {
     }
     if constexpr (IN == kRowsNorm) {
       const float d = (float)p.K;
-      float s = 0.f;
+      float x[CH][4];
 #pragma unroll
       for (int c = 0; c < CH; ++c)
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
           const float h = v[i][c][t] + w[i][c][t];
           v[i][c][t] = h;
-          if (256u * c < p.K) s += h;                               // (K is a multiple of 256)
+          x[c][t] = 256u * c < p.K ? h : 0.f;                       // (K is a multiple of 256)
         }
-      const float mu = wave_sum_f(s) / d;
-      float q = 0.f;
+      const float mu = wave_sum_f(lane_sum_f(x)) / d;
 #pragma unroll
       for (int c = 0; c < CH; ++c)
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
           const float h = v[i][c][t] - mu;
           v[i][c][t] = h;
-          if (256u * c < p.K) q += h * h;
+          x[c][t] = 256u * c < p.K ? h * h : 0.f;
         }
-      const float inv = __fdiv_rn(1.0f, sqrtf(wave_sum_f(q) / d + p.eps));
+      const float inv = __fdiv_rn(1.0f, sqrtf(wave_sum_f(lane_sum_f(x)) / d + p.eps));
 #pragma unroll
       for (int c = 0; c < CH; ++c)
 #pragma unroll

@@ -179,8 +179,7 @@ __global__ __launch_bounds__(kWave) void k_layer_norm_wave(const float* __restri
     gv[c] = load(gamma, c);
     bv[c] = load(beta, c);
   }
-  float h[CH][4];
-  float s = 0.f;
+  float h[CH][4], sq[CH][4];
 #pragma unroll
   for (int c = 0; c < CH; ++c)
 #pragma unroll
@@ -189,18 +188,16 @@ __global__ __launch_bounds__(kWave) void k_layer_norm_wave(const float* __restri
       float v = at(av[c]);
       if constexpr (GATED) v = sigmoidf_(at(z1[c])) * v + sigmoidf_(at(z2[c])) * at(fv[c]);
       h[c][t] = v + at(rv[c]);
-      s += h[c][t];
     }
-  const float mu = wave_sum_f(s) / (float)d;
-  float q = 0.f;
+  const float mu = wave_sum_f(lane_sum_f(h)) / (float)d;
 #pragma unroll
   for (int c = 0; c < CH; ++c)
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       h[c][t] -= mu;
-      q += h[c][t] * h[c][t];
+      sq[c][t] = h[c][t] * h[c][t];
     }
-  const float var = wave_sum_f(q) / (float)d;
+  const float var = wave_sum_f(lane_sum_f(sq)) / (float)d;
   const float inv = __fdiv_rn(1.0f, sqrtf(var + eps));
   float mx = 0.f;
 #pragma unroll
