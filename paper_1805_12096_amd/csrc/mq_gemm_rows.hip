@@ -7,7 +7,7 @@
 // between workgroups, so the glue kernel, the abs-max pass and the quantizer that stood in front of the product
 // disappear: at these sizes each of them is a launch (2.4 us on the host, 2 - 4 us on the device) around a few hundred
 // nanoseconds of work.  The price is that the input is read and converted once per 32 columns.
-// Measured: decoder layer of one sentence (512 / 2048) 53.3 -> 37.1 us, nine launches for fourteen.  Beyond 32 rows a
+// Measured: decoder layer of one sentence (512 / 2048) 53.3 -> 35.6 us, nine launches for fourteen.  Beyond 32 rows a
 // workgroup would have to read rows it does not multiply, which the two-launch forms win.
 #include "mq_gemm_common.h"
 #include "mq_glue.h"
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_rows(const RowsParams p) {
           v[i][c][t] = h;
           x[c][t] = 256u * c < p.K ? h : 0.f;                       // (K is a multiple of 256)
         }
-      const float mu = wave_sum_f(lane_sum_f(x)) / d;
+      const float mu = row_sum_f(x) / d;
 #pragma unroll
       for (int c = 0; c < CH; ++c)
 #pragma unroll
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_rows(const RowsParams p) {
           v[i][c][t] = h;
           x[c][t] = 256u * c < p.K ? h * h : 0.f;
         }
-      const float inv = __fdiv_rn(1.0f, sqrtf(wave_sum_f(lane_sum_f(x)) / d + p.eps));
+      const float inv = __fdiv_rn(1.0f, sqrtf(row_sum_f(x) / d + p.eps));
 #pragma unroll
       for (int c = 0; c < CH; ++c)
 #pragma unroll

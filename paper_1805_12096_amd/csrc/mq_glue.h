@@ -14,16 +14,34 @@ __device__ __forceinline__ float wave_sum_f(float v) {
   return v;
 }
 
-// Sum of the CH x 4 elements of a row that a lane holds, in pairs: as short a chain of additions as with a thread per
-// element.  Layer normalisation of 2048 rows of 256 / 512 / 768 / 1024, relative error against 64 bits: 7.10 / 7.10 / 7.11 /
-// 7.13e-8 (k_layer_norm, a thread per element: 7.12 / 7.13 / 7.23 / 7.06e-8; 300 x 512 with a running sum 7.04e-8, so 6.98).
+// Value of lane (l - N) mod 16 (row_ror) or of another lane of the quad, of the same row of 16 lanes.
+template <int CTRL>
+__device__ __forceinline__ float dpp16_f(float x) {
+  return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xF, 0xF, true));
+}
+
+// Sum of a row of 256 CH floats, lane l of the wave holding elements 256 c + 4 l + t as x[c][t]; the same in every lane.
+// The additions are those of k_layer_norm, a thread per element of a piece and four waves, in the same order -- element
+// by element over the pieces, a tree over 64 neighbours, four of those one after the other -- so that the rows come out the
+// same whichever kernel normalises them: a last bit decides on which side of a half an integer falls further on, and in a
+// decoder layer of one sentence that can move a tensor's maximum with it.
 template <int CH>
-__device__ __forceinline__ float lane_sum_f(const float (&x)[CH][4]) {
-  static_assert(CH <= 4, "pieces of a row per lane");
-  float p[4] = {};
+__device__ __forceinline__ float row_sum_f(const float (&x)[CH][4]) {
+  float p[4];
 #pragma unroll
-  for (int c = 0; c < CH; ++c) p[c] = (x[c][0] + x[c][1]) + (x[c][2] + x[c][3]);
-  return (p[0] + p[1]) + (p[2] + p[3]);
+  for (int t = 0; t < 4; ++t) {
+    p[t] = x[0][t];
+#pragma unroll
+    for (int c = 1; c < CH; ++c) p[t] += x[c][t];
+    // element 64 w + e sits in lane 16 w + e / 4 as t = e % 4: the tree's steps 32, 16, 8, 4 are lanes 8, 4, 2, 1 apart
+    p[t] += dpp16_f<0x128>(p[t]);      // row_ror:8
+    p[t] += dpp16_f<0x124>(p[t]);      // row_ror:4 (lanes 8 apart hold the same value by now)
+    p[t] += dpp16_f<0x4E>(p[t]);       // quad_perm [2,3,0,1]
+    p[t] += dpp16_f<0xB1>(p[t]);       // quad_perm [1,0,3,2]
+  }
+  const unsigned s = __float_as_uint((p[0] + p[2]) + (p[1] + p[3]));
+  auto part = [&](int w) { return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)s, 16 * w)); };
+  return ((part(0) + part(1)) + part(2)) + part(3);
 }
 
 __device__ __forceinline__ float sigmoidf_(float z) { return __fdiv_rn(1.0f, 1.0f + expf(-z)); }

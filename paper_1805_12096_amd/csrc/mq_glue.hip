@@ -191,7 +191,7 @@ __global__ __launch_bounds__(kWave) void k_layer_norm_wave(const float* __restri
       if constexpr (GATED) v = sigmoidf_(at(z1[c])) * v + sigmoidf_(at(z2[c])) * at(fv[c]);
       h[c][t] = v + at(rv[c]);
     }
-  const float mu = wave_sum_f(lane_sum_f(h)) / (float)d;
+  const float mu = row_sum_f(h) / (float)d;
 #pragma unroll
   for (int c = 0; c < CH; ++c)
 #pragma unroll
@@ -199,7 +199,7 @@ __global__ __launch_bounds__(kWave) void k_layer_norm_wave(const float* __restri
       h[c][t] -= mu;
       sq[c][t] = h[c][t] * h[c][t];
     }
-  const float var = wave_sum_f(lane_sum_f(sq)) / (float)d;
+  const float var = row_sum_f(sq) / (float)d;
   const float inv = __fdiv_rn(1.0f, sqrtf(var + eps));
   float mx = 0.f;
 #pragma unroll

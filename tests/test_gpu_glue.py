@@ -76,6 +76,28 @@ def test_gate_mix_layer_norm(M, d):
     assert close(host(y), glue.add_layer_norm(glue.gate_mix(x, f, z), x, gamma, beta, 1e-6))
 
 
+@pytest.mark.parametrize("M,d", [(1, 256), (33, 512), (5, 768), (300, 1024)])
+def test_layer_norm_kernels_give_the_same_bits(M, d):
+    # rows that do not start on 16 bytes take the kernel with a thread per element; the order of the additions is the same
+    rng = np.random.default_rng(M + d)
+
+    def shifted(a):
+        buf = torch.empty(a.size + 4, dtype=torch.float32, device=DEV)
+        v = buf[1:1 + a.size].view(a.shape)
+        v.copy_(dev(a))
+        return v
+
+    a, r, z = (rng.standard_normal(s, dtype=np.float32) for s in ((M, d), (M, d), (M, 2 * d)))
+    gamma, beta = (1 + 0.1 * rng.standard_normal(d)).astype(np.float32), (0.1 * rng.standard_normal(d)).astype(np.float32)
+    got = []
+    for put in (dev, shifted):
+        y1, y2 = (torch.empty((M, d), dtype=torch.float32, device=DEV) for _ in range(2))
+        mq.mq_add_layer_norm_f32(put(a), put(r), put(gamma), put(beta), M, d, 1e-6, y1)
+        mq.mq_gate_mix_layer_norm_f32(put(a), put(r), put(z), put(gamma), put(beta), M, d, 1e-6, y2)
+        got.append((host(y1), host(y2)))
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+
+
 @pytest.mark.parametrize("M,S,d,heads", [(1, 1, 8, 1), (7, 5, 48, 3), (300, 25, 512, 8), (9, 130, 256, 4),
                                           (5, 7, 1024, 16), (6, 9, 512, 4), (4, 3, 256, 64), (3, 6, 512, 2),
                                           # around the rows of V held in registers (8 per thread group) and 64 scores a head
