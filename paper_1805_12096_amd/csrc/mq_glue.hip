@@ -72,15 +72,16 @@ __global__ __launch_bounds__(kT) void k_running_average4(const float4* __restric
                                                          float* __restrict__ partial, unsigned* __restrict__ clear,
                                                          unsigned nclear, float* __restrict__ partial_x) {
   __shared__ float red[2][kT / kWave];
-  const size_t i = (size_t)blockIdx.x * kT + threadIdx.x, ic = i < n4 ? i : n4 - 1;      // past the end: the last one again
+  const size_t i = (size_t)blockIdx.x * kT + threadIdx.x, ic = i < n4 ? i : n4 - 1;
   const float4 xv = x[ic], gv = g_prev[ic];
   const float4 v = make_float4(__fdiv_rn(__fmaf_rn(tm1, gv.x, xv.x), t), __fdiv_rn(__fmaf_rn(tm1, gv.y, xv.y), t),
                                __fdiv_rn(__fmaf_rn(tm1, gv.z, xv.z), t), __fdiv_rn(__fmaf_rn(tm1, gv.w, xv.w), t));
   if (i < n4) g[i] = v;
   if (clear != nullptr && blockIdx.x == 0 && threadIdx.x < nclear) clear[threadIdx.x] = 0u;
   if (partial == nullptr) return;
-  // maxima of |g| and |x| (fmaxf drops NaN; non-negative floats order like their bits)
-  const float mg = fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w)));
+  // maxima of |g| and |x| (fmaxf drops NaN; non-negative floats order like their bits).  Threads past the end loaded the
+  // last vector, which with g = g_prev another wave may have averaged already: their average counts for nothing.
+  const float mg = i < n4 ? fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))) : 0.f;
   const float mx = fmaxf(fmaxf(fabsf(xv.x), fabsf(xv.y)), fmaxf(fabsf(xv.z), fabsf(xv.w)));
   const float wg = __uint_as_float(wave_max_u32(__float_as_uint(fmaxf(mg, 0.f))));
   const float wx = __uint_as_float(wave_max_u32(__float_as_uint(fmaxf(mx, 0.f))));

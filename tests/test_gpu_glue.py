@@ -290,16 +290,19 @@ def test_decoder_layer_of_one_row_block_stage_by_stage(shape):
     test_decoder_layer_stage_by_stage(shape)
 
 
-def test_decoder_layer_updates_the_average_in_place():
-    # g_out = g_prev: no workgroup may read an average that another one has already replaced
-    c = workloads.config5_chained(M=20, layers=1, V=8, t=20)
+@pytest.mark.parametrize("M", [20, 33, 1])
+def test_decoder_layer_updates_the_average_in_place(M):
+    # g_out = g_prev: no workgroup may read an average that another one has already replaced.  The last elements hold the
+    # largest average, and averaging them a second time would nearly double it.
+    c = workloads.config5_chained(M=M, layers=1, V=8, t=20)
     layer = prepare_layer(c["layers"][0], 512, 2048, 2048)
     K, V = (dev(a) for a in c["KV"][0])
     x, g = dev(c["x0"]), dev(c["g_prev"][0])
+    x[-1, -4:], g[-1, -4:] = 200.0, 0.0
     want_y, want_g = run_layer(layer, x, g, 20, K, V, 8)
-    nb = mq.mq_aan_layer_ws_bytes(20, 512, 2048, 2048)
+    nb = mq.mq_aan_layer_ws_bytes(M, 512, 2048, 2048)
     ws, y = torch.empty(nb, dtype=torch.uint8, device=DEV), torch.empty_like(x)
-    mq.mq_aan_layer_f32(layer, x, g, 20, K, V, 20, K.shape[1], 8, True, True, glue.LN_EPS, y, g, ws, nb)
+    mq.mq_aan_layer_f32(layer, x, g, 20, K, V, M, K.shape[1], 8, True, True, glue.LN_EPS, y, g, ws, nb)
     assert torch.equal(g, want_g) and torch.equal(y, want_y)
 
 
