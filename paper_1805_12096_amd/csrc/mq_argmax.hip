@@ -142,7 +142,7 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
   constexpr int STAGE = kKG * kFragBytes;
   constexpr int SHIFT = shift_of(KG), TAGS = (1 << SHIFT) - 1;
   static_assert(kKG == kWaves, "one direct-to-LDS load per wave and stage");
-  static_assert(KG % kKG == 0 && (NH == 1 || S % NH == 0), "stages of a unit");
+  static_assert(KG % kKG == 0 && (NH == 1 || (NH == 2 && S % 2 == 0)), "stages of a unit");
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
 
   const int lane = threadIdx.x % 64;
@@ -197,6 +197,7 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
   // memory counter retires loads in order, so waiting for "all but the newest n" later covers stages 0
   // and 1 and the operands while the newer stages are still on their way.
   constexpr int kEarly = 2;
+  constexpr int kAhead = NH == 1 ? S - 1 : S - 2;     // stages issued before the first one is multiplied
 #pragma unroll
   for (int s = 0; s < kEarly; ++s) issue(s);
   // 16-sentence tiles this wave owns
@@ -273,6 +274,9 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
   // (newest = S - 3 - s).
   // This wave's LDS reads of stage s have returned, too: the compiler would otherwise wait for ALL outstanding reads,
   // the first ones of stage s + 1 included, before the stage's first matrix instructions.
+  // With two stages per unit the waves meet once per unit: its first stage waits for stages s to s + 2 out of the s + S - 2
+  // issued (newest = S - 5) and refills the two slots that everybody is past, its second one only waits for this wave's
+  // own LDS reads.  300 sentences of width 1024, 36 000 words: 31.2 -> 30.3 us for the whole output layer.
   auto land = [&](int newest) {
     wait_vmcnt_n(newest);
     __builtin_amdgcn_s_waitcnt(0xC07F);                // lgkmcnt(0)
@@ -317,11 +321,11 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
       }
     }
 #pragma unroll
-    for (int s = kEarly; s < S - 1; ++s) issue(s);
+    for (int s = kEarly; s < kAhead; ++s) issue(s);
     // stage 0 has to be in registers before the loop, and so have the operands: everything but the
     // stages issued after the operands may still be outstanding
     v4i e0[kKG], e1[kKG];                   // two stages per trip, so that the buffers swap roles without copies
-    wait_vmcnt_n(S - 1 - kEarly);
+    wait_vmcnt_n(kAhead - kEarly);
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -345,9 +349,15 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
                      const v4i (&prev)[TPW], const v4i (&e)[kKG], v4i (&enext)[kKG]) {
       constexpr int PART = decltype(part_tag)::value;
       constexpr bool FIRST = decltype(first_tag)::value;
-      land(newest);
-      // everybody is past stage s - 1 (and has its copy of stage s in registers), so slot s - 1 can be refilled
-      if constexpr (decltype(refill_tag)::value) issue(s + S - 1);
+      if constexpr (PART == 0) {
+        land(newest);
+        // everybody is past stage s - 1 (and has its copy of stage s in registers), so slot s - 1 can be refilled
+        if constexpr (NH > 1) issue(s + S - 2);
+        if constexpr (decltype(refill_tag)::value) issue(s + S - 1);
+      } else {
+        __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0), see land
+        asm volatile("" ::: "memory");
+      }
       // the next stage's LDS reads go two at a time between the first MFMA groups: eight in a row would fill the LDS
       // queue (all eight waves read at the same time) and hold this wave's MFMAs back behind them, and they should be
       // back before the next barrier (after the last stage they read a finished slot again and the result is unused)
@@ -404,11 +414,11 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
       }
     } else {
       for (unsigned n = 0; n < nlocal; n += 2) {
-        stage(T{}, F{}, P0{}, S - 3, 2 * n, acc0, acc1, e0, e1);
-        stage(T{}, F{}, P1{}, S - 3, 2 * n + 1, acc0, acc1, e1, e0);
+        stage(T{}, F{}, P0{}, S - 5, 2 * n, acc0, acc1, e0, e1);
+        stage(T{}, F{}, P1{}, 0, 2 * n + 1, acc0, acc1, e1, e0);
         if (n + 1 < nlocal) {
-          stage(T{}, F{}, P0{}, S - 3, 2 * n + 2, acc1, acc0, e0, e1);
-          stage(T{}, F{}, P1{}, S - 3, 2 * n + 3, acc1, acc0, e1, e0);
+          stage(T{}, F{}, P0{}, S - 5, 2 * n + 2, acc1, acc0, e0, e1);
+          stage(T{}, F{}, P1{}, 0, 2 * n + 3, acc1, acc0, e1, e0);
         }
       }
     }
