@@ -965,6 +965,12 @@ int default_variant(const GemmArgs& a) {
     const float t = (float)((tiles + kCUs - 1) / kCUs) * (c.fixed + c.per_step * (float)steps);
     if (best_cost == 0.f || t < best_cost) { best = c.variant; best_cost = t; }
   }
+  // The same 128 x 128 tile on four waves instead of eight reads a third less from LDS but has half the waves to hide a wait
+  // behind: with all compute units busy and K long the former counts (256 tiles, K = 2048: 14.9 -> 14.4 us for 8192 x 512,
+  // 15.2 -> 14.3 for 4096 x 1024; K = 4096 24.2 -> 23.2), with units idle or K short the latter (160 tiles, K = 2048: 11.8
+  // against 12.2 us, K = 4096 19.1 against 20.0; 128 tiles, K = 512: 6.0 against 6.2).
+  const size_t tiles = ((a.M + 127) / 128) * ((a.N + 127) / 128);
+  if (best == 8 && steps >= 32 && tiles > 224 && tiles <= kCUs) return 3;
   return best;
 }
 }  // namespace

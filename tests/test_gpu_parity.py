@@ -613,7 +613,7 @@ def test_gemm_packed_full_range_all_variants(dtype, M, N, K):
 
 @pytest.mark.parametrize("dtype", [np.int8, np.int16])
 @pytest.mark.parametrize("M,N,K", [(640, 1024, 96), (641, 1024, 96), (704, 1100, 70), (1500, 700, 160), (2049, 1024, 700),
-                                   (4100, 1030, 96), (2304, 4096, 64)])
+                                   (4100, 1030, 96), (2304, 4096, 64), (3700, 1000, 2048), (4096, 1024, 1990)])
 def test_gemm_packed_default_choice(dtype, M, N, K):
     # no forced variant: shapes on both sides of the lines where the default changes from the split-K kernel to the tiles
     # and from one tile size to the next
