@@ -391,7 +391,9 @@ size_t mq_linear_ws_bytes(int bits, size_t M, size_t K);
  * `stream`; for 8-bit products with at most 512 rows and K a multiple of 32 up
  * to 1024 (a decode step) quant_int runs inside the product kernel: one launch
  * with a given multiplier, two with abs-max.
- * A: device float [M x K], 16-byte aligned.  out_amax: optional device float
+ * A: device float [M x K], 16-byte aligned.  Y may share memory with A (an
+ * in-place call, or any other overlap): A is then quantized whole, in a launch
+ * of its own, before anything is stored.  out_amax: optional device float
  * that is raised to max|Y| (the caller zeroes it).  ws: device workspace of
  * mq_linear_ws_bytes bytes, 16-byte aligned, contents irrelevant. */
 int mq_linear_f32(const float* A, size_t M, size_t K, const float* sA_or_null,

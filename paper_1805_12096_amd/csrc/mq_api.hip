@@ -874,10 +874,12 @@ int mq_linear_f32(const float* A, size_t M, size_t K, const float* sA_or_null, c
   a.packedW = packedW; a.bits = bits; a.M = M; a.N = N; a.K = K;
   a.sW = sW; a.bias = bias; a.relu = relu != 0; a.Y = Y; a.out_amax = out_amax;
   int rc;
+  // Products that quantize in their operand fetch read A from every tile column while other workgroups already store Y:
+  // where the two share memory, A is quantized in a launch of its own first.
+  const bool apart = !overlap(A, M * K, Y, M * N);
   // one block of rows: abs-max, quant_int and product in one launch (a forced or tuned variant names a packed product)
-  if (gemm_rows_supported(bits, M, N, K) && forced_variant() == 0 && !overlap(A, M * K, Y, M * N))
-    return launch_gemm_rows(A, sA, a, s);
-  if (bits == 8 && gemm_small_f32_supported(M, N, K)) {
+  if (apart && gemm_rows_supported(bits, M, N, K) && forced_variant() == 0) return launch_gemm_rows(A, sA, a, s);
+  if (apart && bits == 8 && gemm_small_f32_supported(M, N, K)) {
     // decode-sized input: quant_int happens inside the product's operand fetch (same arithmetic, same
     // results), one launch with a given multiplier, two with abs-max
     if (sA != nullptr) return launch_gemm_small_f32(A, sA, 0, nullptr, a, s);

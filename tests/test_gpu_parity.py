@@ -358,6 +358,27 @@ def test_mq_linear_f32_of_one_row_block(M, N, K, relu, fixed, bits):
         assert np.array_equal(host(B), want)
 
 
+@pytest.mark.parametrize("bits", [8, 16])
+@pytest.mark.parametrize("fixed", [False, True])
+@pytest.mark.parametrize("M,K", [(20, 512), (32, 256), (33, 512), (300, 512), (512, 1024), (600, 512)])
+def test_mq_linear_f32_in_place(M, K, fixed, bits):
+    # Y on top of A, and Y beginning in the middle of A: no workgroup may read rows that another one has already replaced,
+    # whichever form serves these sizes otherwise (one launch, quant_int in the operand fetch, separate quantizer)
+    p = workloads.random_problem(M + K + bits, M, K, K)
+    s0 = None if not fixed else 1024.0 if bits == 16 else 63.5
+    pw = mq.prepare_weight(dev(p["Wt"]), bits)
+    nb = mq.mq_linear_ws_bytes(bits, M, K)
+    ws = torch.full((nb,), 0x5A, dtype=torch.uint8, device=DEV)
+    sA = torch.full((1,), s0, dtype=torch.float32, device=DEV) if fixed else None
+    want = oracle.linear(p["A"], p["Wt"], bits, p["bias"], False, sA=s0)["Y"]
+    for first in (0, M // 2):
+        both = torch.zeros((M + first, K), dtype=torch.float32, device=DEV)
+        both[:M] = dev(p["A"])
+        mq.mq_linear_f32(both[:M], M, K, sA, pw.packed, pw.scale, bits, K, dev(p["bias"]), False, both[first:], None, ws, nb)
+        assert np.array_equal(host(both[first:]), want)
+        assert np.array_equal(host(both[:first]), p["A"][:first])
+
+
 # -------------------------------------------------------------------- arg-max
 
 def gpu_greedy(Hd, E, pw=None):
