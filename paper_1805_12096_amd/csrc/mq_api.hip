@@ -47,6 +47,8 @@ bool overlap(const void* a, size_t na, const void* b, size_t nb) {
   return pa < pb + 4 * nb && pb < pa + 4 * na;
 }
 bool bits_ok(int bits) { return bits == 8 || bits == 16; }
+// whether mq_set_gemm_variant or mq_autotune_gemm has chosen the packed product's configuration for this shape
+bool variant_named(int bits, size_t M, size_t N, size_t K) { return forced_variant() > 0 || tuned_variant(bits, M, N, K) > 0; }
 bool dims_ok(size_t M, size_t N, size_t K) {
   if (M == 0 || N == 0 || K == 0) return false;
   if (M >= kMaxDim || N >= kMaxDim || K >= kMaxDim) return false;
@@ -877,9 +879,12 @@ int mq_linear_f32(const float* A, size_t M, size_t K, const float* sA_or_null, c
   // Products that quantize in their operand fetch read A from every tile column while other workgroups already store Y:
   // where the two share memory, A is quantized in a launch of its own first.
   const bool apart = !overlap(A, M * K, Y, M * N);
-  // one block of rows: abs-max, quant_int and product in one launch (a forced or tuned variant names a packed product)
-  if (apart && gemm_rows_supported(bits, M, N, K) && forced_variant() == 0) return launch_gemm_rows(A, sA, a, s);
-  if (apart && bits == 8 && gemm_small_f32_supported(M, N, K)) {
+  const bool in_fetch = bits == 8 && gemm_small_f32_supported(M, N, K);
+  // one block of rows: abs-max, quant_int and product in one launch -- unless the other route leads to the packed products
+  // and the caller has forced or tuned one of them for this shape
+  if (apart && gemm_rows_supported(bits, M, N, K) && (in_fetch || !variant_named(bits, M, N, K)))
+    return launch_gemm_rows(A, sA, a, s);
+  if (apart && in_fetch) {
     // decode-sized input: quant_int happens inside the product's operand fetch (same arithmetic, same
     // results), one launch with a given multiplier, two with abs-max
     if (sA != nullptr) return launch_gemm_small_f32(A, sA, 0, nullptr, a, s);
@@ -1060,7 +1065,7 @@ int mq_aan_layer_f32(const mq_aan_layer* P, const float* x, const float* g_prev,
   int rc;
   if (gemm_rows_glue_supported(M, d) && use_ffn && use_gate && aligned(g_prev, 16) && aligned(P->ln1.gamma, 16) &&
       aligned(P->ln1.beta, 16) && aligned(P->ln2.gamma, 16) && aligned(P->ln2.beta, 16) && !overlap(g_prev, M * d, g_out, M * d) &&
-      !overlap(x, M * d, g_out, M * d)) {
+      !overlap(x, M * d, g_out, M * d) && (gemm_small_f32_supported(M, 2 * d, 2 * d) || !variant_named(8, M, 2 * d, 2 * d))) {
     // One block of rows: the running average, the normalisations in front of a product and every quantizer happen in the
     // operand fetch of the product that follows, and the gate in the epilogue of its own product: nine launches for
     // fourteen.
@@ -1072,7 +1077,8 @@ int mq_aan_layer_f32(const mq_aan_layer* P, const float* x, const float* g_prev,
     };
     // H (with partial maxima, for the form that quantizes in a launch of its own) times the second parameter
     auto second = [&](size_t width, const mq_product& W, float* Y) {
-      if (gemm_rows_supported(8, M, d, width)) return launch_gemm_rows(hid, nullptr, args(W, d, width, 0, Y), s);
+      if (gemm_rows_supported(8, M, d, width) && (gemm_small_f32_supported(M, d, width) || !variant_named(8, M, d, width)))
+        return launch_gemm_rows(hid, nullptr, args(W, d, width, 0, Y), s);      // (see mq_linear_f32)
       return product(hid, width, W, d, 0, Y, hpart, gemm_rows_partials(width), false, nullptr, nullptr);
     };
     GemmArgs g1 = args(P->aan_ffn1, aan_ffn, d, 1, hid), g5 = args(P->ffn1, ffn, d, 1, hid);

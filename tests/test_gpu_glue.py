@@ -290,6 +290,41 @@ def test_decoder_layer_of_one_row_block_stage_by_stage(shape):
     test_decoder_layer_stage_by_stage(shape)
 
 
+def test_decoder_layer_of_one_row_block_runs_the_variant_named():
+    # the products of the layer that go through the packed products otherwise (wider than 1024) keep to a variant the
+    # caller has forced or tuned, also up to 32 sentences, where one launch quantizes and multiplies: launches of the layer
+    from test_gpu_parity import launches, tune
+    M, d, ffn = 5, 768, 1056
+    c = workloads.config5_chained(M=M, layers=1, V=8, d=d, ffn=ffn, aan_ffn=d, t=3)
+    layer = prepare_layer(c["layers"][0], d, ffn, d)
+    K, V = (dev(a) for a in c["KV"][0])
+    x, gp = dev(c["x0"]), dev(c["g_prev"][0])
+    want = run_layer(layer, x, gp, 3, K, V, 12)
+    nb = mq.mq_aan_layer_ws_bytes(M, d, ffn, d)
+    ws, y, g = torch.empty(nb, dtype=torch.uint8, device=DEV), torch.empty_like(x), torch.empty_like(x)
+
+    def call(stream):
+        mq.mq_aan_layer_f32(layer, x, gp, 3, K, V, M, K.shape[1], 12, True, True, glue.LN_EPS, y, g, ws, nb, stream)
+
+    assert launches(call) == 9
+    try:
+        mq.mq_set_gemm_variant(1)
+        several = launches(call)
+        mq.mq_set_gemm_variant(15)                     # a variant that does not exist is refused
+        with pytest.raises(mq.MqError) as e:
+            call(torch.cuda.current_stream())
+        assert e.value.status == 6
+    finally:
+        mq.mq_set_gemm_variant(0)
+    assert several > 10                                # the gate's product (width 1536) and the second feed-forward product
+    tune(8, M, d, ffn)
+    assert launches(call) == 10                        # a quantizer and the tuned product in place of one launch
+    y.fill_(-3.0)
+    call(torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    assert torch.equal(y, want[0]) and torch.equal(g, want[1])
+
+
 @pytest.mark.parametrize("M", [20, 33, 1])
 def test_decoder_layer_updates_the_average_in_place(M):
     # g_out = g_prev: no workgroup may read an average that another one has already replaced.  The last elements hold the

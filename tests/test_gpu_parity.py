@@ -4,6 +4,7 @@ seeded inputs, through the C boundary.  Integer results (quantized tensors,
 the same single-FMA formula from the same integers and are expected to be
 identical, with 1e-5 relative as the stated bar.
 """
+import ctypes
 import functools
 
 import numpy as np
@@ -377,6 +378,60 @@ def test_mq_linear_f32_in_place(M, K, fixed, bits):
         mq.mq_linear_f32(both[:M], M, K, sA, pw.packed, pw.scale, bits, K, dev(p["bias"]), False, both[first:], None, ws, nb)
         assert np.array_equal(host(both[first:]), want)
         assert np.array_equal(host(both[:first]), p["A"][:first])
+
+
+@functools.lru_cache(None)
+def hip_runtime():
+    """The HIP runtime this process runs on (the one torch has loaded)."""
+    with open("/proc/self/maps") as f:
+        return ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
+
+
+def launches(call):
+    """Kernels that call(stream) enqueues: the nodes of a graph captured from it, after one call that really runs."""
+    hip, graph, n = hip_runtime(), ctypes.c_void_p(), ctypes.c_size_t()
+    stream = torch.cuda.Stream()
+    call(stream)
+    torch.cuda.synchronize()
+    assert hip.hipStreamBeginCapture(ctypes.c_void_p(stream.cuda_stream), 1) == 0
+    try:
+        call(stream)
+    finally:
+        assert hip.hipStreamEndCapture(ctypes.c_void_p(stream.cuda_stream), ctypes.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    assert hip.hipGraphDestroy(graph) == 0
+    return n.value
+
+
+def tune(bits, M, N, K):
+    nb = mq.mq_autotune_ws_bytes(bits, M, N, K)
+    return mq.mq_autotune_gemm(bits, M, N, K, 2, torch.empty(nb, dtype=torch.uint8, device=DEV), nb)[0]
+
+
+@pytest.mark.parametrize("bits,M,N,K,before,after", [(16, 11, 72, 92, 1, 3), (8, 11, 72, 92, 1, 3), (8, 11, 72, 1036, 1, 3),
+                                                     (8, 11, 72, 96, 1, 1), (16, 43, 72, 92, 3, 3)])
+def test_a_tuned_or_forced_variant_is_the_product_that_runs(bits, M, N, K, before, after):
+    # Up to 32 rows one launch does everything, until the caller has named a packed product for the shape: then abs-max,
+    # quantizer and that product run.  (8 bit with K a multiple of 32 up to 1024 never takes a packed product.)
+    p = workloads.random_problem(M + N + K, M, N, K)
+    pw, A = mq.prepare_weight(dev(p["Wt"]), bits), dev(p["A"])
+    nb = mq.mq_linear_ws_bytes(bits, M, K)
+    ws, Y = torch.empty(nb, dtype=torch.uint8, device=DEV), torch.empty((M, N), dtype=torch.float32, device=DEV)
+
+    def call(stream):
+        mq.mq_linear_f32(A, M, K, None, pw.packed, pw.scale, bits, N, None, False, Y, None, ws, nb, stream)
+
+    want = oracle.linear(p["A"], p["Wt"], bits)["Y"]
+    assert launches(call) == before and np.array_equal(host(Y), want)
+    try:
+        mq.mq_set_gemm_variant(1)
+        Y.fill_(-3.0)
+        assert launches(call) == after and np.array_equal(host(Y), want)
+    finally:
+        mq.mq_set_gemm_variant(0)
+    tune(bits, M, N, K)
+    Y.fill_(-3.0)
+    assert launches(call) == after and np.array_equal(host(Y), want)
 
 
 # -------------------------------------------------------------------- arg-max
