@@ -549,6 +549,7 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
 // 128-byte line per group and load), the groups' maxima meet in LDS, and 16 lanes decode.  Bound by the round trip to
 // keys that other dies' workgroups have just written: a lane's loads (16 for 256 workgroups) all go out before the first
 // is looked at (four at a time the output layer took 0.7 us longer for 300 and for 61 sentences).
+// cols: at most 256 (cut_stream).
 __global__ __launch_bounds__(256) void k_argmax_reduce(const unsigned long long* __restrict__ partial, unsigned cols,
                                                        unsigned M, const float* __restrict__ sA,
                                                        const float* __restrict__ sW, int32_t* __restrict__ tok,
@@ -569,10 +570,6 @@ __global__ __launch_bounds__(256) void k_argmax_reduce(const unsigned long long*
     }
 #pragma unroll
     for (int t = 0; t < 16; ++t) key = k[t] > key ? k[t] : key;
-    for (unsigned g = gs + 256; g < cols; g += 16) {
-      const unsigned long long v = col[(size_t)g * Mpad];
-      if (v > key) key = v;
-    }
   }
   red[gs][mi] = key;
   __syncthreads();
@@ -757,12 +754,12 @@ static int launch_argmax_any(const uint8_t* hidden, bool row_major, const void* 
     size_t nrows = M - row0;
     StreamCut c = cut_stream(nrows, units, rows_max, max_units);
     while (nrows > rows_max && (c.chunks > 16 || (size_t)c.columns * round_up(nrows, 16) > ws_keys)) {
-      const size_t fewer = (c.chunks > 16 ? 16 : c.chunks - 1) * rows_max;
-      nrows = fewer < nrows ? fewer : nrows - 16;
+      nrows = (c.chunks > 16 ? 16 : c.chunks - 1) * rows_max;      // whole chunks, so row0 stays a multiple of 32 rows
       c = cut_stream(nrows, units, rows_max, max_units);
     }
-    while (c.columns > 2 && (size_t)c.columns * round_up(nrows, 16) > ws_keys) --c.columns;
-    if ((units + c.columns - 1) / c.columns > max_units) return MQ_ERR_UNSUPPORTED;
+    // (one chunk always fits: 256 columns of at most 384 rows)
+    if ((size_t)c.columns * round_up(nrows, 16) > ws_keys || (units + c.columns - 1) / c.columns > max_units)
+      return MQ_ERR_UNSUPPORTED;
     ArgmaxParams p{};
     p.packedA = row_major ? hidden + row0 * K : hidden + dAll.frag_offset(row0 / 32, 0);   // (row0: whole 32-row blocks)
     p.packedW = static_cast<const uint8_t*>(packedW);

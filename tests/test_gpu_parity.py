@@ -928,10 +928,26 @@ def test_config3_output_layer_full_packed():
 
 
 def test_greedy_packed_more_rows_than_one_pass_holds():
-    # 1000 rows: three passes of 384 rows each stream the embedding
+    # 1000 rows: three chunks of rows in one launch, each over a third of the compute units
     c = workloads.config3(M=1000, V=5000, d=128, seed_extra=11)
     o = oracle.greedy_output_layer(c["Hd"], c["E"])
     tok, val = gpu_greedy_packed(c["Hd"], c["E"])
+    assert np.array_equal(tok, o["tok"])
+    assert np.array_equal(val, o["maxlogit"])
+
+
+@pytest.mark.parametrize("M,V,d", [(6145, 300, 64), (6144 + 390, 4100, 96), (2 * 6144 + 1, 33, 32)])
+def test_greedy_packed_more_rows_than_one_launch_holds(M, V, d):
+    # sixteen chunks of 384 rows per launch: the launches behind the first one start at a later row of the hidden states
+    # and of both results, and reuse the workspace
+    c = workloads.config3(M=M, V=V, d=d, seed_extra=M)
+    o = oracle.greedy_output_layer(c["Hd"], c["E"])
+    tok, val = gpu_greedy_packed(c["Hd"], c["E"])
+    assert np.array_equal(tok, o["tok"])
+    assert np.array_equal(val, o["maxlogit"])
+    sl = np.arange(0, V, 3, dtype=np.int32)
+    o = oracle.greedy_output_layer(c["Hd"], c["E"], shortlist=sl)
+    tok, val = gpu_greedy_shortlist(c["Hd"], c["E"], sl)
     assert np.array_equal(tok, o["tok"])
     assert np.array_equal(val, o["maxlogit"])
 

@@ -41,7 +41,7 @@ def run_both(Hd, E):
 def test_static_scratch_output_layer_two_calls_second_smaller():
     assert torch.cuda.is_available()
     mq.load_library()
-    # first call: more rows than one pass of the kernel takes (two passes reuse the array) and the full vocabulary
+    # first call: more rows than a workgroup holds (two chunks in one launch share the array) and the full vocabulary
     c = workloads.config3(M=500, V=36000, d=512)
     (tw, vw), (ts, vs) = run_both(c["Hd"], c["E"])
     assert np.array_equal(ts, tw) and np.array_equal(vs, vw)
@@ -56,6 +56,20 @@ def test_static_scratch_output_layer_two_calls_second_smaller():
     # and the first size once more after the small one
     (tw, vw), (ts, vs) = run_both(c["Hd"], c["E"])
     assert np.array_equal(ts, tw) and np.array_equal(vs, vw)
+
+
+def test_static_scratch_output_layer_in_several_launches():
+    # so many words that every chunk of rows needs a hundred columns of candidates: three chunks do not fit the array
+    # together, the third goes in a launch of its own that reuses it
+    M, V, d = 1000, 400000, 16
+    rng = np.random.default_rng(77)
+    Hd, E = rng.standard_normal((M, d), dtype=np.float32), rng.standard_normal((V, d), dtype=np.float32)
+    (tw, vw), (ts, vs) = run_both(Hd, E)
+    assert np.array_equal(ts, tw) and np.array_equal(vs, vw)
+    (qA, sA), (qW, sW) = oracle.quant_int_absmax(Hd, 8), oracle.quant_int_absmax(E, 8)
+    for m in range(0, M, 200):                   # (the sums of all rows at once are 1.6 GB)
+        tok, val = oracle.argmax_i32(oracle.dot_int(qA[m:m + 200], qW), sA, sW)
+        assert np.array_equal(ts[m:m + 200], tok) and np.array_equal(vs[m:m + 200], val)
 
 
 def test_static_scratch_entry_rejects_what_it_cannot_serve():
