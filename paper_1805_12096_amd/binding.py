@@ -176,14 +176,17 @@ def _p(t):
 
 
 # The current stream's handle without building a torch.cuda.Stream object: a decode-sized call enqueues two or three
-# launches of 2.4 us each, and torch.cuda.current_stream() alone took another 3.2 us of the host's time.
-_raw_stream = torch._C._cuda_getCurrentRawStream
-_device = torch._C._cuda_getDevice
+# launches of 2.4 us each, and torch.cuda.current_stream() alone took another 3.2 us of the host's time.  Both names are
+# private to torch; a build without them (one without a GPU backend, say) takes the public way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream(stream):
     if stream is None:
-        return _raw_stream(_device()) if torch.cuda.is_initialized() else torch.cuda.current_stream().cuda_stream
+        if _raw_stream is not None and _device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_device())
+        return torch.cuda.current_stream().cuda_stream
     return stream if isinstance(stream, int) else stream.cuda_stream
 
 

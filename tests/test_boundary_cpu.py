@@ -4,6 +4,8 @@ the device."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -27,6 +29,16 @@ def test_header_symbols_are_exported(lib):
     assert declared == set(mq.exported_symbols())
     for name in declared:
         assert hasattr(lib, name), name
+
+
+def test_imports_where_torch_lacks_its_private_stream_queries(lib):
+    code = ("import torch\n"
+            "for name in ('_cuda_getCurrentRawStream', '_cuda_getDevice'):\n"
+            "    if hasattr(torch._C, name): delattr(torch._C, name)\n"
+            "import paper_1805_12096_amd as mq\n"
+            "assert mq.mq_version() >= 100 and mq.mq_packed_bytes(8, 1, 1) == 32 * 64\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
 
 
 def test_version_and_status_strings(lib):
