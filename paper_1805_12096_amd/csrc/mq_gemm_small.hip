@@ -245,8 +245,10 @@ struct SmallF32Params {
 };
 
 // Four elements of quant_int as bytes.  CLAMP = false: the multiplier is 127 / max over a set these elements belong to,
-// rounded, so |x s| <= 127 (1 + 2^-23) rounds to at most 127 and no clamp can act (an infinite max gives s = 0, products
-// 0 or NaN, and NaN converts to 0 either way).
+// rounded, so where it is finite |x s| <= 127 (1 + 2^-23) rounds to at most 127 and no clamp can act (an infinite max
+// gives s = 0, products 0 or NaN, and NaN converts to 0 either way).  A max below 127 / FLT_MAX (3.7e-37) gives s = inf,
+// and unclamped infinities convert to bytes -1 and 0 where quant_int says 127 and -127: the sums are others then, but
+// they are finite and meet the factor 1 / (s sW) = 0, so the result is the bias either way.
 template <bool CLAMP>
 __device__ __forceinline__ uint32_t quant_pack4(float4 v, float s) {
   auto q = [&](float x) -> uint32_t {

@@ -380,6 +380,21 @@ def test_mq_linear_f32_in_place(M, K, fixed, bits):
         assert np.array_equal(host(both[:first]), p["A"][:first])
 
 
+@pytest.mark.parametrize("bits,M,K", [(8, 20, 64), (8, 40, 64), (8, 300, 1024), (8, 600, 64), (16, 20, 64), (16, 40, 64)])
+@pytest.mark.parametrize("top", [1e-38, 3e-37, 1e-42])
+def test_mq_linear_f32_of_tiny_values(bits, M, K, top):
+    # a maximum so small that Qmax / max is infinite: the dequantizing factor is 0 and every result its bias, whatever
+    # the form that serves the size makes of the infinite products
+    p = workloads.random_problem(M + K + bits, M, 48, K)
+    A = np.clip(p["A"], -1, 1).astype(np.float32) * np.float32(top)
+    pw = mq.prepare_weight(dev(p["Wt"]), bits)
+    nb = mq.mq_linear_ws_bytes(bits, M, K)
+    ws, Y = torch.empty(nb, dtype=torch.uint8, device=DEV), torch.empty((M, 48), dtype=torch.float32, device=DEV)
+    mq.mq_linear_f32(dev(A), M, K, None, pw.packed, pw.scale, bits, 48, dev(p["bias"]), False, Y, None, ws, nb)
+    assert np.array_equal(host(Y), np.broadcast_to(p["bias"], (M, 48)))
+    assert np.array_equal(host(Y), oracle.linear(A, p["Wt"], bits, p["bias"])["Y"])
+
+
 @functools.lru_cache(None)
 def hip_runtime():
     """The HIP runtime this process runs on (the one torch has loaded)."""
