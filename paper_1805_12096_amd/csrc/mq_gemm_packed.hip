@@ -924,53 +924,74 @@ int launch_gemm_requant_fixed_i16(const GemmArgs& a, const float* s_fixed, void*
 }
 
 namespace {
-// Default tile configuration of a packed product, for shapes nobody has timed with mq_autotune_gemm.
-//
-// A launch is a number of rounds of one workgroup per compute unit (every candidate here but the split-K kernel fills
-// a compute unit's LDS with one workgroup), and a round takes a fixed part (launch, first operands, stores) plus a part
-// per 64-element K step, whether it is full or not: the best tile is the one with the smallest
-// rounds x (fixed + per_step x steps).  The constants are fitted to the timed shapes below, in microseconds (8 bit) and
-// relative (16 bit, where K steps dominate and cancel).
-// Measured on 66 shapes per width (M 300 .. 8192, parameters 512 x 512 to 4096 x 1024): this rule is 1.9 % (8 bit) and
-// 0.7 % (16 bit) slower than the best variant of each shape on average, the rule it replaces ("the largest tile that
-// still gives 200 workgroups", split K up to 512 rows only) 12 % and 7 %; e.g. 8 bit, 1001 x 512 x 2048 6.3 instead of
-// 10.0 us (split K), 2000 x 4096 x 1024 18.7 instead of 24.2, 5003 x 1024 x 1024 12.4 instead of 13.8 us.
+// Default configuration of a packed product, for shapes nobody has timed with mq_autotune_gemm.  Timed: every candidate on
+// 34 parameters (64 x 4096 to 4096 x 4096, half of them odd) with 26 batches each (33 .. 8192 rows), 884 shapes per width,
+// each product behind the quantizer that writes its input (alone and repeated, split K looks up to 40 % better than it is
+// on thousands of rows: its re-reads then hit).  This rule is 0.3 % slower than the best candidate of each shape on average
+// in either width, at worst 13 % (profiles/default_configuration_timings.csv); a fit on whole multiples of 256 with split K up to 320 / 384 workgroups was 5.3 % (8 bit)
+// and 2.4 % (16 bit), at worst 70 % (384 x 1024 x 4096 in 8 bit 15.5 us on tiles, 8.3 with split K), and one size threshold
+// per tile 11 %.
 constexpr size_t kCUs = 256;
-struct TileCost { int variant; size_t bm, bn; float fixed, per_step; };
+
+// Split K (variant 10 / 6) while it stays ahead of the tiles.  With one block of rows per workgroup (fewer than 256 workgroups
+// of two) always: at most 511 workgroups, 8 bit 3.7 - 13 us where the tiles take 5 - 18.  With two blocks a workgroup reads
+// its rows' fragments without sharing them in LDS: behind the first 256 workgroups that costs more than a tile unless K is
+// short (one trip of loads) or long (the tiles then walk through many steps with few workgroups: 600 x 1024 x 4096 in 8 bit
+// 0.93 of the tiles' time, 300 x 2048 x 2048 in 16 bit 0.93), in 16 bit, whose tiles are slower, a little earlier.  A narrow
+// result has thousands of rows behind those workgroups, read afresh by each of its few columns (8192 x 128 x 512 in 8 bit:
+// 512 workgroups 9.4 us, the tiles 5.7; 5003 x 100 x 3000 in 16 bit 27.7 against 23.8).  max|y| into words of the caller's
+// ends every workgroup with another trip to memory (16-bit block of 512 words, 512 workgroups: 33.8 us, on tiles 30.4).
+bool split_k_pays(const GemmArgs& a) {
+  if (!gemm_small_two_blocks(a.M, a.N)) return true;
+  struct Line { size_t steps, width, workgroups; };              // up to so many 64-element steps, from that width on
+  constexpr Line l8[] = {{8, 256, 512}, {16, ~(size_t)0, 0}, {32, 768, 320}, {~(size_t)0, 768, 512}};
+  const Line l16[] = {{8, 256, 512}, {16, 640, 384}, {~(size_t)0, 512, a.N < 768 ? (size_t)384 : (size_t)512}};
+  const Line* l = a.bits == 16 ? l16 : l8;
+  while ((a.K + 63) / 64 > l->steps) ++l;
+  const size_t most = a.N >= l->width ? l->workgroups : 256;
+  return gemm_small_workgroups(a.M, a.N) <= (a.out_amax != nullptr && most > 384 ? 384 : most);
+}
+
+// The tiles.  A launch is a number of rounds of one workgroup per compute unit (every candidate here fills a compute unit's LDS
+// with one), and takes a fixed part, a part per 64-element K step of the first round and of every later one (a later round
+// hides its start behind the one before), and a part for the results, which all workgroups write.  The largest 16-bit tile
+// also takes longer per step the more units are busy.  In microseconds, fitted.
+struct TileCost {
+  int variant;
+  size_t bm, bn;
+  float fixed, step, later, later_step, results, busy_step;
+  float of(const GemmArgs& a) const {
+    const size_t tiles = ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn), more = (tiles + kCUs - 1) / kCUs - 1;
+    const float steps = (float)((a.K + 63) / 64);
+    return fixed + step * steps + (float)more * (later + later_step * steps) +
+           (results + busy_step * steps) * (float)tiles / (float)kCUs;
+  }
+};
 
 int default_variant(const GemmArgs& a) {
-  const size_t steps = (a.K + 63) / 64;
-  const size_t small_wg = gemm_small_workgroups(a.M, a.N);
-  if (a.bits == 16) {
-    // split K while its workgroups are at most one and a half rounds (3.7 - 14 us where the tiles take 7 - 27)
-    if (small_wg <= 384) return 6;
-    const TileCost cost[] = {{3, 64, 128, 0.f, 103.f}, {1, 128, 128, 0.f, 128.f}, {8, 256, 128, 0.f, 223.f}};
-    int best = 1;
-    float best_cost = 0.f;
-    for (const TileCost& c : cost) {
-      const size_t tiles = ((a.M + c.bm - 1) / c.bm) * ((a.N + c.bn - 1) / c.bn);
-      // (256 workgroups of the 64 x 128 tile do not land one per compute unit: 15.6 us against 11.9 for 192 of them)
-      const size_t per_round = c.variant == 3 ? kCUs - 1 : kCUs;
-      const float t = (float)((tiles + per_round - 1) / per_round) * c.per_step;
-      if (best_cost == 0.f || t < best_cost) { best = c.variant; best_cost = t; }
-    }
-    return best;
-  }
-  if (small_wg <= 320) return 10;
-  const TileCost cost[] = {{7, 128, 64, 1.6f, 0.22f}, {8, 128, 128, 1.3f, 0.31f}, {6, 256, 128, 1.0f, 0.45f}, {1, 256, 256, 3.0f, 0.52f}};
-  int best = 1;
-  float best_cost = 0.f;
-  for (const TileCost& c : cost) {
-    const size_t tiles = ((a.M + c.bm - 1) / c.bm) * ((a.N + c.bn - 1) / c.bn);
-    const float t = (float)((tiles + kCUs - 1) / kCUs) * (c.fixed + c.per_step * (float)steps);
-    if (best_cost == 0.f || t < best_cost) { best = c.variant; best_cost = t; }
-  }
-  // The same 128 x 128 tile on four waves instead of eight reads a third less from LDS but has half the waves to hide a wait
-  // behind: with all compute units busy and K long the former counts (256 tiles, K = 2048: 14.9 -> 14.4 us for 8192 x 512,
-  // 15.2 -> 14.3 for 4096 x 1024; K = 4096 24.2 -> 23.2), with units idle or K short the latter (160 tiles, K = 2048: 11.8
-  // against 12.2 us, K = 4096 19.1 against 20.0; 128 tiles, K = 512: 6.0 against 6.2).
+  if (split_k_pays(a)) return a.bits == 16 ? 6 : 10;
+  const TileCost cost16[] = {{3, 64, 128, 3.37f, 0.57f, 0.08f, 0.59f, 2.82f, 0.f},
+                             {1, 128, 128, 3.89f, 0.60f, 0.06f, 0.78f, 4.17f, 0.f},
+                             {8, 256, 128, 6.90f, 1.20f, 3.15f, 1.14f, 5.36f, 0.16f}};
+  const TileCost cost8[] = {{7, 128, 64, 4.36f, 0.16f, 4.62f, 0.14f, 0.80f, 0.f},
+                            {8, 128, 128, 3.51f, 0.21f, 0.08f, 0.70f, 3.60f, 0.f},
+                            {6, 256, 128, 4.26f, 0.30f, 8.83f, 0.21f, 5.61f, 0.f},
+                            {1, 256, 256, 6.32f, 0.49f, 2.81f, 0.56f, 9.48f, 0.f},
+                            {3, 128, 128, 4.25f, 0.18f, 0.00f, 0.20f, 2.91f, 0.f}};
+  // The 128 x 128 tile on four waves (variant 3) reads a third less from LDS than on eight (variant 8) but has half the waves
+  // to hide a wait behind: with all compute units busy and K long, or with several rounds, the former counts (256 tiles,
+  // K = 2048: 14.9 -> 14.4 us for 8192 x 512; 448 tiles, K = 2048: 26.7 -> 23.4), with units idle or K short the latter (160
+  // tiles, K = 2048: 11.8 against 12.2 us; 128 tiles, K = 512: 6.0 against 6.2).
   const size_t tiles = ((a.M + 127) / 128) * ((a.N + 127) / 128);
-  if (best == 8 && steps >= 32 && tiles > 224 && tiles <= kCUs) return 3;
+  const int not_this = tiles > kCUs || (a.K > 31 * 64 && tiles > 224) ? 8 : 3;
+  int best = 1;
+  float least = 0.f;
+  auto pick = [&](const TileCost& c) {
+    const float t = c.of(a);
+    if (!(a.bits == 8 && c.variant == not_this) && (least == 0.f || t < least)) { best = c.variant; least = t; }
+  };
+  if (a.bits == 16) for (const TileCost& c : cost16) pick(c);
+  else for (const TileCost& c : cost8) pick(c);
   return best;
 }
 }  // namespace

@@ -511,10 +511,10 @@ int launch_small_tmw(const GemmArgs& a, int dequant, size_t kfrags, hipStream_t 
 }  // namespace
 
 // Workgroups of launch_gemm_small / launch_gemm_small_f32 for a shape = maxima written to GemmArgs::partial.
+bool gemm_small_two_blocks(size_t M, size_t N) { return ((M + 31) / 32 + 1) / 2 * ((N + 31) / 32) >= 256; }
 size_t gemm_small_workgroups(size_t M, size_t N) {
-  const size_t rbs = (M + 31) / 32, cbs = (N + 31) / 32;
-  const bool wide = ((rbs + 1) / 2) * cbs >= 256;
-  return (wide ? (rbs + 1) / 2 : rbs) * cbs;
+  const size_t rbs = (M + 31) / 32;
+  return (gemm_small_two_blocks(M, N) ? (rbs + 1) / 2 : rbs) * ((N + 31) / 32);
 }
 size_t gemm_small_partials(size_t M, size_t N, size_t K) {
   (void)K;
@@ -531,10 +531,10 @@ size_t gemm_small_f32_partials(size_t M, size_t N, size_t K) {
 // Any shape is computed correctly; it is the fast choice when the result is small.
 int launch_gemm_small(const GemmArgs& a, Epilogue epi, hipStream_t s) {
   if ((a.bits != 8 && a.bits != 16) || (epi != kEpiRaw && epi != kEpiDequant)) return MQ_ERR_UNSUPPORTED;
-  const PackedDims dA(a.bits, a.M, a.K), dW(a.bits, a.N, a.K);
+  const PackedDims dA(a.bits, a.M, a.K);
   const int dequant = epi == kEpiDequant;
   // two row blocks per workgroup only when that still leaves a workgroup for every compute unit
-  const bool wide = ((dA.nblocks + 1) / 2) * dW.nblocks >= 256;
+  const bool wide = gemm_small_two_blocks(a.M, a.N);
   if (a.bits == 16)
     return wide ? launch_small_tmw<16, 2>(a, dequant, dA.kfrags, s) : launch_small_tmw<16, 1>(a, dequant, dA.kfrags, s);
   return wide ? launch_small_tmw<8, 2>(a, dequant, dA.kfrags, s) : launch_small_tmw<8, 1>(a, dequant, dA.kfrags, s);

@@ -95,6 +95,7 @@ int launch_gemm_packed(const GemmArgs& a, Epilogue epi, hipStream_t s);
 int launch_gemm_small(const GemmArgs& a, Epilogue epi, hipStream_t s);
 // With the dequantizing epilogue both small-product launchers also write max|y| of every workgroup to
 // a.partial (if not NULL): gemm_small_partials / gemm_small_f32_partials values.
+bool gemm_small_two_blocks(size_t M, size_t N);       // whether a workgroup takes two blocks of 32 rows
 size_t gemm_small_workgroups(size_t M, size_t N);
 size_t gemm_small_partials(size_t M, size_t N, size_t K);
 size_t gemm_small_f32_partials(size_t M, size_t N, size_t K);

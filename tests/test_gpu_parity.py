@@ -402,8 +402,14 @@ def hip_runtime():
         return ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
 
 
-def launches(call):
-    """Kernels that call(stream) enqueues: the nodes of a graph captured from it, after one call that really runs."""
+class KernelNode(ctypes.Structure):              # hipKernelNodeParams
+    _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint * 3),
+                ("params", ctypes.c_void_p), ("lds", ctypes.c_uint)]
+
+
+def launched_grids(call):
+    """(workgroups, threads of one) of the kernels that call(stream) enqueues: the nodes of a graph captured from it, after
+    one call that really runs."""
     hip, graph, n = hip_runtime(), ctypes.c_void_p(), ctypes.c_size_t()
     stream = torch.cuda.Stream()
     call(stream)
@@ -414,8 +420,19 @@ def launches(call):
     finally:
         assert hip.hipStreamEndCapture(ctypes.c_void_p(stream.cuda_stream), ctypes.byref(graph)) == 0
     assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
+    grids = []
+    for node in nodes:
+        k = KernelNode()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(k)) == 0
+        grids.append((k.grid[0] * k.grid[1] * k.grid[2], k.block[0]))
     assert hip.hipGraphDestroy(graph) == 0
-    return n.value
+    return grids
+
+
+def launches(call):
+    return len(launched_grids(call))
 
 
 def tune(bits, M, N, K):
@@ -704,7 +721,9 @@ def test_gemm_packed_full_range_all_variants(dtype, M, N, K):
 
 @pytest.mark.parametrize("dtype", [np.int8, np.int16])
 @pytest.mark.parametrize("M,N,K", [(640, 1024, 96), (641, 1024, 96), (704, 1100, 70), (1500, 700, 160), (2049, 1024, 700),
-                                   (4100, 1030, 96), (2304, 4096, 64), (3700, 1000, 2048), (4096, 1024, 1990)])
+                                   (4100, 1030, 96), (2304, 4096, 64), (3700, 1000, 2048), (4096, 1024, 1990),
+                                   (504, 1030, 130), (513, 1030, 130), (1024, 1024, 96), (1025, 1024, 96), (2048, 250, 100), (2050, 250, 1000),
+                                   (2050, 256, 500), (600, 878, 1100), (384, 1024, 2100), (1000, 1024, 2100)])
 def test_gemm_packed_default_choice(dtype, M, N, K):
     # no forced variant: shapes on both sides of the lines where the default changes from the split-K kernel to the tiles
     # and from one tile size to the next
@@ -713,6 +732,20 @@ def test_gemm_packed_default_choice(dtype, M, N, K):
     qA = rng.integers(-lim, lim + 1, size=(M, K)).astype(dtype)
     qB = rng.integers(-lim, lim + 1, size=(N, K)).astype(dtype)
     assert np.array_equal(gpu_dot_int_packed(qA, qB), oracle.dot_int(qA, qB))
+
+
+@pytest.mark.parametrize("bits,M,N,K,workgroups,threads", [
+    (8, 384, 1024, 4096, 384, 1024), (8, 512, 700, 700, 352, 512), (8, 300, 1536, 512, 480, 256), (16, 300, 1536, 512, 480, 256),
+    (16, 300, 2048, 2048, 320, 512), (8, 1001, 512, 2048, 256, 512),                      # split K ahead of the tiles
+    (8, 5003, 100, 3000, 80, 256), (8, 8192, 128, 512, 128, 256), (8, 8192, 512, 2048, 256, 256), (8, 1300, 512, 2048, 88, 256),     # tiles ahead of split K
+    (16, 5003, 100, 3000, 79, 256), (16, 8192, 4096, 1024, 256, 512)])
+def test_gemm_packed_default_configuration(bits, M, N, K, workgroups, threads):
+    # which kernel serves shapes on which a wrong choice costs 15 % to 100 %: seen by its grid
+    q = torch.zeros(mq.mq_packed_bytes(bits, M, K), dtype=torch.uint8, device=DEV)
+    w = torch.zeros(mq.mq_packed_bytes(bits, N, K), dtype=torch.uint8, device=DEV)
+    one, Y = torch.ones(1, dtype=torch.float32, device=DEV), torch.empty((M, N), dtype=torch.float32, device=DEV)
+    got = launched_grids(lambda s: mq.mq_gemm_dequant_packed(q, w, bits, M, N, K, one, one, None, False, Y, None, s))
+    assert got == [(workgroups, threads)]
 
 
 @pytest.mark.parametrize("dtype", [np.int8, np.int16])
