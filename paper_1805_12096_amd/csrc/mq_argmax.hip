@@ -548,8 +548,11 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
 // One workgroup per tile of 16 sentences: 16 groups of 16 lanes each take every 16th workgroup's keys of the tile (one
 // 128-byte line per group and load), the groups' maxima meet in LDS, and 16 lanes decode.  Bound by the round trip to
 // keys that other dies' workgroups have just written: a lane's loads (16 for 256 workgroups) all go out before the first
-// is looked at (four at a time the output layer took 0.7 us longer for 300 and for 61 sentences).
-// cols: at most 256 (cut_stream).
+// is looked at (four at a time the output layer took 0.7 us longer for 300 and for 61 sentences).  There is one wave per
+// SIMD, so the instructions in front of the loads count as well: as many loads as there are columns for, and 32-bit offsets
+// by addition (sixteen loads always, each with a 64-bit product for its address: 7.5 us for one sentence and a list of 200
+// words, 7.0 for 61 sentences; now 5.8 and 6.4).
+// cols: at most 256 (cut_stream); M: rows of one launch, so that an offset fits 32 bits.
 __global__ __launch_bounds__(256) void k_argmax_reduce(const unsigned long long* __restrict__ partial, unsigned cols,
                                                        unsigned M, const float* __restrict__ sA,
                                                        const float* __restrict__ sW, int32_t* __restrict__ tok,
@@ -558,19 +561,22 @@ __global__ __launch_bounds__(256) void k_argmax_reduce(const unsigned long long*
   __shared__ unsigned long long red[16][16];
   const unsigned mi = threadIdx.x % 16, gs = threadIdx.x / 16;
   const unsigned m = blockIdx.x * 16 + mi;
-  const size_t Mpad = ((size_t)M + 15) / 16 * 16;
+  const unsigned pitch = (M + 15) / 16 * 16 * 8;           // bytes of a column of keys
   unsigned long long key = 0ull;
-  if (m < M) {
-    const unsigned long long* col = partial + m;
-    unsigned long long k[16];
+  auto columns = [&](auto trips) {
+    constexpr int T = decltype(trips)::value;
+    const char* keys = reinterpret_cast<const char*>(partial);
+    const unsigned row = min(m, M - 1) * 8, first = row + gs * pitch, last = row + (cols - 1) * pitch;
+    unsigned long long k[T];
 #pragma unroll
-    for (int t = 0; t < 16; ++t) {                // (a slot past the end reads a valid key again, which changes nothing)
-      const unsigned g = gs + 16 * t < cols ? gs + 16 * t : gs % cols;
-      k[t] = col[(size_t)g * Mpad];
-    }
+    for (int t = 0; t < T; ++t)                            // (past the last column: that one again, which changes nothing)
+      k[t] = *reinterpret_cast<const unsigned long long*>(keys + min(first + t * (16 * pitch), last));
 #pragma unroll
-    for (int t = 0; t < 16; ++t) key = k[t] > key ? k[t] : key;
-  }
+    for (int t = 0; t < T; ++t) key = k[t] > key ? k[t] : key;
+  };
+  if (cols <= 16) columns(std::integral_constant<int, 1>{});
+  else if (cols <= 64) columns(std::integral_constant<int, 4>{});
+  else columns(std::integral_constant<int, 16>{});
   red[gs][mi] = key;
   __syncthreads();
   if (gs == 0 && m < M) {

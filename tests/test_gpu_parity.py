@@ -984,6 +984,21 @@ def test_greedy_packed_more_rows_than_one_pass_holds():
     assert np.array_equal(val, o["maxlogit"])
 
 
+@pytest.mark.parametrize("M", [1, 33])
+@pytest.mark.parametrize("columns", [1, 2, 15, 16, 17, 63, 64, 65, 240, 256])
+def test_greedy_packed_every_column_of_candidates_counts(columns, M):
+    # 16 words to a workgroup (up to 256 workgroups): the number of keys the reducing kernel loads goes by that count.
+    # The best word of sentence m sits in another workgroup's share for each m, the last one's included.
+    rng = np.random.default_rng(columns)
+    V, d = 16 * columns - 3, 64
+    Hd, E = rng.standard_normal((M, d), dtype=np.float32), rng.standard_normal((V, d), dtype=np.float32)
+    for m in range(min(M, V)):
+        E[V - 1 - m * V // M] = 3 * Hd[m]
+    o = oracle.greedy_output_layer(Hd, E)
+    tok, val = gpu_greedy_packed(Hd, E)
+    assert np.array_equal(tok, o["tok"]) and np.array_equal(val, o["maxlogit"])
+
+
 @pytest.mark.parametrize("M,V,d", [(6145, 300, 64), (6144 + 390, 4100, 96), (2 * 6144 + 1, 33, 32)])
 def test_greedy_packed_more_rows_than_one_launch_holds(M, V, d):
     # sixteen chunks of 384 rows per launch: the launches behind the first one start at a later row of the hidden states
