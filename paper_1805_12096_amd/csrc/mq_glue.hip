@@ -5,8 +5,6 @@
 // sub-layer ends in residual + layer normalisation).  All tensors are binary32, a decode step has a
 // few hundred rows of model width, so every kernel here is one short pass over a few 100 KB: one
 // workgroup per sentence, the row staged in LDS, reductions inside the workgroup.
-#include <type_traits>
-
 #include "mq_glue.h"
 #include "mq_grid_max.h"
 #include "mq_internal.h"
@@ -314,9 +312,13 @@ __global__ __launch_bounds__(kTA) void k_cross_attention(const float* __restrict
 // every load is a float4, a wave reads whole 1 KB pieces of a K row and all heads' partial dot products of one
 // source position come out of one pass; the context phase splits the source positions over thread groups so
 // that every thread has several rows of V in flight.
-// Bound by memory latency (one sentence) and bytes in flight (hundreds): K and the first rows of V are asked for together,
-// the lanes' dot products of a trip share the steps of the exchange between lanes, and up to 64 scores of a head are
-// normalised in registers.  300 sentences x 25 words, d = 512: 11.3 -> 9.6 us (3.2 TB/s), one sentence 5.7 -> 4.3 us.
+// Bound by memory latency (one sentence) and bytes in flight (hundreds): the lanes' dot products of a trip share the steps of
+// the exchange between lanes, and up to 64 scores of a head are normalised in registers.  Nothing is asked for that is not
+// needed (a branch that all lanes take alike costs less than a load), and registers stay at 36 / 54 / 96 (d = 256 / 512 /
+// 1024), so that four, four and two workgroups share a compute unit.  With the first rows of V asked for together with K
+// and rows past the end read again instead of left out, both were worse (72 / 100 / 144 registers): kernel times before
+// the exchange was shared, with that, now, in us: 1 x 25 words, d = 512 6.0, 4.9, 4.7; 300 x 25 8.5, 7.4, 7.2 (4.3 TB/s);
+// 600 x 25 12.1, 12.8, 11.0; 600 x 1 6.4, 8.2, 4.8; 300 x 25, d = 1024 15.8, 18.0, 13.2.
 template <int CH>      // CH = d / 256: float4 pieces of a row per lane
 __global__ __launch_bounds__(kTA) void k_cross_attention_fast(const float* __restrict__ q, const float* __restrict__ K,
                                                               const float* __restrict__ V, unsigned S, unsigned heads,
@@ -326,13 +328,12 @@ __global__ __launch_bounds__(kTA) void k_cross_attention_fast(const float* __res
   constexpr unsigned COLS = d / 4;                 // float4 columns of a row
   constexpr unsigned SG = kTA / COLS;              // groups of threads that share the source positions
   static_assert(kTA % COLS == 0 && SG >= 1, "context phase layout");
-  constexpr int kAhead = 8;                        // rows of V in registers: 32 source positions at d = 512
   __shared__ float sc[kMaxScores];
   __shared__ float4 part[SG > 1 ? kTA : 1];
   __shared__ float red[NWV];
   const size_t m = blockIdx.x;
   const unsigned dh = d / heads, grp = dh / 4;     // lanes per head inside a 256-float piece
-  const unsigned lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const unsigned lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const float scale = __fdiv_rn(1.0f, sqrtf((float)dh));
   const float4* q4 = reinterpret_cast<const float4*>(q + m * d);
   const float4* K4 = reinterpret_cast<const float4*>(K + m * S * d);
@@ -340,21 +341,17 @@ __global__ __launch_bounds__(kTA) void k_cross_attention_fast(const float* __res
   float4 qr[CH];
 #pragma unroll
   for (int c = 0; c < CH; ++c) qr[c] = q4[c * 64 + lane];
-  // this thread's first kAhead rows of V are asked for before the first scores are formed: no second round trip to memory
-  const unsigned col = threadIdx.x % COLS, sg = threadIdx.x / COLS;
-  float4 va[kAhead];
-  auto scores = [&](unsigned s0, auto ahead) {
+  for (unsigned s0 = wave; s0 < S; s0 += 4 * NWV) {
     float4 kr[4][CH];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const unsigned s = s0 + u * NWV < S ? s0 + u * NWV : S - 1;    // past the end: a valid row again, result unused
+      if (s0 + u * NWV < S) {
 #pragma unroll
-      for (int c = 0; c < CH; ++c) kr[u][c] = K4[(size_t)s * COLS + c * 64 + lane];
-    }
-    if constexpr (decltype(ahead)::value) {
+        for (int c = 0; c < CH; ++c) kr[u][c] = K4[(size_t)(s0 + u * NWV) * COLS + c * 64 + lane];
+      } else {
 #pragma unroll
-      for (int j = 0; j < kAhead; ++j) va[j] = V4[(size_t)(sg + j * SG < S ? sg + j * SG : S - 1) * COLS + col];
-      __builtin_amdgcn_sched_barrier(0);
+        for (int c = 0; c < CH; ++c) kr[u][c] = make_float4(0.f, 0.f, 0.f, 0.f);
+      }
     }
     // (all sums of a trip take one step of the exchange together: one after the other they are 4 CH serial chains)
     float a[4][CH];
@@ -374,9 +371,7 @@ __global__ __launch_bounds__(kTA) void k_cross_attention_fast(const float* __res
 #pragma unroll
         for (int c = 0; c < CH; ++c)
           if (s0 + u * NWV < S) sc[(c * 256 + 4 * lane) / dh * S + s0 + u * NWV] = a[u][c] * scale;
-  };
-  scores(wave, std::true_type{});
-  for (unsigned s0 = wave + 4 * NWV; s0 < S; s0 += 4 * NWV) scores(s0, std::false_type{});
+  }
   __syncthreads();
   for (unsigned h = wave; h < heads; h += NWV) {
     if (S <= kWave) {                                // the scores stay in a register
@@ -405,18 +400,10 @@ __global__ __launch_bounds__(kTA) void k_cross_attention_fast(const float* __res
     for (unsigned s = lane; s < S; s += kWave) sc[h * S + s] *= inv;
   }
   __syncthreads();
+  const unsigned col = threadIdx.x % COLS, sg = threadIdx.x / COLS;
   const unsigned h = (4 * col) / dh;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-  for (int j = 0; j < kAhead; ++j)
-    if (sg + j * SG < S) {
-      const float p0 = sc[h * S + sg + j * SG];
-      acc.x = fmaf(p0, va[j].x, acc.x);
-      acc.y = fmaf(p0, va[j].y, acc.y);
-      acc.z = fmaf(p0, va[j].z, acc.z);
-      acc.w = fmaf(p0, va[j].w, acc.w);
-    }
-  unsigned s = sg + kAhead * SG;
+  unsigned s = sg;
   for (; s + 3 * SG < S; s += 4 * SG) {
     const float4 v0 = V4[(size_t)s * COLS + col], v1 = V4[(size_t)(s + SG) * COLS + col],
                  v2 = V4[(size_t)(s + 2 * SG) * COLS + col], v3 = V4[(size_t)(s + 3 * SG) * COLS + col];
@@ -537,15 +524,12 @@ int launch_cross_attention(const float* q, const float* K, const float* V, size_
   const bool vec_ok = (reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(K) | reinterpret_cast<uintptr_t>(V) |
                        reinterpret_cast<uintptr_t>(ctx)) % 16 == 0;
   if (vec_ok && pow2 && dh >= 4 && dh <= 256 && (d == 256 || d == 512 || d == 1024)) {
-    if (d == 256)
-      hipLaunchKernelGGL((k_cross_attention_fast<1>), dim3((unsigned)M), dim3(kTA), 0, s, q, K, V, (unsigned)S,
-                         (unsigned)heads, ctx, partial);
-    else if (d == 512)
-      hipLaunchKernelGGL((k_cross_attention_fast<2>), dim3((unsigned)M), dim3(kTA), 0, s, q, K, V, (unsigned)S,
-                         (unsigned)heads, ctx, partial);
-    else
-      hipLaunchKernelGGL((k_cross_attention_fast<4>), dim3((unsigned)M), dim3(kTA), 0, s, q, K, V, (unsigned)S,
-                         (unsigned)heads, ctx, partial);
+    auto go = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3((unsigned)M), dim3(kTA), 0, s, q, K, V, (unsigned)S, (unsigned)heads, ctx, partial);
+    };
+    if (d == 256) go(k_cross_attention_fast<1>);
+    else if (d == 512) go(k_cross_attention_fast<2>);
+    else go(k_cross_attention_fast<4>);
     return check_hip(hipGetLastError());
   }
   hipLaunchKernelGGL(k_cross_attention, dim3((unsigned)M), dim3(kTA), 0, s, q, K, V, (unsigned)S, (unsigned)d,

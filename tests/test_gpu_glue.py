@@ -100,9 +100,11 @@ def test_layer_norm_kernels_give_the_same_bits(M, d):
 
 @pytest.mark.parametrize("M,S,d,heads", [(1, 1, 8, 1), (7, 5, 48, 3), (300, 25, 512, 8), (9, 130, 256, 4),
                                           (5, 7, 1024, 16), (6, 9, 512, 4), (4, 3, 256, 64), (3, 6, 512, 2),
-                                          # around the rows of V held in registers (8 per thread group) and 64 scores a head
+                                          # around the trips of 32 source positions and 64 scores a head
                                           (3, 31, 512, 8), (2, 33, 512, 8), (5, 64, 512, 1), (2, 65, 1024, 4), (1, 17, 1024, 16),
-                                          (3, 63, 256, 2), (3, 64, 256, 1), (2, 150, 256, 8), (4, 1, 1024, 8)])
+                                          (3, 63, 256, 2), (3, 64, 256, 1), (2, 150, 256, 8), (4, 1, 1024, 8),
+                                          # fewer positions than waves, and than rows of a trip; more sentences than compute units
+                                          (600, 1, 512, 8), (300, 8, 1024, 16), (1, 9, 256, 4), (2, 24, 512, 8), (257, 26, 512, 8)])
 def test_cross_attention(M, S, d, heads):
     rng = np.random.default_rng(M + S + d)
     q = rng.standard_normal((M, d), dtype=np.float32) * np.float32(2)
