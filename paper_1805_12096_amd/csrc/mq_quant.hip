@@ -1,6 +1,8 @@
 // quant_int on gfx950: per-tensor abs-max, multiplier, and the float -> int8 /
 // int16 conversion (arxiv 1805.12096, Section 4.2).  All three are bound by HBM
 // traffic: wide coalesced loads, one pass each.
+#include <type_traits>
+
 #include "mq_grid_max.h"
 #include "mq_internal.h"
 
@@ -86,17 +88,22 @@ __global__ void k_scale(const float* __restrict__ amax, float qmax, float* __res
 }
 
 // One element of quant_int: binary32 multiply, round half to even, symmetric
-// clamp; NaN becomes 0.
-__device__ __forceinline__ int quant1(float x, float s, float lim) {
+// clamp; NaN becomes 0.  Four instructions: the conversion saturates and takes NaN
+// to 0 by itself, so the clamp is one on integers.
+__device__ __forceinline__ int quant1(float x, float s, int lim) {
   const float r = rintf(__fmul_rn(x, s));
-  const float c = fminf(fmaxf(r, -lim), lim);
-  return (r != r) ? 0 : (int)c;
+  int i;
+  asm("v_cvt_i32_f32 %0, %1" : "=v"(i) : "v"(r));
+  return min(max(i, -lim), lim);
 }
 
-__device__ __forceinline__ uint32_t pack4_i8(int a, int b, int c, int d) {
-  return (uint32_t)(a & 0xFF) | ((uint32_t)(b & 0xFF) << 8) | ((uint32_t)(c & 0xFF) << 16) |
-         ((uint32_t)(d & 0xFF) << 24);
+// Byte BYTE of four words: two byte permutes and an or (0x0c selects zero).
+template <unsigned BYTE>
+__device__ __forceinline__ uint32_t pack4_bytes(int a, int b, int c, int d) {
+  return __builtin_amdgcn_perm((uint32_t)b, (uint32_t)a, 0x0c0c0000u | (4u + BYTE) << 8 | BYTE) |
+         __builtin_amdgcn_perm((uint32_t)d, (uint32_t)c, (4u + BYTE) << 24 | BYTE << 16 | 0x0c0cu);
 }
+__device__ __forceinline__ uint32_t pack4_i8(int a, int b, int c, int d) { return pack4_bytes<0>(a, b, c, d); }
 __device__ __forceinline__ uint32_t pack2_i16(int a, int b) {
   return (uint32_t)(a & 0xFFFF) | ((uint32_t)(b & 0xFFFF) << 16);
 }
@@ -108,7 +115,7 @@ __global__ __launch_bounds__(kThreads) void k_quantize_flat(const float* __restr
                                                             const float* __restrict__ scale,
                                                             void* __restrict__ qv) {
   const float s = *scale;
-  const float lim = BITS == 8 ? 127.0f : 32767.0f;
+  const int lim = BITS == 8 ? 127 : 32767;
   const size_t tid = (size_t)blockIdx.x * kThreads + threadIdx.x;
   const size_t nthreads = (size_t)gridDim.x * kThreads;
   const size_t nvec = n / 8;
@@ -146,7 +153,7 @@ __global__ __launch_bounds__(kThreads) void k_quantize_rows(const float* __restr
                                                             void* __restrict__ qv,
                                                             int32_t* __restrict__ rowsum) {
   const float s = *scale;
-  const float lim = BITS == 8 ? 127.0f : 32767.0f;
+  const int lim = BITS == 8 ? 127 : 32767;
   const int lane = threadIdx.x % kWave;
   const size_t wave = (size_t)blockIdx.x * (kThreads / kWave) + threadIdx.x / kWave;
   const size_t nwaves = (size_t)gridDim.x * (kThreads / kWave);
@@ -299,41 +306,52 @@ __device__ __forceinline__ float block_max_of_partials(const float* __restrict__
   return r;
 }
 
-// Four consecutive elements of a row from column k on, always from addresses inside the tensor (what lies past its end is
-// masked after the conversion): a load under a condition is a branch with a wait of its own behind it, which makes the
-// loads of a trip follow one another instead of being in flight together (quantizing kernel of a 5003 x 1024 product 7.4
-// -> 6.4 us = 4.0 TB/s, of 8192 x 4096 to 16 bit 35.7 -> 34.3 us = 5.9 TB/s; one-kernel form, 300 x 512, 4.8 -> 4.6 us).
-template <bool VEC>
+// Four consecutive elements of a row from column k on, always from addresses inside the tensor: a load under a condition of
+// its own is a branch with a wait of its own behind it, which makes the loads of a trip follow one another instead of being
+// in flight together (quantizing kernel of a 5003 x 1024 product 7.4 -> 6.4 us = 4.0 TB/s, of 8192 x 4096 to 16 bit 35.7 ->
+// 34.3 us = 5.9 TB/s; one-kernel form, 300 x 512, 4.8 -> 4.6 us).  What lies past the row's end is taken out of the
+// converted bytes by place4.  Rows of any length are read in vectors, too: one element at a time, each with its own clamp,
+// 1001 x 2050 took 5.4 us where it now takes 4.0 (16 bit 8.0, now 6.3; with abs-max in one kernel 12.1, now 8.9).
+enum Cols {
+  kColsVec,       // a multiple of 4: rows are 16-byte aligned
+  kColsAny,       // at least 4: rows are 4-byte aligned; the last vector of a row ends at its end
+  kColsFew,       // 1 .. 3
+};
+inline Cols cols_kind(size_t cols) { return cols % 4 == 0 ? kColsVec : cols > 4 ? kColsAny : kColsFew; }
+
+template <Cols COLS>
 __device__ __forceinline__ float4 load4_clamped(const float* __restrict__ row, unsigned k, unsigned cols) {
-  if constexpr (VEC) {                       // cols is a multiple of 4, rows are 16-byte aligned
-    return *reinterpret_cast<const float4*>(row + min(k, cols - 4));
-  } else {
+  if constexpr (COLS == kColsFew) {
     const unsigned last = cols - 1;
     return make_float4(row[min(k, last)], row[min(k + 1, last)], row[min(k + 2, last)], row[min(k + 3, last)]);
+  } else {
+    float4 v;
+    const float* src = row + min(k, cols - 4);
+    if constexpr (COLS == kColsVec) v = *reinterpret_cast<const float4*>(src);
+    else __builtin_memcpy(&v, src, sizeof(v));
+    return v;
   }
 }
-// Bit masks that clear the bytes of elements k .. k + 3 that lie past the row's end, or all of them past the last row.
-template <bool VEC>
-__device__ __forceinline__ uint32_t mask4(bool row_ok, unsigned k, unsigned cols) {
-  if constexpr (VEC) {
-    return row_ok && k < cols ? 0xFFFFFFFFu : 0u;
-  } else {
-    const unsigned n = row_ok && k < cols ? min(cols - k, 4u) : 0u;
-    return n == 0 ? 0u : 0xFFFFFFFFu >> (8 * (4 - n));
-  }
+// The bytes of what load4_clamped read, as elements k .. k + 3 of the row: zero past the row's end, and past the last row.
+template <Cols COLS>
+__device__ __forceinline__ uint32_t place4(uint32_t bytes, bool row_ok, unsigned k, unsigned cols) {
+  if (!row_ok || k >= cols) return 0u;
+  if constexpr (COLS == kColsVec) return bytes;
+  if constexpr (COLS == kColsAny) return bytes >> (8 * (k - min(k, cols - 4)));      // read up to three elements early
+  return bytes & (0xFFFFFFFFu >> (8 * (4 - min(cols - k, 4u))));
 }
 
 // Converts four elements and stores their bytes at dst (16 bit: two planes; q = 256 h + l + 128, high bytes and low
 // bytes with the top bit flipped).  Returns the sum of the four quantized values (16 bit).
-template <int BITS>
-__device__ __forceinline__ int store4(uint8_t* dst, float4 v, float s, float lim, uint32_t mask) {
+template <int BITS, Cols COLS>
+__device__ __forceinline__ int store4(uint8_t* dst, float4 v, float s, int lim, bool row_ok, unsigned k, unsigned cols) {
   const int q0 = quant1(v.x, s, lim), q1 = quant1(v.y, s, lim), q2 = quant1(v.z, s, lim), q3 = quant1(v.w, s, lim);
-  const uint32_t lo = pack4_i8(q0, q1, q2, q3) & mask;
+  const uint32_t lo = place4<COLS>(pack4_i8(q0, q1, q2, q3), row_ok, k, cols);
   if constexpr (BITS == 8) {
     *reinterpret_cast<uint32_t*>(dst) = lo;
     return 0;
   } else {
-    const uint32_t hi = pack4_i8(q0 >> 8, q1 >> 8, q2 >> 8, q3 >> 8) & mask;
+    const uint32_t hi = place4<COLS>(pack4_bytes<1>(q0, q1, q2, q3), row_ok, k, cols);
     *reinterpret_cast<uint32_t*>(dst) = hi;
     *reinterpret_cast<uint32_t*>(dst + kFragBytes) = lo ^ 0x80808080u;
     // sum of the values = sum of the low bytes (unsigned) + 256 x sum of the high bytes (signed)
@@ -347,7 +365,7 @@ __device__ __forceinline__ int store4(uint8_t* dst, float4 v, float s, float lim
 // A work item is `per` fragments along K of a group of eight rows, kQuantFlight of them loaded at a time; the first item's
 // first loads go out before the partial maxima are asked for, so that the two round trips to memory are one.
 constexpr int kQuantFlight = 4;
-template <int BITS, bool VEC, bool FROM_PARTIALS>
+template <int BITS, Cols COLS, bool FROM_PARTIALS>
 __global__ __launch_bounds__(kThreads) void k_quantize_pack(const float* __restrict__ x, size_t rows,
                                                             size_t cols, const float* __restrict__ scale,
                                                             uint8_t* __restrict__ packed, unsigned ksplit,
@@ -356,25 +374,26 @@ __global__ __launch_bounds__(kThreads) void k_quantize_pack(const float* __restr
   // words a later kernel wants zero (spread over the grid: one workgroup walking through them is a serial tail)
   for (unsigned i = blockIdx.x * kThreads + threadIdx.x; i < nclear; i += gridDim.x * kThreads) clear[i] = 0u;
   const PackedDims d(BITS, rows, cols);
-  const float lim = BITS == 8 ? 127.0f : 32767.0f;
+  const int lim = BITS == 8 ? 127 : 32767;
   const int lane = threadIdx.x % kWave;
   const int sub = lane % 8;                       // which 4 floats of a 32-element fragment row
   // (indexes of fragments, row groups and items fit 32 bits: rows and columns are below 2^31, items below 2^29 x 16)
   const unsigned kfrags = (unsigned)d.kfrags, row_groups = (unsigned)(d.Np / 8);
-  const unsigned wave = blockIdx.x * (kThreads / kWave) + threadIdx.x / kWave;
+  const unsigned wave_in = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);      // scalar, like the item made of it
+  const unsigned wave = blockIdx.x * (kThreads / kWave) + wave_in;
   const unsigned nwaves = gridDim.x * (kThreads / kWave);
   const unsigned per = (kfrags + ksplit - 1) / ksplit;   // fragments along K per work item
   // 16 bit, long rows: the workgroup's waves share a row group, each takes its part of K (four times the loads in
   // flight of one wave per row group, which leaves a chip with a thousand row groups at four waves per compute
   // unit), and the rows' sums meet in LDS.  ksplit is the number of waves of the workgroup then.
   const bool shared_rows = BITS == 16 && ksplit > 1;
-  unsigned rg = shared_rows ? blockIdx.x : wave / ksplit, part = shared_rows ? threadIdx.x / kWave : wave % ksplit;
+  unsigned rg = shared_rows ? blockIdx.x : wave / ksplit, part = shared_rows ? wave_in : wave % ksplit;
   const unsigned ncols = (unsigned)cols, nrows = (unsigned)rows;
   float4 v[kQuantFlight];
   auto load = [&](unsigned kb0) {
     const float* xr = x + (size_t)min(rg * 8 + lane / 8, nrows - 1) * cols;
 #pragma unroll
-    for (int j = 0; j < kQuantFlight; ++j) v[j] = load4_clamped<VEC>(xr, (kb0 + j) * kFragK + 4 * sub, ncols);
+    for (int j = 0; j < kQuantFlight; ++j) v[j] = load4_clamped<COLS>(xr, (kb0 + j) * kFragK + 4 * sub, ncols);
   };
   if (rg < row_groups) load(part * per);
   float s;
@@ -396,8 +415,8 @@ __global__ __launch_bounds__(kThreads) void k_quantize_pack(const float* __restr
 #pragma unroll
       for (int j = 0; j < kQuantFlight; ++j) {
         if (kb0 + j >= kb_end) break;
-        sum += store4<BITS>(out + (size_t)(kb0 + j) * (kFragBytes * (BITS == 16 ? 2 : 1)), v[j], s, lim,
-                            mask4<VEC>(row < nrows, (kb0 + j) * kFragK + 4 * sub, ncols));
+        sum += store4<BITS, COLS>(out + (size_t)(kb0 + j) * (kFragBytes * (BITS == 16 ? 2 : 1)), v[j], s, lim, row < nrows,
+                                  (kb0 + j) * kFragK + 4 * sub, ncols);
       }
     }
     if (BITS == 16) {
@@ -441,7 +460,7 @@ __global__ __launch_bounds__(kThreads) void k_quantize_pack(const float* __restr
 // grid: every wave loads its share (8 rows x 4 NI fragments), the workgroups agree on max|x| (see
 // mq_grid_max.h), and the share is converted from registers.  Same work split, rounding and layout as
 // k_quantize_pack; x is read once instead of twice and one kernel boundary disappears.
-template <int BITS, bool VEC, int NI>
+template <int BITS, Cols COLS, int NI>
 __global__ __launch_bounds__(512) void k_absmax_quantize_pack(const float* __restrict__ x, size_t rows, size_t cols,
                                                               uint8_t* __restrict__ packed, unsigned ksplit,
                                                               unsigned* barrier, unsigned long long ticks,
@@ -453,26 +472,31 @@ __global__ __launch_bounds__(512) void k_absmax_quantize_pack(const float* __res
   if (clear_words != nullptr && blockIdx.x == 0)
     for (unsigned i = threadIdx.x; i < nclear; i += 512) clear_words[i] = 0u;
   const PackedDims d(BITS, rows, cols);
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);      // scalar, as the item
   const int sub = lane % 8;                       // which 4 floats of a 32-element fragment row
-  const size_t row_groups = d.Np / 8;
-  const size_t per = (d.kfrags + ksplit - 1) / ksplit;   // fragments along K per wave, at most 4 NI
-  const size_t item = (size_t)blockIdx.x * kW + wave;
+  // (a resident grid's items and the tensor's rows, columns and fragments all fit 32 bits)
+  const unsigned kfrags = (unsigned)d.kfrags, row_groups = (unsigned)(d.Np / 8), ncols = (unsigned)cols, nrows = (unsigned)rows;
+  const unsigned per = (kfrags + ksplit - 1) / ksplit;   // fragments along K per wave, at most 4 NI
+  const unsigned item = blockIdx.x * kW + wave;
   const bool active = item < row_groups * ksplit;
-  const size_t rg = item / ksplit, part = item % ksplit;
-  const size_t row = rg * 8 + lane / 8;
-  const size_t kb_begin = part * per;
-  const size_t kb_end = (part + 1) * per < d.kfrags ? (part + 1) * per : d.kfrags;
-  // every load from inside the tensor and without a condition around it (see load4_clamped); fragments past this wave's
-  // part and inactive waves read elements that other lanes hold as well, so the maximum needs no mask
-  const unsigned ncols = (unsigned)cols;
-  const float* xr = x + min(row, rows - 1) * cols;
+  const unsigned rg = item / ksplit, part = item % ksplit;
+  const unsigned row = rg * 8 + lane / 8;
+  const unsigned kb_begin = part * per, kb_end = min(kb_begin + per, kfrags);
+  // every load from inside the tensor and without a condition of its own (see load4_clamped); fragments past this wave's
+  // part, rows past the end and inactive waves read elements that other lanes hold as well, so the maximum needs no mask
+  const float* xr = x + (size_t)min(row, nrows - 1) * cols;
   float4 v[NI][4];
   float m = 0.f;
 #pragma unroll
-  for (int t = 0; t < NI; ++t)
+  for (int t = 0; t < NI; ++t) {
+    if (t == 0 || kb_begin + 4 * t < kb_end) {      // scalar: trips past this wave's part are left out
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[t][j] = load4_clamped<VEC>(xr, ((unsigned)kb_begin + 4 * t + j) * kFragK + 4 * sub, ncols);
+      for (int j = 0; j < 4; ++j) v[t][j] = load4_clamped<COLS>(xr, (kb_begin + 4 * t + j) * kFragK + 4 * sub, ncols);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[t][j] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  }
 #pragma unroll
   for (int t = 0; t < NI; ++t)
 #pragma unroll
@@ -496,20 +520,19 @@ __global__ __launch_bounds__(512) void k_absmax_quantize_pack(const float* __res
   // count goes out now and is looked at after the stores); the first still has to look at the sticky word.
   unsigned retired_before = 0u;
   if (self_clean && blockIdx.x != 0 && threadIdx.x == 0) retired_before = grid_max_retire(barrier);
-  const float lim = BITS == 8 ? 127.0f : 32767.0f;
-  const float s = (amax > 0.0f) ? __fdiv_rn(lim, amax) : 1.0f;
+  const int lim = BITS == 8 ? 127 : 32767;
+  const float s = (amax > 0.0f) ? __fdiv_rn((float)lim, amax) : 1.0f;
   int sum = 0;
   if (active) {
-    const size_t nb = row / kFragRows;
-    const int slot = (int)(row % kFragRows) + 32 * (sub / 4);
+    uint8_t* out = packed + d.frag_offset(row / kFragRows, 0) + (row % kFragRows + 32 * (sub / 4)) * 16 + 4 * (sub % 4);
 #pragma unroll
     for (int t = 0; t < NI; ++t)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const size_t kb = kb_begin + 4 * t + j;
+        const unsigned kb = kb_begin + 4 * t + j;
         if (kb < kb_end)
-          sum += store4<BITS>(packed + d.frag_offset(nb, kb) + (size_t)slot * 16 + 4 * (sub % 4), v[t][j], s, lim,
-                              mask4<VEC>(row < rows, (unsigned)kb * kFragK + 4 * sub, ncols));
+          sum += store4<BITS, COLS>(out + (size_t)kb * (kFragBytes * (BITS == 16 ? 2 : 1)), v[t][j], s, lim, row < nrows,
+                                    kb * kFragK + 4 * sub, ncols);
       }
   }
   if (BITS == 16) {
@@ -560,15 +583,18 @@ int launch_quantize_pack(const float* x, size_t rows, size_t cols, int bits, con
   }
   const unsigned grid = bits == 16 && ksplit > 1 ? grid_for(row_groups, 1, 8192) : grid_for(row_groups * ksplit, kThreads / kWave, 8192);
   uint8_t* p = static_cast<uint8_t*>(packed);
-  const bool vec = cols % 4 == 0;
-  float* none = nullptr;
-  if (bits == 8) {
-    if (vec) hipLaunchKernelGGL((k_quantize_pack<8, true, false>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, scale, p, ksplit, 0u, none, clear, nclear);
-    else hipLaunchKernelGGL((k_quantize_pack<8, false, false>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, scale, p, ksplit, 0u, none, clear, nclear);
-  } else {
-    if (vec) hipLaunchKernelGGL((k_quantize_pack<16, true, false>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, scale, p, ksplit, 0u, none, clear, nclear);
-    else hipLaunchKernelGGL((k_quantize_pack<16, false, false>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, scale, p, ksplit, 0u, none, clear, nclear);
-  }
+  const Cols kind = cols_kind(cols);
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), 0, s, x, rows, cols, scale, p, ksplit, 0u, (float*)nullptr, clear, nclear);
+  };
+  auto by_kind = [&](auto bits_tag) {
+    constexpr int B = decltype(bits_tag)::value;
+    if (kind == kColsVec) go(k_quantize_pack<B, kColsVec, false>);
+    else if (kind == kColsAny) go(k_quantize_pack<B, kColsAny, false>);
+    else go(k_quantize_pack<B, kColsFew, false>);
+  };
+  if (bits == 8) by_kind(std::integral_constant<int, 8>{});
+  else by_kind(std::integral_constant<int, 16>{});
   return check_hip(hipGetLastError());
 }
 
@@ -601,23 +627,27 @@ int launch_quantize_pack_partials(const float* x, size_t rows, size_t cols, int 
   }
   const unsigned grid = bits == 16 && ksplit > 1 ? grid_for(row_groups, 1, 8192) : grid_for(row_groups * ksplit, kThreads / kWave, 8192);
   uint8_t* p = static_cast<uint8_t*>(packed);
-  const bool vec = cols % 4 == 0;
-  if (bits == 8) {
-    if (vec) hipLaunchKernelGGL((k_quantize_pack<8, true, true>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, partials, p, ksplit, g1, scale_out, (unsigned*)nullptr, 0u);
-    else hipLaunchKernelGGL((k_quantize_pack<8, false, true>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, partials, p, ksplit, g1, scale_out, (unsigned*)nullptr, 0u);
-  } else {
-    if (vec) hipLaunchKernelGGL((k_quantize_pack<16, true, true>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, partials, p, ksplit, g1, scale_out, (unsigned*)nullptr, 0u);
-    else hipLaunchKernelGGL((k_quantize_pack<16, false, true>), dim3(grid), dim3(kThreads), 0, s, x, rows, cols, partials, p, ksplit, g1, scale_out, (unsigned*)nullptr, 0u);
-  }
+  const Cols kind = cols_kind(cols);
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), 0, s, x, rows, cols, partials, p, ksplit, g1, scale_out, (unsigned*)nullptr, 0u);
+  };
+  auto by_kind = [&](auto bits_tag) {
+    constexpr int B = decltype(bits_tag)::value;
+    if (kind == kColsVec) go(k_quantize_pack<B, kColsVec, true>);
+    else if (kind == kColsAny) go(k_quantize_pack<B, kColsAny, true>);
+    else go(k_quantize_pack<B, kColsFew, true>);
+  };
+  if (bits == 8) by_kind(std::integral_constant<int, 8>{});
+  else by_kind(std::integral_constant<int, 16>{});
   return check_hip(hipGetLastError());
 }
 
 namespace {
-template <int BITS, bool VEC, int NI>
+template <int BITS, Cols COLS, int NI>
 int launch_fused_one(const float* x, size_t rows, size_t cols, uint8_t* packed, unsigned ksplit, unsigned grid,
                      unsigned* barrier, float* scale_out, hipStream_t s, unsigned* clear_words, unsigned nclear,
                      int self_clean) {
-  auto kern = k_absmax_quantize_pack<BITS, VEC, NI>;
+  auto kern = k_absmax_quantize_pack<BITS, COLS, NI>;
   static int max_blocks = -1;       // workgroups the device can hold at once, asked once
   if (max_blocks < 0) {
     int per_cu = 0, dev = 0, cus = 0;
@@ -633,15 +663,15 @@ int launch_fused_one(const float* x, size_t rows, size_t cols, uint8_t* packed, 
   return check_hip(hipGetLastError());
 }
 
-template <int BITS, bool VEC>
+template <int BITS, Cols COLS>
 int launch_fused_ni(int ni, const float* x, size_t rows, size_t cols, uint8_t* packed, unsigned ksplit, unsigned grid,
                     unsigned* barrier, float* scale_out, hipStream_t s, unsigned* clear_words, unsigned nclear,
                     int self_clean) {
   switch (ni) {
-    case 1: return launch_fused_one<BITS, VEC, 1>(x, rows, cols, packed, ksplit, grid, barrier, scale_out, s, clear_words, nclear, self_clean);
-    case 2: return launch_fused_one<BITS, VEC, 2>(x, rows, cols, packed, ksplit, grid, barrier, scale_out, s, clear_words, nclear, self_clean);
-    case 4: return launch_fused_one<BITS, VEC, 4>(x, rows, cols, packed, ksplit, grid, barrier, scale_out, s, clear_words, nclear, self_clean);
-    default: return launch_fused_one<BITS, VEC, 8>(x, rows, cols, packed, ksplit, grid, barrier, scale_out, s, clear_words, nclear, self_clean);
+    case 1: return launch_fused_one<BITS, COLS, 1>(x, rows, cols, packed, ksplit, grid, barrier, scale_out, s, clear_words, nclear, self_clean);
+    case 2: return launch_fused_one<BITS, COLS, 2>(x, rows, cols, packed, ksplit, grid, barrier, scale_out, s, clear_words, nclear, self_clean);
+    case 4: return launch_fused_one<BITS, COLS, 4>(x, rows, cols, packed, ksplit, grid, barrier, scale_out, s, clear_words, nclear, self_clean);
+    default: return launch_fused_one<BITS, COLS, 8>(x, rows, cols, packed, ksplit, grid, barrier, scale_out, s, clear_words, nclear, self_clean);
   }
 }
 }  // namespace
@@ -668,13 +698,15 @@ int launch_absmax_quantize_pack_fused(const float* x, size_t rows, size_t cols, 
   const int ni = per <= 4 ? 1 : per <= 8 ? 2 : per <= 16 ? 4 : 8;
   const unsigned grid = (unsigned)((row_groups * ksplit + 512 / kWave - 1) / (512 / kWave));
   uint8_t* p = static_cast<uint8_t*>(packed);
-  const bool vec = cols % 4 == 0;
-  if (bits == 8) {
-    return vec ? launch_fused_ni<8, true>(ni, x, rows, cols, p, ksplit, grid, barrier, scale_out, s, clear_words, nclear, self_clean)
-               : launch_fused_ni<8, false>(ni, x, rows, cols, p, ksplit, grid, barrier, scale_out, s, clear_words, nclear, self_clean);
-  }
-  return vec ? launch_fused_ni<16, true>(ni, x, rows, cols, p, ksplit, grid, barrier, scale_out, s, clear_words, nclear, self_clean)
-             : launch_fused_ni<16, false>(ni, x, rows, cols, p, ksplit, grid, barrier, scale_out, s, clear_words, nclear, self_clean);
+  const Cols kind = cols_kind(cols);
+  auto go = [&](auto bits_tag) {
+    constexpr int B = decltype(bits_tag)::value;
+    // (1 .. 3 columns are two fragments along K)
+    if (kind == kColsFew) return launch_fused_one<B, kColsFew, 1>(x, rows, cols, p, ksplit, grid, barrier, scale_out, s, clear_words, nclear, self_clean);
+    return kind == kColsVec ? launch_fused_ni<B, kColsVec>(ni, x, rows, cols, p, ksplit, grid, barrier, scale_out, s, clear_words, nclear, self_clean)
+                            : launch_fused_ni<B, kColsAny>(ni, x, rows, cols, p, ksplit, grid, barrier, scale_out, s, clear_words, nclear, self_clean);
+  };
+  return bits == 8 ? go(std::integral_constant<int, 8>{}) : go(std::integral_constant<int, 16>{});
 }
 
 // abs-max + quant_int into the packed layout in two launches, no atomics, no fill:

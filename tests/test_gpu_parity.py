@@ -686,6 +686,50 @@ def test_quantize_pack_matches_oracle(bits, shape):
         assert np.array_equal(sums[:shape[0]], oq.astype(np.int64).sum(1).astype(np.int32))
 
 
+@pytest.mark.parametrize("bits", [8, 16])
+@pytest.mark.parametrize("rows", [1, 8, 33])
+@pytest.mark.parametrize("cols", [1, 2, 3, 4, 5, 6, 7, 9, 29, 31, 33, 62, 65, 67, 511, 513, 1022, 1157, 2050, 2307])
+def test_quantizers_at_row_ends(bits, rows, cols):
+    # rows that end anywhere in a vector of four, in a fragment, in a trip of four fragments, in a wave's part of K: all
+    # three entry points give the oracle's integers; 8 bit: zero padding as in a prepared copy, 16 bit: the row sums, zero
+    # for the padding rows
+    rng = np.random.default_rng(rows * 7919 + cols * 3 + bits)
+    x = rng.standard_normal((rows, cols), dtype=np.float32) * np.float32(2)
+    x[-1, -1] = -9.5                                  # the largest magnitude is the last element of all
+    x[rows // 2, max(cols - 3, 0)] = np.nan
+
+    def check(packed, q):
+        if bits == 8:
+            one = torch.ones(1, dtype=torch.float32, device=DEV)
+            assert torch.equal(packed, mq.prepare_weight(dev(q.astype(np.float32)), 8, scale=one).packed)
+            return
+        got = torch.empty((rows, cols), dtype=torch.int16, device=DEV)
+        mq.mq_unpack_weight(packed, 16, rows, cols, got)
+        assert np.array_equal(host(got), q)
+        sums = np.zeros((rows + 31) // 32 * 32, dtype=np.int32)
+        sums[:rows] = q.sum(1, dtype=np.int32)
+        assert np.array_equal(host(packed)[-4 * len(sums):].view(np.int32), sums)
+
+    x_inf = x.copy()                                  # a given multiplier: values beyond the range saturate
+    x_inf[0, cols // 2], x_inf[-1, 0] = np.inf, -1e30
+    packed, _ = gpu_quantize_pack(x_inf, bits, scale=63.5)
+    check(packed, oracle.quant_int(x_inf, bits, 63.5))
+
+    oq, os_ = oracle.quant_int_absmax(x, bits)
+    xd, nb = dev(x), mq.mq_quantize_absmax_ws_bytes()
+    for prepared in (False, True):
+        ws = torch.full((nb,), 0x6D, dtype=torch.uint8, device=DEV)
+        packed = torch.full((mq.mq_packed_bytes(bits, rows, cols),), 0x5A, dtype=torch.uint8, device=DEV)
+        s = torch.empty(1, dtype=torch.float32, device=DEV)
+        if prepared:
+            mq.mq_quantize_absmax_ws_prepare(ws, nb)
+            mq.mq_quantize_absmax_pack_f32_prepared(xd, rows, cols, bits, packed, s, ws, nb)
+        else:
+            mq.mq_quantize_absmax_pack_f32(xd, rows, cols, bits, packed, s, ws, nb)
+        assert host(s)[0] == os_
+        check(packed, oq)
+
+
 def gpu_dot_int_packed(qA, qB):
     bits = 8 if qA.dtype == np.int8 else 16
     one = torch.ones(1, dtype=torch.float32, device=DEV)
