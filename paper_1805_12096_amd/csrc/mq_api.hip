@@ -881,8 +881,9 @@ int mq_linear_f32(const float* A, size_t M, size_t K, const float* sA_or_null, c
   const bool apart = !overlap(A, M * K, Y, M * N);
   const bool in_fetch = bits == 8 && gemm_small_f32_supported(M, N, K);
   // one block of rows: abs-max, quant_int and product in one launch -- unless the other route leads to the packed products
-  // and the caller has forced or tuned one of them for this shape
-  if (apart && gemm_rows_supported(bits, M, N, K) && (in_fetch || !variant_named(bits, M, N, K)))
+  // and the caller has forced or tuned one of them for this shape, or is the shorter one (a given multiplier)
+  if (apart && gemm_rows_supported(bits, M, N, K) && (sA == nullptr || gemm_rows_ahead_given(bits, M, K, in_fetch)) &&
+      (in_fetch || !variant_named(bits, M, N, K)))
     return launch_gemm_rows(A, sA, a, s);
   if (apart && in_fetch) {
     // decode-sized input: quant_int happens inside the product's operand fetch (same arithmetic, same

@@ -7,8 +7,9 @@
 // between workgroups, so the glue kernel, the abs-max pass and the quantizer that stood in front of the product
 // disappear: at these sizes each of them is a launch (2.4 us on the host, 2 - 4 us on the device) around a few hundred
 // nanoseconds of work.  The price is that the input is read and converted once per 32 columns.
-// Measured: decoder layer of one sentence (512 / 2048) 53.3 -> 35.6 us, nine launches for fourteen.  Beyond 32 rows a
-// workgroup would have to read rows it does not multiply, which the two-launch forms win.
+// Measured: decoder layer of one sentence (512 / 2048) 53.3 -> 35.6 us, nine launches for fourteen.  32 rows are what one
+// workgroup's matrix instructions take; at 32 rows and K = 2048 it converts 64 K elements for 32 columns and is still ahead
+// with abs-max (7.7 against 9.1 us), no longer with a given multiplier: see gemm_rows_ahead_given.
 #include "mq_gemm_common.h"
 #include "mq_glue.h"
 #include "mq_grid_max.h"
@@ -368,6 +369,22 @@ RowsParams rows_params(const GemmArgs& a) {
 bool gemm_rows_supported(int bits, size_t M, size_t N, size_t K) {
   if (M < 1 || M > 32 || N < 1 || K < 4 || K % 4 != 0) return false;
   return K <= 2048 || (bits == 8 && K <= 4096 && M <= 16);
+}
+// With abs-max this form saves one launch at least and wins everywhere (K 4 .. 4096, 1 .. 32 rows, in us: 8 bit, K = 512 4.1
+// against 7.3, K = 1024 5.2 against 8.1, K = 2048 17 rows 7.6 against 9.0, K = 4096 9.3 against 10.1; 16 bit, K = 2048 17
+// rows 10.3 against 13.1).  With a given multiplier the others need one launch less and convert an element once, not once
+// per 32 columns, so it depends on how much every workgroup here converts, all pieces of 256 elements of every row a wave
+// holds (see launch_rows_k):
+//   * 8 bit with quant_int in the operand fetch, K in 513 .. 1024, four rows per wave: 5.0 - 5.1 against 4.6 - 4.8 us
+//     (K = 512 3.9 against 4.3, one row per wave 3.7 against 4.7);
+//   * 8 bit, two launches: K in 1025 .. 2048 with two rows per wave 7.2 - 7.4 against 6.3 - 6.5 (with one 5.1 - 5.4 against
+//     6.2 - 6.5), K above 2048 8.5 - 9.1 against 7.0 - 7.6;
+//   * 16 bit, whose product takes longer the longer K is: K in 1025 .. 1536 with two rows per wave 9.6 - 9.8 against 8.7 -
+//     9.5, K = 1800 10.1 against 10.2, K = 2048 10.1 against 10.4 (with one row 7.0 - 7.6 against 8.4 - 10.4).
+bool gemm_rows_ahead_given(int bits, size_t M, size_t K, bool in_fetch) {
+  if (in_fetch) return M <= 8 || K <= 512;
+  if (bits == 16) return M <= 16 || K <= 1024 || K > 1664;
+  return K <= 1024 || (K <= 2048 && M <= 16);
 }
 size_t gemm_rows_partials(size_t N) { return (N + 31) / 32; }
 bool gemm_rows_glue_supported(size_t M, size_t d) { return M >= 1 && M <= 32 && d % 256 == 0 && d <= 1024; }

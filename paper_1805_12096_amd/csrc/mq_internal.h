@@ -113,6 +113,8 @@ int launch_gemm_small_f32_pair(const float* A1, size_t K1, const float* part1, u
 // bit for the plain form; K a multiple of 4 up to 2048 (4096 for 8 bit and at most 16 rows), rows 16-byte aligned;
 // a.qA and a.sA are not used.  The result must not overlap the input.  a.partial receives gemm_rows_partials(N) maxima.
 bool gemm_rows_supported(int bits, size_t M, size_t N, size_t K);
+// Whether it is ahead of the other route where the multiplier is given (in_fetch: that route is one launch as well).
+bool gemm_rows_ahead_given(int bits, size_t M, size_t K, bool in_fetch);
 size_t gemm_rows_partials(size_t N);
 int launch_gemm_rows(const float* A, const float* scale, const GemmArgs& a, hipStream_t s);
 // The same with the input formed in the operand fetch, model width d = 256, 512, 768 or 1024, all tensors 16-byte aligned:

@@ -466,6 +466,26 @@ def test_a_tuned_or_forced_variant_is_the_product_that_runs(bits, M, N, K, befor
     assert launches(call) == after and np.array_equal(host(Y), want)
 
 
+@pytest.mark.parametrize("bits,M,N,K,fixed,count", [
+    (8, 32, 40, 512, True, 1), (8, 9, 40, 544, True, 1), (8, 32, 70, 1024, True, 1), (8, 9, 40, 516, True, 1),
+    (8, 32, 40, 1020, True, 1), (8, 16, 40, 1028, True, 1), (8, 17, 40, 1028, True, 2), (8, 16, 40, 2048, True, 1),
+    (8, 32, 40, 2048, True, 2), (8, 1, 40, 2052, True, 2), (8, 16, 40, 4096, True, 2), (8, 32, 40, 2048, False, 1),
+    (8, 16, 40, 4096, False, 1), (8, 17, 40, 4096, False, 3), (16, 32, 40, 1024, True, 1), (16, 16, 40, 1028, True, 1),
+    (16, 17, 40, 1028, True, 2), (16, 32, 40, 1664, True, 2), (16, 32, 40, 1668, True, 1), (16, 32, 40, 2048, False, 1)])
+def test_mq_linear_f32_of_few_rows_on_both_sides_of_its_lines(bits, M, N, K, fixed, count):
+    # which form serves up to 32 rows, seen by its launches, and that both sides of each line give the oracle's results
+    p = workloads.random_problem(M + N + K, M, N, K)
+    s0 = None if not fixed else 1024.0 if bits == 16 else 40.0
+    pw, A = mq.prepare_weight(dev(p["Wt"]), bits), dev(p["A"])
+    sA = torch.full((1,), s0, dtype=torch.float32, device=DEV) if fixed else None
+    nb = mq.mq_linear_ws_bytes(bits, M, K)
+    ws, Y = torch.full((nb,), 0x5A, dtype=torch.uint8, device=DEV), torch.full((M, N), -3.0, dtype=torch.float32, device=DEV)
+    bias = dev(p["bias"])
+    assert launches(lambda stream: mq.mq_linear_f32(A, M, K, sA, pw.packed, pw.scale, bits, N, bias, False, Y, None, ws, nb,
+                                                    stream)) == count
+    assert np.array_equal(host(Y), oracle.linear(p["A"], p["Wt"], bits, p["bias"], False, sA=s0)["Y"])
+
+
 # -------------------------------------------------------------------- arg-max
 
 def gpu_greedy(Hd, E, pw=None):
