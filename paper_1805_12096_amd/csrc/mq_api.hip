@@ -582,8 +582,8 @@ int mq_gemm_argmax(const void* qA, const void* packedW, size_t M, size_t N, size
     return MQ_ERR_ALIGN;
   if (ws_bytes < mq_argmax_ws_bytes(M, N)) return MQ_ERR_WORKSPACE;
   hipStream_t s = as_stream(stream);
-  // widths up to 1024 in whole 16-byte pieces: the streaming kernel (two launches, no atomics), see mq_argmax.hip
-  if (argmax_stream_rows_supported(N, K))
+  // widths up to 1024 in whole 16-byte pieces: the streaming kernel (two launches, no atomics) where it is ahead
+  if (argmax_stream_rows_supported(N, K) && argmax_stream_rows_ahead(M, N, K))
     return launch_argmax_stream_rows(qA, packedW, M, N, K, sA, sW, tok, maxlogit, ws, mq_argmax_ws_bytes(M, N), s);
   unsigned long long* keys = static_cast<unsigned long long*>(ws);
   rc = launch_argmax_init(keys, M, s);

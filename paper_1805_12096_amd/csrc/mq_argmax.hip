@@ -742,9 +742,60 @@ bool argmax_stream_supported(size_t M, size_t N, size_t K) {
   return K <= 64 * kKG && N <= (size_t)max_units_of(kKG) * 256 * 16;
 }
 
+namespace {
+// How a call's rows go into launches: chunks of rows per launch as many as run side by side with the fewest columns the
+// vocabulary needs (more only queue up behind a round that is nearly empty: 4096 rows, width 1024, 36 000 words in one launch
+// of 16 x 18 workgroups 216 us, in two of 8 x 32 136), spread evenly over the launches.  A launch's columns x rows never
+// exceed 256 x rows_max keys.
+struct StreamPlan {
+  size_t units, rows_max, max_units, launch_rows;
+};
+StreamPlan plan_stream(size_t M, size_t units, bool wide) {
+  StreamPlan p;
+  p.units = units;
+  p.rows_max = (size_t)kWaves * 16 * (wide ? kWideTPW : kMaxTPW);
+  p.max_units = max_units_of(wide ? kWideKG : kKG);
+  const size_t fewest = (units + p.max_units - 1) / p.max_units;
+  const size_t chunks = (M + p.rows_max - 1) / p.rows_max, side_by_side = compute_units() / (fewest < 2 ? 2 : fewest);
+  const size_t launches = side_by_side == 0 ? chunks : (chunks + side_by_side - 1) / side_by_side;
+  p.launch_rows = (chunks + launches - 1) / launches * p.rows_max;      // (whole 32-row blocks)
+  return p;
+}
+unsigned tiles_per_wave(const StreamCut& c) { return (c.chunk_rows / 16 + kWaves - 1) / kWaves; }
+}  // namespace
+
 // The same on plain row-major hidden states, K up to 1024 in whole 16-byte pieces.
 bool argmax_stream_rows_supported(size_t N, size_t K) {
   return K % 16 == 0 && K <= 64 * kWideKG && N <= (size_t)max_units_of(K <= 64 * kKG ? kKG : kWideKG) * 256 * 16;
+}
+
+// Plain rows: the streaming kernel or the tiled product with the arg-max in its epilogue.  The tiled one multiplies 128 x 128
+// tiles and wins where the matrix instructions are few (narrow widths, which the streaming kernel multiplies as 512 or 1024
+// elements all the same) or the rows many against the words; one atomic maximum per row and 128 words holds it back.  In
+// microseconds, kernels alone, fitted to 1771 timed calls (widths 16 to 1024, 300 to 50 000 words, 1 to 16 384 rows,
+// profiles/output_layer_form_timings.csv; 5 - 7 % off on average): choosing by these is 0.4 % slower than the faster form
+// of each call on average, at worst 29 %, and on 1944 others (200 to 80 000 words) never more than 14 % slower than the
+// tiled product; always streaming 6.7 % (8192 rows, width 128, 2500 words 20.1 for 14.8 us), never
+// streaming 14 % (300 rows, width 1024, 36 000 words 35.6 for 22.8 us).
+bool argmax_stream_rows_ahead(size_t M, size_t N, size_t K) {
+  const bool wide = K > 64 * kKG;
+  const float k = (float)((K + 63) / 64);
+  const StreamPlan plan = plan_stream(M, PackedDims(8, N, K).nblocks * 2, wide);
+  auto launch = [&](size_t nrows) {
+    const StreamCut c = cut_stream(nrows, plan.units, plan.rows_max, plan.max_units);
+    const unsigned tpw = tiles_per_wave(c);
+    const float units = (float)((plan.units + c.columns - 1) / c.columns), rows = (float)c.chunk_rows;      // of a workgroup
+    if (wide)
+      return 5.5f + units * (0.43f + (tpw > 1 ? 0.244f : 0.f) + 0.0074f * k) + rows * (0.0114f + 0.0015f * k + 0.000093f * (float)c.chunks);
+    return 5.2f + units * (0.217f + (tpw > 2 ? 0.305f : tpw > 1 ? 0.19f : 0.f) + 0.0015f * k) + rows * (0.0094f + 0.0012f * k);
+  };
+  const size_t full = (M - 1) / plan.launch_rows;                  // launches of launch_rows rows in front of the last one
+  const float stream = (full != 0 ? (float)full * launch(plan.launch_rows) : 0.f) + launch(M - full * plan.launch_rows);
+  const size_t tiles_n = (N + 127) / 128, tiles = (M + 127) / 128 * tiles_n;
+  const float rounds = (float)((tiles + 255) / 256), rounds_of_two = (float)((tiles + 511) / 512);
+  const float tiled = 7.6f + rounds * (0.116f + 0.158f * k) + rounds_of_two * 0.179f * k +
+                      (float)tiles_n * (0.0067f + 0.0000193f * (float)M + 0.0000608f * (float)(M < 128 ? M : 128));
+  return stream < tiled;
 }
 
 // hidden: packed, or (row_major) plain rows.  ws_keys: keys the partials array at ws holds.
@@ -753,18 +804,11 @@ static int launch_argmax_any(const uint8_t* hidden, bool row_major, const void* 
                              const int32_t* shortlist, size_t shortlist_len, hipStream_t s) {
   const bool wide = K > 64 * kKG;
   const PackedDims dW(8, N, K), dAll(8, M, K);
-  const size_t units = shortlist != nullptr ? (shortlist_len + 15) / 16 : dW.nblocks * 2;
-  const size_t rows_max = (size_t)kWaves * 16 * (wide ? kWideTPW : kMaxTPW), max_units = max_units_of(wide ? kWideKG : kKG);
-  // as many chunks of rows per launch as the partials array serves (and the compute units: more only queue up)
+  const StreamPlan plan = plan_stream(M, shortlist != nullptr ? (shortlist_len + 15) / 16 : dW.nblocks * 2, wide);
   for (size_t row0 = 0; row0 < M;) {
-    size_t nrows = M - row0;
-    StreamCut c = cut_stream(nrows, units, rows_max, max_units);
-    while (nrows > rows_max && (c.chunks > 16 || (size_t)c.columns * round_up(nrows, 16) > ws_keys)) {
-      nrows = (c.chunks > 16 ? 16 : c.chunks - 1) * rows_max;      // whole chunks, so row0 stays a multiple of 32 rows
-      c = cut_stream(nrows, units, rows_max, max_units);
-    }
-    // (one chunk always fits: 256 columns of at most 384 rows)
-    if ((size_t)c.columns * round_up(nrows, 16) > ws_keys || (units + c.columns - 1) / c.columns > max_units)
+    const size_t nrows = M - row0 < plan.launch_rows ? M - row0 : plan.launch_rows;
+    const StreamCut c = cut_stream(nrows, plan.units, plan.rows_max, plan.max_units);
+    if ((size_t)c.columns * round_up(nrows, 16) > ws_keys || (plan.units + c.columns - 1) / c.columns > plan.max_units)
       return MQ_ERR_UNSUPPORTED;
     ArgmaxParams p{};
     p.packedA = row_major ? hidden + row0 * K : hidden + dAll.frag_offset(row0 / 32, 0);   // (row0: whole 32-row blocks)
@@ -775,7 +819,7 @@ static int launch_argmax_any(const uint8_t* hidden, bool row_major, const void* 
     p.L = shortlist != nullptr ? (unsigned)shortlist_len : (unsigned)N;
     p.sA = sA; p.sW = sW;
     p.chunk_rows = c.chunk_rows;
-    const int tpw = (int)((c.chunk_rows / 16 + kWaves - 1) / kWaves);
+    const unsigned tpw = tiles_per_wave(c);
     const unsigned g = c.columns, ny = c.chunks;
     int rc;
     if (shortlist != nullptr)
@@ -884,7 +928,7 @@ int launch_topk_stream(const void* packedA, const void* packedW, size_t M, size_
   p.shortlist = shortlist;
   p.L = shortlist != nullptr ? (unsigned)shortlist_len : (unsigned)N;
   p.chunk_rows = c.chunk_rows;
-  const int tpw = (int)((c.chunk_rows / 16 + kWaves - 1) / kWaves);
+  const unsigned tpw = tiles_per_wave(c);
   const unsigned grid = c.columns, ny = c.chunks;
   auto go = [&](auto gather, auto beam_tag) -> int {
     constexpr bool G = decltype(gather)::value;

@@ -211,6 +211,7 @@ int launch_argmax_stream(const void* packedA, const void* packedW, size_t M, siz
                          size_t shortlist_len, hipStream_t s);
 // The same on plain row-major 8-bit hidden states, K a multiple of 16 up to 1024.
 bool argmax_stream_rows_supported(size_t N, size_t K);
+bool argmax_stream_rows_ahead(size_t M, size_t N, size_t K);      // of the tiled product with the arg-max epilogue
 int launch_argmax_stream_rows(const void* qA, const void* packedW, size_t M, size_t N, size_t K, const float* sA,
                               const float* sW, int32_t* tok, float* maxlogit, void* ws, size_t ws_bytes, hipStream_t s);
 // The same with the partial winners in a static device array of the library (no workspace, no allocation).

@@ -1063,10 +1063,10 @@ def test_greedy_packed_every_column_of_candidates_counts(columns, M):
     assert np.array_equal(tok, o["tok"]) and np.array_equal(val, o["maxlogit"])
 
 
-@pytest.mark.parametrize("M,V,d", [(6145, 300, 64), (6144 + 390, 4100, 96), (2 * 6144 + 1, 33, 32)])
+@pytest.mark.parametrize("M,V,d", [(6145, 300, 64), (6144 + 390, 4100, 96), (2 * 6144 + 1, 33, 32), (128 * 384 + 33, 33, 32)])
 def test_greedy_packed_more_rows_than_one_launch_holds(M, V, d):
-    # sixteen chunks of 384 rows per launch: the launches behind the first one start at a later row of the hidden states
-    # and of both results, and reuse the workspace
+    # up to 128 chunks of 384 rows per launch: the launch behind the first one starts at a later row of the hidden states
+    # and of both results, and reuses the workspace
     c = workloads.config3(M=M, V=V, d=d, seed_extra=M)
     o = oracle.greedy_output_layer(c["Hd"], c["E"])
     tok, val = gpu_greedy_packed(c["Hd"], c["E"])
@@ -1077,6 +1077,51 @@ def test_greedy_packed_more_rows_than_one_launch_holds(M, V, d):
     tok, val = gpu_greedy_shortlist(c["Hd"], c["E"], sl)
     assert np.array_equal(tok, o["tok"])
     assert np.array_equal(val, o["maxlogit"])
+
+
+@pytest.mark.parametrize("M,V,d,form", [(800, 400000, 16, "shortlist"), (800, 400000, 16, "packed"), (400, 270000, 528, "rows"),
+                                        (800, 400000, 256, "rows")])
+def test_greedy_vocabularies_that_leave_few_chunks_to_a_launch(M, V, d, form):
+    # So many words that a chunk of rows needs a large share of the compute units: its neighbours go in launches of their own,
+    # at a later row of the hidden states and of both results.  Checked against the oracle where the launches meet.
+    rng = np.random.default_rng(V + d)
+    Hd, E = rng.standard_normal((M, d), dtype=np.float32), rng.standard_normal((V, d), dtype=np.float32)
+    if form == "rows":
+        pw = mq.prepare_weight(dev(E), 8)
+        q, s, _ = gpu_quantize(Hd, 8)
+        nb = mq.mq_argmax_ws_bytes(M, V)
+        ws = torch.full((nb,), 0xAB, dtype=torch.uint8, device=DEV)
+        t, v = torch.empty(M, dtype=torch.int32, device=DEV), torch.empty(M, dtype=torch.float32, device=DEV)
+        assert launches(lambda st: mq.mq_gemm_argmax(q, pw.packed, M, V, d, s, pw.scale, t, v, ws, nb, st)) >= 4
+        tok, val = host(t), host(v)
+    elif form == "packed":
+        tok, val = gpu_greedy_packed(Hd, E)
+    else:
+        tok, val = gpu_greedy_shortlist(Hd, E, np.arange(V, dtype=np.int32))
+    (qA, sA), (qW, sW) = oracle.quant_int_absmax(Hd, 8), oracle.quant_int_absmax(E, 8)
+    for m in (0, 250, 380, 508, M - 8):                 # (chunks of 256 rows above a width of 512, of 384 up to it)
+        want_tok, want_val = oracle.argmax_i32(oracle.dot_int(qA[m:m + 8], qW), sA, sW)
+        assert np.array_equal(tok[m:m + 8], want_tok) and np.array_equal(val[m:m + 8], want_val)
+
+
+@pytest.mark.parametrize("M,V,d,count", [(300, 3000, 1024, 2), (600, 9000, 1024, 3), (1000, 3000, 128, 3), (100, 2000, 128, 2),
+                                         (385, 2500, 512, 2), (384, 2500, 512, 3), (200, 300, 640, 3), (17, 777, 528, 2),
+                                         (257, 1777, 16, 3), (1023, 129, 48, 3), (900, 10000, 64, 3), (300, 20000, 512, 2)])
+def test_greedy_row_major_takes_the_shorter_form(M, V, d, count):
+    # the streaming kernel and its reduction (two launches) or the tiled product (three), ties planted in either
+    rng = np.random.default_rng(M + V + d)
+    Hd, E = rng.standard_normal((M, d), dtype=np.float32), rng.standard_normal((V, d), dtype=np.float32)
+    E[V - 2] = E[V // 3]                                # equal sums: the lower index wins
+    Hd[M // 2] = 4 * E[V // 3]
+    pw = mq.prepare_weight(dev(E), 8)
+    q, s, _ = gpu_quantize(Hd, 8)
+    nb = mq.mq_argmax_ws_bytes(M, V)
+    ws = torch.full((nb,), 0xAB, dtype=torch.uint8, device=DEV)
+    tok, val = torch.empty(M, dtype=torch.int32, device=DEV), torch.empty(M, dtype=torch.float32, device=DEV)
+    assert launches(lambda st: mq.mq_gemm_argmax(q, pw.packed, M, V, d, s, pw.scale, tok, val, ws, nb, st)) == count
+    o = oracle.greedy_output_layer(Hd, E)
+    assert np.array_equal(host(tok), o["tok"]) and np.array_equal(host(val), o["maxlogit"])
+    assert host(tok)[M // 2] == V // 3
 
 
 # ----------------------------------------------------------- fused FFN (8 bit)
