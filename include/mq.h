@@ -252,7 +252,10 @@ int mq_gemm_requant_packed(const void* packedA, const void* packedW, size_t M, s
 
 /* The same result in ONE pass over the operands, for results small enough that
  * every 256 x 256 tile is resident on the chip at once (at most one tile per
- * compute unit; MQ_ERR_UNSUPPORTED beyond that, nothing computed): each tile
+ * compute unit; MQ_ERR_UNSUPPORTED beyond that, nothing computed).  The result is
+ * cut into the smallest of 128 x 128, 256 x 128 and 256 x 256 tiles whose workgroups
+ * are all resident, so it occupies more compute units than it has 256 x 256 tiles
+ * (2048 x 2048: 256, not 64).  Each tile
  * keeps its sums in registers while all workgroups agree on max|y| through the
  * agreement area at the start of ws (2112 words, see "Single-pass kernels" at
  * the top), then quantizes and stores.  Two launches (clearing the area, the
@@ -387,10 +390,14 @@ size_t mq_linear_ws_bytes(int bits, size_t M, size_t K);
  * parameter (Section 4.3: the integer product as a drop-in for the float one):
  * abs-max and quant_int of A (or quant_int with the given multiplier if
  * sA_or_null is not NULL), dot'_int, dequantize + bias (+ReLU), with the results
- * of mq_quantize_f32 + mq_gemm_dequant bit for bit.  Two or three launches on
- * `stream`; for 8-bit products with at most 512 rows and K a multiple of 32 up
- * to 1024 (a decode step) quant_int runs inside the product kernel: one launch
- * with a given multiplier, two with abs-max.
+ * of mq_quantize_f32 + mq_gemm_dequant bit for bit.  Three launches on `stream`
+ * with abs-max, two with a given multiplier; for 8-bit products with at most
+ * 512 rows and K a multiple of 32 up to 1024 (a decode step) quant_int runs
+ * inside the product kernel: two and one.  Up to 32 rows with K a multiple of 4
+ * up to 2048 (8 bit and at most 16 rows: 4096) everything is ONE launch, with a
+ * given multiplier only where that is the faster form; a shape that
+ * mq_autotune_gemm or mq_set_gemm_variant has named a packed product for takes
+ * that product instead, unless the form above serves it.
  * A: device float [M x K], 16-byte aligned.  Y may share memory with A (an
  * in-place call, or any other overlap): A is then quantized whole, in a launch
  * of its own, before anything is stored.  out_amax: optional device float
@@ -555,7 +562,8 @@ typedef struct mq_aan_layer {
  *   y   = LN(ffn2(relu(ffn1(y2))) + y2)                -> y [M x d]
  * use_ffn / use_gate = 0 give the "-ffn" / "-gate" variants of Table 2.
  * ws: device, 256-byte aligned, mq_aan_layer_ws_bytes bytes, contents irrelevant.
- * Only enqueues; y and g_out must not alias x or g_prev. */
+ * Only enqueues.  g_out may be g_prev itself (the average is then updated in
+ * place); apart from that y and g_out must not alias x, g_prev or each other. */
 size_t mq_aan_layer_ws_bytes(size_t M, size_t d, size_t ffn, size_t aan_ffn);
 int mq_aan_layer_f32(const mq_aan_layer* P, const float* x, const float* g_prev, int t, const float* K,
                      const float* V, size_t M, size_t S, int heads, int use_ffn, int use_gate, float eps,
