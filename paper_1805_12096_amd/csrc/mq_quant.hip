@@ -382,12 +382,13 @@ __global__ __launch_bounds__(kThreads) void k_quantize_pack(const float* __restr
   const unsigned wave_in = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);      // scalar, like the item made of it
   const unsigned wave = blockIdx.x * (kThreads / kWave) + wave_in;
   const unsigned nwaves = gridDim.x * (kThreads / kWave);
-  const unsigned per = (kfrags + ksplit - 1) / ksplit;   // fragments along K per work item
+  const unsigned shift = 31 - __builtin_clz(ksplit);     // (a power of two)
+  const unsigned per = (kfrags + ksplit - 1) >> shift;   // fragments along K per work item
   // 16 bit, long rows: the workgroup's waves share a row group, each takes its part of K (four times the loads in
   // flight of one wave per row group, which leaves a chip with a thousand row groups at four waves per compute
   // unit), and the rows' sums meet in LDS.  ksplit is the number of waves of the workgroup then.
   const bool shared_rows = BITS == 16 && ksplit > 1;
-  unsigned rg = shared_rows ? blockIdx.x : wave / ksplit, part = shared_rows ? wave_in : wave % ksplit;
+  unsigned rg = shared_rows ? blockIdx.x : wave >> shift, part = shared_rows ? wave_in : wave & (ksplit - 1);
   const unsigned ncols = (unsigned)cols, nrows = (unsigned)rows;
   float4 v[kQuantFlight];
   auto load = [&](unsigned kb0) {
@@ -445,8 +446,8 @@ __global__ __launch_bounds__(kThreads) void k_quantize_pack(const float* __restr
   }
   for (unsigned item = wave; item < row_groups * ksplit; item += nwaves) {
     if (item != wave) {
-      rg = item / ksplit;
-      part = item % ksplit;
+      rg = item >> shift;
+      part = item & (ksplit - 1);
       load(part * per);
     }
     const int sum = convert();
@@ -476,10 +477,11 @@ __global__ __launch_bounds__(512) void k_absmax_quantize_pack(const float* __res
   const int sub = lane % 8;                       // which 4 floats of a 32-element fragment row
   // (a resident grid's items and the tensor's rows, columns and fragments all fit 32 bits)
   const unsigned kfrags = (unsigned)d.kfrags, row_groups = (unsigned)(d.Np / 8), ncols = (unsigned)cols, nrows = (unsigned)rows;
-  const unsigned per = (kfrags + ksplit - 1) / ksplit;   // fragments along K per wave, at most 4 NI
+  const unsigned shift = 31 - __builtin_clz(ksplit);     // (a power of two)
+  const unsigned per = (kfrags + ksplit - 1) >> shift;   // fragments along K per wave, at most 4 NI
   const unsigned item = blockIdx.x * kW + wave;
   const bool active = item < row_groups * ksplit;
-  const unsigned rg = item / ksplit, part = item % ksplit;
+  const unsigned rg = item >> shift, part = item & (ksplit - 1);
   const unsigned row = rg * 8 + lane / 8;
   const unsigned kb_begin = part * per, kb_end = min(kb_begin + per, kfrags);
   // every load from inside the tensor and without a condition of its own (see load4_clamped); fragments past this wave's
