@@ -3,8 +3,11 @@
 // cumulative uniform average that is updated from the last step only, followed by a feed-forward
 // network and a gate; Section 3.1: source attention and the position-wise feed-forward block; every
 // sub-layer ends in residual + layer normalisation).  All tensors are binary32, a decode step has a
-// few hundred rows of model width, so every kernel here is one short pass over a few 100 KB: one
-// workgroup per sentence, the row staged in LDS, reductions inside the workgroup.
+// few hundred rows of model width, so every kernel here is one short pass over a few 100 KB: rows of up
+// to 1024 floats in whole pieces of 256 are normalised by one wave in registers, other widths and the
+// source attention take one workgroup per sentence with the row or the scores in LDS.
+#include <type_traits>
+
 #include "mq_glue.h"
 #include "mq_grid_max.h"
 #include "mq_internal.h"
@@ -313,13 +316,15 @@ __global__ __launch_bounds__(kTA) void k_cross_attention(const float* __restrict
 // source position come out of one pass; the context phase splits the source positions over thread groups so
 // that every thread has several rows of V in flight.
 // Bound by memory latency (one sentence) and bytes in flight (hundreds): the lanes' dot products of a trip share the steps of
-// the exchange between lanes, and up to 64 scores of a head are normalised in registers.  Nothing is asked for that is not
-// needed (a branch that all lanes take alike costs less than a load), and registers stay at 36 / 54 / 96 (d = 256 / 512 /
-// 1024), so that four, four and two workgroups share a compute unit.  With the first rows of V asked for together with K
-// and rows past the end read again instead of left out, both were worse (72 / 100 / 144 registers): kernel times before
-// the exchange was shared, with that, now, in us: 1 x 25 words, d = 512 6.0, 4.9, 4.7; 300 x 25 8.5, 7.4, 7.2 (4.3 TB/s);
-// 600 x 25 12.1, 12.8, 11.0; 600 x 1 6.4, 8.2, 4.8; 300 x 25, d = 1024 15.8, 18.0, 13.2.
-template <int CH>      // CH = d / 256: float4 pieces of a row per lane
+// the exchange between lanes, and up to 64 scores of a head are normalised in registers.
+// AHEAD: K and the first rows of V are asked for together and without branches between the loads (past the end: the last row
+// again), so that V's round trip is over when the scores are: for at most one workgroup per compute unit, where neither the
+// registers (70 / 94 / 132 for d = 256 / 512 / 1024) nor the surplus loads are in anybody's way.  Otherwise nothing is asked
+// for that is not needed, and 36 / 54 / 96 registers let four, four and two workgroups share a compute unit.  In us, K and V
+// from the last-level cache, with and without AHEAD: d = 512, 100 sentences x 25 words 5.6, 6.2; x 8 4.9, 4.5; 300 x 25 9.1,
+// 8.5; 600 x 1 8.2, 6.3; d = 1024, 100 x 14 6.9, 7.6; 300 x 25 19.0, 14.7.  Before the exchange was shared 300 x 25, d = 512
+// took 8.5 us in the L2s, now 7.2 (4.3 TB/s), one sentence 6.0 and 4.7.
+template <int CH, bool AHEAD>      // CH = d / 256: float4 pieces of a row per lane
 __global__ __launch_bounds__(kTA) void k_cross_attention_fast(const float* __restrict__ q, const float* __restrict__ K,
                                                               const float* __restrict__ V, unsigned S, unsigned heads,
                                                               float* __restrict__ ctx, float* __restrict__ partial) {
@@ -328,6 +333,7 @@ __global__ __launch_bounds__(kTA) void k_cross_attention_fast(const float* __res
   constexpr unsigned COLS = d / 4;                 // float4 columns of a row
   constexpr unsigned SG = kTA / COLS;              // groups of threads that share the source positions
   static_assert(kTA % COLS == 0 && SG >= 1, "context phase layout");
+  constexpr int kAhead = AHEAD ? 8 : 0;            // rows of V in registers: 32 source positions at d = 512
   __shared__ float sc[kMaxScores];
   __shared__ float4 part[SG > 1 ? kTA : 1];
   __shared__ float red[NWV];
@@ -341,17 +347,25 @@ __global__ __launch_bounds__(kTA) void k_cross_attention_fast(const float* __res
   float4 qr[CH];
 #pragma unroll
   for (int c = 0; c < CH; ++c) qr[c] = q4[c * 64 + lane];
-  for (unsigned s0 = wave; s0 < S; s0 += 4 * NWV) {
+  const unsigned col = threadIdx.x % COLS, sg = threadIdx.x / COLS;
+  float4 va[AHEAD ? kAhead : 1];
+  auto scores = [&](unsigned s0, auto first) {
     float4 kr[4][CH];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      if (s0 + u * NWV < S) {
+      const unsigned s = s0 + u * NWV;
+      if (AHEAD || s < S) {
 #pragma unroll
-        for (int c = 0; c < CH; ++c) kr[u][c] = K4[(size_t)(s0 + u * NWV) * COLS + c * 64 + lane];
+        for (int c = 0; c < CH; ++c) kr[u][c] = K4[(size_t)(!AHEAD || s < S ? s : S - 1) * COLS + c * 64 + lane];
       } else {
 #pragma unroll
         for (int c = 0; c < CH; ++c) kr[u][c] = make_float4(0.f, 0.f, 0.f, 0.f);
       }
+    }
+    if constexpr (AHEAD && decltype(first)::value) {
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j) va[j] = V4[(size_t)(sg + j * SG < S ? sg + j * SG : S - 1) * COLS + col];
+      __builtin_amdgcn_sched_barrier(0);
     }
     // (all sums of a trip take one step of the exchange together: one after the other they are 4 CH serial chains)
     float a[4][CH];
@@ -371,7 +385,9 @@ __global__ __launch_bounds__(kTA) void k_cross_attention_fast(const float* __res
 #pragma unroll
         for (int c = 0; c < CH; ++c)
           if (s0 + u * NWV < S) sc[(c * 256 + 4 * lane) / dh * S + s0 + u * NWV] = a[u][c] * scale;
-  }
+  };
+  if (AHEAD || wave < S) scores(wave, std::true_type{});
+  for (unsigned s0 = wave + 4 * NWV; s0 < S; s0 += 4 * NWV) scores(s0, std::false_type{});
   __syncthreads();
   for (unsigned h = wave; h < heads; h += NWV) {
     if (S <= kWave) {                                // the scores stay in a register
@@ -400,10 +416,18 @@ __global__ __launch_bounds__(kTA) void k_cross_attention_fast(const float* __res
     for (unsigned s = lane; s < S; s += kWave) sc[h * S + s] *= inv;
   }
   __syncthreads();
-  const unsigned col = threadIdx.x % COLS, sg = threadIdx.x / COLS;
   const unsigned h = (4 * col) / dh;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  unsigned s = sg;
+#pragma unroll
+  for (int j = 0; j < kAhead; ++j)
+    if (sg + j * SG < S) {
+      const float p0 = sc[h * S + sg + j * SG];
+      acc.x = fmaf(p0, va[j].x, acc.x);
+      acc.y = fmaf(p0, va[j].y, acc.y);
+      acc.z = fmaf(p0, va[j].z, acc.z);
+      acc.w = fmaf(p0, va[j].w, acc.w);
+    }
+  unsigned s = sg + kAhead * SG;
   for (; s + 3 * SG < S; s += 4 * SG) {
     const float4 v0 = V4[(size_t)s * COLS + col], v1 = V4[(size_t)(s + SG) * COLS + col],
                  v2 = V4[(size_t)(s + 2 * SG) * COLS + col], v3 = V4[(size_t)(s + 3 * SG) * COLS + col];
@@ -527,9 +551,12 @@ int launch_cross_attention(const float* q, const float* K, const float* V, size_
     auto go = [&](auto kern) {
       hipLaunchKernelGGL(kern, dim3((unsigned)M), dim3(kTA), 0, s, q, K, V, (unsigned)S, (unsigned)heads, ctx, partial);
     };
-    if (d == 256) go(k_cross_attention_fast<1>);
-    else if (d == 512) go(k_cross_attention_fast<2>);
-    else go(k_cross_attention_fast<4>);
+    // up to 8 words asking ahead reads rows again for nothing (d = 512: 0.87 - 0.98 of the time without), from 14 on it wins
+    // while every sentence has a compute unit to itself (1.02 - 1.14)
+    const bool ahead = M <= 256 && S > 12;
+    if (d == 256) ahead ? go(k_cross_attention_fast<1, true>) : go(k_cross_attention_fast<1, false>);
+    else if (d == 512) ahead ? go(k_cross_attention_fast<2, true>) : go(k_cross_attention_fast<2, false>);
+    else ahead ? go(k_cross_attention_fast<4, true>) : go(k_cross_attention_fast<4, false>);
     return check_hip(hipGetLastError());
   }
   hipLaunchKernelGGL(k_cross_attention, dim3((unsigned)M), dim3(kTA), 0, s, q, K, V, (unsigned)S, (unsigned)d,

@@ -104,7 +104,10 @@ def test_layer_norm_kernels_give_the_same_bits(M, d):
                                           (3, 31, 512, 8), (2, 33, 512, 8), (5, 64, 512, 1), (2, 65, 1024, 4), (1, 17, 1024, 16),
                                           (3, 63, 256, 2), (3, 64, 256, 1), (2, 150, 256, 8), (4, 1, 1024, 8),
                                           # fewer positions than waves, and than rows of a trip; more sentences than compute units
-                                          (600, 1, 512, 8), (300, 8, 1024, 16), (1, 9, 256, 4), (2, 24, 512, 8), (257, 26, 512, 8)])
+                                          (600, 1, 512, 8), (300, 8, 1024, 16), (1, 9, 256, 4), (2, 24, 512, 8), (257, 26, 512, 8),
+                                          # either side of where V is asked for ahead: 256 sentences, 12 positions
+                                          (256, 13, 256, 4), (257, 13, 256, 4), (256, 12, 512, 8), (257, 33, 1024, 16),
+                                          (9, 40, 1024, 16), (300, 70, 512, 8)])
 def test_cross_attention(M, S, d, heads):
     rng = np.random.default_rng(M + S + d)
     q = rng.standard_normal((M, d), dtype=np.float32) * np.float32(2)
