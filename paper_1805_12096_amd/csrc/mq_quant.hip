@@ -379,7 +379,7 @@ __global__ __launch_bounds__(kThreads) void k_quantize_pack(const float* __restr
   const int sub = lane % 8;                       // which 4 floats of a 32-element fragment row
   // (indexes of fragments, row groups and items fit 32 bits: rows and columns are below 2^31, items below 2^29 x 16)
   const unsigned kfrags = (unsigned)d.kfrags, row_groups = (unsigned)(d.Np / 8);
-  const unsigned wave_in = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);      // scalar, like the item made of it
+  const unsigned wave_in = threadIdx.x / kWave;
   const unsigned wave = blockIdx.x * (kThreads / kWave) + wave_in;
   const unsigned nwaves = gridDim.x * (kThreads / kWave);
   const unsigned shift = 31 - __builtin_clz(ksplit);     // (a power of two)
