@@ -286,23 +286,25 @@ __global__ __launch_bounds__(kThreads) void k_absmax_partial(const float* __rest
   }
 }
 
-// Maximum of `count` partial maxima, computed redundantly by every block that needs it.
+// Maximum of `count` partial maxima, computed redundantly by every block of W waves that needs it.
+template <int W>
 __device__ __forceinline__ float block_max_of_partials(const float* __restrict__ partial, unsigned count) {
+  constexpr unsigned kT = W * kWave, kFlight = kAbsmaxPartials / kT;      // kAbsmaxPartials of them: one trip
   float m = 0.f;
-  for (unsigned i0 = 0; i0 < count; i0 += 4 * kThreads) {      // kAbsmaxPartials of them: one trip, four loads in flight
-    float v[4];
+  for (unsigned i0 = 0; i0 < count; i0 += kFlight * kT) {
+    float v[kFlight];
 #pragma unroll
-    for (unsigned t = 0; t < 4; ++t) v[t] = partial[min(i0 + t * kThreads + threadIdx.x, count - 1)];
+    for (unsigned t = 0; t < kFlight; ++t) v[t] = partial[min(i0 + t * kT + threadIdx.x, count - 1)];
 #pragma unroll
-    for (unsigned t = 0; t < 4; ++t) m = fmaxf(m, v[t]);
+    for (unsigned t = 0; t < kFlight; ++t) m = fmaxf(m, v[t]);
   }
   m = __uint_as_float(wave_max_u32(__float_as_uint(m)));      // non-negative: ordered like its bits
-  __shared__ float red[kThreads / kWave];
+  __shared__ float red[W];
   if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = m;
   __syncthreads();
   float r = red[0];
 #pragma unroll
-  for (int k = 1; k < kThreads / kWave; ++k) r = fmaxf(r, red[k]);
+  for (int k = 1; k < W; ++k) r = fmaxf(r, red[k]);
   return r;
 }
 
@@ -365,14 +367,15 @@ __device__ __forceinline__ int store4(uint8_t* dst, float4 v, float s, int lim, 
 // A work item is `per` fragments along K of a group of eight rows, kQuantFlight of them loaded at a time; the first item's
 // first loads go out before the partial maxima are asked for, so that the two round trips to memory are one.
 constexpr int kQuantFlight = 4;
-template <int BITS, Cols COLS, bool FROM_PARTIALS>
-__global__ __launch_bounds__(kThreads) void k_quantize_pack(const float* __restrict__ x, size_t rows,
+template <int BITS, Cols COLS, bool FROM_PARTIALS, int W>
+__global__ __launch_bounds__(W * kWave) void k_quantize_pack(const float* __restrict__ x, size_t rows,
                                                             size_t cols, const float* __restrict__ scale,
                                                             uint8_t* __restrict__ packed, unsigned ksplit,
                                                             unsigned npartial, float* __restrict__ scale_out,
                                                             unsigned* __restrict__ clear, unsigned nclear) {
   // words a later kernel wants zero (spread over the grid: one workgroup walking through them is a serial tail)
-  for (unsigned i = blockIdx.x * kThreads + threadIdx.x; i < nclear; i += gridDim.x * kThreads) clear[i] = 0u;
+  constexpr unsigned kT = W * kWave;
+  for (unsigned i = blockIdx.x * kT + threadIdx.x; i < nclear; i += gridDim.x * kT) clear[i] = 0u;
   const PackedDims d(BITS, rows, cols);
   const int lim = BITS == 8 ? 127 : 32767;
   const int lane = threadIdx.x % kWave;
@@ -380,13 +383,13 @@ __global__ __launch_bounds__(kThreads) void k_quantize_pack(const float* __restr
   // (indexes of fragments, row groups and items fit 32 bits: rows and columns are below 2^31, items below 2^29 x 16)
   const unsigned kfrags = (unsigned)d.kfrags, row_groups = (unsigned)(d.Np / 8);
   const unsigned wave_in = threadIdx.x / kWave;
-  const unsigned wave = blockIdx.x * (kThreads / kWave) + wave_in;
-  const unsigned nwaves = gridDim.x * (kThreads / kWave);
+  const unsigned wave = blockIdx.x * W + wave_in;
+  const unsigned nwaves = gridDim.x * W;
   const unsigned shift = 31 - __builtin_clz(ksplit);     // (a power of two)
   const unsigned per = (kfrags + ksplit - 1) >> shift;   // fragments along K per work item
-  // 16 bit, long rows: the workgroup's waves share a row group, each takes its part of K (four times the loads in
+  // 16 bit, long rows: the workgroup's waves share a row group, each takes its part of K (W times the loads in
   // flight of one wave per row group, which leaves a chip with a thousand row groups at four waves per compute
-  // unit), and the rows' sums meet in LDS.  ksplit is the number of waves of the workgroup then.
+  // unit), and the rows' sums meet in LDS.  ksplit is the number of waves of the workgroup then (see pack_split).
   const bool shared_rows = BITS == 16 && ksplit > 1;
   unsigned rg = shared_rows ? blockIdx.x : wave >> shift, part = shared_rows ? wave_in : wave & (ksplit - 1);
   const unsigned ncols = (unsigned)cols, nrows = (unsigned)rows;
@@ -399,7 +402,7 @@ __global__ __launch_bounds__(kThreads) void k_quantize_pack(const float* __restr
   if (rg < row_groups) load(part * per);
   float s;
   if (FROM_PARTIALS) {
-    const float amax = block_max_of_partials(scale, npartial);
+    const float amax = block_max_of_partials<W>(scale, npartial);
     s = (amax > 0.0f) ? __fdiv_rn(BITS == 8 ? 127.0f : 32767.0f, amax) : 1.0f;
     if (blockIdx.x == 0 && threadIdx.x == 0) *scale_out = s;
   } else {
@@ -428,7 +431,7 @@ __global__ __launch_bounds__(kThreads) void k_quantize_pack(const float* __restr
     return sum;
   };
   if (shared_rows) {
-    __shared__ int s_part[kThreads / kWave][8];
+    __shared__ int s_part[W][8];
     for (; rg < row_groups; rg += gridDim.x) {
       if (rg != blockIdx.x) load(part * per);
       const int sum = convert();
@@ -437,7 +440,7 @@ __global__ __launch_bounds__(kThreads) void k_quantize_pack(const float* __restr
       if (part == 0 && sub == 0) {
         int total = 0;
 #pragma unroll
-        for (int k = 0; k < kThreads / kWave; ++k) total += s_part[k][lane / 8];
+        for (int k = 0; k < W; ++k) total += s_part[k][lane / 8];
         reinterpret_cast<int32_t*>(packed + d.plane_bytes())[(size_t)rg * 8 + lane / 8] = total;
       }
       __syncthreads();
@@ -571,33 +574,60 @@ __global__ __launch_bounds__(512) void k_absmax_quantize_pack(const float* __res
 
 }  // namespace
 
-int launch_quantize_pack(const float* x, size_t rows, size_t cols, int bits, const float* scale,
-                         void* packed, hipStream_t s, unsigned* clear, unsigned nclear) {
-  const PackedDims d(bits, rows, cols);
+namespace {
+// How many waves share a row group along K and, for 16 bit, how many a workgroup has.  8 bit: split K so that even a 300-row
+// batch fills the chip.  16 bit: the rows' sums have to meet in one workgroup, rows of 512 elements or more are shared by its
+// waves, shorter ones stay whole.  Four waves leave a batch of a few hundred rows with one wave per SIMD on a part of the
+// compute units, each with a long chain of trips along K, so up to 128 row groups take 16 waves and up to 256 eight, as long
+// as a wave keeps eight fragments (quantizer and product of 300 x 4096, given multiplier, 25.4 -> 22.7 us, 1001 x 4096 38.1 ->
+// 36.0, 500 x 2048 13.6 -> 12.9; shorter runs than that gain nothing).  Beyond, the chip is full and larger workgroups only
+// meet more often: eight waves for 4000 rows of 2050 elements 30.1 -> 31.1 us, sixteen 32.2.
+struct PackSplit {
+  unsigned ksplit, waves;
+};
+PackSplit pack_split(int bits, const PackedDims& d) {
   const size_t row_groups = d.Np / 8;
-  // 8-bit: split K so that even a 300-row batch fills the chip; 16-bit: rows of 512 elements or more are shared by the
-  // waves of a workgroup (their sums meet in LDS), shorter ones stay whole
   unsigned ksplit = 1;
   if (bits == 8) {
     while (row_groups * ksplit < 2048 && ksplit * 4 <= d.kfrags) ksplit *= 2;
-  } else if (d.kfrags >= 16) {
-    ksplit = kThreads / kWave;
+    return {ksplit, kThreads / kWave};
   }
-  const unsigned grid = bits == 16 && ksplit > 1 ? grid_for(row_groups, 1, 8192) : grid_for(row_groups * ksplit, kThreads / kWave, 8192);
-  uint8_t* p = static_cast<uint8_t*>(packed);
+  if (d.kfrags < 16) return {1, kThreads / kWave};
+  unsigned waves = kThreads / kWave;
+  while (waves < 16 && row_groups * waves < 1024u && waves * 8 <= d.kfrags) waves *= 2;
+  return {waves, waves};
+}
+
+// FROM_PARTIALS: `scale` holds `npartial` partial maxima and scale_out receives the multiplier (see the kernel).
+template <bool FROM_PARTIALS>
+int launch_pack(const float* x, size_t rows, size_t cols, int bits, const float* scale, unsigned npartial, float* scale_out,
+                void* packed, unsigned* clear, unsigned nclear, hipStream_t s) {
+  const PackedDims d(bits, rows, cols);
+  const size_t row_groups = d.Np / 8;
+  const PackSplit sp = pack_split(bits, d);
+  const unsigned grid = bits == 16 && sp.ksplit > 1 ? grid_for(row_groups, 1, 8192) : grid_for(row_groups * sp.ksplit, sp.waves, 8192);
   const Cols kind = cols_kind(cols);
   auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), 0, s, x, rows, cols, scale, p, ksplit, 0u, (float*)nullptr, clear, nclear);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(sp.waves * kWave), 0, s, x, rows, cols, scale, static_cast<uint8_t*>(packed),
+                       sp.ksplit, npartial, scale_out, clear, nclear);
   };
-  auto by_kind = [&](auto bits_tag) {
-    constexpr int B = decltype(bits_tag)::value;
-    if (kind == kColsVec) go(k_quantize_pack<B, kColsVec, false>);
-    else if (kind == kColsAny) go(k_quantize_pack<B, kColsAny, false>);
-    else go(k_quantize_pack<B, kColsFew, false>);
+  auto by_kind = [&](auto bits_tag, auto waves_tag) {
+    constexpr int B = decltype(bits_tag)::value, W = decltype(waves_tag)::value;
+    if (kind == kColsVec) go(k_quantize_pack<B, kColsVec, FROM_PARTIALS, W>);
+    else if (kind == kColsAny) go(k_quantize_pack<B, kColsAny, FROM_PARTIALS, W>);
+    else if constexpr (W == 4) go(k_quantize_pack<B, kColsFew, FROM_PARTIALS, W>);      // (two fragments along K)
   };
-  if (bits == 8) by_kind(std::integral_constant<int, 8>{});
-  else by_kind(std::integral_constant<int, 16>{});
+  if (bits == 8) by_kind(std::integral_constant<int, 8>{}, std::integral_constant<int, 4>{});
+  else if (sp.waves == 4) by_kind(std::integral_constant<int, 16>{}, std::integral_constant<int, 4>{});
+  else if (sp.waves == 8) by_kind(std::integral_constant<int, 16>{}, std::integral_constant<int, 8>{});
+  else by_kind(std::integral_constant<int, 16>{}, std::integral_constant<int, 16>{});
   return check_hip(hipGetLastError());
+}
+}  // namespace
+
+int launch_quantize_pack(const float* x, size_t rows, size_t cols, int bits, const float* scale,
+                         void* packed, hipStream_t s, unsigned* clear, unsigned nclear) {
+  return launch_pack<false>(x, rows, cols, bits, scale, 0u, nullptr, packed, clear, nclear, s);
 }
 
 int launch_fill_pattern(void* p, size_t bytes, unsigned seed, hipStream_t s) {
@@ -618,30 +648,7 @@ int launch_clear_words(unsigned* p, unsigned n, hipStream_t s) {
 // maxima (one is enough: a single max|x| in device memory); scale_out[0] receives the multiplier.
 int launch_quantize_pack_partials(const float* x, size_t rows, size_t cols, int bits, const float* partials,
                                   unsigned npartials, float* scale_out, void* packed, hipStream_t s) {
-  const unsigned g1 = npartials;
-  const PackedDims d(bits, rows, cols);
-  const size_t row_groups = d.Np / 8;
-  unsigned ksplit = 1;
-  if (bits == 8) {
-    while (row_groups * ksplit < 2048 && ksplit * 4 <= d.kfrags) ksplit *= 2;
-  } else if (d.kfrags >= 16) {
-    ksplit = kThreads / kWave;      // the workgroup's waves share a row group
-  }
-  const unsigned grid = bits == 16 && ksplit > 1 ? grid_for(row_groups, 1, 8192) : grid_for(row_groups * ksplit, kThreads / kWave, 8192);
-  uint8_t* p = static_cast<uint8_t*>(packed);
-  const Cols kind = cols_kind(cols);
-  auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), 0, s, x, rows, cols, partials, p, ksplit, g1, scale_out, (unsigned*)nullptr, 0u);
-  };
-  auto by_kind = [&](auto bits_tag) {
-    constexpr int B = decltype(bits_tag)::value;
-    if (kind == kColsVec) go(k_quantize_pack<B, kColsVec, true>);
-    else if (kind == kColsAny) go(k_quantize_pack<B, kColsAny, true>);
-    else go(k_quantize_pack<B, kColsFew, true>);
-  };
-  if (bits == 8) by_kind(std::integral_constant<int, 8>{});
-  else by_kind(std::integral_constant<int, 16>{});
-  return check_hip(hipGetLastError());
+  return launch_pack<true>(x, rows, cols, bits, partials, npartials, scale_out, packed, nullptr, 0u, s);
 }
 
 namespace {

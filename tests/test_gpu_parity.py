@@ -750,6 +750,32 @@ def test_quantizers_at_row_ends(bits, rows, cols):
         check(packed, oq)
 
 
+@pytest.mark.parametrize("rows", [1017, 1025, 2048, 2049])
+@pytest.mark.parametrize("cols", [2047, 2052])
+def test_quantize_pack_16_bit_waves_per_row_group(rows, cols):
+    # 16-bit rows are shared by 16, 8 or 4 waves of a workgroup, by the number of row groups: both sides of the lines, a
+    # number of fragments that 16 waves do not share evenly (the last ones get none), with and without abs-max
+    rng = np.random.default_rng(rows + cols)
+    x = rng.standard_normal((rows, cols), dtype=np.float32)
+    oq, os_ = oracle.quant_int_absmax(x, 16)
+    sums = np.zeros((rows + 31) // 32 * 32, dtype=np.int32)
+    sums[:rows] = oq.sum(1, dtype=np.int32)
+    nb = mq.mq_quantize_absmax_ws_bytes()
+    ws, s = torch.full((nb,), 0x6D, dtype=torch.uint8, device=DEV), torch.empty(1, dtype=torch.float32, device=DEV)
+    packed = torch.full((mq.mq_packed_bytes(16, rows, cols),), 0x5A, dtype=torch.uint8, device=DEV)
+    try:
+        mq.mq_set_quantize_single_pass(0)
+        mq.mq_quantize_absmax_pack_f32(dev(x), rows, cols, 16, packed, s, ws, nb)
+    finally:
+        mq.mq_set_quantize_single_pass(1)
+    assert host(s)[0] == os_
+    for p in (packed, gpu_quantize_pack(x, 16, scale=os_)[0]):
+        q = torch.empty((rows, cols), dtype=torch.int16, device=DEV)
+        mq.mq_unpack_weight(p, 16, rows, cols, q)
+        assert np.array_equal(host(q), oq)
+        assert np.array_equal(host(p)[-4 * len(sums):].view(np.int32), sums)
+
+
 def gpu_dot_int_packed(qA, qB):
     bits = 8 if qA.dtype == np.int8 else 16
     one = torch.ones(1, dtype=torch.float32, device=DEV)
