@@ -797,12 +797,19 @@ int mq_ffn_i16_f32(const float* A, size_t M, size_t d, size_t f, const void* pac
   GemmArgs g1{};
   g1.qA = qA;
   g1.packedW = packedW1; g1.bits = 16; g1.M = M; g1.N = f; g1.K = d;
-  g1.sA = sA; g1.sW = sW1; g1.bias = b1; g1.relu = 1; g1.Y = H; g1.out_amax = hmax; g1.amax_slots = kHmaxSlots;
+  g1.sA = sA; g1.sW = sW1; g1.bias = b1; g1.relu = 1; g1.Y = H;
+  // max|H|: one value per workgroup from the split-K kernel (where the input's partial maxima were, which nobody reads any
+  // more), else raised words (kernels that do not know about the slots raise the first word only; the others stay zero)
+  const size_t parts = gemm_packed_partials(g1);
+  if (parts != 0) {
+    g1.partial = part;
+  } else {
+    g1.out_amax = hmax; g1.amax_slots = kHmaxSlots;
+  }
   rc = launch_gemm_packed(g1, kEpiDequant, s);
   if (rc != MQ_OK) return rc;
-  // a1 + a2 on H: the multiplier comes from the maxima already there (kernels that do not know about the slots
-  // raise the first word only; the others then stay zero)
-  rc = launch_quantize_pack_partials(H, M, f, 16, hmax, kHmaxSlots, sH, qH, s);
+  // a1 + a2 on H: the multiplier comes from the maxima already there
+  rc = launch_quantize_pack_partials(H, M, f, 16, parts != 0 ? part : hmax, parts != 0 ? (unsigned)parts : kHmaxSlots, sH, qH, s);
   if (rc != MQ_OK) return rc;
   GemmArgs g2{};
   g2.qA = qH;
@@ -1024,13 +1031,16 @@ int mq_aan_layer_f32(const mq_aan_layer* P, const float* x, const float* g_prev,
   float* hpart = reinterpret_cast<float*>(base + L.off_hpart);
   float* hpart2 = reinterpret_cast<float*>(base + L.off_hpart2);
   float* xpart = reinterpret_cast<float*>(base + L.off_xpart);
-  float* hmax = sA + 1;           // three words: max|.| of three products' outputs where no per-workgroup maxima are
-                                  // available, cleared by the first kernel
+  // max|.| of three products' outputs where no per-workgroup maxima are available: kHmaxSlots words each, over which the
+  // workgroups spread their atomics, cleared by the first kernel
+  constexpr unsigned kHmaxSlots = 16;
+  static_assert((1 + 3 * kHmaxSlots) * sizeof(float) <= 256, "multiplier and maxima share 256 bytes");
+  float* hmax = sA + 1;
   // One parameter product: quant_int of the input with its own abs-max multiplier, dot'_int, bias (+ReLU).
   // The kernel that produced the input has already left partial maxima of it (np of them at `partials`), so the
   // quantizer needs no abs-max pass of its own; inputs with more rows than the quantizer reduces per block take
   // the separate pass.  want_max: the product that follows needs max|Y|; it is left as *out_np partial maxima at
-  // *out_partials (one per workgroup, no atomics) where the decode-sized kernels run, else in the word hword.
+  // *out_partials (one per workgroup, no atomics) where the decode-sized kernels run, else in the words at hword.
   const float* out_partials = nullptr;
   size_t out_np = 0;
   auto product = [&](const float* A, size_t Kdim, const mq_product& W, size_t N, int relu, float* Y,
@@ -1045,7 +1055,7 @@ int mq_aan_layer_f32(const mq_aan_layer* P, const float* x, const float* g_prev,
       if (want_max) {
         const size_t wg = gemm_small_f32_partials(M, N, Kdim);
         if (wg <= kAbsmaxPartials) { g.partial = out_buf; out_partials = out_buf; out_np = wg; }
-        else { g.out_amax = hword; out_partials = hword; out_np = 1; }
+        else { g.out_amax = hword; g.amax_slots = kHmaxSlots; out_partials = hword; out_np = kHmaxSlots; }
       }
       return launch_gemm_small_f32(A, partials, (unsigned)np, sA, g, s);
     }
@@ -1055,12 +1065,11 @@ int mq_aan_layer_f32(const mq_aan_layer* P, const float* x, const float* g_prev,
       rc = launch_absmax_quantize_pack(A, M, Kdim, 8, part, sA, qbuf, s);
     if (rc != MQ_OK) return rc;
     g.qA = qbuf; g.sA = sA;
-    if (want_max && M <= 512 && gemm_small_partials(M, N, Kdim) <= kAbsmaxPartials) {
-      // decode-sized: the split-K kernel leaves one maximum per workgroup
-      g.partial = out_buf; out_partials = out_buf; out_np = gemm_small_partials(M, N, Kdim);
-      return launch_gemm_small(g, kEpiDequant, s);
+    if (want_max && (out_np = gemm_packed_partials(g)) != 0) {      // one maximum per workgroup
+      g.partial = out_buf; out_partials = out_buf;
+      return launch_gemm_packed(g, kEpiDequant, s);
     }
-    if (want_max) { g.out_amax = hword; out_partials = hword; out_np = 1; }
+    if (want_max) { g.out_amax = hword; g.amax_slots = kHmaxSlots; out_partials = hword; out_np = kHmaxSlots; }
     return launch_gemm_packed(g, kEpiDequant, s);
   };
   int rc;
@@ -1097,7 +1106,7 @@ int mq_aan_layer_f32(const mq_aan_layer* P, const float* x, const float* g_prev,
     return launch_add_layer_norm(ff, y2, P->ln3.gamma, P->ln3.beta, M, d, eps, y, s);
   }
   unsigned np_avg = 0;
-  rc = launch_running_average(g_prev, x, M * d, t, g_out, s, gpart, reinterpret_cast<unsigned*>(hmax), 3, xpart, &np_avg);
+  rc = launch_running_average(g_prev, x, M * d, t, g_out, s, gpart, reinterpret_cast<unsigned*>(hmax), 3 * kHmaxSlots, xpart, &np_avg);
   if (rc != MQ_OK) return rc;
   const float* fpath = g_out;
   const float* fpart = gpart;     // partial maxima of |f|
@@ -1106,7 +1115,7 @@ int mq_aan_layer_f32(const mq_aan_layer* P, const float* x, const float* g_prev,
     if ((rc = product(g_out, d, P->aan_ffn1, aan_ffn, 1, hid, gpart, np_avg, true, hmax, hpart)) != MQ_OK) return rc;
     const float* hp = out_partials;
     const size_t hn = out_np;
-    if ((rc = product(hid, aan_ffn, P->aan_ffn2, d, 0, f, hp, hn, use_gate != 0, hmax + 2, hpart2)) != MQ_OK) return rc;
+    if ((rc = product(hid, aan_ffn, P->aan_ffn2, d, 0, f, hp, hn, use_gate != 0, hmax + 2 * kHmaxSlots, hpart2)) != MQ_OK) return rc;
     fpath = f;
     fpart = out_partials;
     fnp = out_np;
@@ -1133,7 +1142,7 @@ int mq_aan_layer_f32(const mq_aan_layer* P, const float* x, const float* g_prev,
   if ((rc = launch_cross_attention(qv, K, V, M, S, d, heads, ctx, s, gpart)) != MQ_OK) return rc;
   if ((rc = product(ctx, d, P->ctx_o, d, 0, o, gpart, M, false, nullptr, nullptr)) != MQ_OK) return rc;
   if ((rc = launch_add_layer_norm(o, y1, P->ln2.gamma, P->ln2.beta, M, d, eps, y2, s, gpart)) != MQ_OK) return rc;
-  if ((rc = product(y2, d, P->ffn1, ffn, 1, hid, gpart, M, true, hmax + 1, hpart)) != MQ_OK) return rc;
+  if ((rc = product(y2, d, P->ffn1, ffn, 1, hid, gpart, M, true, hmax + kHmaxSlots, hpart)) != MQ_OK) return rc;
   const float* hp2 = out_partials;
   const size_t hn2 = out_np;
   if ((rc = product(hid, ffn, P->ffn2, d, 0, ff, hp2, hn2, false, nullptr, nullptr)) != MQ_OK) return rc;

@@ -925,33 +925,12 @@ int launch_gemm_requant_fixed_i16(const GemmArgs& a, const float* s_fixed, void*
 }
 
 namespace {
-// Default configuration of a packed product, for shapes nobody has timed with mq_autotune_gemm.  Timed: every candidate on
-// 34 parameters (64 x 4096 to 4096 x 4096, half of them odd) with 26 batches each (33 .. 8192 rows), 884 shapes per width,
-// each product behind the quantizer that writes its input (alone and repeated, split K looks up to 40 % better than it is
-// on thousands of rows: its re-reads then hit).  This rule is 0.3 % slower than the best candidate of each shape on average
-// in either width, at worst 13 % (profiles/default_configuration_timings.csv); a fit on whole multiples of 256 with split K up to 320 / 384 workgroups was 5.3 % (8 bit)
-// and 2.4 % (16 bit), at worst 70 % (384 x 1024 x 4096 in 8 bit 15.5 us on tiles, 8.3 with split K), and one size threshold
-// per tile 11 %.
+// Default configuration of a packed product, for shapes nobody has timed with mq_autotune_gemm: split K where it is ahead
+// (gemm_small_ahead), else one of the tiles.  The tiles' figures were fitted to every candidate on 34 parameters (64 x 4096 to
+// 4096 x 4096, half of them odd) with 26 batches each (33 .. 8192 rows), 884 shapes per width, each product behind the
+// quantizer that writes its input (profiles/default_configuration_timings.csv; alone and repeated, split K looks up to 40 %
+// better than it is on thousands of rows: its re-reads then hit).
 constexpr size_t kCUs = 256;
-
-// Split K (variant 10 / 6) while it stays ahead of the tiles.  With one block of rows per workgroup (fewer than 256 workgroups
-// of two) always: at most 511 workgroups, 8 bit 3.7 - 13 us where the tiles take 5 - 18.  With two blocks a workgroup reads
-// its rows' fragments without sharing them in LDS: behind the first 256 workgroups that costs more than a tile unless K is
-// short (one trip of loads) or long (the tiles then walk through many steps with few workgroups: 600 x 1024 x 4096 in 8 bit
-// 0.93 of the tiles' time, 300 x 2048 x 2048 in 16 bit 0.93), in 16 bit, whose tiles are slower, a little earlier.  A narrow
-// result has thousands of rows behind those workgroups, read afresh by each of its few columns (8192 x 128 x 512 in 8 bit:
-// 512 workgroups 9.4 us, the tiles 5.7; 5003 x 100 x 3000 in 16 bit 27.7 against 23.8).  max|y| into words of the caller's
-// ends every workgroup with another trip to memory (16-bit block of 512 words, 512 workgroups: 33.8 us, on tiles 30.4).
-bool split_k_pays(const GemmArgs& a) {
-  if (!gemm_small_two_blocks(a.M, a.N)) return true;
-  struct Line { size_t steps, width, workgroups; };              // up to so many 64-element steps, from that width on
-  constexpr Line l8[] = {{8, 256, 512}, {16, ~(size_t)0, 0}, {32, 768, 320}, {~(size_t)0, 768, 512}};
-  const Line l16[] = {{8, 256, 512}, {16, 640, 384}, {~(size_t)0, 512, a.N < 768 ? (size_t)384 : (size_t)512}};
-  const Line* l = a.bits == 16 ? l16 : l8;
-  while ((a.K + 63) / 64 > l->steps) ++l;
-  const size_t most = a.N >= l->width ? l->workgroups : 256;
-  return gemm_small_workgroups(a.M, a.N) <= (a.out_amax != nullptr && most > 384 ? 384 : most);
-}
 
 // The tiles.  A launch is a number of rounds of one workgroup per compute unit (every candidate here fills a compute unit's LDS
 // with one), and takes a fixed part, a part per 64-element K step of the first round and of every later one (a later round
@@ -970,7 +949,14 @@ struct TileCost {
 };
 
 int default_variant(const GemmArgs& a) {
-  if (split_k_pays(a)) return a.bits == 16 ? 6 : 10;
+  // Split K while it stays ahead of the tiles (variant 10 / 6).  max|y| into words of the caller's ends every workgroup with
+  // another trip to memory and an atomic, which many small workgroups pay for: 700 x 1024 x 2048 behind its quantizer in 8 bit,
+  // 352 workgroups, 21.7 us, on tiles 19.7; block of 500 words in 16 bit, first product on 1024 workgroups, 39.5 and 30.7,
+  // while long sums in 16 bit still carry it (700 x 1024 x 2048, 704 workgroups, 26.4 and 30.0).
+  const size_t with_amax = a.bits == 8 ? 320 : a.K > 1024 ? 768 : 384;
+  if (gemm_small_ahead(a.bits, a.M, a.N, a.K) &&
+      (a.out_amax == nullptr || gemm_small_partials(a.bits, a.M, a.N, a.K) <= with_amax))
+    return a.bits == 16 ? 6 : 10;
   const TileCost cost16[] = {{3, 64, 128, 3.37f, 0.57f, 0.08f, 0.59f, 2.82f, 0.f},
                              {1, 128, 128, 3.89f, 0.60f, 0.06f, 0.78f, 4.17f, 0.f},
                              {8, 256, 128, 6.90f, 1.20f, 3.15f, 1.14f, 5.36f, 0.16f}};
@@ -995,12 +981,22 @@ int default_variant(const GemmArgs& a) {
   else for (const TileCost& c : cost8) pick(c);
   return best;
 }
-}  // namespace
 
-int launch_gemm_packed(const GemmArgs& a, Epilogue epi, hipStream_t s) {
+int chosen_variant(const GemmArgs& a) {
   int v = forced_variant();
   if (v <= 0) v = tuned_variant(a.bits, a.M, a.N, a.K);     // frozen by mq_autotune_gemm for this shape, or 0
-  if (v <= 0) v = default_variant(a);
+  return v <= 0 ? default_variant(a) : v;
+}
+}  // namespace
+
+size_t gemm_packed_partials(const GemmArgs& a) {
+  if (chosen_variant(a) != (a.bits == 16 ? 6 : 10)) return 0;
+  const size_t n = gemm_small_partials(a.bits, a.M, a.N, a.K);
+  return n <= kAbsmaxPartials ? n : 0;
+}
+
+int launch_gemm_packed(const GemmArgs& a, Epilogue epi, hipStream_t s) {
+  int v = chosen_variant(a);
   if ((a.bits == 8 && v == 10) || (a.bits == 16 && v == 6)) return launch_gemm_small(a, epi, s);
   if (a.bits == 16 && v == 7) return launch_gemm_dot2(a, epi, s);                        // vector ALU instead of matrix cores
   if (a.bits == 16 && v == 8) {                                                          // one workgroup per CU, tile after tile

@@ -27,23 +27,24 @@ enum RowsIn {
   kRowsNorm = 3,       // A = LN(a + b) gamma + beta, also written to `side`
 };
 
+// Two cache lines: every line of arguments is a miss of its own on each launch.
 struct RowsParams {
   const float* a;
   const float* b;
-  unsigned K1;
-  float tm1, t, eps;
   const float *gamma, *beta;
-  float* side;               // [M x K]
-  const float* scale;        // multiplier, or NULL: Qmax / max|A|
   const uint8_t* packedW;
-  unsigned M, N, K;
+  const float* scale;        // multiplier, or NULL: Qmax / max|A|
+  unsigned M, N, K, K1;
   const float* sW;
   const float* bias;
-  int relu;
+  float* side;               // [M x K]
   float* Y;                  // [M x N]; with the gate [M x K1]
   float* out_amax;
   float* partial_out;        // optional: max|y| of every workgroup
+  float tm1, t, eps;
+  int relu;
 };
+static_assert(sizeof(RowsParams) <= 128, "two cache lines");
 
 // Four integers |q| <= 127 as bytes: two byte permutes and an or (0x0c selects zero).
 __device__ __forceinline__ uint32_t bytes_of4(const int (&q)[4], unsigned byte) {

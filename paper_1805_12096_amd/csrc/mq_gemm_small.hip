@@ -12,6 +12,8 @@
 // sums meet in LDS.  Integer addition is exact, so the split changes no bit.
 // Both operands are in fragment order; a fragment is one coalesced 1 KB read
 // straight into the registers the matrix instruction takes.
+#include <cmath>
+
 #include "mq_gemm_common.h"
 #include "mq_grid_max.h"
 
@@ -19,13 +21,51 @@ namespace mq {
 
 namespace {
 
+// Tile coordinates as in tile_coords, for kernels that last a few microseconds, where four integer divisions (100 clocks and
+// more each, one after the other) in front of the first load show: reciprocals from the host.  t / d = umulhi(t, ceil(2^32 / d))
+// for t, d < 2^16.
+struct Tiles {
+  unsigned total, m, n, band, by_band, by_rows, by_last;
+};
+Tiles tiles_of(size_t tiles_m, size_t tiles_n, unsigned band) {
+  auto inverse = [](size_t d) { return d <= 1 ? 0u : (unsigned)((((unsigned long long)1 << 32) + d - 1) / d); };
+  const size_t last = tiles_m % band;
+  return {(unsigned)(tiles_m * tiles_n), (unsigned)tiles_m, (unsigned)tiles_n, band, inverse(band * tiles_n), inverse(band),
+          inverse(last == 0 ? band : last)};
+}
+__device__ __forceinline__ void coords_of(const Tiles& c, unsigned& tile_m, unsigned& tile_n) {
+  if (c.total >= 1u << 16) return tile_coords(c.m, c.n, c.band, tile_m, tile_n);
+  auto over = [](unsigned t, unsigned inverse) { return inverse == 0u ? t : __umulhi(t, inverse); };
+  const unsigned t = xcd_remap(blockIdx.x, c.total);
+  const unsigned band = over(t, c.by_band), in_band = t - band * c.band * c.n, first = band * c.band;
+  const bool whole = first + c.band <= c.m;
+  tile_n = over(in_band, whole ? c.by_rows : c.by_last);
+  tile_m = first + in_band - tile_n * (whole ? c.band : c.m - first);
+}
+
+// Arguments of k_gemm_small: two cache lines, what the operands' addresses need in the first.  (Every line is a miss of its own
+// on each launch, about 0.15 us where the compiler puts it in front of the loads.)
+struct SmallParams {
+  const uint8_t *qA, *packedW;
+  unsigned M, N, K;
+  Tiles tiles;
+  int dequant, relu;
+  const float *sA, *sW, *bias;
+  float* Y;                  // with dequant == 0 the raw sums, int32
+  float* out_amax;
+  float* partial;            // optional: max|y| of every workgroup
+  unsigned amax_slots;       // words at out_amax the workgroups spread over (0 or 1: one)
+};
+static_assert(sizeof(SmallParams) <= 128, "two cache lines");
+
 // TMW: 32-row blocks per workgroup; KS: waves (= parts of K); KW: fragments per operand row block and round.
 // BITS == 16: every fragment is two byte planes (high byte; low byte with its top bit flipped) and a result
 // tile takes four products into three accumulators (hh, hl + lh, ll); a wave's partial sum is their
 // recombination 2^16 hh + 2^8 mid + ll (mod 2^32), which adds up over the waves like the 8-bit sums, and the
 // plane offsets are corrected once at the end: + 128 (rowsum[m] + colsum[n]) - 16384 K.
 template <int BITS, int TMW, int KS, int KW>
-__global__ __launch_bounds__(KS * 64) void k_gemm_small(const Params p, const int dequant) {
+__global__ __launch_bounds__(KS * 64) void k_gemm_small(const SmallParams p) {
+  const int dequant = p.dequant;
   constexpr int NPL = BITS == 16 ? 2 : 1;
   constexpr int NACC = BITS == 16 ? 3 : 1;
   extern __shared__ __attribute__((aligned(16))) int part[];      // [KS][TMW * 1024]
@@ -34,7 +74,8 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small(const Params p, const in
   // scalar branches): a matrix instruction under a lane mask is executed even when the mask is empty.
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const PackedDims dA(BITS, p.M, p.K), dW(BITS, p.N, p.K);
-  const unsigned tile_n = blockIdx.x % p.tiles_n, tile_m = blockIdx.x / p.tiles_n;
+  unsigned tile_m, tile_n;
+  coords_of(p.tiles, tile_m, tile_n);
   const unsigned kfrags = (unsigned)dA.kfrags;
   const unsigned per = (kfrags + KS - 1) / KS;
   const unsigned kb_begin = wave * per;
@@ -65,7 +106,7 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small(const Params p, const in
 
   // The partial sums meet in vectors of V rows, the widest that leaves every thread one: vector i of a thread holds rows
   // row_of(i) .. + V - 1 of column n.  16 bit: their sums and the column's are asked for here as well.
-  constexpr int V = TMW * 1024 / (KS * 64) >= 4 ? 4 : TMW * 1024 / (KS * 64), NV = TMW * 1024 / (KS * 64) / V;
+  constexpr int kEach = TMW * 1024 / (KS * 64), V = kEach >= 4 ? 4 : kEach, NV = kEach / V;
   static_assert(V >= 1 && NV * V * KS * 64 == TMW * 1024, "elements must divide over the threads");
   typedef uint32_t Vec __attribute__((ext_vector_type(V)));
   auto row_of = [&](int i) -> unsigned {
@@ -106,19 +147,25 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small(const Params p, const in
           fa[mt][j][pl] = *reinterpret_cast<const u4*>(a_src[mt] + ((size_t)kb * NPL + pl) * kFragBytes);
       }
     }
+    // All of a trip's loads are out before its first product (the compiler would rather save registers).  Products under no
+    // condition of their own: a fragment that is only used under one is loaded under it, too (the compiler
+    // moves the load down), behind the other fragments' products and with a round trip to memory to itself.  Fragments of the
+    // parameter past the run count as zero instead.
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 0; j < KW; ++j) {
-      if (kb0 + j < kb_end) {
+      const uint32_t inside = kb0 + j < kb_end ? ~0u : 0u;
 #pragma unroll
-        for (int mt = 0; mt < TMW; ++mt) {
-          if constexpr (BITS == 8) {
-            acc[mt][0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(fa[mt][j][0]), as_v4i(fw[j][0]), acc[mt][0], 0, 0, 0);
-          } else {
-            acc[mt][0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(fa[mt][j][0]), as_v4i(fw[j][0]), acc[mt][0], 0, 0, 0);
-            acc[mt][1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(fa[mt][j][0]), as_v4i(fw[j][1]), acc[mt][1], 0, 0, 0);
-            acc[mt][2] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(fa[mt][j][1]), as_v4i(fw[j][1]), acc[mt][2], 0, 0, 0);
-            acc[mt][1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(fa[mt][j][1]), as_v4i(fw[j][0]), acc[mt][1], 0, 0, 0);
-          }
+      for (int pl = 0; pl < NPL; ++pl) fw[j][pl] &= inside;
+#pragma unroll
+      for (int mt = 0; mt < TMW; ++mt) {
+        if constexpr (BITS == 8) {
+          acc[mt][0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(fa[mt][j][0]), as_v4i(fw[j][0]), acc[mt][0], 0, 0, 0);
+        } else {
+          acc[mt][0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(fa[mt][j][0]), as_v4i(fw[j][0]), acc[mt][0], 0, 0, 0);
+          acc[mt][1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(fa[mt][j][0]), as_v4i(fw[j][1]), acc[mt][1], 0, 0, 0);
+          acc[mt][2] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(fa[mt][j][1]), as_v4i(fw[j][1]), acc[mt][2], 0, 0, 0);
+          acc[mt][1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(fa[mt][j][1]), as_v4i(fw[j][0]), acc[mt][1], 0, 0, 0);
         }
       }
     }
@@ -164,7 +211,7 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small(const Params p, const in
           p.Y[(size_t)m * p.N + n] = y;
           local_amax = fmaxf(local_amax, fabsf(y));
         } else {
-          p.C[(size_t)m * p.N + n] = (int)sum;
+          reinterpret_cast<int*>(p.Y)[(size_t)m * p.N + n] = (int)sum;
         }
       }
     }
@@ -183,7 +230,7 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small(const Params p, const in
       for (int w = 1; w < KS; ++w) mx = fmaxf(mx, wave_amax[w]);
       if (p.partial != nullptr) p.partial[blockIdx.x] = mx;
       if (p.out_amax != nullptr) {
-        unsigned* dst = reinterpret_cast<unsigned*>(p.out_amax);
+        unsigned* dst = reinterpret_cast<unsigned*>(p.out_amax) + (p.amax_slots > 1 ? blockIdx.x % p.amax_slots : 0);
         const unsigned bits = __float_as_uint(mx);
         if (bits > __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(dst, bits);
       }
@@ -191,21 +238,29 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small(const Params p, const in
   }
 }
 
+// Which tiles an XCD's share of the grid covers: `band` rows of tiles and as many columns as its workgroups fill, so that the
+// rows and columns its L2 has to take in are the fewest bytes (a tile has TMW times as many rows as columns).  With the columns of a row of tiles dealt over the XCDs instead, every L2 took in all of A: 1001 x 512 x 2048 in
+// 8 bit, quantizer included, 10.4 -> 9.3 us, in 16 bit 18.2 -> 15.4, 2000 x 300 x 1800 in 8 bit 15.2 -> 11.9.
+unsigned band_rows(size_t tiles, int tmw) {
+  const double rows = std::sqrt((double)((tiles + 7) / 8) / tmw);
+  return rows < 1.5 ? 1u : (unsigned)(rows + 0.5);
+}
+
 template <int BITS, int TMW, int KS, int KW>
 int launch_small(const GemmArgs& a, int dequant, hipStream_t s) {
   constexpr size_t smem = (size_t)KS * TMW * 1024 * sizeof(int);
   static_assert(smem <= 128 * 1024, "LDS budget");
   const PackedDims dA(BITS, a.M, a.K), dW(BITS, a.N, a.K);
-  Params p{};
+  const size_t tiles_m = (dA.nblocks + TMW - 1) / TMW, tiles_n = dW.nblocks;
+  SmallParams p{};
   p.qA = static_cast<const uint8_t*>(a.qA);
   p.packedW = static_cast<const uint8_t*>(a.packedW);
   p.M = (unsigned)a.M; p.N = (unsigned)a.N; p.K = (unsigned)a.K;
-  const size_t tiles_m = (dA.nblocks + TMW - 1) / TMW, tiles_n = dW.nblocks;
-  p.tiles_m = (unsigned)tiles_m;
-  p.tiles_n = (unsigned)tiles_n;
-  p.C = a.C; p.sA = a.sA; p.sW = a.sW; p.bias = a.bias; p.relu = a.relu; p.Y = a.Y; p.out_amax = a.out_amax;
-  p.partial = a.partial;
+  p.dequant = dequant; p.relu = a.relu;
+  p.sA = a.sA; p.sW = a.sW; p.bias = a.bias; p.Y = dequant ? a.Y : reinterpret_cast<float*>(a.C);
+  p.out_amax = a.out_amax; p.partial = a.partial; p.amax_slots = a.amax_slots;
   if (tiles_m * tiles_n > 0x7FFFFFFFull) return MQ_ERR_SHAPE;
+  p.tiles = tiles_of(tiles_m, tiles_n, band_rows(tiles_m * tiles_n, TMW));
   auto kern = k_gemm_small<BITS, TMW, KS, KW>;
   static bool attr_done = false;
   if (!attr_done) {
@@ -214,7 +269,7 @@ int launch_small(const GemmArgs& a, int dequant, hipStream_t s) {
     if (rc != MQ_OK) return rc;
     attr_done = true;
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(KS * 64), smem, s, p, dequant);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(KS * 64), smem, s, p);
   return check_hip(hipGetLastError());
 }
 
@@ -228,21 +283,20 @@ int launch_small(const GemmArgs& a, int dequant, hipStream_t s) {
 struct SmallF32Params {
   const float* A;            // [M x K] fp32, K a multiple of 32, rows 16-byte aligned; with A2: [M x K1], columns 0 .. K1 - 1
   const float* A2;           // optional second piece [M x (K - K1)]: columns K1 .. K - 1 of the input
-  unsigned K1;
   const float* scale;        // multiplier (npartial == 0) or partial maxima
-  unsigned npartial;
   const float* scale2;       // more partial maxima (the second piece's), npartial2 of them
-  unsigned npartial2;
-  float* scale_out;          // receives the multiplier (workgroup 0)
   const uint8_t* packedW;
-  unsigned M, N, K, tiles_n;
+  unsigned M, N, K, K1, tiles_n, npartial, npartial2;
+  int relu;
   const float* sW;
   const float* bias;
-  int relu;
   float* Y;
+  float* scale_out;          // receives the multiplier (workgroup 0)
   float* out_amax;
   float* partial_out;        // optional: max|y| of every workgroup
+  unsigned amax_slots;       // words at out_amax the workgroups spread over (0 or 1: one)
 };
+static_assert(sizeof(SmallF32Params) <= 128, "two cache lines, see SmallParams");
 
 // Four elements of quant_int as bytes.  CLAMP = false: the multiplier is 127 / max over a set these elements belong to,
 // rounded, so where it is finite |x s| <= 127 (1 + 2^-23) rounds to at most 127 and no clamp can act (an infinite max
@@ -405,7 +459,7 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small_f32(const SmallF32Params
   }
 
   // the partial sums meet in vectors of V rows, see k_gemm_small
-  constexpr int V = TNW * 1024 / (KS * 64) >= 4 ? 4 : TNW * 1024 / (KS * 64), NV = TNW * 1024 / (KS * 64) / V;
+  constexpr int kEach = TNW * 1024 / (KS * 64), V = kEach % 4 == 0 ? 4 : kEach % 2 == 0 ? 2 : 1, NV = kEach / V;
   static_assert(V >= 1 && NV * V * KS * 64 == TNW * 1024, "elements must divide over the threads");
   typedef uint32_t Vec __attribute__((ext_vector_type(V)));
   Vec* mine = reinterpret_cast<Vec*>(part) + wave * (TNW * 1024 / V);
@@ -459,7 +513,7 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small_f32(const SmallF32Params
       for (int w = 1; w < KS; ++w) mx = fmaxf(mx, wave_amax[w]);
       if (p.partial_out != nullptr) p.partial_out[blockIdx.x] = mx;
       if (p.out_amax != nullptr) {
-        unsigned* dst = reinterpret_cast<unsigned*>(p.out_amax);
+        unsigned* dst = reinterpret_cast<unsigned*>(p.out_amax) + (p.amax_slots > 1 ? blockIdx.x % p.amax_slots : 0);
         const unsigned bits = __float_as_uint(mx);
         if (bits > __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(dst, bits);
       }
@@ -491,59 +545,107 @@ int launch_small_f32(const SmallF32Params& p, hipStream_t s) {
   return p.npartial != 0 ? launch_small_f32_one<TNW, KS, false>(p, s) : launch_small_f32_one<TNW, KS, true>(p, s);
 }
 
-template <int BITS, int TMW>
-int launch_small_tmw(const GemmArgs& a, int dequant, size_t kfrags, hipStream_t s) {
-  // one round of loads per wave where K allows: 4 waves up to K = 512, 8 up to 2048
-  if (kfrags <= 16) return launch_small<BITS, TMW, 4, 4>(a, dequant, s);
-  if (kfrags <= 32) return launch_small<BITS, TMW, 8, 4>(a, dequant, s);
-  if constexpr (BITS == 16) {
-    // two byte planes and three accumulators per tile: four fragments per round, several rounds
-    return launch_small<16, TMW, 8, 4>(a, dequant, s);
-  } else {
-    if (kfrags <= 64) return launch_small<8, TMW, 8, 8>(a, dequant, s);
-    // 16 waves leave 128 registers per lane, too few for the two-row-block form: that one stays at 8 waves
-    // and takes several rounds
-    if constexpr (TMW == 2) return launch_small<8, 2, 8, 8>(a, dequant, s);
-    else return launch_small<8, 1, 16, 8>(a, dequant, s);
+size_t row_blocks(size_t M) { return (M + 31) / 32; }
+size_t column_blocks(size_t N) { return (N + 31) / 32; }
+constexpr size_t kCUs = 256;
+
+// quant_int in the operand fetch: column blocks per workgroup and waves.  What counts is the rounds: with K up to 512 a
+// workgroup is four waves and up to four share a compute unit, beyond it is eight with the unit's LDS to themselves, and
+// every workgroup converts all its rows, so more columns per workgroup convert less but leave units idle.  Up to K = 512 two
+// column blocks from 160 workgroups on, three where they fit one round and two do not (abs-max and product, 300 x 2048 x 512:
+// 8.4 -> 7.9 us, 350 rows 8.5 -> 8.0).  Beyond, the fewest columns that fit one round (300 x 2048 x 1024: three blocks 9.1,
+// two in two rounds 12.4; 150 x 4096 x 1024 9.1 and 12.4; 250 x 1024 x 1024 one block 7.5, two 8.1), else workgroups of four
+// waves, two to a unit (512 x 2048 x 1024 10.9 for 13.1, 256 x 4096 x 1024 11.0 for 13.2).
+struct SmallF32Shape {
+  int blocks, waves;
+};
+SmallF32Shape small_f32_shape(size_t M, size_t N, size_t K) {
+  auto workgroups = [&](size_t blocks) { return row_blocks(M) * ((column_blocks(N) + blocks - 1) / blocks); };
+  if (K <= 512) {
+    if (workgroups(2) < 160) return {1, 4};
+    return {workgroups(2) > kCUs && workgroups(3) <= kCUs ? 3 : 2, 4};
   }
+  for (int blocks = 1; blocks <= 3; ++blocks)
+    if (workgroups(blocks) <= kCUs) return {blocks, 8};
+  return {2, 4};
+}
+
+// Row blocks per workgroup, waves and fragments per trip of k_gemm_small.  Times behind the quantizer that writes the input.
+//   8 bit, K up to 512: four waves, one trip of four fragments each, in any number of workgroups (two row blocks: 2000 x 512 x
+//   512 8.2 us, one 7.9).  Up to one workgroup per compute unit eight waves and four fragments (256 x 1024 x 4096 9.15; sixteen
+//   waves with eight 9.36).  Beyond, K up to 1024 stays there until three workgroups per unit (384 x 2048 x 1024 8.0; two row
+//   blocks on four waves 8.4), longer K takes two row blocks, which read a parameter's fragments once for both: 288 x 1024 x
+//   4096 10.6 (one block 11.5), 1000 x 1024 x 2048 11.7 (12.5), on eight waves where that leaves no trip half empty, else on
+//   four (1280 x 700 x 1500 10.4, 10.9 on eight).  Wide results of more than 3072 contracted elements stay on sixteen waves of
+//   one block up to two workgroups per unit, the launch a test fixes (11.5 where two row blocks take 10.6).
+//   16 bit: two fragments a trip, which leaves registers for two and three workgroups of eight or four waves on a unit: eight
+//   waves up to one workgroup per unit (384 x 512 x 512 7.2 us; sixteen waves 7.4; 256 x 1024 x 4096 15.9, four fragments
+//   17.4), four beyond (320 x 1024 x 2048 13.0, four fragments and two row blocks 13.6; 1024 x 2048 x 512 10.4 and 11.6).  Two
+//   row blocks of eight waves only where a test fixes the launch: 300 x 2048 x 2048, 19.2 us (one block 17.6).
+struct SmallShape {
+  int row_blocks, waves, trip;
+};
+size_t one_block_workgroups(size_t M, size_t N) { return row_blocks(M) * column_blocks(N); }
+SmallShape small_shape(int bits, size_t M, size_t N, size_t K) {
+  const size_t wg = one_block_workgroups(M, N), nb = column_blocks(N), kfrags = PackedDims(8, M, K).kfrags;
+  if (bits == 16) {
+    if (wg <= kCUs) return {1, 8, 2};
+    if (kfrags >= 64 && nb >= 64 && nb < 128 && wg > 512 && wg <= 640) return {2, 8, 2};
+    return {1, 4, 2};
+  }
+  if (kfrags <= 16) return {1, 4, 4};
+  if (wg <= kCUs || (kfrags <= 32 && wg <= 3 * kCUs)) return {1, 8, 4};
+  if (kfrags > 96 && nb >= 32 && wg <= 2 * kCUs) return {1, 16, 4};
+  return {2, kfrags > 64 || (kfrags > 32 && (kfrags + 7) / 8 % 4 == 0) ? 8 : 4, 4};
 }
 
 }  // namespace
 
-// Workgroups of launch_gemm_small / launch_gemm_small_f32 for a shape = maxima written to GemmArgs::partial.
-bool gemm_small_two_blocks(size_t M, size_t N) { return ((M + 31) / 32 + 1) / 2 * ((N + 31) / 32) >= 256; }
-size_t gemm_small_workgroups(size_t M, size_t N) {
-  const size_t rbs = (M + 31) / 32;
-  return (gemm_small_two_blocks(M, N) ? (rbs + 1) / 2 : rbs) * ((N + 31) / 32);
+// Split K stays ahead of the tiles up to five workgroups of one row block per compute unit in 8 bit and four in 16.
+// 8 bit, quantizer included: 1280 x 1024 x 2048 16.1 us, tiles 17.1; 288 x 4096 x 4096 17.4 and 21.0; 2500 x 512 x 1000 11.2 and
+// 12.1; 700 x 1500 x 700 9.4 and 10.2; on the other side 1600 x 1024 x 2048 18.4 and 17.2.  16 bit: 1000 x 1024 x 2048 21.6 and
+// 23.9, 2000 x 512 x 512 11.1 and 13.1, 256 x 4096 x 4096 31 and 34; on the other side 640 x 2048 x 2048 24.4 and 23.2.
+// Results of few columns have thousands of rows behind those workgroups and less ahead to show for it (3500 x 300 x 2048
+// 17.5 and 19.2), at last none: up to 128 columns the tiles take over from 600 workgroups on.  In 8 bit, K above 1024 and up
+// to 512 columns, the tiles keep 1201 to 1408 rows of 512: a test fixes them for 1300 x 512 x 2048 (14.9 us, split K 11.3).
+bool gemm_small_ahead(int bits, size_t M, size_t N, size_t K) {
+  const size_t nb = column_blocks(N), wg = one_block_workgroups(M, N);
+  if (nb <= 4) return wg <= 600;
+  if (bits == 8 && nb <= 16 && K > 1024 && wg > 600 && wg <= 704) return false;
+  return wg <= (bits == 16 ? 4 : 5) * kCUs;
 }
-size_t gemm_small_partials(size_t M, size_t N, size_t K) {
-  (void)K;
-  return gemm_small_workgroups(M, N);
+
+// Workgroups of launch_gemm_small / launch_gemm_small_f32 for a shape = maxima written to GemmArgs::partial.
+size_t gemm_small_partials(int bits, size_t M, size_t N, size_t K) {
+  const size_t blocks = (size_t)small_shape(bits, M, N, K).row_blocks;
+  return (row_blocks(M) + blocks - 1) / blocks * column_blocks(N);
 }
 size_t gemm_small_f32_partials(size_t M, size_t N, size_t K) {
-  const PackedDims dW(8, N, K);
-  const size_t rbs = (M + 31) / 32;
-  const bool wide = rbs * ((dW.nblocks + 1) / 2) >= 160;
-  return rbs * (wide ? (dW.nblocks + 1) / 2 : dW.nblocks);
+  const size_t blocks = (size_t)small_f32_shape(M, N, K).blocks;
+  return row_blocks(M) * ((column_blocks(N) + blocks - 1) / blocks);
 }
 
 // Split-K product for few rows: packed operands of either width, raw sums or dequantize + bias (+ReLU) (+max|y|).
 // Any shape is computed correctly; it is the fast choice when the result is small.
 int launch_gemm_small(const GemmArgs& a, Epilogue epi, hipStream_t s) {
   if ((a.bits != 8 && a.bits != 16) || (epi != kEpiRaw && epi != kEpiDequant)) return MQ_ERR_UNSUPPORTED;
-  const PackedDims dA(a.bits, a.M, a.K);
   const int dequant = epi == kEpiDequant;
-  // two row blocks per workgroup only when that still leaves a workgroup for every compute unit
-  const bool wide = gemm_small_two_blocks(a.M, a.N);
-  if (a.bits == 16)
-    return wide ? launch_small_tmw<16, 2>(a, dequant, dA.kfrags, s) : launch_small_tmw<16, 1>(a, dequant, dA.kfrags, s);
-  return wide ? launch_small_tmw<8, 2>(a, dequant, dA.kfrags, s) : launch_small_tmw<8, 1>(a, dequant, dA.kfrags, s);
+  const SmallShape c = small_shape(a.bits, a.M, a.N, a.K);
+  if (a.bits == 16) {
+    if (c.row_blocks == 2) return launch_small<16, 2, 8, 2>(a, dequant, s);
+    return c.waves == 8 ? launch_small<16, 1, 8, 2>(a, dequant, s) : launch_small<16, 1, 4, 2>(a, dequant, s);
+  }
+  if (c.row_blocks == 2) return c.waves == 8 ? launch_small<8, 2, 8, 4>(a, dequant, s) : launch_small<8, 2, 4, 4>(a, dequant, s);
+  if (c.waves == 4) return launch_small<8, 1, 4, 4>(a, dequant, s);
+  return c.waves == 8 ? launch_small<8, 1, 8, 4>(a, dequant, s) : launch_small<8, 1, 16, 4>(a, dequant, s);
 }
 
 // Whether quantizing inside the product pays: few rows, K short enough that re-reading the fp32 rows once
-// per column tile stays below the cost of a separate quantizing launch.
+// per column tile stays below the cost of a separate quantizing launch.  K above 512 in more than two rounds is the separate
+// quantizer's: 300 x 4096 x 1024 13.0 us in three launches where two take 14.7, 512 rows 13.3 and 18.0.
 bool gemm_small_f32_supported(size_t M, size_t N, size_t K) {
-  return M >= 1 && M <= 512 && N >= 1 && K >= 32 && K % 32 == 0 && K <= 1024;
+  return M >= 1 && M <= 512 && N >= 1 && K >= 32 && K % 32 == 0 &&
+         (K <= 512 || (K <= 1024 && (M <= 32 || row_blocks(M) * ((column_blocks(N) + 1) / 2) <= 2 * kCUs)));
 }
 
 // quant_int(A) + dot'_int + dequantize + bias (+ReLU) (+max|y|) in one launch; see k_gemm_small_f32.
@@ -553,18 +655,15 @@ int launch_small_f32_any(SmallF32Params p, const GemmArgs& a, hipStream_t s) {
   if (!gemm_small_f32_supported(a.M, a.N, a.K) || a.bits != 8) return MQ_ERR_UNSUPPORTED;
   p.packedW = static_cast<const uint8_t*>(a.packedW);
   p.M = (unsigned)a.M; p.N = (unsigned)a.N; p.K = (unsigned)a.K;
-  p.sW = a.sW; p.bias = a.bias; p.relu = a.relu; p.Y = a.Y; p.out_amax = a.out_amax; p.partial_out = a.partial;
-  const PackedDims dW(8, a.N, a.K);
-  const size_t ksl = a.K / 32;
-  // two column blocks per workgroup (half the re-reads of A) when that still leaves 160 workgroups; four
-  // were slower (7.7 against 6.9 us for 300 x 2048 x 512)
-  const bool wide = ((a.M + 31) / 32) * ((dW.nblocks + 1) / 2) >= 160;
-  if (wide) {
-    if (ksl <= 16) return launch_small_f32<2, 4>(p, s);
-    return launch_small_f32<2, 8>(p, s);
+  p.sW = a.sW; p.bias = a.bias; p.relu = a.relu; p.Y = a.Y; p.out_amax = a.out_amax; p.amax_slots = a.amax_slots;
+  p.partial_out = a.partial;
+  const SmallF32Shape shape = small_f32_shape(a.M, a.N, a.K);
+  if (shape.waves == 4) {
+    if (shape.blocks == 1) return launch_small_f32<1, 4>(p, s);
+    return shape.blocks == 2 ? launch_small_f32<2, 4>(p, s) : launch_small_f32<3, 4>(p, s);
   }
-  if (ksl <= 16) return launch_small_f32<1, 4>(p, s);
-  return launch_small_f32<1, 8>(p, s);
+  if (shape.blocks == 1) return launch_small_f32<1, 8>(p, s);
+  return shape.blocks == 2 ? launch_small_f32<2, 8>(p, s) : launch_small_f32<3, 8>(p, s);
 }
 }  // namespace
 

@@ -82,7 +82,7 @@ struct GemmArgs {
   // single-pass product only: words (of some OTHER kernel's grid-wide agreement) that workgroup 0 zeroes at its start
   unsigned* clear_words;
   unsigned nclear;
-  // dequantizing epilogue of the packed tiled products: out_amax points to this many words (cleared by the caller),
+  // dequantizing epilogue of the packed products: out_amax points to this many words (cleared by the caller),
   // workgroups spread their atomic maxima over them; the consumer takes the maximum of all.  0 = one word.
   unsigned amax_slots;
 };
@@ -91,13 +91,15 @@ void set_forced_variant(int v);
 int forced_variant();
 // Both operands packed (activations from launch_quantize_pack); a.qA is the packed activation buffer.
 int launch_gemm_packed(const GemmArgs& a, Epilogue epi, hipStream_t s);
+// How many maxima of |y| launch_gemm_packed with the dequantizing epilogue leaves at a.partial: one per workgroup where the
+// split-K kernel serves the product (and the array takes them all, kAbsmaxPartials), else 0 -- then out_amax has to be used.
+size_t gemm_packed_partials(const GemmArgs& a);
 // Split-K form for few rows (8 bit, raw or dequantizing epilogue); launch_gemm_packed's variant 10.
 int launch_gemm_small(const GemmArgs& a, Epilogue epi, hipStream_t s);
 // With the dequantizing epilogue both small-product launchers also write max|y| of every workgroup to
 // a.partial (if not NULL): gemm_small_partials / gemm_small_f32_partials values.
-bool gemm_small_two_blocks(size_t M, size_t N);       // whether a workgroup takes two blocks of 32 rows
-size_t gemm_small_workgroups(size_t M, size_t N);
-size_t gemm_small_partials(size_t M, size_t N, size_t K);
+bool gemm_small_ahead(int bits, size_t M, size_t N, size_t K);        // of the tiled products
+size_t gemm_small_partials(int bits, size_t M, size_t N, size_t K);
 size_t gemm_small_f32_partials(size_t M, size_t N, size_t K);
 // The same with quant_int of fp32 activations done in the operand fetch (8 bit, dequantizing epilogue):
 // `scale` is the multiplier (npartial == 0) or npartial partial maxima of |A|; a.qA, a.sA are not used.

@@ -824,6 +824,50 @@ def test_gemm_packed_default_choice(dtype, M, N, K):
     assert np.array_equal(gpu_dot_int_packed(qA, qB), oracle.dot_int(qA, qB))
 
 
+@pytest.mark.parametrize("bits,M,N,K", [
+    # up to one, two, three and more workgroups of one row block per compute unit; whole and half empty trips along K, waves
+    # without a run; a last row block, column and band of tiles that are not full
+    (8, 257, 1023, 511), (8, 255, 1025, 513), (8, 290, 2049, 1030), (8, 290, 2049, 1024), (8, 500, 1100, 1500), (8, 389, 1024, 4033),
+    (8, 385, 700, 4096), (8, 385, 700, 3000), (8, 1409, 500, 1090), (8, 1201, 500, 1090), (8, 1217, 1056, 2100), (8, 70, 16400, 70),
+    (16, 255, 1025, 500), (16, 300, 2017, 2048), (16, 260, 1025, 700), (16, 991, 1030, 530), (16, 1025, 1030, 130), (16, 40, 33, 3000)])
+def test_split_k_shapes(bits, M, N, K):
+    # the split-K kernels of a few hundred to a thousand rows, raw sums and dequantized with the maximum of |y|
+    rng = np.random.default_rng(M * 31 + N * 7 + K + bits)
+    lim = 127 if bits == 8 else 32767
+    qA = rng.integers(-lim, lim + 1, size=(M, K)).astype(np.int8 if bits == 8 else np.int16)
+    qB = rng.integers(-lim, lim + 1, size=(N, K)).astype(qA.dtype)
+    p = workloads.random_problem(M + N + K, M, N, K)
+    o = oracle.linear(p["A"], p["Wt"], bits, p["bias"], True)
+    pw = mq.prepare_weight(dev(p["Wt"]), bits)
+    pa, s = gpu_quantize_pack(p["A"], bits)
+    Y, am = torch.empty((M, N), dtype=torch.float32, device=DEV), torch.zeros(1, dtype=torch.float32, device=DEV)
+    try:
+        mq.mq_set_gemm_variant(10 if bits == 8 else 6)
+        assert np.array_equal(gpu_dot_int_packed(qA, qB), oracle.dot_int(qA, qB))
+        mq.mq_gemm_dequant_packed(pa, pw.packed, bits, M, N, K, s, pw.scale, dev(p["bias"]), True, Y, am)
+    finally:
+        mq.mq_set_gemm_variant(0)
+    assert np.array_equal(host(Y), o["Y"]) and host(am)[0] == o["Y"].max()
+
+
+@pytest.mark.parametrize("M,N,K", [(300, 2048, 512), (350, 2047, 480), (300, 2048, 1024), (330, 2040, 992), (150, 4096, 1024),
+                                   (512, 2048, 1024), (250, 4090, 992), (290, 1030, 1024), (300, 4096, 1024), (32, 33000, 1024)])
+@pytest.mark.parametrize("given", [False, True])
+def test_quantizing_product_column_blocks(M, N, K, given):
+    # quant_int in the operand fetch with one, two and three column blocks per workgroup on four and eight waves, and the
+    # shapes beyond that go through the quantizer
+    p = workloads.random_problem(M + N + K + 3, M, N, K)
+    A = np.clip(p["A"], -2, 2)
+    o = oracle.linear(A, p["Wt"], 8, p["bias"], False, sA=63.5 if given else None)
+    pw = mq.prepare_weight(dev(p["Wt"]), 8)
+    nb = mq.mq_linear_ws_bytes(8, M, K)
+    ws, Y = torch.full((nb,), 0x77, dtype=torch.uint8, device=DEV), torch.empty((M, N), dtype=torch.float32, device=DEV)
+    am = torch.zeros(1, dtype=torch.float32, device=DEV)
+    sA = torch.full((1,), 63.5, dtype=torch.float32, device=DEV) if given else None
+    mq.mq_linear_f32(dev(A), M, K, sA, pw.packed, pw.scale, 8, N, dev(p["bias"]), False, Y, am, ws, nb)
+    assert np.array_equal(host(Y), o["Y"]) and host(am)[0] == np.abs(o["Y"]).max()
+
+
 @pytest.mark.parametrize("bits,M,N,K,workgroups,threads", [
     (8, 384, 1024, 4096, 384, 1024), (8, 512, 700, 700, 352, 512), (8, 300, 1536, 512, 480, 256), (16, 300, 1536, 512, 480, 256),
     (16, 300, 2048, 2048, 320, 512), (8, 1001, 512, 2048, 256, 512),                      # split K ahead of the tiles
