@@ -35,8 +35,7 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
 // max over the workgroup of a non-negative value, to partial[blockIdx.x] (for the abs-max of the tensor
 // this kernel writes, so that the quantizer of the next product needs no pass of its own)
 __device__ __forceinline__ void block_absmax_out(float v, float* red, float* __restrict__ partial) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, kWave));
+  v = wave_max_f(v);
   __syncthreads();
   if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = v;
   __syncthreads();
@@ -265,8 +264,7 @@ __global__ __launch_bounds__(kTA) void k_cross_attention(const float* __restrict
   for (unsigned h = wave; h < heads; h += NWV) {
     float mx = -INFINITY;
     for (unsigned s = lane; s < S; s += kWave) mx = fmaxf(mx, sc[h * S + s]);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, kWave));
+    mx = wave_max_f(mx);
     float sum = 0.f;
     for (unsigned s = lane; s < S; s += kWave) {
       const float e = expf(sc[h * S + s] - mx);
@@ -297,8 +295,7 @@ __global__ __launch_bounds__(kTA) void k_cross_attention(const float* __restrict
   }
   if (partial != nullptr) {
     // (the helper is written for kT threads; here the workgroup is kTA wide)
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, kWave));
+    mx = wave_max_f(mx);
     __syncthreads();
     if (lane == 0) red[wave] = mx;
     __syncthreads();
@@ -367,18 +364,13 @@ __global__ __launch_bounds__(kTA) void k_cross_attention_fast(const float* __res
       for (int j = 0; j < kAhead; ++j) va[j] = V4[(size_t)(sg + j * SG < S ? sg + j * SG : S - 1) * COLS + col];
       __builtin_amdgcn_sched_barrier(0);
     }
-    // (all sums of a trip take one step of the exchange together: one after the other they are 4 CH serial chains)
     float a[4][CH];
 #pragma unroll
     for (int u = 0; u < 4; ++u)
 #pragma unroll
       for (int c = 0; c < CH; ++c)
         a[u][c] = fmaf(qr[c].x, kr[u][c].x, fmaf(qr[c].y, kr[u][c].y, fmaf(qr[c].z, kr[u][c].z, qr[c].w * kr[u][c].w)));
-    for (unsigned off = grp / 2; off >= 1; off >>= 1)
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int c = 0; c < CH; ++c) a[u][c] += __shfl_xor(a[u][c], off, kWave);
+    group_sums_f(a, grp);
     if (lane % grp == 0)
 #pragma unroll
       for (int u = 0; u < 4; ++u)
@@ -394,8 +386,7 @@ __global__ __launch_bounds__(kTA) void k_cross_attention_fast(const float* __res
       const bool in = lane < S;
       const float x = in ? sc[h * S + lane] : -INFINITY;
       float mx = x;
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, kWave));
+      mx = wave_max_f(mx);
       const float e = in ? expf(x - mx) : 0.f;
       const float inv = __fdiv_rn(1.0f, wave_sum_f(e));
       if (in) sc[h * S + lane] = e * inv;
@@ -403,8 +394,7 @@ __global__ __launch_bounds__(kTA) void k_cross_attention_fast(const float* __res
     }
     float mx = -INFINITY;
     for (unsigned s = lane; s < S; s += kWave) mx = fmaxf(mx, sc[h * S + s]);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, kWave));
+    mx = wave_max_f(mx);
     float sum = 0.f;
     for (unsigned s = lane; s < S; s += kWave) {
       const float e = expf(sc[h * S + s] - mx);
@@ -462,8 +452,7 @@ __global__ __launch_bounds__(kTA) void k_cross_attention_fast(const float* __res
     mx = fmaxf(fmaxf(fabsf(acc.x), fabsf(acc.y)), fmaxf(fabsf(acc.z), fabsf(acc.w)));
   }
   if (partial != nullptr) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, kWave));
+    mx = wave_max_f(mx);
     __syncthreads();
     if (lane == 0) red[wave] = mx;
     __syncthreads();
