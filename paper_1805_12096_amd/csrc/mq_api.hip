@@ -1095,6 +1095,19 @@ int mq_aan_layer_f32(const mq_aan_layer* P, const float* x, const float* g_prev,
     g1.partial = g5.partial = hpart;
     if (gemm_rows_partials(aan_ffn) > kAbsmaxPartials) g1.partial = nullptr;
     if (gemm_rows_partials(ffn) > kAbsmaxPartials) g5.partial = nullptr;
+    if (layer_rows_supported(M, S, d, aan_ffn, ffn, heads) && aligned(K, 16) && aligned(V, 16) && aligned(y, 16) &&
+        aligned(P->ln3.gamma, 16) && aligned(P->ln3.beta, 16) && !variant_named(8, M, 2 * d, 2 * d) && !variant_named(8, M, d, aan_ffn) &&
+        !variant_named(8, M, d, ffn)) {
+      // at most eight sentences: everything behind the first product is one launch, whose exchange buffers that product's
+      // launch fills -- in the space of the float intermediates from f on, and of the packed activations for H (32 rows of the
+      // widest input in 8 bit hold eight rows of floats)
+      unsigned* w = reinterpret_cast<unsigned*>(base + L.off_f);
+      const size_t row = M * d;
+      const LayerExchange e{w, w + row, w + 2 * row, w + 3 * row, w + 4 * row, reinterpret_cast<unsigned*>(qbuf), w + 5 * row, w + 6 * row};
+      const RowsFill fill{w, e.hid2, (unsigned)(6 * row + kLayerClaims) / 4, (unsigned)(M * ffn / 4)};
+      if ((rc = launch_gemm_rows_average(g_prev, x, t, g_out, g1, s, fill)) != MQ_OK) return rc;
+      return launch_layer_rows(*P, x, hid, K, V, M, S, heads, eps, e, y, s);
+    }
     if ((rc = launch_gemm_rows_average(g_prev, x, t, g_out, g1, s)) != MQ_OK) return rc;
     if ((rc = second(aan_ffn, P->aan_ffn2, f)) != MQ_OK) return rc;
     if ((rc = launch_gemm_rows_gate(x, f, args(P->aan_gate, 2 * d, 2 * d, 0, z), s)) != MQ_OK) return rc;

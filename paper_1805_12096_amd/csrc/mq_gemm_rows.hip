@@ -58,7 +58,7 @@ __device__ __forceinline__ uint32_t bytes_of4(const int (&q)[4], unsigned byte) 
 // w KW .. of K for all 32 rows, and the partial sums meet in LDS (see k_gemm_small).  Rows past M repeat row M - 1 (their
 // results are never stored), K elements past K are zero bytes as in a packed operand.
 template <int BITS, int IN, int KS, int CH, int NR>
-__global__ __launch_bounds__(KS * 64) void k_gemm_rows(const RowsParams p) {
+__global__ __launch_bounds__(KS * 64) void k_gemm_rows(const RowsParams p, const RowsFill fill) {
   constexpr int NPL = BITS == 16 ? 2 : 1, NACC = BITS == 16 ? 3 : 1;
   constexpr int NB = IN == kRowsPairGate ? 2 : 1;           // column blocks per workgroup: z1 and z2 of the same columns
   constexpr int KW = (CH * 8 + KS - 1) / KS;                // fragments of K per wave
@@ -139,6 +139,13 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_rows(const RowsParams p) {
   const bool given = p.scale != nullptr;
   const float s_given = *(given ? p.scale : p.sW);
   __builtin_amdgcn_sched_barrier(0);
+
+  if constexpr (IN == kRowsAverage) {
+    const unsigned step = (p.N + 31) / 32 * KS * 64;
+    const u4 unset = {kUnsetWord, kUnsetWord, kUnsetWord, kUnsetWord};
+    for (unsigned i = blockIdx.x * KS * 64 + tid; i < fill.na; i += step) reinterpret_cast<u4*>(fill.a)[i] = unset;
+    for (unsigned i = blockIdx.x * KS * 64 + tid; i < fill.nb; i += step) reinterpret_cast<u4*>(fill.b)[i] = unset;
+  }
 
   // ---- the input's rows, their maximum
   float mx = 0.f;
@@ -322,7 +329,7 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_rows(const RowsParams p) {
 }
 
 template <int BITS, int IN, int KS, int CH, int NR>
-int launch_rows(const RowsParams& p, hipStream_t s) {
+int launch_rows(const RowsParams& p, hipStream_t s, const RowsFill& fill) {
   constexpr int NPL = BITS == 16 ? 2 : 1, NB = IN == kRowsPairGate ? 2 : 1;
   constexpr size_t stage = (size_t)CH * 8 * NPL * 2 * (512 + 16), part = (size_t)KS * NB * 1024 * sizeof(int);
   constexpr size_t smem = stage + part > 150 * 1024 ? (stage > part ? stage : part) : stage + part;
@@ -336,23 +343,23 @@ int launch_rows(const RowsParams& p, hipStream_t s) {
     attr_done = true;
   }
   const unsigned grid = IN == kRowsPairGate ? p.K1 / 32 : (unsigned)PackedDims(BITS, p.N, p.K).nblocks;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(KS * 64), smem, s, p);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(KS * 64), smem, s, p, fill);
   return check_hip(hipGetLastError());
 }
 
 // Eight waves up to K = 1024; sixteen beyond (64 registers of input per lane: two rows of 2048 or one of 4096).  Few rows
 // take the form that holds one row per wave: the others would be converted for nothing.
 template <int BITS, int IN>
-int launch_rows_k(const RowsParams& p, hipStream_t s) {
-  auto by_rows = [&](auto few, auto many) { return p.M <= 8 ? few(p, s) : many(p, s); };
+int launch_rows_k(const RowsParams& p, hipStream_t s, const RowsFill& fill = {}) {
+  auto by_rows = [&](auto few, auto many) { return p.M <= 8 ? few(p, s, fill) : many(p, s, fill); };
   if constexpr (IN != kRowsPairGate)
     if (p.K <= 256) return by_rows(launch_rows<BITS, IN, 8, 1, 1>, launch_rows<BITS, IN, 8, 1, 4>);
   if (p.K <= 512) return by_rows(launch_rows<BITS, IN, 8, 2, 1>, launch_rows<BITS, IN, 8, 2, 4>);
   if (p.K <= 1024) return by_rows(launch_rows<BITS, IN, 8, 4, 1>, launch_rows<BITS, IN, 8, 4, 4>);
   if constexpr (IN == kRowsPlain || IN == kRowsPairGate) {
-    if (p.K <= 2048) return p.M <= 16 ? launch_rows<BITS, IN, 16, 8, 1>(p, s) : launch_rows<BITS, IN, 16, 8, 2>(p, s);
+    if (p.K <= 2048) return p.M <= 16 ? launch_rows<BITS, IN, 16, 8, 1>(p, s, fill) : launch_rows<BITS, IN, 16, 8, 2>(p, s, fill);
     if constexpr (BITS == 8 && IN == kRowsPlain)
-      if (p.K <= 4096 && p.M <= 16) return launch_rows<8, IN, 16, 16, 1>(p, s);
+      if (p.K <= 4096 && p.M <= 16) return launch_rows<8, IN, 16, 16, 1>(p, s, fill);
   }
   return MQ_ERR_UNSUPPORTED;
 }
@@ -397,11 +404,12 @@ int launch_gemm_rows(const float* A, const float* scale, const GemmArgs& a, hipS
   return a.bits == 16 ? launch_rows_k<16, kRowsPlain>(p, s) : launch_rows_k<8, kRowsPlain>(p, s);
 }
 
-int launch_gemm_rows_average(const float* g_prev, const float* x, int t, float* g, const GemmArgs& a, hipStream_t s) {
+int launch_gemm_rows_average(const float* g_prev, const float* x, int t, float* g, const GemmArgs& a, hipStream_t s,
+                             const RowsFill& fill) {
   if (!gemm_rows_glue_supported(a.M, a.K) || a.bits != 8) return MQ_ERR_UNSUPPORTED;
   RowsParams p = rows_params(a);
   p.a = g_prev; p.b = x; p.tm1 = (float)(t - 1); p.t = (float)t; p.side = g;
-  return launch_rows_k<8, kRowsAverage>(p, s);
+  return launch_rows_k<8, kRowsAverage>(p, s, fill);
 }
 
 int launch_gemm_rows_gate(const float* x, const float* f, const GemmArgs& a, hipStream_t s) {

@@ -123,10 +123,26 @@ int launch_gemm_rows(const float* A, const float* scale, const GemmArgs& a, hipS
 // the running average of (g_prev, x), also written to g; LN(h + r) gamma + beta, also written to y; and the pair [x | f]
 // into a product of 2 d columns whose result is mixed, Y[M x d] = sigmoid(z1) x + sigmoid(z2) f.
 bool gemm_rows_glue_supported(size_t M, size_t d);
-int launch_gemm_rows_average(const float* g_prev, const float* x, int t, float* g, const GemmArgs& a, hipStream_t s);
+// Words a launch fills with kUnsetWord for the next one's exchange (two runs of 16-byte pieces).
+constexpr unsigned kUnsetWord = 0x7FFFDEADu;      // a NaN no kernel publishes
+struct RowsFill {
+  unsigned *a, *b;
+  unsigned na, nb;
+};
+int launch_gemm_rows_average(const float* g_prev, const float* x, int t, float* g, const GemmArgs& a, hipStream_t s,
+                             const RowsFill& fill = {});
 int launch_gemm_rows_norm(const float* h, const float* r, const float* gamma, const float* beta, float eps, float* y,
                           const GemmArgs& a, hipStream_t s);
 int launch_gemm_rows_gate(const float* x, const float* f, const GemmArgs& a, hipStream_t s);
+// The decoder layer of at most eight sentences behind launch_gemm_rows_average, in one launch (mq_layer_rows.hip).  Exchange:
+// M x d words each (hid2 M x ffn), and one claim word per 32 columns of the widest product, all kUnsetWord when it starts.
+struct LayerExchange {
+  unsigned *f, *mix, *q, *ctx, *o, *hid2, *ff, *claim;
+};
+constexpr unsigned kLayerClaims = 128;
+bool layer_rows_supported(size_t M, size_t S, size_t d, size_t aan, size_t ffn, int heads);
+int launch_layer_rows(const mq_aan_layer& P, const float* x, const float* hid, const float* K, const float* V, size_t M, size_t S,
+                      int heads, float eps, const LayerExchange& e, float* y, hipStream_t s);
 // clear / nclear (optional): words of a later kernel that this one zeroes.
 int launch_quantize_pack(const float* x, size_t rows, size_t cols, int bits, const float* scale,
                          void* packed, hipStream_t s, unsigned* clear = nullptr, unsigned nclear = 0);

@@ -295,6 +295,62 @@ def test_decoder_layer_of_one_row_block_stage_by_stage(shape):
     test_decoder_layer_stage_by_stage(shape)
 
 
+@pytest.mark.parametrize("shape", [dict(M=1, d=256, ffn=64, aan_ffn=2048, S=1, heads=1),       # one head as wide as it may be
+                                   dict(M=8, d=256, ffn=2048, aan_ffn=64, S=64, heads=64),     # heads of four columns
+                                   dict(M=7, d=512, ffn=192, aan_ffn=320, S=100, heads=32),
+                                   dict(M=2, d=512, ffn=2048, aan_ffn=2048, S=33, heads=4),
+                                   dict(M=8, d=1024, ffn=4096, aan_ffn=4096, S=17, heads=16),
+                                   dict(M=3, d=1024, ffn=64, aan_ffn=1088, S=256, heads=16)])
+def test_decoder_layer_of_a_few_rows(shape):
+    # up to eight sentences: two launches, whose workgroups wait for each other's rows.  The bits of the launches stage by
+    # stage (and of the route that a named variant takes), also when y overwrites x, when no row comes within the time a
+    # workgroup waits (each then takes roles over and begins again), with NaN and infinities, and replayed.
+    from test_gpu_parity import launches
+    M, d, S, heads = (shape[k] for k in ("M", "d", "S", "heads"))
+    test_decoder_layer_stage_by_stage(shape)
+    c = workloads.config5_chained(M=M, layers=1, d=d, ffn=shape["ffn"], aan_ffn=shape["aan_ffn"], S=S, V=8, t=4, seed_extra=d)
+    layer = prepare_layer(c["layers"][0], d, shape["ffn"], shape["aan_ffn"])
+    K, V = (dev(a) for a in c["KV"][0])
+    x, gp = dev(c["x0"]), dev(c["g_prev"][0])
+    odd = x.clone()
+    odd[0, 5], odd[-1, -1] = float("inf"), float("nan")
+
+    def same(a, b):
+        return torch.equal(torch.nan_to_num(a, 7.5, 8.5, 9.5), torch.nan_to_num(b, 7.5, 8.5, 9.5))
+
+    try:
+        mq.mq_set_gemm_variant(1)
+        want, want_odd = run_layer(layer, x, gp, 4, K, V, heads), run_layer(layer, odd, gp, 4, K, V, heads)
+    finally:
+        mq.mq_set_gemm_variant(0)
+    for xs, w in ((x, want), (odd, want_odd)):
+        y, g = run_layer(layer, xs, gp, 4, K, V, heads)
+        assert same(y, w[0]) and same(g, w[1])
+    try:
+        mq.mq_set_barrier_timeout_us(0)
+        y, g = run_layer(layer, x, gp, 4, K, V, heads)
+        torch.cuda.synchronize()
+        assert torch.equal(y, want[0]) and torch.equal(g, want[1])
+    finally:
+        mq.mq_set_barrier_timeout_us(500000)
+    nb = mq.mq_aan_layer_ws_bytes(M, d, shape["ffn"], shape["aan_ffn"])
+    ws, io, g = torch.empty(nb, dtype=torch.uint8, device=DEV), x.clone(), torch.empty_like(x)
+
+    def call(stream):
+        mq.mq_aan_layer_f32(layer, io, gp, 4, K, V, M, S, heads, True, True, glue.LN_EPS, io, g, ws, nb, stream)
+
+    assert launches(call) == 2
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(torch.cuda.current_stream())
+    for _ in range(4):
+        io.copy_(x)
+        ws.fill_(0x3C)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(io, want[0]) and torch.equal(g, want[1])
+
+
 def test_decoder_layer_of_one_row_block_runs_the_variant_named():
     # the products of the layer that go through the packed products otherwise (wider than 1024) keep to a variant the
     # caller has forced or tuned, also up to 32 sentences, where one launch quantizes and multiplies: launches of the layer
