@@ -919,6 +919,7 @@ int launch_gemm_requant_fixed_i16(const GemmArgs& a, const float* s_fixed, void*
   GemmArgs b = a;
   b.s_out = const_cast<float*>(s_fixed);
   b.packed_out = packed_out;
+  if (gemm_small_requant_ahead(a.M, a.N)) return launch_gemm_small_requant_i16(b, s);
   // (measured against the 256 x 128 tile of the fastest plain product on one device in alternation, config 4's first
   // product: 136 us here, 143 us there -- its 192 accumulator registers leave this epilogue too few to work with)
   return launch_pp<16, 128, 128, 4, 2, 4, kPRequant>(b, s);

@@ -51,8 +51,8 @@ struct SmallParams {
   Tiles tiles;
   int dequant, relu;
   const float *sA, *sW, *bias;
-  float* Y;                  // with dequant == 0 the raw sums, int32
-  float* out_amax;
+  float* Y;                  // with dequant == 0 the raw sums, int32; with REQUANT the packed operand
+  float* out_amax;           // with REQUANT the multiplier
   float* partial;            // optional: max|y| of every workgroup
   unsigned amax_slots;       // words at out_amax the workgroups spread over (0 or 1: one)
 };
@@ -63,9 +63,14 @@ static_assert(sizeof(SmallParams) <= 128, "two cache lines");
 // tile takes four products into three accumulators (hh, hl + lh, ll); a wave's partial sum is their
 // recombination 2^16 hh + 2^8 mid + ll (mod 2^32), which adds up over the waves like the 8-bit sums, and the
 // plane offsets are corrected once at the end: + 128 (rowsum[m] + colsum[n]) - 16384 K.
-template <int BITS, int TMW, int KS, int KW>
+//
+// REQUANT (16 bit, one row block): the results go to memory once, as the packed operand of the next product, quantized with a
+// multiplier that was given.  The operands change places in the matrix instruction, so that a thread's four values are four
+// columns of a row, which are neighbours in a fragment.
+template <int BITS, int TMW, int KS, int KW, bool REQUANT = false>
 __global__ __launch_bounds__(KS * 64) void k_gemm_small(const SmallParams p) {
-  const int dequant = p.dequant;
+  static_assert(!REQUANT || (BITS == 16 && TMW == 1 && KS >= 4), "one form");
+  const int dequant = REQUANT ? 1 : p.dequant;
   constexpr int NPL = BITS == 16 ? 2 : 1;
   constexpr int NACC = BITS == 16 ? 3 : 1;
   extern __shared__ __attribute__((aligned(16))) int part[];      // [KS][TMW * 1024]
@@ -106,8 +111,8 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small(const SmallParams p) {
 
   // The partial sums meet in vectors of V rows, the widest that leaves every thread one: vector i of a thread holds rows
   // row_of(i) .. + V - 1 of column n.  16 bit: their sums and the column's are asked for here as well.
-  constexpr int kEach = TMW * 1024 / (KS * 64), V = kEach >= 4 ? 4 : kEach, NV = kEach / V;
-  static_assert(V >= 1 && NV * V * KS * 64 == TMW * 1024, "elements must divide over the threads");
+  constexpr int kEach = TMW * 1024 / (KS * 64), V = kEach >= 4 || REQUANT ? 4 : kEach, NV = REQUANT ? 1 : kEach / V;
+  static_assert(V >= 1 && (REQUANT || NV * V * KS * 64 == TMW * 1024), "elements must divide over the threads");
   typedef uint32_t Vec __attribute__((ext_vector_type(V)));
   auto row_of = [&](int i) -> unsigned {
     const int g = (tid + i * KS * 64) / 64 * V, mt = g / 16, r = g % 16;
@@ -115,7 +120,20 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small(const SmallParams p) {
   };
   uint32_t rs[BITS == 16 ? NV : 1][V];
   uint32_t cs = 0;
-  if constexpr (BITS == 16) {
+  // REQUANT: threads 0 .. 255 finish row lj of the block, columns q0 .. q0 + 3
+  const unsigned q0 = 8 * (wave % 4) + 4 * lh;
+  float s_given = 0.f, bias4[4];
+  if constexpr (REQUANT) {
+    const uint32_t* rowsum = reinterpret_cast<const uint32_t*>(p.qA + dA.plane_bytes());
+    const uint32_t* colsum = reinterpret_cast<const uint32_t*>(p.packedW + dW.plane_bytes());
+    s_given = *p.out_amax;
+    cs = rowsum[tile_m * 32 + lj];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      rs[0][t] = colsum[tile_n * 32 + q0 + t];
+      bias4[t] = (has_bias ? p.bias : some)[has_bias ? min(tile_n * 32 + q0 + t, p.N - 1) : 0u];
+    }
+  } else if constexpr (BITS == 16) {
     const uint32_t* rowsum = reinterpret_cast<const uint32_t*>(p.qA + dA.plane_bytes());
     const uint32_t* colsum = reinterpret_cast<const uint32_t*>(p.packedW + dW.plane_bytes());
     cs = colsum[n];                                                // (the sums cover the padded rows of both operands)
@@ -162,6 +180,13 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small(const SmallParams p) {
         if constexpr (BITS == 8) {
           acc[mt][0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(fa[mt][j][0]), as_v4i(fw[j][0]), acc[mt][0], 0, 0, 0);
         } else {
+          if constexpr (REQUANT) {
+            acc[mt][0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(fw[j][0]), as_v4i(fa[mt][j][0]), acc[mt][0], 0, 0, 0);
+            acc[mt][1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(fw[j][1]), as_v4i(fa[mt][j][0]), acc[mt][1], 0, 0, 0);
+            acc[mt][2] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(fw[j][1]), as_v4i(fa[mt][j][1]), acc[mt][2], 0, 0, 0);
+            acc[mt][1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(fw[j][0]), as_v4i(fa[mt][j][1]), acc[mt][1], 0, 0, 0);
+            continue;
+          }
           acc[mt][0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(fa[mt][j][0]), as_v4i(fw[j][0]), acc[mt][0], 0, 0, 0);
           acc[mt][1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(fa[mt][j][0]), as_v4i(fw[j][1]), acc[mt][1], 0, 0, 0);
           acc[mt][2] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(fa[mt][j][1]), as_v4i(fw[j][1]), acc[mt][2], 0, 0, 0);
@@ -175,6 +200,7 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small(const SmallParams p) {
   const uint32_t corr = 128u * cs - 16384u * p.K;
   float local_amax = 0.f;
   // partial sums of this wave, V consecutive rows at a time: vector e = group * 64 + lane, group = (mt * 16 + r) / V
+  // (REQUANT: registers are columns and lanes rows)
   Vec* mine = reinterpret_cast<Vec*>(part) + wave * (TMW * 1024 / V);
 #pragma unroll
   for (int mt = 0; mt < TMW; ++mt)
@@ -189,6 +215,48 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small(const SmallParams p) {
       mine[(mt * 16 + r) / V * 64 + lane] = v;
     }
   __syncthreads();
+
+  if constexpr (REQUANT) {
+    // (the padding is the value 0, as the quantizer writes it; the row sums the next product corrects with are of the values)
+    const PackedDims dO(16, p.M, p.N);
+    __shared__ int row_part[4][32];
+    if (wave < 4) {
+      Vec v = reinterpret_cast<const Vec*>(part)[tid];
+#pragma unroll
+      for (int w = 1; w < KS; ++w) v += reinterpret_cast<const Vec*>(part)[w * 256 + tid];      // mod 2^32
+      const unsigned m = tile_m * 32 + lj;
+      uint32_t hi = 0, lo = 0;
+      int row = 0;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const unsigned sum = v[t] + 128u * rs[0][t] + corr;
+        float y = fmaf((float)(int)sum, u, has_bias ? bias4[t] : 0.f);
+        if (p.relu) y = fmaxf(y, 0.0f);                          // NaN -> 0
+        const float r = rintf(__fmul_rn(y, s_given));
+        int q;
+        asm("v_cvt_i32_f32 %0, %1" : "=v"(q) : "v"(r));          // saturates, NaN -> 0
+        q = min(max(q, -32767), 32767);
+        if (m >= p.M || tile_n * 32 + q0 + t >= p.N) q = 0;
+        row += q;
+        hi |= (uint32_t)((q >> 8) & 0xFF) << (8 * t);
+        lo |= (uint32_t)((q & 0xFF) ^ 0x80) << (8 * t);
+      }
+      uint8_t* dst = reinterpret_cast<uint8_t*>(p.Y) + dO.frag_offset(tile_m, tile_n) + (lj + 32 * (q0 / 16)) * 16 + q0 % 16;
+      *reinterpret_cast<uint32_t*>(dst) = hi;
+      *reinterpret_cast<uint32_t*>(dst + kFragBytes) = lo;
+      if (tile_n + 1 == dW.nblocks && dO.kfrags > dW.nblocks) {  // the packed width is whole pairs of fragments
+        *reinterpret_cast<uint32_t*>(dst + 2 * kFragBytes) = 0u;
+        *reinterpret_cast<uint32_t*>(dst + 3 * kFragBytes) = 0x80808080u;
+      }
+      row += __shfl_xor(row, 32, 64);
+      if (lh == 0) row_part[wave][lj] = row;
+    }
+    __syncthreads();
+    if (tid < 32 && tile_m * 32 + tid < p.M)
+      atomicAdd(reinterpret_cast<int*>(reinterpret_cast<uint8_t*>(p.Y) + dO.plane_bytes()) + tile_m * 32 + tid,
+                row_part[0][tid] + row_part[1][tid] + row_part[2][tid] + row_part[3][tid]);
+    return;
+  }
 
   // Every thread adds up the KS partial sums of NV vectors.
 #pragma unroll
@@ -246,7 +314,7 @@ unsigned band_rows(size_t tiles, int tmw) {
   return rows < 1.5 ? 1u : (unsigned)(rows + 0.5);
 }
 
-template <int BITS, int TMW, int KS, int KW>
+template <int BITS, int TMW, int KS, int KW, bool REQUANT = false>
 int launch_small(const GemmArgs& a, int dequant, hipStream_t s) {
   constexpr size_t smem = (size_t)KS * TMW * 1024 * sizeof(int);
   static_assert(smem <= 128 * 1024, "LDS budget");
@@ -259,9 +327,13 @@ int launch_small(const GemmArgs& a, int dequant, hipStream_t s) {
   p.dequant = dequant; p.relu = a.relu;
   p.sA = a.sA; p.sW = a.sW; p.bias = a.bias; p.Y = dequant ? a.Y : reinterpret_cast<float*>(a.C);
   p.out_amax = a.out_amax; p.partial = a.partial; p.amax_slots = a.amax_slots;
+  if constexpr (REQUANT) {
+    p.Y = static_cast<float*>(a.packed_out);
+    p.out_amax = a.s_out;
+  }
   if (tiles_m * tiles_n > 0x7FFFFFFFull) return MQ_ERR_SHAPE;
   p.tiles = tiles_of(tiles_m, tiles_n, band_rows(tiles_m * tiles_n, TMW));
-  auto kern = k_gemm_small<BITS, TMW, KS, KW>;
+  auto kern = k_gemm_small<BITS, TMW, KS, KW, REQUANT>;
   static bool attr_done = false;
   if (!attr_done) {
     int rc = check_hip(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -462,6 +534,7 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small_f32(const SmallF32Params
   constexpr int kEach = TNW * 1024 / (KS * 64), V = kEach % 4 == 0 ? 4 : kEach % 2 == 0 ? 2 : 1, NV = kEach / V;
   static_assert(V >= 1 && NV * V * KS * 64 == TNW * 1024, "elements must divide over the threads");
   typedef uint32_t Vec __attribute__((ext_vector_type(V)));
+  // (REQUANT: registers are columns and lanes rows)
   Vec* mine = reinterpret_cast<Vec*>(part) + wave * (TNW * 1024 / V);
 #pragma unroll
   for (int c = 0; c < TNW; ++c)
@@ -638,6 +711,17 @@ int launch_gemm_small(const GemmArgs& a, Epilogue epi, hipStream_t s) {
   if (c.row_blocks == 2) return c.waves == 8 ? launch_small<8, 2, 8, 4>(a, dequant, s) : launch_small<8, 2, 4, 4>(a, dequant, s);
   if (c.waves == 4) return launch_small<8, 1, 4, 4>(a, dequant, s);
   return c.waves == 8 ? launch_small<8, 1, 8, 4>(a, dequant, s) : launch_small<8, 1, 16, 4>(a, dequant, s);
+}
+
+// The 16-bit product whose results are quantized with a given multiplier: packed_out, and its row sums (cleared before) by one
+// addition per workgroup and row.
+// Ahead of the 128 x 128 tiles up to six workgroups per compute unit.  16-bit block with fixed multipliers, 512 / 2048: 200 rows
+// 14.3 us, on tiles 19.2, 700 rows 21.7 and 23.5, 1001 rows (2048 workgroups) 24.1 and 24.9, 1300 30.3 and 27.8; 1024 / 4096: 200
+// rows 23.2 and 27.9, 500 rows (2048 workgroups) 33.7 and 32.9; 1000 / 1000: 900 rows 24.0 and 29.6, 1500 rows 31.7 and 33.9;
+// 700 / 600: 2500 rows (1501 workgroups) 29.0 and 31.0, 3500 rows 32.8 and 32.6; 300 / 3333: 500 rows (1680) 22.0 and 21.8.
+bool gemm_small_requant_ahead(size_t M, size_t N) { return one_block_workgroups(M, N) <= 6 * kCUs; }
+int launch_gemm_small_requant_i16(const GemmArgs& a, hipStream_t s) {
+  return one_block_workgroups(a.M, a.N) <= kCUs ? launch_small<16, 1, 8, 2, true>(a, 1, s) : launch_small<16, 1, 4, 2, true>(a, 1, s);
 }
 
 // Whether quantizing inside the product pays: few rows, K short enough that re-reading the fp32 rows once

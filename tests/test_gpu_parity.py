@@ -1756,6 +1756,36 @@ def test_ffn_int16_with_the_fixed_multiplier(M, d, f):
         assert np.array_equal(host(Y), o2["Y"])
 
 
+@pytest.mark.parametrize("M,N,K,relu,grid", [(1, 33, 1, False, (2, 512)),              # an odd number of fragments: padding
+                                             (33, 64, 70, True, (4, 512)), (255, 1024, 33, False, (256, 512)),
+                                             (257, 1000, 520, False, (288, 256)), (5, 4100, 129, True, (129, 512)),
+                                             (16384, 96, 5, False, (1536, 256)), (16385, 96, 5, False, (129, 512))])
+def test_requantizing_int16_product_shapes(M, N, K, relu, grid):
+    # split K with four or eight waves up to six workgroups per compute unit, tiles beyond: the bytes of the quantizer on the
+    # oracle's result (planes, padding, row sums), with values beyond the 16-bit range, infinities among the biases and none
+    p = workloads.random_problem(M + N + K, M, N, K)
+    sc, s_out = (torch.full((1,), v, dtype=torch.float32, device=DEV) for v in (1024.0, 5000.0))
+    pw = mq.prepare_weight(dev(p["Wt"]), 16, scale=sc)
+    qA = torch.empty(mq.mq_packed_bytes(16, M, K), dtype=torch.uint8, device=DEV)
+    mq.mq_quantize_pack_f32(dev(p["A"]), M, K, 16, sc, qA)
+    bias = np.random.default_rng(N).normal(0, 6, N).astype(np.float32)
+    bias[:2] = np.inf, -np.inf
+    got = torch.empty(mq.mq_packed_bytes(16, M, N), dtype=torch.uint8, device=DEV)
+    for b in (bias, None):
+        o = oracle.linear(p["A"], p["Wt"], 16, b, relu, sA=np.float32(1024.0), sW=np.float32(1024.0))
+        ref = torch.empty_like(got)
+        mq.mq_quantize_pack_f32(dev(o["Y"]), M, N, 16, s_out, ref)
+        got.fill_(0x5D)
+        db = None if b is None else dev(b)
+
+        def call(stream):
+            mq.mq_gemm_requant_fixed_packed_i16(qA, pw.packed, M, N, K, sc, sc, db, relu, s_out, got, stream)
+
+        grids = launched_grids(call)
+        assert torch.equal(got, ref)
+        assert tuple(grids[-1]) == grid
+
+
 def test_ffn_int16_fixed_multiplier_full_size_equals_oracle_on_all_rows():
     # the paper's 16-bit scheme at the benchmark's 8192 x 1024 x 4096, one call, every row against the oracle;
     # with 2^10 no 32-bit sum wraps (Section 4.2 chose the multiplier for that)
