@@ -253,9 +253,10 @@ int mq_gemm_requant_packed(const void* packedA, const void* packedW, size_t M, s
 /* The same result in ONE pass over the operands, for results small enough that
  * every 256 x 256 tile is resident on the chip at once (at most one tile per
  * compute unit; MQ_ERR_UNSUPPORTED beyond that, nothing computed).  The result is
- * cut into the smallest of 128 x 128, 256 x 128 and 256 x 256 tiles whose workgroups
- * are all resident, so it occupies more compute units than it has 256 x 256 tiles
- * (2048 x 2048: 256, not 64).  Each tile
+ * cut into the smallest of 32 x 32, 64 x 32, 128 x 32 and 128 x 64 pieces (the
+ * contraction split over a workgroup's waves) and 128 x 128, 256 x 128 and
+ * 256 x 256 tiles whose workgroups are all resident, so it occupies more compute
+ * units than it has 256 x 256 tiles (2048 x 2048: 256, not 64).  Each workgroup
  * keeps its sums in registers while all workgroups agree on max|y| through the
  * agreement area at the start of ws (2112 words, see "Single-pass kernels" at
  * the top), then quantizes and stores.  Two launches (clearing the area, the

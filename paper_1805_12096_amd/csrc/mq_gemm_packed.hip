@@ -883,12 +883,14 @@ int launch_gemm_requant_coop(const GemmArgs& a, float* s_out, void* packed_out, 
   b.barrier = barrier;
   b.s_out = s_out;
   b.packed_out = packed_out;
-  // The smallest tile whose workgroups are all resident at once: a workgroup's time is its tile's, so a result that
-  // leaves compute units idle with 256 x 256 tiles (1001 x 2048: 32 workgroups) is cut finer.  Measured on whole FFN blocks
-  // (the finer second product included): d = 512, f = 2048 600 rows 31.1 -> 20.1 us, 1001 rows 32.9 -> 22.7, 2048 rows
-  // 29.9 -> 26.3, 4096 rows 33.6 -> 30.3; d = 1024, f = 4096 600 rows 45.2 -> 35.5, 2048 rows 45.8 -> 39.4; d = 128, f = 4096
-  // 1001 rows 37.6 -> 22.2; 1 to 8192 rows of these, of 256 / 1024, 300 / 1100 and 1000 / 700: 0.57 to 0.99 of the time.
-  int rc = launch_coop<128, 128, 4, 2, 6>(b, s);
+  // Up to 128 x 64 of the result per compute unit K is split over a workgroup's waves (see k_gemm_small_agree); beyond, tiles.
+  int rc = launch_gemm_small_requant_agree(b, s);
+  if (rc != MQ_ERR_UNSUPPORTED) return rc;
+  // The smallest tile whose workgroups are all resident at once: a workgroup's time is its tile's, so a result that leaves
+  // compute units idle with 256 x 256 tiles is cut finer.  Measured on whole FFN blocks (the finer second product included):
+  // d = 512, f = 2048 2048 rows 29.9 -> 26.3 us, 4096 rows 33.6 -> 30.3; d = 1024, f = 4096 600 rows 45.2 -> 35.5, 2048 rows
+  // 45.8 -> 39.4; d = 128, f = 4096 1001 rows 37.6 -> 22.2.
+  rc = launch_coop<128, 128, 4, 2, 6>(b, s);
   if (rc == MQ_ERR_UNSUPPORTED) rc = launch_coop<256, 128, 4, 2, 6>(b, s);
   if (rc != MQ_ERR_UNSUPPORTED) return rc;
   static_assert(kBarrierSlots == 256, "single_pass_fits describes this last attempt: it assumes the tile and slot count");

@@ -345,6 +345,186 @@ int launch_small(const GemmArgs& a, int dequant, hipStream_t s) {
   return check_hip(hipGetLastError());
 }
 
+// The first product of the 8-bit block for few rows: relu?(A W + b), max|.| over the whole result, quant_int with 127 / max, in
+// one launch (see mq_grid_max.h; every workgroup is resident).  The tiles' form (k_gemm_pp) walks K behind a pipeline and gives
+// 128 x 128 of the result to a workgroup: up to a few hundred rows it leaves most of the chip idle.  Here K is split over the
+// waves as in k_gemm_small; a workgroup takes TMW row blocks, the fewest that fit the grid's one round, and keeps its values in
+// registers while the maxima travel.  The operands change places in the matrix instruction, so that a thread's four values are
+// neighbours in a fragment of the packed result.  TMW row blocks, NB column blocks of a workgroup: two column blocks share the
+// rows' reads (4 x 1 at 1001 rows would not fit the round, and reads 1.7 times as much per result).
+// Whole block on a prepared workspace, us, tiles and this: 512 / 2048: 64 rows 16.0 and 12.4, 200 rows 17.0 and 13.7, 500 rows 18.1
+// and 15.5, 1001 rows 20.4 and 18.4, 1024 rows 18.8 and 18.4; 1024 / 4096: 64 rows 19.2 and 14.0, 200 rows 21.0 and 17.3, 500
+// rows 25.2 and 23.2; 1000 / 1000: 1200 rows 24.0 and 21.4; 128 / 4096: 400 rows 16.7 and 16.8.
+struct AgreeParams {
+  const uint8_t *qA, *packedW;
+  unsigned M, N, K;
+  Tiles tiles;
+  int relu;
+  unsigned nclear;
+  const float *sA, *sW, *bias;
+  uint8_t* packed_out;
+  float* s_out;
+  unsigned* barrier;
+  unsigned* clear_words;     // optional: words of an earlier kernel's agreement, left zero
+  unsigned long long ticks;
+};
+
+template <int TMW, int NB>
+__global__ __launch_bounds__(512) void k_gemm_small_agree(const AgreeParams p) {
+  constexpr int KS = 8 / NB, KW = 4, NV = TMW * NB <= 2 ? 1 : TMW * NB / 2;      // a vector: four columns of a row
+  static_assert(NB == 1 || TMW == 4, "a round of vectors lies in one column block");
+  extern __shared__ __attribute__((aligned(16))) int part[];      // [NB][KS][TMW * 256] vectors
+  __shared__ float red[8];
+  const int tid = threadIdx.x, lane = tid % 64, lj = lane % 32, lh = lane / 32;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const PackedDims dA(8, p.M, p.K), dW(8, p.N, p.K), dO(8, p.M, p.N);
+  unsigned tile_m, tile_n;
+  coords_of(p.tiles, tile_m, tile_n);
+  const unsigned kfrags = (unsigned)dA.kfrags, per = (kfrags + KS - 1) / KS;
+  const unsigned k_part = wave % KS, block = min(tile_n * NB + wave / KS, (unsigned)dW.nblocks - 1);      // of this wave
+  const unsigned kb_begin = min(k_part * per, kfrags - 1), kb_end = min(k_part * per + per, kfrags);
+  const bool some_k = k_part * per < kfrags;
+  const uint8_t* a_src[TMW];
+#pragma unroll
+  for (int mt = 0; mt < TMW; ++mt) a_src[mt] = p.qA + dA.frag_offset(min(tile_m * TMW + mt, (unsigned)dA.nblocks - 1), 0) + lane * 16;
+  const uint8_t* w_src = p.packedW + dW.frag_offset(block, 0) + lane * 16;
+
+  // vector i of a thread: column block 2 i / TMW of the tile, row block (wave + 8 i) / 4 % TMW, row lj, columns q0 .. q0 + 3
+  const unsigned q0 = 8 * (wave % 4) + 4 * lh;
+  auto column = [&](int i) { return (tile_n * NB + (NB == 1 ? 0 : 2 * i / TMW)) * 32 + q0; };
+  auto row_block = [&](int i) { return tile_m * TMW + (wave + 8 * i) / 4 % TMW; };
+  const float* some = reinterpret_cast<const float*>(p.packedW);
+  const float s_a = *p.sA, s_w = *p.sW;
+  float bias[NB][4];
+#pragma unroll
+  for (int c = 0; c < NB; ++c)
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      bias[c][t] = (p.bias != nullptr ? p.bias : some)[p.bias != nullptr ? min((tile_n * NB + c) * 32 + q0 + t, p.N - 1) : 0u];
+
+  v16i acc[TMW];
+#pragma unroll
+  for (int mt = 0; mt < TMW; ++mt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[mt][r] = 0;
+  if (some_k)
+    for (unsigned kb0 = kb_begin; kb0 < kb_end; kb0 += KW) {
+      u4 fa[TMW][KW], fw[KW];
+#pragma unroll
+      for (int j = 0; j < KW; ++j) {
+        const unsigned kb = min(kb0 + j, kb_end - 1);
+        fw[j] = *reinterpret_cast<const u4*>(w_src + (size_t)kb * kFragBytes);
+#pragma unroll
+        for (int mt = 0; mt < TMW; ++mt) fa[mt][j] = *reinterpret_cast<const u4*>(a_src[mt] + (size_t)kb * kFragBytes);
+      }
+      __builtin_amdgcn_sched_barrier(0);                           // (see k_gemm_small)
+#pragma unroll
+      for (int j = 0; j < KW; ++j) {
+        fw[j] &= kb0 + j < kb_end ? ~0u : 0u;
+#pragma unroll
+        for (int mt = 0; mt < TMW; ++mt)
+          acc[mt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(fw[j]), as_v4i(fa[mt][j]), acc[mt], 0, 0, 0);
+      }
+    }
+  if (p.clear_words != nullptr && blockIdx.x == 0)
+    for (unsigned i = tid; i < p.nclear; i += 512) p.clear_words[i] = 0u;
+
+  typedef uint32_t Vec __attribute__((ext_vector_type(4)));
+  Vec* sums = reinterpret_cast<Vec*>(part);
+#pragma unroll
+  for (int mt = 0; mt < TMW; ++mt)
+#pragma unroll
+    for (int r = 0; r < 16; r += 4)
+      sums[wave * (TMW * 256) + (mt * 4 + r / 4) * 64 + lane] =
+          Vec{(unsigned)acc[mt][r], (unsigned)acc[mt][r + 1], (unsigned)acc[mt][r + 2], (unsigned)acc[mt][r + 3]};
+  __syncthreads();
+  const float u = __fdiv_rn(1.0f, __fmul_rn(s_a, s_w));
+  const bool active = TMW * NB > 1 || wave < 4;
+  float y[NV][4], top = 0.f;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const unsigned m = row_block(i) * 32 + lj, n0 = column(i);
+    const int c = NB == 1 ? 0 : 2 * i / TMW;
+    Vec v = {0u, 0u, 0u, 0u};
+    if (active)
+#pragma unroll
+      for (int w = 0; w < KS; ++w) v += sums[(c * KS + w) * (TMW * 256) + (tid + i * 512) % (TMW * 256)];      // mod 2^32
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      y[i][t] = fmaf((float)(int)v[t], u, p.bias != nullptr ? bias[c][t] : 0.f);
+      if (p.relu) y[i][t] = fmaxf(y[i][t], 0.0f);                  // NaN -> 0
+      if (!active || m >= p.M || n0 + t >= p.N) y[i][t] = 0.f;     // the padding is the value 0
+      top = fmaxf(top, fabsf(y[i][t]));
+    }
+  }
+  top = __uint_as_float(wave_max_u32(__float_as_uint(top)));
+  if (lane == 0) red[wave] = top;
+  __syncthreads();
+  if (wave == 0) {
+    if (lane == 0) {
+#pragma unroll
+      for (int w = 1; w < 8; ++w) top = fmaxf(top, red[w]);
+      grid_max_publish(p.barrier, top);
+    }
+    const float amax = grid_max_collect(p.barrier, p.ticks);
+    if (lane == 0) red[0] = amax;
+  }
+  __syncthreads();
+  const float amax = red[0], s2 = amax > 0.0f ? __fdiv_rn(127.0f, amax) : 1.0f;
+  if (active)
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const unsigned rb = row_block(i), cb = column(i) / 32;
+      if (rb >= dO.nblocks || cb >= dW.nblocks) continue;
+      int q[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const float r = rintf(__fmul_rn(y[i][t], s2));
+        asm("v_cvt_i32_f32 %0, %1" : "=v"(q[t]) : "v"(r));         // saturates, NaN -> 0
+        q[t] = min(max(q[t], -127), 127);
+      }
+      uint8_t* dst = p.packed_out + dO.frag_offset(rb, cb) + (lj + 32 * (q0 / 16)) * 16 + q0 % 16;
+      *reinterpret_cast<uint32_t*>(dst) = __builtin_amdgcn_perm((uint32_t)q[1], (uint32_t)q[0], 0x0c0c0400u) |
+                                          __builtin_amdgcn_perm((uint32_t)q[3], (uint32_t)q[2], 0x04000c0cu);
+      if (cb + 1 == dW.nblocks && dO.kfrags > dW.nblocks) *reinterpret_cast<uint32_t*>(dst + kFragBytes) = 0u;     // whole pairs
+    }
+  if (blockIdx.x == 0 && tid == 0) *p.s_out = grid_max_failed(p.barrier) ? __builtin_nanf("") : s2;
+}
+
+template <int TMW, int NB>
+int launch_agree(const GemmArgs& a, hipStream_t s) {
+  constexpr size_t smem = (size_t)8 * TMW * 4096;
+  static_assert(smem <= 128 * 1024, "LDS budget");
+  const PackedDims dA(8, a.M, a.K), dW(8, a.N, a.K);
+  const size_t tiles_m = (dA.nblocks + TMW - 1) / TMW, tiles_n = (dW.nblocks + NB - 1) / NB;
+  auto kern = k_gemm_small_agree<TMW, NB>;
+  static int max_blocks = -1;                   // workgroups the device can hold at once, asked once
+  if (max_blocks < 0) {
+    int rc = check_hip(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+    if (rc != MQ_OK) return rc;
+    int per_cu = 0, dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kern), 512, smem) != hipSuccess)
+      return MQ_ERR_HIP;
+    max_blocks = per_cu * cus;
+  }
+  if (tiles_m * tiles_n > (size_t)max_blocks || tiles_m * tiles_n > kBarrierSlots) return MQ_ERR_UNSUPPORTED;
+  if (a.barrier == nullptr) return MQ_ERR_NULL;
+  AgreeParams p{};
+  p.qA = static_cast<const uint8_t*>(a.qA);
+  p.packedW = static_cast<const uint8_t*>(a.packedW);
+  p.M = (unsigned)a.M; p.N = (unsigned)a.N; p.K = (unsigned)a.K;
+  p.tiles = tiles_of(tiles_m, tiles_n, band_rows(tiles_m * tiles_n, TMW / NB));
+  p.relu = a.relu; p.nclear = a.nclear;
+  p.sA = a.sA; p.sW = a.sW; p.bias = a.bias;
+  p.packed_out = static_cast<uint8_t*>(a.packed_out); p.s_out = a.s_out;
+  p.barrier = a.barrier; p.clear_words = a.clear_words;
+  p.ticks = barrier_timeout_ticks();
+  hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(512), smem, s, p);
+  return check_hip(hipGetLastError());
+}
 
 // quant_int fused into the operand fetch (Section 4.2: activations are quantized on every call): A comes as
 // fp32 rows, each lane loads the 16 floats of its fragment slot, multiplies by the multiplier, rounds to
@@ -722,6 +902,15 @@ int launch_gemm_small(const GemmArgs& a, Epilogue epi, hipStream_t s) {
 bool gemm_small_requant_ahead(size_t M, size_t N) { return one_block_workgroups(M, N) <= 6 * kCUs; }
 int launch_gemm_small_requant_i16(const GemmArgs& a, hipStream_t s) {
   return one_block_workgroups(a.M, a.N) <= kCUs ? launch_small<16, 1, 8, 2, true>(a, 1, s) : launch_small<16, 1, 4, 2, true>(a, 1, s);
+}
+
+// Product + bias (+ReLU) -> max|y| -> quant_int(y) for few rows, the smallest workgroups that fit one round of the grid;
+// MQ_ERR_UNSUPPORTED where none does.
+int launch_gemm_small_requant_agree(const GemmArgs& a, hipStream_t s) {
+  int rc = launch_agree<1, 1>(a, s);
+  if (rc == MQ_ERR_UNSUPPORTED) rc = launch_agree<2, 1>(a, s);
+  if (rc == MQ_ERR_UNSUPPORTED) rc = launch_agree<4, 1>(a, s);
+  return rc != MQ_ERR_UNSUPPORTED ? rc : launch_agree<4, 2>(a, s);
 }
 
 // Whether quantizing inside the product pays: few rows, K short enough that re-reading the fp32 rows once

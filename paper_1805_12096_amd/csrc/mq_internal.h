@@ -95,6 +95,7 @@ int launch_gemm_packed(const GemmArgs& a, Epilogue epi, hipStream_t s);
 // split-K kernel serves the product (and the array takes them all, kAbsmaxPartials), else 0 -- then out_amax has to be used.
 size_t gemm_packed_partials(const GemmArgs& a);
 // Split-K form for few rows (8 bit, raw or dequantizing epilogue); launch_gemm_packed's variant 10.
+int launch_gemm_small_requant_agree(const GemmArgs& a, hipStream_t s);
 bool gemm_small_requant_ahead(size_t M, size_t N);
 int launch_gemm_small_requant_i16(const GemmArgs& a, hipStream_t s);
 int launch_gemm_small(const GemmArgs& a, Epilogue epi, hipStream_t s);

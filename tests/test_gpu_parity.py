@@ -1575,6 +1575,38 @@ def test_single_pass_requantizing_product(shape):
         assert torch.equal(out, ref.packed)
 
 
+@pytest.mark.parametrize("M,N,K,grid", [(31, 33, 31, (2, 512)), (32, 8192, 70, (256, 512)), (33, 4100, 300, (129, 512)),
+                                        (200, 2000, 257, (252, 512)), (260, 2048, 1100, (192, 512)),
+                                        (1030, 1000, 64, (144, 512)), (2048, 1024, 96, (256, 512)),
+                                        (1001, 2050, 520, (136, 512)), (2048, 2048, 96, (256, 512))])
+def test_single_pass_requantizing_product_split_k(M, N, K, grid):
+    # the forms of the split-K kernel in the order of size and the first tiles behind them, with and without ReLU and bias, a
+    # NaN and infinities among the biases (max = inf: multiplier 0, every output 0)
+    p = workloads.random_problem(77 + M, M, N, K)
+    pw = mq.prepare_weight(dev(p["Wt"]), 8)
+    pa, s = gpu_quantize_pack(p["A"], 8)
+    nb = mq.mq_gemm_amax_ws_bytes(M, N)
+    ws = torch.full((nb,), 0xA5, dtype=torch.uint8, device=DEV)
+    out, s2 = torch.empty(mq.mq_packed_bytes(8, M, N), dtype=torch.uint8, device=DEV), torch.empty(1, dtype=torch.float32, device=DEV)
+    nan, inf = p["bias"].copy(), p["bias"].copy()
+    nan[N // 3], inf[N // 2] = np.nan, -np.inf
+    for bias, relu in ((p["bias"], True), (None, False), (nan, False), (inf, True), (inf, False)):
+        o = oracle.linear(p["A"], p["Wt"], 8, bias, relu)
+        os2 = oracle.scale_from_amax(oracle.absmax(o["Y"]), 8)
+        oq = oracle.quant_int(o["Y"], 8, os2)
+        ref = mq.prepare_weight(dev(oq.astype(np.float32)), 8, scale=torch.ones(1, dtype=torch.float32, device=DEV))
+        db = None if bias is None else dev(bias)
+        out.fill_(0x22)
+
+        def call(stream):
+            mq.mq_gemm_requant_single_packed(pa, pw.packed, M, N, K, s, pw.scale, db, relu, ws, nb, s2, out, stream)
+
+        grids = launched_grids(call)
+        assert host(s2)[0] == os2
+        assert torch.equal(out, ref.packed)
+        assert tuple(grids[-1]) == grid
+
+
 @pytest.mark.parametrize("shape", [(512, 768, 192), (300, 520, 256)])
 def test_single_pass_requantizing_product_special_bias(shape):
     # whole tiles + ReLU take the kernel whose re-quantization is a single rounding addition per element;
