@@ -10,8 +10,8 @@
 // store to everybody's registers, where a kernel boundary and the loads behind it cost 2.5 to 3).
 // Figures: at launch_layer_rows.
 //
-// Who does what, and why no wait is for ever.  Role r owns columns 32 r .. 32 r + 31 of each product that has them (role r < M
-// also sentence r's source attention, role 0 the last normalisation).  A workgroup claims the role of its block index when it
+// Who does what, and why no wait is for ever.  Role r owns columns 32 r .. 32 r + 31 of each product that has them (and the
+// source attention of every sentence for their heads; role 0 also the last normalisation).  A workgroup claims the role of its block index when it
 // starts.  If other kernels keep some workgroups of this one from starting, the others do not wait for them: one that has
 // polled in vain for a while (LayerParams::patience) looks for roles nobody has claimed, claims some, and begins again at the first phase with them
 // (everything it has published already it publishes again, the same words); a workgroup whose role is gone when it starts
@@ -137,8 +137,7 @@ __global__ __launch_bounds__(kLT) void k_layer_rows(const LayerParams p) {
   constexpr unsigned COLS = d / 4, SG = kLT / COLS;            // source attention: float4 columns, groups that share the positions
   __shared__ __attribute__((aligned(16))) uint8_t stage[kStage];
   __shared__ __attribute__((aligned(16))) int part[kLW * 2 * 256];
-  __shared__ float scores[4096];
-  __shared__ f4 att_part[SG > 1 ? kLT : 1];
+  __shared__ float scores[4096];                               // [kLW][heads of 32 columns][S]
   __shared__ float red[2][kLW];
   __shared__ unsigned owned[kLayerClaims], n_owned, claimed_own, some_left;
   int tid = threadIdx.x, lane = tid % 64, lj = lane % 32, lh = lane / 32;
@@ -380,83 +379,88 @@ __global__ __launch_bounds__(kLT) void k_layer_rows(const LayerParams p) {
         if (em < M) publish(p.q + em * d + r * 32 + lj, fmaf((float)sum, u, b));
       });
     }
-    // ---- source attention of the sentences whose roles are owned
-    if (ok && owns_below(M)) {
-      for_roles(M, [&](unsigned m) {
+    // ---- source attention: wave w serves sentence w, for the heads of the workgroup's columns only, on its own (with a
+    // sentence per workgroup instead its 1.8 us were the longest phase)
+    if (ok && narrow)
+      for_roles(nd, [&](unsigned r) {
         if (!ok) return;
-        const unsigned S = p.S, hs = p.head_shift, dh = 1u << hs, grp = dh / 4;
+        const unsigned S = p.S, hs = p.head_shift, dh = 1u << hs, grp = dh / 4, per = 64 / grp;      // positions a trip
+        const unsigned nh = hs >= 5 ? 1u : 32u >> hs, head0 = r * 32 >> hs;                          // heads here
         const float scale = __fdiv_rn(1.0f, sqrtf((float)dh));
-        const f4* K4 = reinterpret_cast<const f4*>(p.K + (size_t)m * S * d);
-        const f4* V4 = reinterpret_cast<const f4*>(p.V + (size_t)m * S * d);
-        const unsigned col = tid % COLS, sg = tid / COLS;
-        constexpr int kAhead = 8;
-        f4 kr[4][CD], va[kAhead], qr[CD];
-        auto keys = [&](unsigned s0) {
+        const f4* K4 = reinterpret_cast<const f4*>(p.K + (size_t)row * S * d);
+        const f4* V4 = reinterpret_cast<const f4*>(p.V + (size_t)row * S * d) + r * 8 + lane % 8;
+        const unsigned sg = lane / 8;                            // groups that share the positions of V
+        constexpr int kTrips = 8;
+        f4 kr[kTrips], va[kTrips], q[1];
+        auto keys = [&](unsigned head, unsigned s0) {
 #pragma unroll
-          for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int c = 0; c < CD; ++c) kr[u][c] = K4[(size_t)min(s0 + u * kLW, S - 1) * COLS + c * 64 + lane];
+          for (int u = 0; u < kTrips; ++u)
+            kr[u] = K4[(size_t)min(s0 + u * per + lane / grp, S - 1) * COLS + head * grp + (lane & (grp - 1))];
         };
-        keys(wave);
+        auto values = [&](unsigned s0) {
 #pragma unroll
-        for (int j = 0; j < kAhead; ++j) va[j] = V4[(size_t)min(sg + j * SG, S - 1) * COLS + col];
+          for (int j = 0; j < kTrips; ++j) va[j] = V4[(size_t)min(s0 + j * SG + sg % SG, S - 1) * COLS];
+        };
+        keys(head0, 0u);
+        values(0u);
         __builtin_amdgcn_sched_barrier(0);
-        ok = poll_row(p.q + (size_t)m * d, d, qr, patience);
-        ok = agree(ok, 0.f);
-        if (!ok) return;
-        for (unsigned s0 = wave; s0 < S; s0 += 4 * kLW) {
-          if (s0 != wave) keys(s0);
-          float a[4][CD];
+        const unsigned q_len = hs >= 5 ? dh : 32u;
+        const bool came = wave >= M || poll_row(p.q + (size_t)row * d + head0 * dh, q_len, q, patience);
+        if (came && wave < M) {
+          float* mine_sc = scores + wave * nh * S;
+          for (unsigned hh = 0; hh < nh; ++hh) {
+            f4 qr;
 #pragma unroll
-          for (int u = 0; u < 4; ++u)
+            for (int t = 0; t < 4; ++t) qr[t] = __shfl(q[0][t], hh * grp + (lane & (grp - 1)), kWave);
+            for (unsigned s0 = 0; s0 < S; s0 += kTrips * per) {
+              if (hh != 0 || s0 != 0) keys(head0 + hh, s0);
+              float a[kTrips][1];
 #pragma unroll
-            for (int c = 0; c < CD; ++c)
-              a[u][c] = fmaf(qr[c].x, kr[u][c].x, fmaf(qr[c].y, kr[u][c].y, fmaf(qr[c].z, kr[u][c].z, qr[c].w * kr[u][c].w)));
-          group_sums_f(a, grp);
-          if ((lane & (grp - 1)) == 0)
+              for (int u = 0; u < kTrips; ++u)
+                a[u][0] = fmaf(qr.x, kr[u].x, fmaf(qr.y, kr[u].y, fmaf(qr.z, kr[u].z, qr.w * kr[u].w)));
+              group_sums_f(a, grp);
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-              for (int c = 0; c < CD; ++c)
-                if (s0 + u * kLW < S) scores[((c * 256 + 4 * lane) >> hs) * S + s0 + u * kLW] = a[u][c] * scale;
-        }
-        __syncthreads();
-        for (unsigned h = wave; h < p.heads; h += kLW) {
-          float mx = -INFINITY;
-          for (unsigned s = lane; s < S; s += kWave) mx = fmaxf(mx, scores[h * S + s]);
-          mx = wave_max_f(mx);
-          float sum = 0.f;
-          for (unsigned s = lane; s < S; s += kWave) {
-            const float e = expf(scores[h * S + s] - mx);
-            scores[h * S + s] = e;
-            sum += e;
+              for (int u = 0; u < kTrips; ++u) {
+                const unsigned at = s0 + u * per + lane / grp;
+                if ((lane & (grp - 1)) == 0 && at < S) mine_sc[hh * S + at] = a[u][0] * scale;
+              }
+            }
+            float* sc = mine_sc + hh * S;
+            float mx = -INFINITY;
+            for (unsigned at = lane; at < S; at += kWave) mx = fmaxf(mx, sc[at]);
+            mx = wave_max_f(mx);
+            float sum = 0.f;
+            for (unsigned at = lane; at < S; at += kWave) {
+              const float e = expf(sc[at] - mx);
+              sc[at] = e;
+              sum += e;
+            }
+            const float inv = __fdiv_rn(1.0f, wave_sum_f(sum));
+            for (unsigned at = lane; at < S; at += kWave) sc[at] *= inv;
           }
-          const float inv = __fdiv_rn(1.0f, wave_sum_f(sum));
-          for (unsigned s = lane; s < S; s += kWave) scores[h * S + s] *= inv;
+          const float* sc = mine_sc + (hs >= 5 ? 0u : (4u * (lane % 8)) >> hs) * S;
+          f4 acc = {0.f, 0.f, 0.f, 0.f};
+          for (unsigned s0 = 0; s0 < S; s0 += kTrips * SG) {
+            if (s0 != 0) values(s0);
+#pragma unroll
+            for (int j = 0; j < kTrips; ++j) {
+              const unsigned at = s0 + j * SG + sg % SG;
+              const float w = sc[min(at, S - 1)];
+#pragma unroll
+              for (int t = 0; t < 4; ++t) acc[t] = at < S ? fmaf(w, va[j][t], acc[t]) : acc[t];
+            }
+          }
+          f4 ctx = acc;
+#pragma unroll
+          for (unsigned g = 1; g < SG; ++g)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) ctx[t] += __shfl(acc[t], g * 8 + lane % 8, kWave);
+          if (lane < 8)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) publish(p.ctx + row * d + r * 32 + 4 * lane + t, ctx[t]);
         }
-        __syncthreads();
-        const unsigned h = (4 * col) >> hs;
-        f4 acc = {0.f, 0.f, 0.f, 0.f};
-        auto add = [&](float w, const f4& v) {
-#pragma unroll
-          for (int t = 0; t < 4; ++t) acc[t] = fmaf(w, v[t], acc[t]);
-        };
-#pragma unroll
-        for (int j = 0; j < kAhead; ++j)
-          if (sg + j * SG < S) add(scores[h * S + sg + j * SG], va[j]);
-        for (unsigned s = sg + kAhead * SG; s < S; s += SG) add(scores[h * S + s], V4[(size_t)s * COLS + col]);
-        if constexpr (SG > 1) {
-          att_part[tid] = acc;
-          __syncthreads();
-          if (sg == 0)
-#pragma unroll
-            for (unsigned g = 1; g < SG; ++g) acc += att_part[g * COLS + col];
-        }
-        if (sg == 0)
-#pragma unroll
-          for (int t = 0; t < 4; ++t) publish(p.ctx + m * d + 4 * col + t, acc[t]);
+        ok = agree(came, 0.f);
       });
-    }
     // ---- o = Wo ctx
     if (ok && narrow) {
       f4 c[CD];
@@ -562,17 +566,18 @@ __global__ __launch_bounds__(kLT) void k_layer_rows(const LayerParams p) {
 
 }  // namespace
 
-// A layer of up to eight rows, microseconds in a captured graph, nine launches and two: 33.8 and 24.4 at 512 / 2048 and one
-// sentence of 25 words (eight sentences 36.0 and 29.9), 51.5 and 36.7 at 1024 / 4096 (54.5 and 43.0), 27.8 and 21.6 at
-// 256 / 1024.  Of the 19 us of this launch at one sentence 2.1 go by before the first rows are there, 1.0 to 1.5 for each of
-// seven exchanges, 1.8 in the attention, 0.6 to 1.3 for the quantization and product of a phase.  The widths are those with
+// A layer of up to eight rows, microseconds in a captured graph, nine launches and two: 33.8 and 23.3 at 512 / 2048 and one
+// sentence of 25 words (eight sentences 35.9 and 29.0), 51.6 and 32.9 at 1024 / 4096 (54.8 and 40.3), 28.1 and 21.3 at
+// 256 / 1024 (29.6 and 26.4).  Of the 18 us of this launch at one sentence 2.1 go by before the first rows are there, 0.8 to 1.7 for
+// each of seven exchanges, 1 in the attention, 0.6 to 1.3 for the quantization and product of a phase.  With the attention
+// of a sentence in one workgroup, all heads, it was 24.5 and 29.8, 35.4 and 43.2, 21.1 and 25.7.  The widths are those with
 // a vector of the row per lane and 256 registers of parameters ahead; the head widths and scores those of the attention kernel
-// this replaces; more rows than waves take the launches.
+// this replaces, with room for eight sentences' scores of 512 words; more rows than waves take the launches.
 bool layer_rows_supported(size_t M, size_t S, size_t d, size_t aan, size_t ffn, int heads) {
   if (M < 1 || M > (size_t)kLW || (d != 256 && d != 512 && d != 1024)) return false;
   const size_t widest = d == 1024 ? 4096 : 2048, dh = d / (size_t)heads;
   if (aan % 64 != 0 || ffn % 64 != 0 || aan > widest || ffn > widest || aan < 64 || ffn < 64) return false;
-  return d % (size_t)heads == 0 && (dh & (dh - 1)) == 0 && dh >= 4 && dh <= 256 && (size_t)heads * S <= 4096;
+  return S <= 512 && d % (size_t)heads == 0 && (dh & (dh - 1)) == 0 && dh >= 4 && dh <= 256 && (size_t)heads * S <= 4096;
 }
 
 int launch_layer_rows(const mq_aan_layer& P, const float* x, const float* hid, const float* K, const float* V, size_t M, size_t S,
