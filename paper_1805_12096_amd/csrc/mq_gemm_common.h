@@ -5,6 +5,7 @@
 #include <type_traits>
 
 #include "mq_internal.h"
+#include "mq_tiles.h"
 
 namespace mq {
 
@@ -40,28 +41,10 @@ struct Params {
 
 __device__ __forceinline__ v4i as_v4i(u4 v) { return __builtin_bit_cast(v4i, v); }
 
-// Block index -> tile.  Workgroups are dealt round-robin to the 8 XCDs, each
-// with its own L2; giving every XCD one contiguous run of tiles (n fastest)
-// makes the blocks that run together on an XCD share A row panels and the
-// parameter in that XCD's L2.
-__device__ __forceinline__ unsigned xcd_remap(unsigned bid, unsigned total) {
-  const unsigned q = total / 8, r = total % 8, x = bid % 8, idx = bid / 8;
-  return x * q + (x < r ? x : r) + idx;
-}
-
-// Tile coordinates of a block.  After the XCD remap, consecutive tile numbers
-// walk down a band of GM tile rows before moving to the next tile column, so
-// the ~32 blocks resident on one XCD cover a GM x (32 / GM) patch of the
-// result: each A row panel and each parameter panel they stream is then shared
-// by several of them in that XCD's L2 instead of being fetched once per block.
+// Tile coordinates of this workgroup, see mq_tiles.h.
 __device__ __forceinline__ void tile_coords(unsigned tiles_m, unsigned tiles_n, unsigned GM, unsigned& tile_m,
                                             unsigned& tile_n) {
-  const unsigned t = xcd_remap(blockIdx.x, gridDim.x);
-  const unsigned band = t / (GM * tiles_n), in_band = t % (GM * tiles_n);
-  const unsigned first = band * GM;
-  const unsigned rows = tiles_m - first < GM ? tiles_m - first : GM;
-  tile_m = first + in_band % rows;
-  tile_n = in_band / rows;
+  tile_at(blockIdx.x, gridDim.x, tiles_m, tiles_n, GM, tile_m, tile_n);
 }
 
 // max |y| over the workgroup's results -> the caller's word: block-wide maximum, then at most one atomic per

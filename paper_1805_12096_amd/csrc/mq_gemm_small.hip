@@ -12,36 +12,12 @@
 // sums meet in LDS.  Integer addition is exact, so the split changes no bit.
 // Both operands are in fragment order; a fragment is one coalesced 1 KB read
 // straight into the registers the matrix instruction takes.
-#include <cmath>
-
 #include "mq_gemm_common.h"
 #include "mq_grid_max.h"
 
 namespace mq {
 
 namespace {
-
-// Tile coordinates as in tile_coords, for kernels that last a few microseconds, where four integer divisions (100 clocks and
-// more each, one after the other) in front of the first load show: reciprocals from the host.  t / d = umulhi(t, ceil(2^32 / d))
-// for t, d < 2^16.
-struct Tiles {
-  unsigned total, m, n, band, by_band, by_rows, by_last;
-};
-Tiles tiles_of(size_t tiles_m, size_t tiles_n, unsigned band) {
-  auto inverse = [](size_t d) { return d <= 1 ? 0u : (unsigned)((((unsigned long long)1 << 32) + d - 1) / d); };
-  const size_t last = tiles_m % band;
-  return {(unsigned)(tiles_m * tiles_n), (unsigned)tiles_m, (unsigned)tiles_n, band, inverse(band * tiles_n), inverse(band),
-          inverse(last == 0 ? band : last)};
-}
-__device__ __forceinline__ void coords_of(const Tiles& c, unsigned& tile_m, unsigned& tile_n) {
-  if (c.total >= 1u << 16) return tile_coords(c.m, c.n, c.band, tile_m, tile_n);
-  auto over = [](unsigned t, unsigned inverse) { return inverse == 0u ? t : __umulhi(t, inverse); };
-  const unsigned t = xcd_remap(blockIdx.x, c.total);
-  const unsigned band = over(t, c.by_band), in_band = t - band * c.band * c.n, first = band * c.band;
-  const bool whole = first + c.band <= c.m;
-  tile_n = over(in_band, whole ? c.by_rows : c.by_last);
-  tile_m = first + in_band - tile_n * (whole ? c.band : c.m - first);
-}
 
 // Arguments of k_gemm_small: two cache lines, what the operands' addresses need in the first.  (Every line is a miss of its own
 // on each launch, about 0.15 us where the compiler puts it in front of the loads.)
@@ -80,7 +56,7 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small(const SmallParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const PackedDims dA(BITS, p.M, p.K), dW(BITS, p.N, p.K);
   unsigned tile_m, tile_n;
-  coords_of(p.tiles, tile_m, tile_n);
+  tile_at(blockIdx.x, p.tiles, tile_m, tile_n);
   const unsigned kfrags = (unsigned)dA.kfrags;
   const unsigned per = (kfrags + KS - 1) / KS;
   const unsigned kb_begin = wave * per;
@@ -306,14 +282,6 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small(const SmallParams p) {
   }
 }
 
-// Which tiles an XCD's share of the grid covers: `band` rows of tiles and as many columns as its workgroups fill, so that the
-// rows and columns its L2 has to take in are the fewest bytes (a tile has TMW times as many rows as columns).  With the columns of a row of tiles dealt over the XCDs instead, every L2 took in all of A: 1001 x 512 x 2048 in
-// 8 bit, quantizer included, 10.4 -> 9.3 us, in 16 bit 18.2 -> 15.4, 2000 x 300 x 1800 in 8 bit 15.2 -> 11.9.
-unsigned band_rows(size_t tiles, int tmw) {
-  const double rows = std::sqrt((double)((tiles + 7) / 8) / tmw);
-  return rows < 1.5 ? 1u : (unsigned)(rows + 0.5);
-}
-
 template <int BITS, int TMW, int KS, int KW, bool REQUANT = false>
 int launch_small(const GemmArgs& a, int dequant, hipStream_t s) {
   constexpr size_t smem = (size_t)KS * TMW * 1024 * sizeof(int);
@@ -332,7 +300,7 @@ int launch_small(const GemmArgs& a, int dequant, hipStream_t s) {
     p.out_amax = a.s_out;
   }
   if (tiles_m * tiles_n > 0x7FFFFFFFull) return MQ_ERR_SHAPE;
-  p.tiles = tiles_of(tiles_m, tiles_n, band_rows(tiles_m * tiles_n, TMW));
+  p.tiles = tiles_of(tiles_m, tiles_n, TMW);
   auto kern = k_gemm_small<BITS, TMW, KS, KW, REQUANT>;
   static bool attr_done = false;
   if (!attr_done) {
@@ -379,7 +347,7 @@ __global__ __launch_bounds__(512) void k_gemm_small_agree(const AgreeParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const PackedDims dA(8, p.M, p.K), dW(8, p.N, p.K), dO(8, p.M, p.N);
   unsigned tile_m, tile_n;
-  coords_of(p.tiles, tile_m, tile_n);
+  tile_at(blockIdx.x, p.tiles, tile_m, tile_n);
   const unsigned kfrags = (unsigned)dA.kfrags, per = (kfrags + KS - 1) / KS;
   const unsigned k_part = wave % KS, block = min(tile_n * NB + wave / KS, (unsigned)dW.nblocks - 1);      // of this wave
   const unsigned kb_begin = min(k_part * per, kfrags - 1), kb_end = min(k_part * per + per, kfrags);
@@ -516,7 +484,7 @@ int launch_agree(const GemmArgs& a, hipStream_t s) {
   p.qA = static_cast<const uint8_t*>(a.qA);
   p.packedW = static_cast<const uint8_t*>(a.packedW);
   p.M = (unsigned)a.M; p.N = (unsigned)a.N; p.K = (unsigned)a.K;
-  p.tiles = tiles_of(tiles_m, tiles_n, band_rows(tiles_m * tiles_n, TMW / NB));
+  p.tiles = tiles_of(tiles_m, tiles_n, TMW / NB);
   p.relu = a.relu; p.nclear = a.nclear;
   p.sA = a.sA; p.sW = a.sW; p.bias = a.bias;
   p.packed_out = static_cast<uint8_t*>(a.packed_out); p.s_out = a.s_out;

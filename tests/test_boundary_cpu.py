@@ -41,6 +41,37 @@ def test_imports_where_torch_lacks_its_private_stream_queries(lib):
     assert r.returncode == 0, r.stderr
 
 
+def test_every_tile_of_a_split_k_product_has_one_workgroup(tmp_path):
+    # the map from workgroups to tiles, compiled for the host: every tile once.  Small grids (reciprocals, all remainders of
+    # the bands), both sides of 2^16 tiles, and single rows of millions of columns (N up to 2^31), where a band is the one row
+    # however many tiles there are.
+    src, so = tmp_path / "tiles.cpp", tmp_path / "tiles.so"
+    src.write_text('#include "mq_tiles.h"\n#include <vector>\n'
+                   'extern "C" size_t missed(size_t m, size_t n, int aspect) {\n'
+                   '  const mq::Tiles t = mq::tiles_of(m, n, aspect);\n'
+                   '  std::vector<bool> seen(m * n);\n'
+                   '  size_t left = m * n;\n'
+                   '  for (size_t b = 0; b < m * n; ++b) {\n'
+                   '    unsigned i, j;\n'
+                   '    mq::tile_at((unsigned)b, t, i, j);\n'
+                   '    if (i < m && j < n && !seen[i * n + j]) { seen[i * n + j] = true; --left; }\n'
+                   '  }\n'
+                   '  return left;\n'
+                   '}\n')
+    csrc = os.path.join(ROOT, "paper_1805_12096_amd", "csrc")
+    r = subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                        "-I" + csrc, str(src), "-o", str(so)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    missed = ctypes.CDLL(str(so)).missed
+    missed.restype, missed.argtypes = ctypes.c_size_t, [ctypes.c_size_t, ctypes.c_size_t, ctypes.c_int]
+    shapes = [(m, n) for m in (1, 2, 3, 5, 8, 13, 32, 63) for n in (1, 2, 7, 16, 33, 64, 129)]
+    shapes += [(256, 256), (255, 257), (13, 5041), (13, 5042), (1, 65535), (1, 65536), (3000, 1000), (70001, 33)]
+    shapes += [(1, 5282863), (2, 5282864), (1, 1 << 25)]
+    for m, n in shapes:
+        for aspect in (1, 2, 4):
+            assert missed(m, n, aspect) == 0, (m, n, aspect)
+
+
 def test_version_and_status_strings(lib):
     assert mq.mq_version() >= 100
     seen = {mq.mq_status_string(i) for i in range(8)}
