@@ -696,6 +696,7 @@ int ffn_i8_run(const float* A, size_t M, size_t d, size_t f, const void* packedW
       rc = launch_clear_words(Q, kBarrierWords, s);
       if (rc != MQ_OK) return rc;
     }
+    g1.variant = gemm_fused_variant(g1);
     rc = launch_gemm_amax_partial(g1, part2, s);
     if (rc != MQ_OK) return rc;
     // second pass: the same sums again, quantized with the multiplier now known, stored as packed int8

@@ -788,14 +788,16 @@ int launch_pp_variant(const GemmArgs& a, int variant, hipStream_t s) {
 
 }  // namespace
 
-namespace {
 // Tile configuration of the fused 8-bit passes: the large tile when it fills the chip, else the small one.
-int fused_variant(const GemmArgs& a) {
+int gemm_fused_variant(const GemmArgs& a) {
+  if (a.variant > 0) return a.variant;
   int v = forced_variant();
   if (v <= 0) v = tuned_variant(8, a.M, a.N, a.K);
   if (v <= 0 || v == 2 || v > 9) v = ((a.M + 255) / 256) * ((a.N + 255) / 256) >= 200 ? 1 : 3;
   return v;
 }
+
+namespace {
 size_t tiles_of(int variant, size_t M, size_t N) {
   size_t bm = 256, bn = 256;
   switch (variant) {
@@ -816,12 +818,12 @@ size_t gemm_amax_partials(size_t M, size_t N) { return ((M + 127) / 128) * ((N +
 int launch_gemm_amax_partial(const GemmArgs& a, float* partials, hipStream_t s) {
   GemmArgs b = a;
   b.partial = partials;
-  return launch_pp_variant<8, kPAmax>(b, fused_variant(a), s);
+  return launch_pp_variant<8, kPAmax>(b, gemm_fused_variant(a), s);
 }
 
 int launch_gemm_requant(const GemmArgs& a, const float* partials, float* s_out, void* packed_out, hipStream_t s) {
   GemmArgs b = a;
-  const int v = fused_variant(a);
+  const int v = gemm_fused_variant(a);
   b.partial = const_cast<float*>(partials);
   b.npartial = (unsigned)tiles_of(v, a.M, a.N);     // what the amax pass wrote with the same variant
   b.s_out = s_out;
@@ -905,7 +907,7 @@ int launch_gemm_requant_fixed(const GemmArgs& a, const float* s_fixed, void* pac
   b.npartial = 0;
   b.s_out = const_cast<float*>(s_fixed);
   b.packed_out = packed_out;
-  return launch_pp_variant<8, kPRequant>(b, fused_variant(a), s);
+  return launch_pp_variant<8, kPRequant>(b, gemm_fused_variant(a), s);
 }
 
 // 16-bit product re-quantized with a fixed multiplier into packed 16-bit activations (planes + row sums).
@@ -986,16 +988,19 @@ int default_variant(const GemmArgs& a) {
 }
 
 int chosen_variant(const GemmArgs& a) {
+  if (a.variant > 0) return a.variant;
   int v = forced_variant();
   if (v <= 0) v = tuned_variant(a.bits, a.M, a.N, a.K);     // frozen by mq_autotune_gemm for this shape, or 0
   return v <= 0 ? default_variant(a) : v;
 }
 }  // namespace
 
-size_t gemm_packed_partials(const GemmArgs& a) {
-  if (chosen_variant(a) != (a.bits == 16 ? 6 : 10)) return 0;
+size_t gemm_packed_partials(GemmArgs& a) {
+  const int v = chosen_variant(a);
   const size_t n = gemm_small_partials(a.bits, a.M, a.N, a.K);
-  return n <= kAbsmaxPartials ? n : 0;
+  if (v != (a.bits == 16 ? 6 : 10) || n > kAbsmaxPartials) return 0;
+  a.variant = v;
+  return n;
 }
 
 int launch_gemm_packed(const GemmArgs& a, Epilogue epi, hipStream_t s) {

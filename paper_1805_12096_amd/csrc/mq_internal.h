@@ -85,6 +85,9 @@ struct GemmArgs {
   // dequantizing epilogue of the packed products: out_amax points to this many words (cleared by the caller),
   // workgroups spread their atomic maxima over them; the consumer takes the maximum of all.  0 = one word.
   unsigned amax_slots;
+  // packed products: the configuration, where more than one step of a call depends on it.  Looked up once and kept here, since
+  // another thread may force or tune one between two looks.  0 = the launcher looks it up.
+  int variant;
 };
 int launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s);
 void set_forced_variant(int v);
@@ -93,7 +96,8 @@ int forced_variant();
 int launch_gemm_packed(const GemmArgs& a, Epilogue epi, hipStream_t s);
 // How many maxima of |y| launch_gemm_packed with the dequantizing epilogue leaves at a.partial: one per workgroup where the
 // split-K kernel serves the product (and the array takes them all, kAbsmaxPartials), else 0 -- then out_amax has to be used.
-size_t gemm_packed_partials(const GemmArgs& a);
+// Settles a.variant where maxima are promised.
+size_t gemm_packed_partials(GemmArgs& a);
 // Split-K form for few rows (8 bit, raw or dequantizing epilogue); launch_gemm_packed's variant 10.
 int launch_gemm_small_requant_agree(const GemmArgs& a, hipStream_t s);
 bool gemm_small_requant_ahead(size_t M, size_t N);
@@ -168,6 +172,7 @@ int launch_quantize_pack_partials(const float* x, size_t rows, size_t cols, int 
 // Fused FFN pieces (8 bit): product + bias + ReLU reduced to per-tile abs-max partials, and the same
 // product re-quantized with the multiplier formed from those partials, written as packed activations.
 size_t gemm_amax_partials(size_t M, size_t N);
+int gemm_fused_variant(const GemmArgs& a);      // for a.variant of both passes
 int launch_gemm_amax_partial(const GemmArgs& a, float* partials, hipStream_t s);
 int launch_gemm_requant(const GemmArgs& a, const float* partials, float* s_out, void* packed_out, hipStream_t s);
 // Words of the grid-wide barrier of the single-pass kernels: eight copies of one slot per workgroup

@@ -1240,6 +1240,45 @@ def test_ffn_single_pass_and_two_pass_agree_with_oracle(M, d, f):
         mq.mq_set_ffn_single_pass(1)
 
 
+@pytest.mark.parametrize("bits,M,d,f", [(16, 70, 64, 600), (8, 700, 128, 600)])
+def test_a_variant_named_by_another_thread_changes_no_result(bits, M, d, f):
+    # Calls in which more than one launch depends on the product's configuration, while another thread forces one and takes it
+    # back: who leaves the maxima of the intermediate (16 bit: the split-K kernel one a workgroup, the tiles in words of their
+    # own) and how many there are (8 bit in two passes: one a tile) is settled once.
+    import threading
+    c = workloads.ffn(2 if bits == 8 else 4, M, d, f, 0.04, bits, seed_extra=M + f)
+    W1, W2 = (mq.prepare_weight(dev(c[n]), bits) for n in ("W1t", "W2t"))
+    A, b1, b2 = dev(c["A"]), dev(c["b1"]), dev(c["b2"])
+    call, need = (mq.mq_ffn_i8_f32, mq.mq_ffn_ws_bytes) if bits == 8 else (mq.mq_ffn_i16_f32, mq.mq_ffn_i16_ws_bytes)
+    nb = need(M, d, f)
+    ws = torch.full((nb,), 0x7F, dtype=torch.uint8, device=DEV)         # (words nobody wrote: 3.4e38 as a maximum)
+    Y, wrong = torch.empty((M, d), dtype=torch.float32, device=DEV), torch.zeros((), dtype=torch.int64, device=DEV)
+    args = (A, M, d, f, W1.packed, W1.scale, b1, W2.packed, W2.scale, b2, Y, ws, nb)
+    done = threading.Event()
+
+    def name_variants():
+        while not done.is_set():
+            mq.mq_set_gemm_variant(1)
+            mq.mq_set_gemm_variant(0)
+
+    other = threading.Thread(target=name_variants)
+    try:
+        mq.mq_set_ffn_single_pass(0)
+        call(*args)
+        want = Y.clone()
+        other.start()
+        for _ in range(3000):
+            call(*args)
+            wrong += (Y != want).any()
+    finally:
+        done.set()
+        if other.ident is not None:
+            other.join()
+        mq.mq_set_gemm_variant(0)
+        mq.mq_set_ffn_single_pass(1)
+    assert int(wrong) == 0
+
+
 @pytest.mark.parametrize("M,d,f", [(1, 1, 1), (37, 64, 200), (300, 256, 520), (2100, 512, 96)])
 def test_ffn_int16_one_call_matches_oracle_chain(M, d, f):
     c = workloads.ffn(4, M, d, f, 0.03, 16, seed_extra=M + d + 3 * f)
