@@ -67,6 +67,15 @@
  *     co-residency cannot be excluded, or switch the single-pass kernels off
  *     (mq_set_ffn_single_pass(0), mq_set_quantize_single_pass(0)): the two-pass forms
  *     give the same bits and wait for nothing.
+ *
+ * Workgroups that wait for each other's rows
+ *   mq_aan_layer_f32 of up to eight sentences is two launches where the shape allows
+ *   it (see there), and in the second a workgroup waits for rows that others compute.
+ *   It needs no co-residency and its results depend on no wait: a workgroup that has
+ *   waited 30 us in vain takes over the work of workgroups that have not started; after
+ *   two waits of 0.5 s (less with mq_set_barrier_timeout_us) with nothing left to take
+ *   over, one workgroup computes the whole layer and the others end.  What else is
+ *   running changes the time of the call only.
  */
 #ifndef MQ_H_
 #define MQ_H_
@@ -270,7 +279,8 @@ int mq_gemm_requant_packed(const void* packedA, const void* packedW, size_t M, s
  * the device holds at once (occupancy x compute units; 256 on MI355X).
  * mq_set_barrier_timeout_us changes the bound on the wait (default 500000, at
  * most 10^7; 0 makes every waiter give up at once, which is how the tests
- * reach the failure path without a kernel that hangs). */
+ * reach the failure path without a kernel that hangs).  In mq_aan_layer_f32 it
+ * bounds waits on which no result depends (see the top). */
 int mq_set_barrier_timeout_us(unsigned us);
 int mq_single_pass_fits(size_t M, size_t N, size_t resident);
 int mq_gemm_requant_single_packed(const void* packedA, const void* packedW, size_t M, size_t N, size_t K,
@@ -564,7 +574,14 @@ typedef struct mq_aan_layer {
  * use_ffn / use_gate = 0 give the "-ffn" / "-gate" variants of Table 2.
  * ws: device, 256-byte aligned, mq_aan_layer_ws_bytes bytes, contents irrelevant.
  * Only enqueues.  g_out may be g_prev itself (the average is then updated in
- * place); apart from that y and g_out must not alias x, g_prev or each other. */
+ * place); apart from that y and g_out must not alias x, g_prev or each other.
+ * Up to 8 sentences are two launches, the second with workgroups that wait for
+ * each other's rows (see the top), if use_ffn and use_gate are on, d is 256, 512
+ * or 1024, ffn and aan_ffn are multiples of 64 up to 2048 (4096 at d = 1024), a
+ * head has 4 to 256 columns, a power of two, S <= 512 and heads S <= 4096, K, V, y,
+ * g_prev and the normalisations' vectors are 16-byte aligned, g_out is not g_prev
+ * and no variant is named for the shapes (mq_set_gemm_variant, mq_autotune_gemm).
+ * Otherwise nothing waits inside a launch.  The bits are the same. */
 size_t mq_aan_layer_ws_bytes(size_t M, size_t d, size_t ffn, size_t aan_ffn);
 int mq_aan_layer_f32(const mq_aan_layer* P, const float* x, const float* g_prev, int t, const float* K,
                      const float* V, size_t M, size_t S, int heads, int use_ffn, int use_gate, float eps,

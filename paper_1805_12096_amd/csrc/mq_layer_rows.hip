@@ -16,7 +16,8 @@
 // polled in vain for a while (LayerParams::patience) looks for roles nobody has claimed, claims some, and begins again at the first phase with them
 // (everything it has published already it publishes again, the same words); a workgroup whose role is gone when it starts
 // ends at once.  So every role belongs to a workgroup that runs, phases only wait for phases before them, and the grid drains
-// under any residency.  (A limit of two seconds bounds the waits all the same; y is NaN then.)
+// under any residency.  The waits are bounded all the same (mq_set_barrier_timeout_us, half a second at most), and no result
+// hangs on one: a workgroup that has waited so long twice ends, but for role 0's, which then does every role itself.
 //
 // Arithmetic and its order are those of the kernels this replaces (mq_gemm_rows.hip, mq_glue.hip): the same bits.
 #include "mq_gemm_common.h"
@@ -33,6 +34,8 @@ typedef unsigned long long u64;
 constexpr int kLW = 8;                         // waves; wave w holds row w
 constexpr int kLT = kLW * 64;
 constexpr unsigned kTake = 4;                  // roles taken over at a time
+constexpr unsigned kTries = 2;                 // passes that wait with every role claimed
+constexpr unsigned kLongest = 50000000u;       // half a second of the 100 MHz wall clock
 constexpr int kHalf8 = 8 * 16 + 16, kFrag8 = 2 * kHalf8;      // a staged fragment: two K halves of eight rows, 16 bytes each
 
 struct LayerParams {
@@ -52,7 +55,7 @@ struct LayerParams {
   const float *gamma2, *beta2, *gamma3, *beta3;
   float* y;
   float eps;
-  unsigned patience, heads;
+  unsigned patience, limit, heads;                               // ticks before roles are taken over, ticks of a wait
 };
 
 __device__ __forceinline__ uint32_t bytes_of4(const int (&q)[4]) {
@@ -145,7 +148,6 @@ __global__ __launch_bounds__(kLT) void k_layer_rows(const LayerParams p) {
   const unsigned M = p.M, nf = p.ffn / 32;
   unsigned row = min(wave, M - 1);
   const unsigned role0 = blockIdx.x;
-  const unsigned long long start = wall_clock64();
   // fragments of a parameter's column block: wave w holds K slices w KW .. w KW + KW - 1
   auto fetch = [&](auto& w, const uint8_t* packed, unsigned block, unsigned K) {
     constexpr int KW = sizeof(w) / sizeof(u4);
@@ -527,34 +529,43 @@ __global__ __launch_bounds__(kLT) void k_layer_rows(const LayerParams p) {
     return ok;
   };
   if (pass(std::true_type{})) return;
-  const unsigned long long hard = 200000000ull;                  // two seconds
+  unsigned tries = 0;                                            // passes begun with every role claimed
   do {
     // Some row did not come.  Roles nobody has claimed are taken over and everything begins again; once all are claimed it
-    // is only a matter of time.
-    if (__syncthreads_or(wall_clock64() - start >= hard)) {
-      bool writer = false;
-      for (unsigned i = 0; i < n_owned; ++i) writer = writer || owned[i] == 0;
+    // is a matter of time, and of kTries passes that wait for it: one may find its time gone because the process was not
+    // running, the next begins its own.  After those role 0's workgroup does the whole layer, which waits for nobody, and
+    // the others end.
+    __syncthreads();
+    if (tries > kTries) {                                        // (its own stores did not come back to it)
       const float nan = __builtin_nanf("");
-      if (writer && wave < M)
+      if (wave < M)
 #pragma unroll
         for (int c = 0; c < CD; ++c) reinterpret_cast<f4*>(p.y + (size_t)row * d)[c * 64 + lane] = f4{nan, nan, nan, nan};
       return;
     }
     if (tid == 0) {
       unsigned taken = 0, left = 0;
-      for (unsigned r = 0; r < p.roles; ++r) {
-        if (__hip_atomic_load(p.claim + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != kUnsetWord) continue;
-        if (taken < kTake && __hip_atomic_exchange(p.claim + r, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kUnsetWord)
-          owned[n_owned + taken++] = r;
-        else
-          left = 1;
+      if (tries < kTries) {
+        for (unsigned r = 0; r < p.roles; ++r) {
+          if (__hip_atomic_load(p.claim + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != kUnsetWord) continue;
+          if (taken < kTake && __hip_atomic_exchange(p.claim + r, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kUnsetWord)
+            owned[n_owned + taken++] = r;
+          else
+            left = 1;
+        }
+        n_owned += taken;
+      } else {
+        bool writer = false;
+        for (unsigned i = 0; i < n_owned; ++i) writer = writer || owned[i] == 0;
+        n_owned = writer ? p.roles : 0;
+        for (unsigned r = 0; r < n_owned; ++r) owned[r] = r;
       }
-      n_owned += taken;
       some_left = left;
     }
     __syncthreads();
     count = __builtin_amdgcn_readfirstlane(n_owned);
-    if (__builtin_amdgcn_readfirstlane(some_left) == 0u) patience = 5000000u;      // 50 ms a try
+    if (count == 0) return;
+    if (__builtin_amdgcn_readfirstlane(some_left) == 0u) patience = tries++ < kTries ? p.limit : kLongest;
     // (a new value each time for the compiler, or it keeps every phase's addresses in registers across the loop)
     asm volatile("" : "+v"(tid));
     lane = tid % 64; lj = lane % 32; lh = lane / 32;
@@ -598,6 +609,7 @@ int launch_layer_rows(const mq_aan_layer& P, const float* x, const float* hid, c
   p.roles = nf > nd ? nf : nd;
   const unsigned long long limit = barrier_timeout_ticks();
   p.patience = limit < 3000 ? (unsigned)limit : 3000u;           // 30 us
+  p.limit = limit < kLongest ? (unsigned)limit : kLongest;
   const dim3 grid(p.roles), block(kLT);
   if (P.d == 256) hipLaunchKernelGGL((k_layer_rows<1, 8>), grid, block, 0, s, p);
   else if (P.d == 512) hipLaunchKernelGGL((k_layer_rows<2, 8>), grid, block, 0, s, p);
