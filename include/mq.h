@@ -75,7 +75,8 @@
  *   waited 30 us in vain takes over the work of workgroups that have not started; after
  *   two waits of 0.5 s (less with mq_set_barrier_timeout_us) with nothing left to take
  *   over, one workgroup computes the whole layer and the others end.  What else is
- *   running changes the time of the call only.
+ *   running changes the time of the call only.  mq_set_ffn_single_pass(0) switches this
+ *   form off as well: the launches in its place give the same bits.
  */
 #ifndef MQ_H_
 #define MQ_H_
@@ -435,8 +436,8 @@ size_t mq_ffn_ws_bytes(size_t M, size_t d, size_t f);
  * result is small enough for one tile per resident workgroup (M f <= 256 x 256 x
  * the number of compute units), the two passes become ONE launch:
  * the sums wait in registers while the grid agrees on max|H| (four launches).
- * mq_set_ffn_single_pass(0) switches that off (two passes always); results are
- * identical either way.
+ * mq_set_ffn_single_pass(0) switches that off (two passes always), and with it the
+ * form of mq_aan_layer_f32 whose workgroups wait; results are identical either way.
  *   A: device float [M x d], 16-byte aligned.  packedW1: 8-bit packed [f x d];
  *   packedW2: 8-bit packed [d x f]; sW1, sW2: their multipliers (device float[1]);
  *   b1: device float [f] or NULL; b2: device float [d] or NULL; Y: device float [M x d];
@@ -579,8 +580,9 @@ typedef struct mq_aan_layer {
  * each other's rows (see the top), if use_ffn and use_gate are on, d is 256, 512
  * or 1024, ffn and aan_ffn are multiples of 64 up to 2048 (4096 at d = 1024), a
  * head has 4 to 256 columns, a power of two, S <= 512 and heads S <= 4096, K, V, y,
- * g_prev and the normalisations' vectors are 16-byte aligned, g_out is not g_prev
- * and no variant is named for the shapes (mq_set_gemm_variant, mq_autotune_gemm).
+ * g_prev and the normalisations' vectors are 16-byte aligned, g_out is not g_prev,
+ * no variant is named for the shapes (mq_set_gemm_variant, mq_autotune_gemm) and
+ * mq_set_ffn_single_pass(0) has not switched it off.
  * Otherwise nothing waits inside a launch.  The bits are the same. */
 size_t mq_aan_layer_ws_bytes(size_t M, size_t d, size_t ffn, size_t aan_ffn);
 int mq_aan_layer_f32(const mq_aan_layer* P, const float* x, const float* g_prev, int t, const float* K,

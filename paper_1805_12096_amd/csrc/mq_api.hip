@@ -1096,10 +1096,10 @@ int mq_aan_layer_f32(const mq_aan_layer* P, const float* x, const float* g_prev,
     g1.partial = g5.partial = hpart;
     if (gemm_rows_partials(aan_ffn) > kAbsmaxPartials) g1.partial = nullptr;
     if (gemm_rows_partials(ffn) > kAbsmaxPartials) g5.partial = nullptr;
-    if (layer_rows_supported(M, S, d, aan_ffn, ffn, heads) && aligned(K, 16) && aligned(V, 16) && aligned(y, 16) &&
+    if (g_ffn_single_pass && layer_rows_supported(M, S, d, aan_ffn, ffn, heads) && aligned(K, 16) && aligned(V, 16) && aligned(y, 16) &&
         aligned(P->ln3.gamma, 16) && aligned(P->ln3.beta, 16) && !variant_named(8, M, 2 * d, 2 * d) && !variant_named(8, M, d, aan_ffn) &&
         !variant_named(8, M, d, ffn)) {
-      // at most eight sentences: everything behind the first product is one launch, whose exchange buffers that product's
+      // at most eight sentences, kernels that wait not switched off: everything behind the first product is one launch, whose exchange buffers that product's
       // launch fills -- in the space of the float intermediates from f on, and of the packed activations for H (32 rows of the
       // widest input in 8 bit hold eight rows of floats)
       unsigned* w = reinterpret_cast<unsigned*>(base + L.off_f);

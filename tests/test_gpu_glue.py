@@ -344,6 +344,13 @@ def test_decoder_layer_of_a_few_rows(shape):
         mq.mq_aan_layer_f32(layer, io, gp, 4, K, V, M, S, heads, True, True, glue.LN_EPS, io, g, ws, nb, stream)
 
     assert launches(call) == (2 if S <= 512 else 9)
+    try:
+        mq.mq_set_ffn_single_pass(0)                     # kernels that wait are switched off: the same bits in launches
+        assert launches(call) == 9
+        y, g0 = run_layer(layer, x, gp, 4, K, V, heads)
+        assert torch.equal(y, want[0]) and torch.equal(g0, want[1])
+    finally:
+        mq.mq_set_ffn_single_pass(1)
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         call(torch.cuda.current_stream())
