@@ -579,9 +579,10 @@ typedef struct mq_aan_layer {
  * Up to 8 sentences are two launches, the second with workgroups that wait for
  * each other's rows (see the top), if use_ffn and use_gate are on, d is 256, 512
  * or 1024, ffn and aan_ffn are multiples of 64 up to 2048 (4096 at d = 1024), a
- * head has 4 to 256 columns, a power of two, S <= 512 and heads S <= 4096, K, V, y,
- * g_prev and the normalisations' vectors are 16-byte aligned, g_out is not g_prev,
- * no variant is named for the shapes (mq_set_gemm_variant, mq_autotune_gemm) and
+ * head has 4 to 256 columns, a power of two, S <= 512 and heads S <= 4096 (less
+ * where the launches are faster: long sources of wide heads), K, V, y, g_prev and
+ * the normalisations' vectors are 16-byte aligned, g_out is not g_prev, no variant
+ * is named for the shapes (mq_set_gemm_variant, mq_autotune_gemm) and
  * mq_set_ffn_single_pass(0) has not switched it off.
  * Otherwise nothing waits inside a launch.  The bits are the same. */
 size_t mq_aan_layer_ws_bytes(size_t M, size_t d, size_t ffn, size_t aan_ffn);

@@ -588,7 +588,19 @@ bool layer_rows_supported(size_t M, size_t S, size_t d, size_t aan, size_t ffn, 
   if (M < 1 || M > (size_t)kLW || (d != 256 && d != 512 && d != 1024)) return false;
   const size_t widest = d == 1024 ? 4096 : 2048, dh = d / (size_t)heads;
   if (aan % 64 != 0 || ffn % 64 != 0 || aan > widest || ffn > widest || aan < 64 || ffn < 64) return false;
-  return S <= 512 && d % (size_t)heads == 0 && (dh & (dh - 1)) == 0 && dh >= 4 && dh <= 256 && (size_t)heads * S <= 4096;
+  if (S > 512 || d % (size_t)heads != 0 || (dh & (dh - 1)) != 0 || dh < 4 || dh > 256 || (size_t)heads * S > 4096) return false;
+  // What the launches cost more, in microseconds (more with wide inner products, less with many rows), against what the
+  // attention costs more here.  One wave walks through a sentence's positions for its 32 columns: a head wider than those has
+  // its keys read once per 32 columns, narrower ones come one after the other, where the attention launch spreads a sentence
+  // over a workgroup.  Nine launches and two, us: eight sentences of 512 / 2048 with heads of 128 columns, 192 words 43.8 and 41.9,
+  // 256 words 46.1 and 47.4; of 256 columns, 64 words 39.0 and 37.3, 96 words 40.4 and 42.0, 256 words 47.1 and 68.6; of 256 /
+  // 1024 with one head, 32 words 29.1 and 28.8, 48 words 29.7 and 30.8; of 256 / 256 with heads of 64, 192 words 31.0 and 30.5,
+  // 320 words 33.9 and 35.0; of 4, 8 words 29.1 and 33.1; one sentence of 512 / 2048 with heads of 64, 512 words 50.5 and 39.6;
+  // of 1024 / 4096 with heads of 256, 192 words 65.2 and 57.8, eight sentences 69.6 and 72.2.
+  const float launches = 1.0f + (float)(aan + ffn) / 700.0f + 0.5f * (float)(kLW - (int)M);
+  constexpr float kPosition[3][3] = {{0.009f, 0.038f, 0.12f}, {0.009f, 0.035f, 0.105f}, {0.009f, 0.024f, 0.085f}};      // wide heads
+  const float attention = dh >= 64 ? kPosition[d / 512][dh / 128] * (float)S : (32.0f / (float)dh - 1.0f) * 240.0f / (float)d - 0.16f * (float)S / (float)dh;
+  return attention <= launches;
 }
 
 int launch_layer_rows(const mq_aan_layer& P, const float* x, const float* hid, const float* K, const float* V, size_t M, size_t S,
@@ -608,7 +620,10 @@ int launch_layer_rows(const mq_aan_layer& P, const float* x, const float* hid, c
   const unsigned nd = (unsigned)P.d / 32, nf = (unsigned)P.ffn / 32;
   p.roles = nf > nd ? nf : nd;
   const unsigned long long limit = barrier_timeout_ticks();
-  p.patience = limit < 3000 ? (unsigned)limit : 3000u;           // 30 us
+  // 30 us, and what the attention may take (without it the workgroups that have no part in it began again in the meantime:
+  // one sentence of 1024 / 4096, 192 words, heads of 256 columns 74.8 us, with it 57.8)
+  const unsigned soon = 3000u + (unsigned)(S * (size_t)P.d / (size_t)heads / 8);
+  p.patience = limit < soon ? (unsigned)limit : soon;
   p.limit = limit < kLongest ? (unsigned)limit : kLongest;
   const dim3 grid(p.roles), block(kLT);
   if (P.d == 256) hipLaunchKernelGGL((k_layer_rows<1, 8>), grid, block, 0, s, p);

@@ -301,8 +301,13 @@ def test_decoder_layer_of_one_row_block_stage_by_stage(shape):
                                    dict(M=2, d=512, ffn=2048, aan_ffn=2048, S=33, heads=4),
                                    dict(M=8, d=1024, ffn=4096, aan_ffn=4096, S=17, heads=16),
                                    dict(M=3, d=1024, ffn=64, aan_ffn=1088, S=256, heads=16),
-                                   dict(M=8, d=512, ffn=64, aan_ffn=64, S=512, heads=2),       # the longest source
-                                   dict(M=1, d=512, ffn=64, aan_ffn=64, S=513, heads=4)])      # the launches again
+                                   dict(M=1, d=512, ffn=2048, aan_ffn=2048, S=512, heads=8),   # the longest source
+                                   dict(M=1, d=1024, ffn=4096, aan_ffn=4096, S=190, heads=4),  # ... of the widest heads
+                                   # where nine launches are ahead (eight sentences of 256 words, two heads: 47.1 us and 68.6)
+                                   dict(M=1, d=1024, ffn=4096, aan_ffn=4096, S=191, heads=4, launches=9),
+                                   dict(M=8, d=512, ffn=64, aan_ffn=64, S=512, heads=2, launches=9),
+                                   dict(M=8, d=256, ffn=256, aan_ffn=256, S=8, heads=64, launches=9),
+                                   dict(M=1, d=512, ffn=64, aan_ffn=64, S=513, heads=4, launches=9)])
 def test_decoder_layer_of_a_few_rows(shape):
     # up to eight sentences: two launches, whose workgroups wait for each other's rows.  The bits of the launches stage by
     # stage (and of the route that a named variant takes), also when y overwrites x, when no row comes within the time a
@@ -343,7 +348,7 @@ def test_decoder_layer_of_a_few_rows(shape):
     def call(stream):
         mq.mq_aan_layer_f32(layer, io, gp, 4, K, V, M, S, heads, True, True, glue.LN_EPS, io, g, ws, nb, stream)
 
-    assert launches(call) == (2 if S <= 512 else 9)
+    assert launches(call) == shape.get("launches", 2)
     try:
         mq.mq_set_ffn_single_pass(0)                     # kernels that wait are switched off: the same bits in launches
         assert launches(call) == 9
