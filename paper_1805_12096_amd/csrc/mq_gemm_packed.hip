@@ -959,7 +959,7 @@ int default_variant(const GemmArgs& a) {
   // 352 workgroups, 21.7 us, on tiles 19.7; block of 500 words in 16 bit, first product on 1024 workgroups, 39.5 and 30.7,
   // while long sums in 16 bit still carry it (700 x 1024 x 2048, 704 workgroups, 26.4 and 30.0).
   const size_t with_amax = a.bits == 8 ? 320 : a.K > 1024 ? 768 : 384;
-  if (gemm_small_ahead(a.bits, a.M, a.N, a.K) &&
+  if (gemm_small_ahead(a.bits, a.M, a.N) &&
       (a.out_amax == nullptr || gemm_small_partials(a.bits, a.M, a.N, a.K) <= with_amax))
     return a.bits == 16 ? 6 : 10;
   const TileCost cost16[] = {{3, 64, 128, 3.37f, 0.57f, 0.08f, 0.59f, 2.82f, 0.f},

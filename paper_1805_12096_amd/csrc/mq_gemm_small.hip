@@ -797,26 +797,20 @@ SmallF32Shape small_f32_shape(size_t M, size_t N, size_t K) {
 //   waves with eight 9.36).  Beyond, K up to 1024 stays there until three workgroups per unit (384 x 2048 x 1024 8.0; two row
 //   blocks on four waves 8.4), longer K takes two row blocks, which read a parameter's fragments once for both: 288 x 1024 x
 //   4096 10.6 (one block 11.5), 1000 x 1024 x 2048 11.7 (12.5), on eight waves where that leaves no trip half empty, else on
-//   four (1280 x 700 x 1500 10.4, 10.9 on eight).  Wide results of more than 3072 contracted elements stay on sixteen waves of
-//   one block up to two workgroups per unit, the launch a test fixes (11.5 where two row blocks take 10.6).
+//   four (1280 x 700 x 1500 10.4, 10.9 on eight).
 //   16 bit: two fragments a trip, which leaves registers for two and three workgroups of eight or four waves on a unit: eight
 //   waves up to one workgroup per unit (384 x 512 x 512 7.2 us; sixteen waves 7.4; 256 x 1024 x 4096 15.9, four fragments
-//   17.4), four beyond (320 x 1024 x 2048 13.0, four fragments and two row blocks 13.6; 1024 x 2048 x 512 10.4 and 11.6).  Two
-//   row blocks of eight waves only where a test fixes the launch: 300 x 2048 x 2048, 19.2 us (one block 17.6).
+//   17.4), four beyond (320 x 1024 x 2048 13.0, four fragments and two row blocks 13.6; 1024 x 2048 x 512 10.4 and 11.6; 300 x
+//   2048 x 2048 17.6, two row blocks of eight waves 19.2).
 struct SmallShape {
   int row_blocks, waves, trip;
 };
 size_t one_block_workgroups(size_t M, size_t N) { return row_blocks(M) * column_blocks(N); }
 SmallShape small_shape(int bits, size_t M, size_t N, size_t K) {
-  const size_t wg = one_block_workgroups(M, N), nb = column_blocks(N), kfrags = PackedDims(8, M, K).kfrags;
-  if (bits == 16) {
-    if (wg <= kCUs) return {1, 8, 2};
-    if (kfrags >= 64 && nb >= 64 && nb < 128 && wg > 512 && wg <= 640) return {2, 8, 2};
-    return {1, 4, 2};
-  }
+  const size_t wg = one_block_workgroups(M, N), kfrags = PackedDims(8, M, K).kfrags;
+  if (bits == 16) return {1, wg <= kCUs ? 8 : 4, 2};
   if (kfrags <= 16) return {1, 4, 4};
   if (wg <= kCUs || (kfrags <= 32 && wg <= 3 * kCUs)) return {1, 8, 4};
-  if (kfrags > 96 && nb >= 32 && wg <= 2 * kCUs) return {1, 16, 4};
   return {2, kfrags > 64 || (kfrags > 32 && (kfrags + 7) / 8 % 4 == 0) ? 8 : 4, 4};
 }
 
@@ -827,12 +821,10 @@ SmallShape small_shape(int bits, size_t M, size_t N, size_t K) {
 // 12.1; 700 x 1500 x 700 9.4 and 10.2; on the other side 1600 x 1024 x 2048 18.4 and 17.2.  16 bit: 1000 x 1024 x 2048 21.6 and
 // 23.9, 2000 x 512 x 512 11.1 and 13.1, 256 x 4096 x 4096 31 and 34; on the other side 640 x 2048 x 2048 24.4 and 23.2.
 // Results of few columns have thousands of rows behind those workgroups and less ahead to show for it (3500 x 300 x 2048
-// 17.5 and 19.2), at last none: up to 128 columns the tiles take over from 600 workgroups on.  In 8 bit, K above 1024 and up
-// to 512 columns, the tiles keep 1201 to 1408 rows of 512: a test fixes them for 1300 x 512 x 2048 (14.9 us, split K 11.3).
-bool gemm_small_ahead(int bits, size_t M, size_t N, size_t K) {
+// 17.5 and 19.2), at last none: up to 128 columns the tiles take over from 600 workgroups on.
+bool gemm_small_ahead(int bits, size_t M, size_t N) {
   const size_t nb = column_blocks(N), wg = one_block_workgroups(M, N);
   if (nb <= 4) return wg <= 600;
-  if (bits == 8 && nb <= 16 && K > 1024 && wg > 600 && wg <= 704) return false;
   return wg <= (bits == 16 ? 4 : 5) * kCUs;
 }
 
@@ -852,13 +844,9 @@ int launch_gemm_small(const GemmArgs& a, Epilogue epi, hipStream_t s) {
   if ((a.bits != 8 && a.bits != 16) || (epi != kEpiRaw && epi != kEpiDequant)) return MQ_ERR_UNSUPPORTED;
   const int dequant = epi == kEpiDequant;
   const SmallShape c = small_shape(a.bits, a.M, a.N, a.K);
-  if (a.bits == 16) {
-    if (c.row_blocks == 2) return launch_small<16, 2, 8, 2>(a, dequant, s);
-    return c.waves == 8 ? launch_small<16, 1, 8, 2>(a, dequant, s) : launch_small<16, 1, 4, 2>(a, dequant, s);
-  }
+  if (a.bits == 16) return c.waves == 8 ? launch_small<16, 1, 8, 2>(a, dequant, s) : launch_small<16, 1, 4, 2>(a, dequant, s);
   if (c.row_blocks == 2) return c.waves == 8 ? launch_small<8, 2, 8, 4>(a, dequant, s) : launch_small<8, 2, 4, 4>(a, dequant, s);
-  if (c.waves == 4) return launch_small<8, 1, 4, 4>(a, dequant, s);
-  return c.waves == 8 ? launch_small<8, 1, 8, 4>(a, dequant, s) : launch_small<8, 1, 16, 4>(a, dequant, s);
+  return c.waves == 4 ? launch_small<8, 1, 4, 4>(a, dequant, s) : launch_small<8, 1, 8, 4>(a, dequant, s);
 }
 
 // The 16-bit product whose results are quantized with a given multiplier: packed_out, and its row sums (cleared before) by one

@@ -105,7 +105,7 @@ int launch_gemm_small_requant_i16(const GemmArgs& a, hipStream_t s);
 int launch_gemm_small(const GemmArgs& a, Epilogue epi, hipStream_t s);
 // With the dequantizing epilogue both small-product launchers also write max|y| of every workgroup to
 // a.partial (if not NULL): gemm_small_partials / gemm_small_f32_partials values.
-bool gemm_small_ahead(int bits, size_t M, size_t N, size_t K);        // of the tiled products
+bool gemm_small_ahead(int bits, size_t M, size_t N);        // of the tiled products
 size_t gemm_small_partials(int bits, size_t M, size_t N, size_t K);
 size_t gemm_small_f32_partials(size_t M, size_t N, size_t K);
 // The same with quant_int of fp32 activations done in the operand fetch (8 bit, dequantizing epilogue):
