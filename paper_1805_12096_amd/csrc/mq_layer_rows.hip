@@ -287,8 +287,7 @@ __global__ __launch_bounds__(kLT) void k_layer_rows(const LayerParams p) {
     unsigned was;
     if (kFirst && tid == 0) was = __hip_atomic_exchange(p.claim + role0, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __builtin_amdgcn_sched_barrier(0);
-    // Whether the role is this workgroup's is not waited for at first: f is right whoever computes it, and y waits for the
-    // answer (until y is written the inputs, which it may overwrite, are as they were).
+    // Whether the role is this workgroup's is not waited for at first: f is right whoever computes it.
     auto mine = [&] {
       if constexpr (!kFirst) return true;
       return __builtin_amdgcn_readfirstlane(claimed_own) != 0u;
