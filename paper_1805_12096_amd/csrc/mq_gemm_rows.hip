@@ -27,7 +27,8 @@ enum RowsIn {
   kRowsNorm = 3,       // A = LN(a + b) gamma + beta, also written to `side`
 };
 
-// Two cache lines: every line of arguments is a miss of its own on each launch.
+// Two cache lines: every line of arguments is a miss of its own on each launch.  (RowsFill is a third, which only the form with
+// the average reads; the others take the same time with it and without, 0.994 to 0.998 in seven calls.)
 struct RowsParams {
   const float* a;
   const float* b;

@@ -322,7 +322,9 @@ int launch_small(const GemmArgs& a, int dequant, hipStream_t s) {
 // rows' reads (4 x 1 at 1001 rows would not fit the round, and reads 1.7 times as much per result).
 // Whole block on a prepared workspace, us, tiles and this: 512 / 2048: 64 rows 16.0 and 12.4, 200 rows 17.0 and 13.7, 500 rows 18.1
 // and 15.5, 1001 rows 20.4 and 18.4, 1024 rows 18.8 and 18.4; 1024 / 4096: 64 rows 19.2 and 14.0, 200 rows 21.0 and 17.3, 500
-// rows 25.2 and 23.2; 1000 / 1000: 1200 rows 24.0 and 21.4; 128 / 4096: 400 rows 16.7 and 16.8.
+// rows 25.2 and 23.2; 1000 / 1000: 1200 rows 24.0 and 21.4; 128 / 4096: 400 rows 16.7 and 16.8.  However long K is: 2048 / 512:
+// 32 rows 20.5 and 12.0, 1001 rows 28.1 and 19.8, 4096 rows 37.9 and 37.5; 4096 / 2048: 100 rows 31.4 and 17.3, 1001 rows 47.0
+// and 43.8; 8192 / 512: 500 rows 53.2 and 27.5, 4096 rows 139 and 138.
 struct AgreeParams {
   const uint8_t *qA, *packedW;
   unsigned M, N, K;
@@ -682,7 +684,6 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small_f32(const SmallF32Params
   constexpr int kEach = TNW * 1024 / (KS * 64), V = kEach % 4 == 0 ? 4 : kEach % 2 == 0 ? 2 : 1, NV = kEach / V;
   static_assert(V >= 1 && NV * V * KS * 64 == TNW * 1024, "elements must divide over the threads");
   typedef uint32_t Vec __attribute__((ext_vector_type(V)));
-  // (REQUANT: registers are columns and lanes rows)
   Vec* mine = reinterpret_cast<Vec*>(part) + wave * (TNW * 1024 / V);
 #pragma unroll
   for (int c = 0; c < TNW; ++c)

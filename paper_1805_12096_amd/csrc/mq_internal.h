@@ -98,11 +98,13 @@ int launch_gemm_packed(const GemmArgs& a, Epilogue epi, hipStream_t s);
 // split-K kernel serves the product (and the array takes them all, kAbsmaxPartials), else 0 -- then out_amax has to be used.
 // Settles a.variant where maxima are promised.
 size_t gemm_packed_partials(GemmArgs& a);
-// Split-K form for few rows (8 bit, raw or dequantizing epilogue); launch_gemm_packed's variant 10.
+// Split-K form for few rows (raw or dequantizing epilogue); launch_gemm_packed's variant 10 in 8 bit, 6 in 16.
+int launch_gemm_small(const GemmArgs& a, Epilogue epi, hipStream_t s);
+// Its forms with quantized results: 8 bit with the grid's agreement on max|y| (MQ_ERR_UNSUPPORTED where the pieces do not fit
+// one round), 16 bit with a given multiplier (and whether that is ahead of the tiles).
 int launch_gemm_small_requant_agree(const GemmArgs& a, hipStream_t s);
 bool gemm_small_requant_ahead(size_t M, size_t N);
 int launch_gemm_small_requant_i16(const GemmArgs& a, hipStream_t s);
-int launch_gemm_small(const GemmArgs& a, Epilogue epi, hipStream_t s);
 // With the dequantizing epilogue both small-product launchers also write max|y| of every workgroup to
 // a.partial (if not NULL): gemm_small_partials / gemm_small_f32_partials values.
 bool gemm_small_ahead(int bits, size_t M, size_t N);        // of the tiled products

@@ -390,7 +390,9 @@ __global__ __launch_bounds__(kLT) void k_layer_rows(const LayerParams p) {
         const float scale = __fdiv_rn(1.0f, sqrtf((float)dh));
         const f4* K4 = reinterpret_cast<const f4*>(p.K + (size_t)row * S * d);
         const f4* V4 = reinterpret_cast<const f4*>(p.V + (size_t)row * S * d) + r * 8 + lane % 8;
-        const unsigned sg = lane / 8;                            // groups that share the positions of V
+        // groups that share the positions of V: SG of the eight, the others repeat them (the order of the additions is that of
+        // the attention kernel this replaces)
+        const unsigned sg = lane / 8;
         constexpr int kTrips = 8;
         f4 kr[kTrips], va[kTrips], q[1];
         auto keys = [&](unsigned head, unsigned s0) {

@@ -1617,7 +1617,10 @@ def test_single_pass_requantizing_product(shape):
 @pytest.mark.parametrize("M,N,K,grid", [(31, 33, 31, (2, 512)), (32, 8192, 70, (256, 512)), (33, 4100, 300, (129, 512)),
                                         (200, 2000, 257, (252, 512)), (260, 2048, 1100, (192, 512)),
                                         (1030, 1000, 64, (144, 512)), (2048, 1024, 96, (256, 512)),
-                                        (1001, 2050, 520, (136, 512)), (2048, 2048, 96, (256, 512))])
+                                        (1001, 2050, 520, (136, 512)), (2048, 2048, 96, (256, 512)),
+                                        # several trips along K for every wave, the last one not full
+                                        (40, 100, 6000, (8, 512)), (200, 2000, 2130, (252, 512)), (260, 2048, 3000, (192, 512)),
+                                        (257, 2760, 2300, (132, 512))])
 def test_single_pass_requantizing_product_split_k(M, N, K, grid):
     # the forms of the split-K kernel in the order of size and the first tiles behind them, with and without ReLU and bias, a
     # NaN and infinities among the biases (max = inf: multiplier 0, every output 0)
