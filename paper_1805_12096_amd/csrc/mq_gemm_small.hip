@@ -822,11 +822,9 @@ SmallShape small_shape(int bits, size_t M, size_t N, size_t K) {
 // 12.1; 700 x 1500 x 700 9.4 and 10.2; on the other side 1600 x 1024 x 2048 18.4 and 17.2.  16 bit: 1000 x 1024 x 2048 21.6 and
 // 23.9, 2000 x 512 x 512 11.1 and 13.1, 256 x 4096 x 4096 31 and 34; on the other side 640 x 2048 x 2048 24.4 and 23.2.
 // Results of few columns have thousands of rows behind those workgroups and less ahead to show for it (3500 x 300 x 2048
-// 17.5 and 19.2), at last none: up to 128 columns the tiles take over from 600 workgroups on.
+// 17.5 and 19.2; 7995 x 100 x 3000 46.9 and 50.4, in 16 bit 62.5 and 66.4; 4955 x 100 x 512 7.9 and 10.5).
 bool gemm_small_ahead(int bits, size_t M, size_t N) {
-  const size_t nb = column_blocks(N), wg = one_block_workgroups(M, N);
-  if (nb <= 4) return wg <= 600;
-  return wg <= (bits == 16 ? 4 : 5) * kCUs;
+  return one_block_workgroups(M, N) <= (bits == 16 ? 4 : 5) * kCUs;
 }
 
 // Workgroups of launch_gemm_small / launch_gemm_small_f32 for a shape = maxima written to GemmArgs::partial.

@@ -871,8 +871,9 @@ def test_quantizing_product_column_blocks(M, N, K, given):
 @pytest.mark.parametrize("bits,M,N,K,workgroups,threads", [
     (8, 384, 1024, 4096, 192, 512), (8, 512, 700, 700, 352, 512), (8, 300, 1536, 512, 480, 256), (16, 300, 1536, 512, 480, 256),
     (16, 300, 2048, 2048, 640, 256), (8, 1001, 512, 2048, 256, 512), (8, 1300, 512, 2048, 336, 512),      # split K ahead of the tiles
-    (8, 5003, 100, 3000, 80, 256), (8, 8192, 128, 512, 128, 256), (8, 8192, 512, 2048, 256, 256),         # tiles ahead of split K
-    (16, 5003, 100, 3000, 79, 256), (16, 8192, 4096, 1024, 256, 512)])
+    (8, 5003, 100, 3000, 316, 512), (8, 8192, 128, 512, 1024, 256), (16, 5003, 100, 3000, 628, 256),      # ... few columns too
+    (8, 12000, 100, 3000, 188, 256), (8, 8192, 512, 2048, 256, 256), (16, 9000, 100, 3000, 141, 256),     # tiles ahead of split K
+    (16, 8192, 4096, 1024, 256, 512)])
 def test_gemm_packed_default_configuration(bits, M, N, K, workgroups, threads):
     # which kernel serves shapes on which a wrong choice costs 15 % to 100 %: seen by its grid
     q = torch.zeros(mq.mq_packed_bytes(bits, M, K), dtype=torch.uint8, device=DEV)
