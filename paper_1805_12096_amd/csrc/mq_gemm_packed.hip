@@ -957,10 +957,11 @@ struct TileCost {
 
 int default_variant(const GemmArgs& a) {
   // Split K while it stays ahead of the tiles (variant 10 / 6).  max|y| into words of the caller's ends every workgroup with
-  // another trip to memory and an atomic, which many small workgroups pay for: 700 x 1024 x 2048 behind its quantizer in 8 bit,
-  // 352 workgroups, 21.7 us, on tiles 19.7; block of 500 words in 16 bit, first product on 1024 workgroups, 39.5 and 30.7,
-  // while long sums in 16 bit still carry it (700 x 1024 x 2048, 704 workgroups, 26.4 and 30.0).
-  const size_t with_amax = a.bits == 8 ? 320 : a.K > 1024 ? 768 : 384;
+  // another trip to memory and an atomic (raise_amax), which many small workgroups pay for.  Split K over tiles, quantizer
+  // included: 8 bit, K = 256, 340 workgroups 0.94, 396 to 480 1.07 to 1.10; K = 512 to 1024, 376 to 480 0.90 to 1.04, 640 1.02
+  // to 1.19; beyond, 300 to 499 0.82 to 0.99.  16 bit, K = 64 and 256, 400 to 480 0.95 to 1.12, 658 1.06 to 1.21; K = 512, 396 to
+  // 512 0.86 to 0.99, 658 1.03; K = 700 and 1024, 400 to 700 0.82 to 1.00; beyond, 800 to 899 0.99 to 1.10.
+  const size_t with_amax = a.bits == 8 ? (a.K <= 256 ? 320 : 440) : a.K <= 256 ? 384 : a.K <= 512 ? 512 : 768;
   if (gemm_small_ahead(a.bits, a.M, a.N) &&
       (a.out_amax == nullptr || gemm_small_partials(a.bits, a.M, a.N, a.K) <= with_amax))
     return a.bits == 16 ? 6 : 10;

@@ -845,9 +845,14 @@ def test_split_k_shapes(bits, M, N, K):
         mq.mq_set_gemm_variant(10 if bits == 8 else 6)
         assert np.array_equal(gpu_dot_int_packed(qA, qB), oracle.dot_int(qA, qB))
         mq.mq_gemm_dequant_packed(pa, pw.packed, bits, M, N, K, s, pw.scale, dev(p["bias"]), True, Y, am)
+        top = o["Y"].max()
+        words = [torch.full((1,), float(f * top), dtype=torch.float32, device=DEV) for f in (0.5, 2.0)]      # never lowered
+        for w in words:
+            mq.mq_gemm_dequant_packed(pa, pw.packed, bits, M, N, K, s, pw.scale, dev(p["bias"]), True, Y, w)
     finally:
         mq.mq_set_gemm_variant(0)
-    assert np.array_equal(host(Y), o["Y"]) and host(am)[0] == o["Y"].max()
+    assert np.array_equal(host(Y), o["Y"]) and host(am)[0] == top
+    assert host(words[0])[0] == top and host(words[1])[0] == np.float32(2.0 * top)
 
 
 @pytest.mark.parametrize("M,N,K", [(300, 2048, 512), (350, 2047, 480), (300, 2048, 1024), (330, 2040, 992), (150, 4096, 1024),
