@@ -779,12 +779,37 @@ int mq_ffn_i16_f32(const float* A, size_t M, size_t d, size_t f, const void* pac
   uint8_t* qA = base + L.off_qA;
   float* H = reinterpret_cast<float*>(base + L.off_H);
   uint8_t* qH = base + L.off_qH;
+  auto second = [&]() {
+    GemmArgs g2{};
+    g2.qA = qH;
+    g2.packedW = packedW2; g2.bits = 16; g2.M = M; g2.N = d; g2.K = f;
+    g2.sA = sH; g2.sW = sW2; g2.bias = b2; g2.relu = 0; g2.Y = Y;
+    return launch_gemm_packed(g2, kEpiDequant, s);
+  };
   // a1 + a2 on the input.  Where the tensor fits the registers of one resident grid it is read once: a small launch
   // clears the agreement words and max|H|, then one kernel finds max|A| across the grid and converts from registers;
   // otherwise two passes (partial maxima, then the quantizer), the first of which zeroes max|H|.
   unsigned* bar = reinterpret_cast<unsigned*>(base + L.off_bar);
   static_assert(sizeof(float) * 3 <= 256, "max|H| sits right in front of the agreement words");
+  // Few rows: quant_int(A) in the first product's operand fetch (unless the caller has forced or tuned a packed product); its
+  // workgroups' maxima of H go where the packed A would be.
+  const size_t wg = gemm_small_f32_partials(16, M, f, d);
+  const bool in_fetch = gemm_small_f32_supported(16, M, f, d) && !variant_named(16, M, f, d) && wg <= kAbsmaxPartials &&
+                        wg * sizeof(float) <= L.off_H - L.off_qA && !overlap(A, M * d, static_cast<const float*>(ws), L.total / 4);
+  GemmArgs g1{};
+  g1.packedW = packedW1; g1.bits = 16; g1.M = M; g1.N = f; g1.K = d;
+  g1.sW = sW1; g1.bias = b1; g1.relu = 1; g1.Y = H;
   int rc = MQ_ERR_UNSUPPORTED;
+  if (in_fetch) {
+    unsigned np = 0;
+    rc = launch_absmax_partials(A, M * d, part, &np, s);
+    if (rc != MQ_OK) return rc;
+    g1.partial = reinterpret_cast<float*>(qA);
+    rc = launch_gemm_small_f32(A, part, np, nullptr, g1, s);
+    if (rc != MQ_OK) return rc;
+    rc = launch_quantize_pack_partials(H, M, f, 16, g1.partial, (unsigned)wg, sH, qH, s);
+    return rc != MQ_OK ? rc : second();
+  }
   if (g_ffn_single_pass && M * d >= ((size_t)1 << 20)) {
     // hmax is the third float of the 256 bytes in front of `bar`: one clearing launch covers both
     rc = launch_clear_words(reinterpret_cast<unsigned*>(hmax), (unsigned)((L.off_bar - L.off_scal) / 4 - 2 + kBarrierWords), s);
@@ -795,10 +820,7 @@ int mq_ffn_i16_f32(const float* A, size_t M, size_t d, size_t f, const void* pac
     rc = launch_absmax_quantize_pack(A, M, d, 16, part, sA, qA, s, reinterpret_cast<unsigned*>(hmax), kHmaxSlots);
   if (rc != MQ_OK) return rc;
   // a4 + a5: H = relu(A W1 + b1) in binary32, max|H| as a by-product of the epilogue
-  GemmArgs g1{};
-  g1.qA = qA;
-  g1.packedW = packedW1; g1.bits = 16; g1.M = M; g1.N = f; g1.K = d;
-  g1.sA = sA; g1.sW = sW1; g1.bias = b1; g1.relu = 1; g1.Y = H;
+  g1.qA = qA; g1.sA = sA;
   // max|H|: one value per workgroup from the split-K kernel (where the input's partial maxima were, which nobody reads any
   // more), else raised words (kernels that do not know about the slots raise the first word only; the others stay zero)
   const size_t parts = gemm_packed_partials(g1);
@@ -811,12 +833,7 @@ int mq_ffn_i16_f32(const float* A, size_t M, size_t d, size_t f, const void* pac
   if (rc != MQ_OK) return rc;
   // a1 + a2 on H: the multiplier comes from the maxima already there
   rc = launch_quantize_pack_partials(H, M, f, 16, parts != 0 ? part : hmax, parts != 0 ? (unsigned)parts : kHmaxSlots, sH, qH, s);
-  if (rc != MQ_OK) return rc;
-  GemmArgs g2{};
-  g2.qA = qH;
-  g2.packedW = packedW2; g2.bits = 16; g2.M = M; g2.N = d; g2.K = f;
-  g2.sA = sH; g2.sW = sW2; g2.bias = b2; g2.relu = 0; g2.Y = Y;
-  return launch_gemm_packed(g2, kEpiDequant, s);
+  return rc != MQ_OK ? rc : second();
 }
 
 size_t mq_ffn_i16_fixed_ws_bytes(size_t M, size_t d, size_t f) {
@@ -887,7 +904,8 @@ int mq_linear_f32(const float* A, size_t M, size_t K, const float* sA_or_null, c
   // Products that quantize in their operand fetch read A from every tile column while other workgroups already store Y:
   // where the two share memory, A is quantized in a launch of its own first.
   const bool apart = !overlap(A, M * K, Y, M * N);
-  const bool in_fetch = bits == 8 && gemm_small_f32_supported(M, N, K);
+  // (16 bit: more than one block of rows, and unless the caller has forced or tuned a packed product)
+  const bool in_fetch = gemm_small_f32_supported(bits, M, N, K) && (bits == 8 || (M > 32 && !variant_named(bits, M, N, K)));
   // one block of rows: abs-max, quant_int and product in one launch -- unless the other route leads to the packed products
   // and the caller has forced or tuned one of them for this shape, or is the shorter one (a given multiplier)
   if (apart && gemm_rows_supported(bits, M, N, K) && (sA == nullptr || gemm_rows_ahead_given(bits, M, K, in_fetch)) &&
@@ -1051,10 +1069,10 @@ int mq_aan_layer_f32(const mq_aan_layer* P, const float* x, const float* g_prev,
     g.packedW = W.packed; g.bits = 8; g.M = M; g.N = N; g.K = Kdim;
     g.sW = W.scale; g.bias = W.bias; g.relu = relu; g.Y = Y;
     out_partials = nullptr; out_np = 0;
-    if (partials != nullptr && np <= kAbsmaxPartials && gemm_small_f32_supported(M, N, Kdim)) {
+    if (partials != nullptr && np <= kAbsmaxPartials && gemm_small_f32_supported(8, M, N, Kdim)) {
       // short K: quant_int inside the product's operand fetch, no quantizing launch
       if (want_max) {
-        const size_t wg = gemm_small_f32_partials(M, N, Kdim);
+        const size_t wg = gemm_small_f32_partials(8, M, N, Kdim);
         if (wg <= kAbsmaxPartials) { g.partial = out_buf; out_partials = out_buf; out_np = wg; }
         else { g.out_amax = hword; g.amax_slots = kHmaxSlots; out_partials = hword; out_np = kHmaxSlots; }
       }
@@ -1076,7 +1094,7 @@ int mq_aan_layer_f32(const mq_aan_layer* P, const float* x, const float* g_prev,
   int rc;
   if (gemm_rows_glue_supported(M, d) && use_ffn && use_gate && aligned(g_prev, 16) && aligned(P->ln1.gamma, 16) &&
       aligned(P->ln1.beta, 16) && aligned(P->ln2.gamma, 16) && aligned(P->ln2.beta, 16) && !overlap(g_prev, M * d, g_out, M * d) &&
-      !overlap(x, M * d, g_out, M * d) && (gemm_small_f32_supported(M, 2 * d, 2 * d) || !variant_named(8, M, 2 * d, 2 * d))) {
+      !overlap(x, M * d, g_out, M * d) && (gemm_small_f32_supported(8, M, 2 * d, 2 * d) || !variant_named(8, M, 2 * d, 2 * d))) {
     // One block of rows: the running average, the normalisations in front of a product and every quantizer happen in the
     // operand fetch of the product that follows, and the gate in the epilogue of its own product: nine launches for
     // fourteen.
@@ -1088,7 +1106,7 @@ int mq_aan_layer_f32(const mq_aan_layer* P, const float* x, const float* g_prev,
     };
     // H (with partial maxima, for the form that quantizes in a launch of its own) times the second parameter
     auto second = [&](size_t width, const mq_product& W, float* Y) {
-      if (gemm_rows_supported(8, M, d, width) && (gemm_small_f32_supported(M, d, width) || !variant_named(8, M, d, width)))
+      if (gemm_rows_supported(8, M, d, width) && (gemm_small_f32_supported(8, M, d, width) || !variant_named(8, M, d, width)))
         return launch_gemm_rows(hid, nullptr, args(W, d, width, 0, Y), s);      // (see mq_linear_f32)
       return product(hid, width, W, d, 0, Y, hpart, gemm_rows_partials(width), false, nullptr, nullptr);
     };
@@ -1138,7 +1156,7 @@ int mq_aan_layer_f32(const mq_aan_layer* P, const float* x, const float* g_prev,
     GemmArgs gg{};
     gg.packedW = P->aan_gate.packed; gg.bits = 8; gg.M = M; gg.N = 2 * d; gg.K = 2 * d;
     gg.sW = P->aan_gate.scale; gg.bias = P->aan_gate.bias; gg.relu = 0; gg.Y = z;
-    if (gemm_small_f32_supported(M, 2 * d, 2 * d) && d % 4 == 0 && fpart != nullptr && fnp >= 1) {
+    if (gemm_small_f32_supported(8, M, 2 * d, 2 * d) && d % 4 == 0 && fpart != nullptr && fnp >= 1) {
       // the gate's input [x, f] is read from its two pieces (with their partial maxima) inside the product
       // kernel: the concatenation is never stored and its launch disappears
       rc = launch_gemm_small_f32_pair(x, d, xpart, np_avg, fpath, fpart, (unsigned)fnp, sA, gg, s);

@@ -516,6 +516,9 @@ int launch_agree(const GemmArgs& a, hipStream_t s) {
 // here from partial maxima left by the kernel that produced A (127 / max, one correctly rounded division,
 // as the separate quantizer does).  Every column block of a row block repeats the conversion of that row
 // block; that is cheap next to a launch as long as K is short (the fp32 rows are four times the bytes).
+// 16 bit: the bytes are those of the two planes, and a wave also adds up its part of every row's values (a lane holds 16 of a
+// row's bytes per fragment for its products; four dot products with ones a plane) and puts 128 of that sum into its partial
+// sums, so that the recombination is corrected without a row sum ever leaving the wave.
 struct SmallF32Params {
   const float* A;            // [M x K] fp32, K a multiple of 32, rows 16-byte aligned; with A2: [M x K1], columns 0 .. K1 - 1
   const float* A2;           // optional second piece [M x (K - K1)]: columns K1 .. K - 1 of the input
@@ -550,6 +553,19 @@ __device__ __forceinline__ uint32_t quant_pack4(float4 v, float s) {
   // bytes 0 of four words: two byte permutes and an or (0x0c selects zero)
   return __builtin_amdgcn_perm(q(v.y), q(v.x), 0x0c0c0400u) | __builtin_amdgcn_perm(q(v.w), q(v.z), 0x04000c0cu);
 }
+// The same in 16 bit, as the bytes of the two planes (32767 / max instead of 127 / max: the same argument without a clamp).
+template <bool CLAMP>
+__device__ __forceinline__ void quant_planes4(float4 v, float s, uint32_t& hi, uint32_t& lo) {
+  auto q = [&](float x) -> uint32_t {
+    const float r = rintf(__fmul_rn(x, s));
+    int i;
+    asm("v_cvt_i32_f32 %0, %1" : "=v"(i) : "v"(r));
+    return (uint32_t)(CLAMP ? min(max(i, -32767), 32767) : i);
+  };
+  const uint32_t x = q(v.x), y = q(v.y), z = q(v.z), w = q(v.w);
+  hi = __builtin_amdgcn_perm(y, x, 0x0c0c0501u) | __builtin_amdgcn_perm(w, z, 0x05010c0cu);
+  lo = (__builtin_amdgcn_perm(y, x, 0x0c0c0400u) | __builtin_amdgcn_perm(w, z, 0x04000c0cu)) ^ 0x80808080u;
+}
 
 // TNW: 32-column blocks per workgroup; KS waves split K; a round is 4 fragments (128 elements of K).
 // Each wave reads its own run of K from the fp32 rows in whole 512-byte pieces (two rows per load
@@ -563,16 +579,16 @@ __device__ __forceinline__ uint32_t quant_pack4(float4 v, float s) {
 // exchange through LDS and lane moves for the maxima: this product with its abs-max 9.15 -> 8.3 us, a decoder layer of 300
 // sentences 74.1 -> 70.1 us.
 // GIVEN: the multiplier is given (elements may exceed it and are clamped); otherwise it comes from partial maxima.
-template <int TNW, int KS, bool GIVEN>
+template <int BITS, int TNW, int KS, bool GIVEN>
 __global__ __launch_bounds__(KS * 64) void k_gemm_small_f32(const SmallF32Params p) {
-  constexpr int KW = 4;
+  constexpr int KW = 4, NPL = BITS == 16 ? 2 : 1, NACC = BITS == 16 ? 3 : 1;
   constexpr int kHalf = 512 + 16, kPitch = 2 * kHalf;
   extern __shared__ __attribute__((aligned(16))) int part[];      // [KS][TNW * 1024], then the staging pieces
   __shared__ float red[KS];
   const int tid = threadIdx.x, lane = tid % 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);      // scalar, see k_gemm_small
-  uint8_t* stage = reinterpret_cast<uint8_t*>(part + KS * TNW * 1024) + wave * (KW * kPitch);
-  const PackedDims dW(8, p.N, p.K);
+  uint8_t* stage = reinterpret_cast<uint8_t*>(part + KS * TNW * 1024) + wave * (NPL * KW * kPitch);
+  const PackedDims dW(BITS, p.N, p.K);
   const unsigned tile_n = blockIdx.x % p.tiles_n, tile_m = blockIdx.x / p.tiles_n;
   const unsigned ksl = p.K / 32;                                  // slices that hold real elements
   const unsigned per = (ksl + KS - 1) / KS;
@@ -601,13 +617,16 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small_f32(const SmallF32Params
   uint8_t* st_dst = stage + (lj / 8) * kPitch + ((lj / 4) % 2) * kHalf + lh * 16 + 4 * (lj % 4);
 
   float4 fa[16];
-  u4 fw[TNW][KW];
+  u4 fw[TNW][KW][NPL];
   auto fetch = [&](unsigned kb0) {
 #pragma unroll
     for (int j = 0; j < KW; ++j) {
       const unsigned kb = kb0 + j < kb_end ? kb0 + j : kb_end - 1;
 #pragma unroll
-      for (int c = 0; c < TNW; ++c) fw[c][j] = *reinterpret_cast<const u4*>(w_src[c] + (size_t)kb * kFragBytes);
+      for (int c = 0; c < TNW; ++c)
+#pragma unroll
+        for (int pl = 0; pl < NPL; ++pl)
+          fw[c][j][pl] = *reinterpret_cast<const u4*>(w_src[c] + ((size_t)kb * NPL + pl) * kFragBytes);
     }
     // a lane whose fragment lies past the run reads the run's last fragment instead (a valid address, unused)
     const unsigned kb = kb0 + lj / 8 < kb_end ? kb0 + lj / 8 : kb_end - 1;
@@ -636,11 +655,14 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small_f32(const SmallF32Params
   }
   const float sW_pre = *p.sW;
   float bias_pre[TNW];
+  uint32_t colsum_pre[BITS == 16 ? TNW : 1];
   const bool has_bias = p.bias != nullptr;
 #pragma unroll
   for (int c = 0; c < TNW; ++c) {
     const unsigned n = (tile_n * TNW + c) * 32 + lj;
     bias_pre[c] = (has_bias ? p.bias : p.sW)[has_bias ? min(n, p.N - 1) : 0u];
+    if constexpr (BITS == 16)
+      colsum_pre[c] = reinterpret_cast<const uint32_t*>(p.packedW + dW.plane_bytes())[min(n, (unsigned)p.N - 1)];
   }
   __builtin_amdgcn_sched_barrier(0);
   // the first round is on its way while the multiplier is formed (a wave without a run of its own fetches the last
@@ -661,37 +683,81 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small_f32(const SmallF32Params
     float amax = red[0];
 #pragma unroll
     for (int w = 1; w < KS; ++w) amax = fmaxf(amax, red[w]);
-    s = (amax > 0.0f) ? __fdiv_rn(127.0f, amax) : 1.0f;
+    s = (amax > 0.0f) ? __fdiv_rn(BITS == 16 ? 32767.0f : 127.0f, amax) : 1.0f;
   } else {
     s = *p.scale;
   }
   if (blockIdx.x == 0 && tid == 0 && p.scale_out != nullptr) *p.scale_out = s;
 
-  v16i acc[TNW];
+  v16i acc[TNW][NACC];
 #pragma unroll
   for (int c = 0; c < TNW; ++c)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[c][r] = 0;
+    for (int b = 0; b < NACC; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[c][b][r] = 0;
+  int row = 0;                 // 16 bit: row lj, this lane's half of every fragment: the sum of both planes as one number
   for (unsigned kb0 = kb_begin; kb0 < kb_end; kb0 += KW) {
     if (kb0 != kb_begin) fetch(kb0);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) *reinterpret_cast<uint32_t*>(st_dst + i * 32) = quant_pack4<GIVEN>(fa[i], s);
+    for (int i = 0; i < 16; ++i) {
+      if constexpr (BITS == 8) {
+        *reinterpret_cast<uint32_t*>(st_dst + i * 32) = quant_pack4<GIVEN>(fa[i], s);
+      } else {
+        uint32_t hi, lo;
+        quant_planes4<GIVEN>(fa[i], s, hi, lo);
+        *reinterpret_cast<uint32_t*>(st_dst + i * 32) = hi;
+        *reinterpret_cast<uint32_t*>(st_dst + KW * kPitch + i * 32) = lo;
+      }
+    }
     // The wave reads back what it wrote itself: LDS operations of one wave complete in order, so the
     // hardware needs no wait.  The compiler does: words are written and 16-byte vectors read, types it may
     // take for non-aliasing, so both sides are fenced against compile-time motion.
     asm volatile("" ::: "memory");
-    u4 a[KW];
+    u4 a[KW][NPL];
 #pragma unroll
-    for (int j = 0; j < KW; ++j) a[j] = *reinterpret_cast<const u4*>(stage + j * kPitch + lh * kHalf + lj * 16);
+    for (int j = 0; j < KW; ++j)
+#pragma unroll
+      for (int pl = 0; pl < NPL; ++pl)
+        a[j][pl] = *reinterpret_cast<const u4*>(stage + (pl * KW + j) * kPitch + lh * kHalf + lj * 16);
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int j = 0; j < KW; ++j) {
       if (kb0 + j < kb_end) {
+        if constexpr (BITS == 8) {
 #pragma unroll
-        for (int c = 0; c < TNW; ++c)
-          acc[c] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(a[j]), as_v4i(fw[c][j]), acc[c], 0, 0, 0);
+          for (int c = 0; c < TNW; ++c)
+            acc[c][0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(a[j][0]), as_v4i(fw[c][j][0]), acc[c][0], 0, 0, 0);
+        } else {
+#pragma unroll
+          for (int c = 0; c < TNW; ++c) {
+            acc[c][0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(a[j][0]), as_v4i(fw[c][j][0]), acc[c][0], 0, 0, 0);
+            acc[c][1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(a[j][0]), as_v4i(fw[c][j][1]), acc[c][1], 0, 0, 0);
+            acc[c][2] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(a[j][1]), as_v4i(fw[c][j][1]), acc[c][2], 0, 0, 0);
+            acc[c][1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(as_v4i(a[j][1]), as_v4i(fw[c][j][0]), acc[c][1], 0, 0, 0);
+          }
+          int high = 0;
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            high = __builtin_amdgcn_sdot4((int)a[j][0][t], 0x01010101, high, false);
+            row = __builtin_amdgcn_sdot4((int)a[j][NPL - 1][t], 0x01010101, row, false);
+          }
+          row += 256 * high;
+        }
       }
     }
+  }
+  // 16 bit, this wave's run of K: sum (q - 128) of the rows 8 g + 4 lh + t of the tile.  128 (rowsum + colsum) - 16384 K is 128
+  // of these sums over the waves + 128 colsum.
+  v4i rows_part[BITS == 16 ? 4 : 1];
+  if constexpr (BITS == 16) {
+    row += __shfl_xor(row, 32, 64);
+    asm volatile("" ::: "memory");
+    if (lh == 0) reinterpret_cast<int*>(stage)[lj] = row;
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int g = 0; g < 4; ++g) rows_part[g] = *reinterpret_cast<const v4i*>(stage + (8 * g + 4 * lh) * 4);
+    asm volatile("" ::: "memory");
   }
 
   // the partial sums meet in vectors of V rows, see k_gemm_small
@@ -705,7 +771,12 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small_f32(const SmallF32Params
     for (int r = 0; r < 16; r += V) {
       Vec v;
 #pragma unroll
-      for (int t = 0; t < V; ++t) v[t] = (unsigned)acc[c][r + t];
+      for (int t = 0; t < V; ++t) {
+        v[t] = (unsigned)acc[c][0][r + t];
+        if constexpr (BITS == 16)
+          v[t] = (v[t] << 16) + ((unsigned)acc[c][1][r + t] << 8) + (unsigned)acc[c][2][r + t] +
+                 128u * (unsigned)rows_part[(r + t) / 4][(r + t) % 4];
+      }
       mine[(c * 16 + r) / V * 64 + lane] = v;
     }
   __syncthreads();
@@ -726,12 +797,20 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small_f32(const SmallF32Params
     for (int cc = 1; cc < TNW; ++cc)
       if (cc == c) bias = bias_pre[cc];
     if (!has_bias) bias = 0.f;
+    uint32_t corr = 0;
+    if constexpr (BITS == 16) {
+      corr = colsum_pre[0];
+#pragma unroll
+      for (int cc = 1; cc < TNW; ++cc)
+        if (cc == c) corr = colsum_pre[cc];
+      corr *= 128u;
+    }
     const unsigned n = (tile_n * TNW + c) * 32 + lj;
     const unsigned m0 = tile_m * 32 + 8 * (r / 4) + 4 * lh + r % 4;
 #pragma unroll
     for (int t = 0; t < V; ++t)
       if (n < p.N && m0 + t < p.M) {
-        float y = fmaf((float)(int)v[t], u, bias);
+        float y = fmaf((float)(int)(v[t] + corr), u, bias);
         if (p.relu) y = (y > 0.0f) ? y : 0.0f;
         p.Y[(size_t)(m0 + t) * p.N + n] = y;
         local_amax = fmaxf(local_amax, fabsf(y));
@@ -748,19 +827,20 @@ __global__ __launch_bounds__(KS * 64) void k_gemm_small_f32(const SmallF32Params
 #pragma unroll
       for (int w = 1; w < KS; ++w) mx = fmaxf(mx, wave_amax[w]);
       if (p.partial_out != nullptr) p.partial_out[blockIdx.x] = mx;
-      if (p.out_amax != nullptr) raise_amax(p.out_amax, p.amax_slots, mx, p.K);
+      if (p.out_amax != nullptr) raise_amax(p.out_amax, p.amax_slots, mx, NPL * p.K);
     }
   }
 }
 
-template <int TNW, int KS, bool GIVEN>
+template <int BITS, int TNW, int KS, bool GIVEN>
 int launch_small_f32_one(SmallF32Params p, hipStream_t s) {
-  constexpr size_t smem = (size_t)KS * TNW * 1024 * sizeof(int) + (size_t)KS * 4 * 2 * (512 + 16);
-  const PackedDims dW(8, p.N, p.K);
+  constexpr size_t smem = (size_t)KS * TNW * 1024 * sizeof(int) + (size_t)KS * (BITS / 8) * 4 * 2 * (512 + 16);
+  static_assert(smem <= 160 * 1024, "LDS budget");
+  const PackedDims dW(BITS, p.N, p.K);
   const size_t tiles_m = (p.M + 31) / 32, tiles_n = (dW.nblocks + TNW - 1) / TNW;
   p.tiles_n = (unsigned)tiles_n;
   if (tiles_m * tiles_n > 0x7FFFFFFFull) return MQ_ERR_SHAPE;
-  auto kern = k_gemm_small_f32<TNW, KS, GIVEN>;
+  auto kern = k_gemm_small_f32<BITS, TNW, KS, GIVEN>;
   static bool attr_done = false;
   if (!attr_done) {
     int rc = check_hip(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -772,9 +852,9 @@ int launch_small_f32_one(SmallF32Params p, hipStream_t s) {
   return check_hip(hipGetLastError());
 }
 
-template <int TNW, int KS>
+template <int BITS, int TNW, int KS>
 int launch_small_f32(const SmallF32Params& p, hipStream_t s) {
-  return p.npartial != 0 ? launch_small_f32_one<TNW, KS, false>(p, s) : launch_small_f32_one<TNW, KS, true>(p, s);
+  return p.npartial != 0 ? launch_small_f32_one<BITS, TNW, KS, false>(p, s) : launch_small_f32_one<BITS, TNW, KS, true>(p, s);
 }
 
 size_t row_blocks(size_t M) { return (M + 31) / 32; }
@@ -788,11 +868,15 @@ constexpr size_t kCUs = 256;
 // 8.4 -> 7.9 us, 350 rows 8.5 -> 8.0).  Beyond, the fewest columns that fit one round (300 x 2048 x 1024: three blocks 9.1,
 // two in two rounds 12.4; 150 x 4096 x 1024 9.1 and 12.4; 250 x 1024 x 1024 one block 7.5, two 8.1), else workgroups of four
 // waves, two to a unit (512 x 2048 x 1024 10.9 for 13.1, 256 x 4096 x 1024 11.0 for 13.2).
+// 16 bit (twice the products and twice the parameter's bytes), abs-max and product: up to K = 512 one column block on four waves
+// (384 x 512 x 512 7.2 us; eight waves 8.0, two blocks 8.0), beyond on eight (200 x 1024 x 1024 8.6, four waves 9.4), two blocks
+// where one does not fit the round (500 x 1024 x 1024 10.8, one block 14.0).
 struct SmallF32Shape {
   int blocks, waves;
 };
-SmallF32Shape small_f32_shape(size_t M, size_t N, size_t K) {
+SmallF32Shape small_f32_shape(int bits, size_t M, size_t N, size_t K) {
   auto workgroups = [&](size_t blocks) { return row_blocks(M) * ((column_blocks(N) + blocks - 1) / blocks); };
+  if (bits == 16) return {K <= 512 || workgroups(1) <= kCUs ? 1 : 2, K <= 512 ? 4 : 8};
   if (K <= 512) {
     if (workgroups(2) < 160) return {1, 4};
     return {workgroups(2) > kCUs && workgroups(3) <= kCUs ? 3 : 2, 4};
@@ -842,8 +926,8 @@ size_t gemm_small_partials(int bits, size_t M, size_t N, size_t K) {
   const size_t blocks = (size_t)small_shape(bits, M, N, K).row_blocks;
   return (row_blocks(M) + blocks - 1) / blocks * column_blocks(N);
 }
-size_t gemm_small_f32_partials(size_t M, size_t N, size_t K) {
-  const size_t blocks = (size_t)small_f32_shape(M, N, K).blocks;
+size_t gemm_small_f32_partials(int bits, size_t M, size_t N, size_t K) {
+  const size_t blocks = (size_t)small_f32_shape(bits, M, N, K).blocks;
   return row_blocks(M) * ((column_blocks(N) + blocks - 1) / blocks);
 }
 
@@ -881,7 +965,17 @@ int launch_gemm_small_requant_agree(const GemmArgs& a, hipStream_t s) {
 // Whether quantizing inside the product pays: few rows, K short enough that re-reading the fp32 rows once
 // per column tile stays below the cost of a separate quantizing launch.  K above 512 in more than two rounds is the separate
 // quantizer's: 300 x 4096 x 1024 13.0 us in three launches where two take 14.7, 512 rows 13.3 and 18.0.
-bool gemm_small_f32_supported(size_t M, size_t N, size_t K) {
+// 16 bit, abs-max, three launches and two: K up to 512 by two workgroups per compute unit (384 x 512 x 512 8.8 and 7.2 us, 1000 x
+// 512 x 512 10.7 and 9.6; 640 workgroups, 300 x 2048 x 512, 11.3 and 11.5; 1008, 2000 x 512 x 512, 13.4 and 14.6); K up to 1024 in
+// one round of up to two column blocks (500 x 1024 x 1024 12.6 and 10.8; 480 of them, 300 x 3072 x 1024, 16.0 and 16.1); K up to
+// 2048 in one round of one (300 x 512 x 2048 12.8 and 11.5; two blocks, 600 x 512 x 2048, with the multiplier given 12.6 and
+// 12.7).  K = 4096 with the multiplier given: 12.7 and 14.0.
+bool gemm_small_f32_supported(int bits, size_t M, size_t N, size_t K) {
+  if (bits == 16) {
+    if (M < 1 || N < 1 || K < 32 || K % 32 != 0 || K > 2048) return false;
+    const size_t blocks = K > 512 && K <= 1024 ? (column_blocks(N) + 1) / 2 : column_blocks(N);
+    return row_blocks(M) * blocks <= (K <= 512 ? 2 * kCUs : kCUs);
+  }
   return M >= 1 && M <= 512 && N >= 1 && K >= 32 && K % 32 == 0 &&
          (K <= 512 || (K <= 1024 && (M <= 32 || row_blocks(M) * ((column_blocks(N) + 1) / 2) <= 2 * kCUs)));
 }
@@ -890,18 +984,22 @@ bool gemm_small_f32_supported(size_t M, size_t N, size_t K) {
 // scale: the multiplier (npartial == 0) or npartial partial maxima of |A|.
 namespace {
 int launch_small_f32_any(SmallF32Params p, const GemmArgs& a, hipStream_t s) {
-  if (!gemm_small_f32_supported(a.M, a.N, a.K) || a.bits != 8) return MQ_ERR_UNSUPPORTED;
+  if (!gemm_small_f32_supported(a.bits, a.M, a.N, a.K)) return MQ_ERR_UNSUPPORTED;
   p.packedW = static_cast<const uint8_t*>(a.packedW);
   p.M = (unsigned)a.M; p.N = (unsigned)a.N; p.K = (unsigned)a.K;
   p.sW = a.sW; p.bias = a.bias; p.relu = a.relu; p.Y = a.Y; p.out_amax = a.out_amax; p.amax_slots = a.amax_slots;
   p.partial_out = a.partial;
-  const SmallF32Shape shape = small_f32_shape(a.M, a.N, a.K);
-  if (shape.waves == 4) {
-    if (shape.blocks == 1) return launch_small_f32<1, 4>(p, s);
-    return shape.blocks == 2 ? launch_small_f32<2, 4>(p, s) : launch_small_f32<3, 4>(p, s);
+  const SmallF32Shape shape = small_f32_shape(a.bits, a.M, a.N, a.K);
+  if (a.bits == 16) {
+    if (shape.waves == 4) return shape.blocks == 1 ? launch_small_f32<16, 1, 4>(p, s) : launch_small_f32<16, 2, 4>(p, s);
+    return shape.blocks == 1 ? launch_small_f32<16, 1, 8>(p, s) : launch_small_f32<16, 2, 8>(p, s);
   }
-  if (shape.blocks == 1) return launch_small_f32<1, 8>(p, s);
-  return shape.blocks == 2 ? launch_small_f32<2, 8>(p, s) : launch_small_f32<3, 8>(p, s);
+  if (shape.waves == 4) {
+    if (shape.blocks == 1) return launch_small_f32<8, 1, 4>(p, s);
+    return shape.blocks == 2 ? launch_small_f32<8, 2, 4>(p, s) : launch_small_f32<8, 3, 4>(p, s);
+  }
+  if (shape.blocks == 1) return launch_small_f32<8, 1, 8>(p, s);
+  return shape.blocks == 2 ? launch_small_f32<8, 2, 8>(p, s) : launch_small_f32<8, 3, 8>(p, s);
 }
 }  // namespace
 

@@ -109,10 +109,10 @@ int launch_gemm_small_requant_i16(const GemmArgs& a, hipStream_t s);
 // a.partial (if not NULL): gemm_small_partials / gemm_small_f32_partials values.
 bool gemm_small_ahead(int bits, size_t M, size_t N);        // of the tiled products
 size_t gemm_small_partials(int bits, size_t M, size_t N, size_t K);
-size_t gemm_small_f32_partials(size_t M, size_t N, size_t K);
-// The same with quant_int of fp32 activations done in the operand fetch (8 bit, dequantizing epilogue):
+size_t gemm_small_f32_partials(int bits, size_t M, size_t N, size_t K);
+// The same with quant_int of fp32 activations done in the operand fetch (dequantizing epilogue):
 // `scale` is the multiplier (npartial == 0) or npartial partial maxima of |A|; a.qA, a.sA are not used.
-bool gemm_small_f32_supported(size_t M, size_t N, size_t K);
+bool gemm_small_f32_supported(int bits, size_t M, size_t N, size_t K);
 int launch_gemm_small_f32(const float* A, const float* scale, unsigned npartial, float* scale_out, const GemmArgs& a,
                           hipStream_t s);
 // The same for an input given as two row-major pieces side by side, [A1 (K1 columns) | A2 (a.K - K1 columns)], each with

@@ -873,6 +873,37 @@ def test_quantizing_product_column_blocks(M, N, K, given):
     assert np.array_equal(host(Y), o["Y"]) and host(am)[0] == np.abs(o["Y"]).max()
 
 
+@pytest.mark.parametrize("M,N,K,count", [
+    # one column block on four and on eight waves, two on eight, waves without a run, a half empty round, ragged rows and
+    # columns; each with its neighbour that goes through the quantizer
+    (33, 1, 32, 1), (384, 512, 512, 1), (1000, 512, 512, 1), (1025, 512, 512, 2), (70, 517, 96, 1), (70, 517, 100, 2), (200, 130, 544, 1),
+    (250, 1000, 1024, 1), (500, 1024, 1024, 1), (520, 1024, 1024, 2), (290, 500, 1056, 1), (290, 510, 2048, 1), (530, 512, 2048, 2),
+    (70, 60, 2080, 2)])
+def test_quantizing_product_int16(M, N, K, count):
+    # quant_int in the operand fetch in 16 bit: sums that wrap, ties and clipped values, infinities and NaN, max|y|; the bits of
+    # the oracle, and the number of launches (without the abs-max one)
+    p = workloads.random_problem(M + N + K + 5, M, N, K)
+    pw = mq.prepare_weight(dev(p["Wt"]), 16)
+    nb = mq.mq_linear_ws_bytes(16, M, K)
+    ws, Y = torch.full((nb,), 0x77, dtype=torch.uint8, device=DEV), torch.empty((M, N), dtype=torch.float32, device=DEV)
+    odd = p["A"].copy()
+    odd[0, :4] = [np.nan, np.inf, -np.inf, 40.0]
+    odd[M - 1, K - 1] = 0.5 / 1024
+    given = torch.full((1,), 1024.0, dtype=torch.float32, device=DEV)
+    for A, sA, bias, relu in ((p["A"], None, p["bias"], False), (odd, given, None, False), (p["A"] * 20, given, p["bias"], True),
+                              (np.zeros_like(odd), None, p["bias"], False), (p["A"] * np.float32(1e-38), None, p["bias"], True)):
+        o = oracle.linear(A, p["Wt"], 16, bias, relu, sA=None if sA is None else 1024.0)
+        am = torch.zeros(1, dtype=torch.float32, device=DEV)
+        Y.fill_(-3.0)
+        x, b = dev(A), None if bias is None else dev(bias)
+
+        def call(stream):
+            mq.mq_linear_f32(x, M, K, sA, pw.packed, pw.scale, 16, N, b, relu, Y, am, ws, nb, stream)
+
+        assert launches(call) == count + (sA is None)
+        assert np.array_equal(host(Y), o["Y"]) and host(am)[0] == np.abs(o["Y"]).max(), (M, N, K, relu)
+
+
 @pytest.mark.parametrize("bits,M,N,K,workgroups,threads", [
     (8, 384, 1024, 4096, 192, 512), (8, 512, 700, 700, 352, 512), (8, 300, 1536, 512, 480, 256), (16, 300, 1536, 512, 480, 256),
     (16, 300, 2048, 2048, 640, 256), (8, 1001, 512, 2048, 256, 512), (8, 1300, 512, 2048, 336, 512),      # split K ahead of the tiles
@@ -1285,7 +1316,8 @@ def test_a_variant_named_by_another_thread_changes_no_result(bits, M, d, f):
     assert int(wrong) == 0
 
 
-@pytest.mark.parametrize("M,d,f", [(1, 1, 1), (37, 64, 200), (300, 256, 520), (2100, 512, 96)])
+@pytest.mark.parametrize("M,d,f", [(1, 1, 1), (37, 64, 200), (300, 256, 520), (2100, 512, 96), (1, 32, 16400), (64, 1024, 4096),
+                                   (250, 512, 2048), (129, 1024, 300)])
 def test_ffn_int16_one_call_matches_oracle_chain(M, d, f):
     c = workloads.ffn(4, M, d, f, 0.03, 16, seed_extra=M + d + 3 * f)
     o1 = oracle.linear(c["A"], c["W1t"], 16, c["b1"], True)
