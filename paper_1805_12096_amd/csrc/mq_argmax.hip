@@ -63,22 +63,41 @@ __device__ __forceinline__ void wait_vmcnt_n(int n) {
   }
 }
 
-struct ArgmaxParams {
+struct ArgmaxParams {        // what the first loads' addresses need in the first 64 bytes
   const uint8_t* packedA;   // hidden states, packed 8 bit [M x K] (or, ROWM, plain rows of K bytes)
   const uint8_t* packedW;   // embedding, packed 8 bit [N x K]
   unsigned M, N, K;
-  unsigned long long* partial;   // BEAM == 1: [gridDim.x][Mpad], Mpad = M rounded up to 16; beam search: [M][gridDim.x][BEAM]
-  const int32_t* shortlist;      // optional: vocabulary rows to score, ascending; NULL = all N rows
   unsigned L;                    // candidates: shortlist length, or N
-  // beam search (BEAM > 1): partial holds [M][gridDim.x][BEAM] keys, norm [M][gridDim.x] (max, sum) pairs of
+  // `columns` workgroups share the vocabulary.  More rows than one workgroup's registers hold: they do for every chunk of
+  // chunk_rows rows (a multiple of 16) out of M; everything else describes all rows of the launch.
+  unsigned columns;
+  unsigned units_each, units_more;      // units of 16 candidates: every column has units_each, the first units_more one more
+  unsigned chunk_rows;
+  // which column and chunk a workgroup is (see chunk_of): side_by_side is 0 or all ones, inner the columns or the chunks and
+  // by_inner = ceil(2^32 / inner) (as 32 bits 0 for inner = 1, which is one workgroup alone: all come out 0)
+  unsigned workgroups, side_by_side, inner, by_inner;
+  const int32_t* shortlist;      // optional: vocabulary rows to score, ascending; NULL = all N rows
+  unsigned long long* partial;   // BEAM == 1: [columns][Mpad], Mpad = M rounded up to 16; beam search: [M][columns][BEAM]
+  // beam search (BEAM > 1): partial holds [M][columns][BEAM] keys, norm [M][columns] (max, sum) pairs of
   // the softmax normaliser in base 2, u2 = log2(e) / (sA sW) is formed in the kernel
   float2* norm;
   const float* sA;
   const float* sW;
-  // more rows than one workgroup's registers hold: the grid's y index picks a chunk of chunk_rows rows (a multiple of
-  // 16) out of M; everything above describes all rows of the launch
-  unsigned chunk_rows;
 };
+
+// Column (of the vocabulary) and chunk (of the rows) of this workgroup.  The chunks of a column read the same units and belong on
+// one XCD, whose L2 then takes the units in once for all of them.  Column after column (chunk y of column x on XCD (y columns +
+// x) % 8) does that where the columns are a multiple of eight (two and four chunks); there it stays (500 rows greedy 13.2 us, 14.0 in the order
+// below).  Elsewhere every chunk took the units from the last-level cache: 1200 rows, k = 4 (five chunks of 51 columns) 41.3 ->
+// 38.8 us, 1000 rows greedy (three of 85) 22.4 -> 20.7, 600 rows of width 1024 31.2 -> 30.0.
+// (One row of workgroups: column + columns chunk, or, with `side_by_side`, chunk + chunks column after the XCD remap.  All by
+// arithmetic: a branch, or what the compiler makes one of, splits the loads of the arguments.)
+__device__ __forceinline__ void chunk_of(const ArgmaxParams& p, unsigned& column, unsigned& chunk) {
+  const unsigned id = blockIdx.x, t = id ^ ((xcd_remap(id, p.workgroups) ^ id) & p.side_by_side);
+  const unsigned q = (unsigned)(((unsigned long long)t * p.by_inner) >> 32), swap = (q ^ (t - q * p.inner)) & p.side_by_side;
+  column = (t - q * p.inner) ^ swap;
+  chunk = q ^ swap;
+}
 
 // What lane l feeds to the 16x16x64 MFMA for rows 16 u .. 16 u + 15 of a packed
 // 8-bit operand and K group g (64 elements): K quarter l / 16 of the group lives
@@ -127,12 +146,16 @@ __device__ __forceinline__ void merge_sorted(unsigned long long (&top)[BEAM], co
 //   * every candidate of the stage before is worked off between two groups of matrix instructions of its own.
 // 1200 rows, k = 4, 36 000 words, with the quantizer and the reduce kernel: 84.7 us with maximum / minimum pairs, a
 // rescaled sum and every chunk of 256 rows spread over all compute units; 52.3 us with the above and the chunks sharing
-// them (launch_topk_stream); 48.3 us with sorted lists merged instead of inserted one by one at the end.  240 rows:
+// them (launch_topk_stream); 48.3 us with sorted lists merged instead of inserted one by one at the end (42 with what follows below).  240 rows:
 // 29.1 -> 26.2 us.  What is left per unit: 0.27 us of LDS reads and waits, 0.13 of matrix instructions, 0.21 of these.
 // Greedy, 36 000 words, kernels of a captured step (quantizer included): 300 sentences of width 512 17.6 -> 16.9 us (the
 // 19th of 24 tile slots' operands no longer fetched for nothing, reduce kernel), 600 sentences against 50 000 words 34.8
 // -> 24.9 us (chunks that share the compute units instead of one launch pair after the other), 300 sentences of width
 // 1024 41.9 -> 31.3 us (the tiled kernel's arg-max epilogue took 32.7 us of them, this one 20).
+// Stages that refill the ring (more than nine units to a workgroup; captured calls, quantizer not counted): addresses and slots
+// by addition, and the updates held between the matrix instructions (see `refill` and `here`): 1200 rows, k = 4 43.9 -> 41.3 us,
+// k = 2 38.8 -> 35.5, 300 rows of width 1024 22.4 -> 20.7; chunks that share XCDs (chunk_of) 41.3 -> 38.8 and 35.5 -> 32.5; the
+// tag as a scalar, and no division in front of the first load, 38.8 -> 37.9, 32.5 -> 31.8, 20.6 -> 19.7.
 // KG: 64-element K groups held (8: K <= 512, 16: K <= 1024).  ROWM: the hidden states are plain rows (K a multiple of
 // 16) instead of packed ones; only the addresses of the operand loads differ.
 template <int TPW, bool GATHER, int BEAM = 1, int KG = kKG, bool ROWM = false>
@@ -147,13 +170,14 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
 
   const int lane = threadIdx.x % 64;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-  const unsigned row0 = blockIdx.y * p.chunk_rows;    // this workgroup's rows: row0 .. row0 + rows - 1
+  unsigned column, chunk;
+  chunk_of(p, column, chunk);
+  const unsigned row0 = chunk * p.chunk_rows;         // this workgroup's rows: row0 .. row0 + rows - 1
   const unsigned rows = p.M - row0 < p.chunk_rows ? p.M - row0 : p.chunk_rows;
   const PackedDims dA(8, p.M, p.K), dW(8, p.N, p.K);
   const unsigned kgroups = (unsigned)(dW.kfrags / 2);          // real K groups (<= KG)
-  const unsigned nunits = GATHER ? (p.L + 15) / 16 : (unsigned)(dW.nblocks * 2);   // 16-candidate units
-  const unsigned first = blockIdx.x, stride = gridDim.x;
-  const unsigned nlocal = (nunits - first + stride - 1) / stride;      // the grid has at most nunits columns: at least 1
+  const unsigned first = column, stride = p.columns;
+  const unsigned nlocal = p.units_each + (first < p.units_more ? 1u : 0u);      // at most as many columns as units: at least 1
   const unsigned lane_off = operand16_lane_offset(lane);
 
   // stage s of the pipeline = 512 elements of K (part s % NH) of this workgroup's (s / NH)-th unit; wave w copies the
@@ -172,6 +196,8 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
     }
     __syncthreads();
   }
+  // A value that has to be there at this point of the program.
+  auto here = [](auto& x) { asm volatile("" : "+v"(x)); };
   // One load per wave for stage s.  Past the workgroup's last unit the same instruction fetches unit 0 again into a
   // per-wave slot behind the stages that nobody reads: every stage then issues exactly one load, the number of loads
   // in flight at a given point is a constant, and the waits need neither a branch nor a table.  Needs nlocal > 0.
@@ -191,6 +217,38 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
     __builtin_amdgcn_global_load_lds(
         (const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
   };
+  // The same for the stages that refill freed slots, one unit after the other: the unit's row, its slot and the address advance by
+  // additions (a unit's offset is below 2^32: 255 x 256 units of 16 rows, 127 x 256 for K > 512).  Divisions and 64-bit products
+  // for every load were 40 scalar instructions of a stage that each wave issues in line with its matrix instructions.
+  unsigned fill_index = 0, fill_unit = 0, fill_slot = 0;
+  const unsigned row_pitch = (unsigned)dW.kfrags * kFragBytes;
+  unsigned fill_group[NH];
+#pragma unroll
+  for (int h = 0; h < NH; ++h) fill_group[h] = min((unsigned)(h * kKG) + wave, kgroups - 1) * (2 * kFragBytes);
+  auto start_refills = [&](unsigned index) {
+    fill_index = index;
+    fill_unit = first + index * stride;
+    fill_slot = (index * NH) % S * STAGE;
+  };
+  auto refill = [&]() {
+    const bool real = fill_index < nlocal;
+    const unsigned dst = real ? fill_slot + wave * kFragBytes : S * STAGE + wave * kFragBytes;
+    if (GATHER) {
+      issue(fill_index);                               // (NH == 1)
+    } else {
+      const unsigned unit = real ? fill_unit : first, at = (unit / 2) * row_pitch + (unit % 2) * 256;
+#pragma unroll
+      for (int h = 0; h < NH; ++h)
+        __builtin_amdgcn_global_load_lds(
+            (const __attribute__((address_space(1))) void*)(p.packedW + (at + fill_group[h]) + lane_off),
+            (__attribute__((address_space(3))) void*)(smem + (dst + (real ? h * STAGE : 0))), 16, 0, 0);
+    }
+    ++fill_index;
+    fill_unit += stride;
+    fill_slot += NH * STAGE;
+    if (fill_slot == S * STAGE) fill_slot = 0;
+  };
+  static_assert(!GATHER || NH == 1, "gathered units are one stage");
   // The first two stages go out first (their memory latency is the longest wait of the kernel), then the
   // hidden-state operands of this wave's sentence tiles (tile t = wave + 8 i covers sentences 16 t ..
   // 16 t + 15; they come from L2, every workgroup reads the same ones), then the remaining stages.  The
@@ -343,17 +401,19 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
     // One stage: 512 elements of K of a unit (in `e`) against this wave's NT sentence tiles into `cur`, while the
     // maxima are updated from `prev` (the sums of the unit before) and the next stage is read from LDS into `enext`.
     // The update's VALU work is cut into slices that sit between the MFMA groups, so it runs while the matrix pipeline
-    // is busy instead of after it; the scheduling fences keep that order.
-    // refill_tag: the freed slot takes a new load; first_tag: unit 0, which has no unit before it; part_tag: s % NH.
-    auto stage = [&](auto refill_tag, auto first_tag, auto part_tag, int newest, unsigned s, v4i (&cur)[TPW],
+    // is busy instead of after it; the scheduling fences keep that order inside a block, and `here` keeps the compiler from
+    // moving the updates of a trip's second stage behind the branch that follows it, where the waves of a SIMD, which are in
+    // step, would all come to them with their matrix instructions done.
+    // refill_tag: the freed slot takes a new load; first_tag: unit 0, which has no unit before it; part_tag: s % NH;
+    // unit: this workgroup's; next_slot: where the next stage is.
+    auto stage = [&](auto refill_tag, auto first_tag, auto part_tag, int newest, unsigned unit, unsigned next_slot, v4i (&cur)[TPW],
                      const v4i (&prev)[TPW], const v4i (&e)[kKG], v4i (&enext)[kKG]) {
       constexpr int PART = decltype(part_tag)::value;
       constexpr bool FIRST = decltype(first_tag)::value;
       if constexpr (PART == 0) {
         land(newest);
         // everybody is past stage s - 1 (and has its copy of stage s in registers), so slot s - 1 can be refilled
-        if constexpr (NH > 1) issue(s + S - 2);
-        if constexpr (decltype(refill_tag)::value) issue(s + S - 1);
+        if constexpr (decltype(refill_tag)::value) refill();
       } else {
         __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0), see land
         asm volatile("" ::: "memory");
@@ -361,8 +421,11 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
       // the next stage's LDS reads go two at a time between the first MFMA groups: eight in a row would fill the LDS
       // queue (all eight waves read at the same time) and hold this wave's MFMAs back behind them, and they should be
       // back before the next barrier (after the last stage they read a finished slot again and the result is unused)
-      const uint8_t* nx = smem + ((s + 1) % S) * STAGE + lane * 16;
-      const int prev_tag = TAGS + 1 - (int)(s / NH);     // TAGS - (unit - 1); unused garbage for unit 0 (prev holds "none")
+      const uint8_t* nx = smem + next_slot + lane * 16;
+      // TAGS - (unit - 1), in a scalar register (masked together with each sum's shift it was an instruction more a key); unused
+      // garbage for unit 0 (prev holds "none")
+      int prev_tag = (TAGS + 1 - (int)unit) & TAGS;
+      if constexpr (decltype(refill_tag)::value || PART != 0) asm("" : "+s"(prev_tag));
       constexpr int ITEMS = NT * 4, PER = (ITEMS + KG - 1) / KG;
       const v4i zero = {0, 0, 0, 0};
 #pragma unroll
@@ -377,8 +440,10 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
         constexpr int J0 = PART * kKG;
         if constexpr (BEAM == 1) {
 #pragma unroll
-          for (int j = (J0 + g) * PER; j < (J0 + g + 1) * PER && j < ITEMS; ++j)
-            best[j / 4][j % 4] = max(best[j / 4][j % 4], (prev[j / 4][j % 4] << SHIFT) | (prev_tag & TAGS));
+          for (int j = (J0 + g) * PER; j < (J0 + g + 1) * PER && j < ITEMS; ++j) {
+            best[j / 4][j % 4] = max(best[j / 4][j % 4], (prev[j / 4][j % 4] << SHIFT) | prev_tag);
+            if constexpr (decltype(refill_tag)::value || PART != 0) here(best[j / 4][j % 4]);
+          }
         } else if constexpr (!FIRST) {
           // exponents of the unit before (norm_expo) are formed in the first group
           if (g == 0) {
@@ -387,8 +452,12 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
           }
 #pragma unroll
           for (int j = (J0 + g) * PER; j < (J0 + g + 1) * PER && j < ITEMS; ++j) {
-            beam_insert(j / 4, j % 4, (prev[j / 4][j % 4] << SHIFT) | (prev_tag & TAGS));
+            beam_insert(j / 4, j % 4, (prev[j / 4][j % 4] << SHIFT) | prev_tag);
             norm_sum[j / 4] += __builtin_amdgcn_exp2f(norm_expo[j / 4][j % 4]);
+            here(best[j / 4][j % 4]);
+#pragma unroll
+            for (int b = 0; b < BEAM - 1; ++b) here(more_best[j / 4][j % 4][b]);
+            here(norm_sum[j / 4]);
           }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -402,23 +471,33 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
       for (int s = 0; s < S - 1; ++s) {
         if ((unsigned)s >= nlocal) break;
         const int newest = S - 3 - s > 0 ? S - 3 - s : 0;
-        if (s == 0) stage(F{}, T{}, P0{}, newest, 0u, acc0, acc1, e0, e1);
-        else if (s % 2 == 0) stage(F{}, F{}, P0{}, newest, (unsigned)s, acc0, acc1, e0, e1);
-        else stage(F{}, F{}, P0{}, newest, (unsigned)s, acc1, acc0, e1, e0);
-      }
-    } else if constexpr (NH == 1) {
-      stage(T{}, T{}, P0{}, S - 3, 0u, acc0, acc1, e0, e1);
-      for (unsigned s = 1; s < nlocal; s += 2) {
-        stage(T{}, F{}, P0{}, S - 3, s, acc1, acc0, e1, e0);
-        if (s + 1 < nlocal) stage(T{}, F{}, P0{}, S - 3, s + 1, acc0, acc1, e0, e1);
+        const unsigned slot = (unsigned)((s + 1) % S * STAGE);
+        if (s == 0) stage(F{}, T{}, P0{}, newest, 0u, slot, acc0, acc1, e0, e1);
+        else if (s % 2 == 0) stage(F{}, F{}, P0{}, newest, (unsigned)s, slot, acc0, acc1, e0, e1);
+        else stage(F{}, F{}, P0{}, newest, (unsigned)s, slot, acc1, acc0, e1, e0);
       }
     } else {
-      for (unsigned n = 0; n < nlocal; n += 2) {
-        stage(T{}, F{}, P0{}, S - 5, 2 * n, acc0, acc1, e0, e1);
-        stage(T{}, F{}, P1{}, 0, 2 * n + 1, acc0, acc1, e1, e0);
-        if (n + 1 < nlocal) {
-          stage(T{}, F{}, P0{}, S - 5, 2 * n + 2, acc1, acc0, e0, e1);
-          stage(T{}, F{}, P1{}, 0, 2 * n + 3, acc1, acc0, e1, e0);
+      start_refills(NH == 1 ? S - 1 : (S - 2) / NH);
+      unsigned slot = 0;
+      auto next = [&]() {
+        slot += STAGE;
+        if (slot == S * STAGE) slot = 0;
+        return slot;
+      };
+      if constexpr (NH == 1) {
+        stage(T{}, T{}, P0{}, S - 3, 0u, next(), acc0, acc1, e0, e1);
+        for (unsigned s = 1; s < nlocal; s += 2) {
+          stage(T{}, F{}, P0{}, S - 3, s, next(), acc1, acc0, e1, e0);
+          if (s + 1 < nlocal) stage(T{}, F{}, P0{}, S - 3, s + 1, next(), acc0, acc1, e0, e1);
+        }
+      } else {
+        for (unsigned n = 0; n < nlocal; n += 2) {
+          stage(T{}, F{}, P0{}, S - 5, n, next(), acc0, acc1, e0, e1);
+          stage(T{}, F{}, P1{}, 0, n, next(), acc0, acc1, e1, e0);
+          if (n + 1 < nlocal) {
+            stage(T{}, F{}, P0{}, S - 5, n + 1, next(), acc1, acc0, e0, e1);
+            stage(T{}, F{}, P1{}, 0, n + 1, next(), acc1, acc0, e1, e0);
+          }
         }
       }
     }
@@ -511,7 +590,7 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
       }
       const unsigned m = (wave + kWaves * i) * 16 + lane % 16;
       if (lane < 16 && m < rows && i < ntl) {
-        const size_t at = (size_t)(row0 + m) * gridDim.x + blockIdx.x;
+        const size_t at = (size_t)(row0 + m) * p.columns + column;
 #pragma unroll
         for (int j = 0; j < BEAM; ++j) p.partial[at * BEAM + j] = top[j];
         p.norm[at] = make_float2(mx, sm);
@@ -541,7 +620,7 @@ __global__ __launch_bounds__(kWaves * 64) void k_argmax_stream(const ArgmaxParam
     if (o > key) key = o;
     const unsigned m = (wave + kWaves * i) * 16 + lane % 16;
     // this workgroup's keys are consecutive in memory: the 16 lanes of a sentence tile fill one 128-byte line
-    if (lane < 16 && m < rows) p.partial[(size_t)blockIdx.x * (((size_t)p.M + 15) / 16 * 16) + row0 + m] = key;
+    if (lane < 16 && m < rows) p.partial[(size_t)column * (((size_t)p.M + 15) / 16 * 16) + row0 + m] = key;
   }
 }
 
@@ -681,7 +760,7 @@ __global__ __launch_bounds__(256) void k_topk_reduce(const unsigned long long* _
 }
 
 template <int TPW, bool GATHER, int BEAM = 1, int KG = kKG, bool ROWM = false>
-int launch_stream(const ArgmaxParams& p, unsigned grid, hipStream_t s, unsigned ny = 1) {
+int launch_stream(ArgmaxParams p, unsigned grid, hipStream_t s, unsigned ny = 1) {
   constexpr size_t smem = (size_t)stages_of(KG) * kKG * kFragBytes + (size_t)kWaves * kFragBytes +
                           (GATHER ? max_units_of(KG) * 16 * sizeof(int32_t) : 0);
   static_assert(smem <= 160 * 1024, "LDS budget");
@@ -693,7 +772,17 @@ int launch_stream(const ArgmaxParams& p, unsigned grid, hipStream_t s, unsigned 
     if (rc != MQ_OK) return rc;
     attr_done = true;
   }
-  hipLaunchKernelGGL(kern, dim3(grid, ny), dim3(kWaves * 64), smem, s, p);
+  // (t / d is the high half of t ceil(2^32 / d) while t d < 2^32: 256 columns at most, and up to 65535 chunks)
+  const bool side_by_side = grid % 8 != 0 && ny > 1 && (size_t)grid * ny * ny < ((size_t)1 << 32);
+  const unsigned units = GATHER ? (p.L + 15) / 16 : (unsigned)(PackedDims(8, p.N, p.K).nblocks * 2);
+  p.columns = grid;
+  p.units_each = units / grid;
+  p.units_more = units % grid;
+  p.workgroups = grid * ny;
+  p.side_by_side = side_by_side ? ~0u : 0u;
+  p.inner = side_by_side ? ny : grid;
+  p.by_inner = (unsigned)((((unsigned long long)1 << 32) + p.inner - 1) / p.inner);
+  hipLaunchKernelGGL(kern, dim3(grid * ny), dim3(kWaves * 64), smem, s, p);
   return check_hip(hipGetLastError());
 }
 

@@ -2026,6 +2026,35 @@ def test_beam_output_layer_growing_logits(M, V, k):
     assert np.allclose(lp, o["logprob"], rtol=0, atol=1e-4)
 
 
+@pytest.mark.parametrize("M,columns,units,more", [
+    # around the ring of ten slots (9 units: nothing is refilled; 10: a refill that nobody reads), once and twice round it, with
+    # an even and an odd number of units and columns of both lengths; one chunk of rows, and three whose 85 columns share XCDs
+    (5, 256, 9, 0), (5, 256, 9, 3), (5, 256, 10, 0), (5, 256, 11, 255), (5, 256, 19, 1), (5, 256, 20, 0), (5, 256, 21, 7),
+    (780, 85, 10, 84), (780, 85, 21, 1)])
+def test_output_layer_units_of_a_workgroup(M, columns, units, more):
+    V, d = 16 * (columns * units + more) - 3, 32
+    c = workloads.config3(M=M, V=V, d=d, seed_extra=units + more)
+    E = c["E"].copy()
+    top = np.abs(E).max()
+    for j, u in enumerate(sorted({0, units - 1, units, 9, 10})):       # best words of the last sentences in these units
+        at = 16 * columns * u + 16 * (more // 2) + j
+        if at < V:
+            E[at] = c["Hd"][M - 1 - j] * (top / np.abs(c["Hd"][M - 1 - j]).max())
+    o = oracle.greedy_output_layer(c["Hd"], E)
+    tok, val = gpu_greedy_packed(c["Hd"], E)
+    assert np.array_equal(tok, o["tok"]) and np.array_equal(val, o["maxlogit"])
+    if M < 100:
+        for k in (2, 4):
+            o = oracle.topk_log_softmax(c["Hd"], E, k)
+            tok, lp = gpu_topk(c["Hd"], E, k)
+            assert np.array_equal(tok, o["tok"]) and np.allclose(lp, o["logprob"], rtol=0, atol=1e-4)
+        wide = np.zeros((M, 528), dtype=np.float32), np.zeros((V, 528), dtype=np.float32)      # two stages a unit, 18 slots
+        wide[0][:, 496:], wide[1][:, 496:] = c["Hd"], E
+        o = oracle.greedy_output_layer(*wide)
+        tok, val = gpu_greedy(*wide)[:2]
+        assert np.array_equal(tok, o["tok"]) and np.array_equal(val, o["maxlogit"])
+
+
 @pytest.mark.parametrize("k", [2, 4])
 @pytest.mark.parametrize("V,L", [(9000, 1234), (120000, 60000)])     # the longer list refills the ring's slots
 def test_beam_output_layer_with_shortlist(k, V, L):
