@@ -5,6 +5,7 @@
 
 #include "mq_grid_max.h"
 #include "mq_internal.h"
+#include "mq_tiles.h"
 
 namespace mq {
 
@@ -251,28 +252,43 @@ int launch_quantize(const float* x, size_t rows, size_t cols, int bits, const fl
 namespace mq {
 namespace {
 
+// This workgroup's place in the order of the data: its index, or with by_xcd (all ones; else zero) the XCDs' shares one after the
+// other.  (By arithmetic: a branch splits the loads of the arguments, 0.15 us of a small quantizer.)
+__device__ __forceinline__ unsigned block_of(unsigned by_xcd) {
+  return blockIdx.x ^ ((xcd_remap(blockIdx.x, gridDim.x) ^ blockIdx.x) & by_xcd);
+}
+
 // Abs-max without atomics or initialisation: block b writes its maximum to partial[b];
-// the consumer reduces the few hundred values itself (block_max_of_partials).
+// the consumer reduces the few hundred values itself (block_max_of_partials).  The blocks walk through the tensor together, one
+// piece of 256 vectors after the other; where the quantizer takes its rows in eighths of the tensor (by_eighths), every block takes
+// one run and every XCD an eighth of the tensor.
 constexpr int kAbsmaxFlight = 4;
-__global__ __launch_bounds__(kThreads) void k_absmax_partial(const float* __restrict__ x, size_t n,
-                                                             float* __restrict__ partial, unsigned* clear, unsigned nclear) {
+// (pitch, span, step: a block's vectors of four are pitch block .. + span - 1, looked at 256 at a time, step apart; from the
+// host: a 64-bit division in front of the loads is 0.1 us)
+__global__ __launch_bounds__(kThreads) void k_absmax_partial(const float* __restrict__ x, size_t n, size_t pitch,
+                                                             size_t span, size_t step,
+                                                             float* __restrict__ partial, unsigned* clear, unsigned nclear,
+                                                             unsigned by_xcd) {
+  // all arguments at once: the condition below would split their loads, a trip to memory each
+  asm volatile("" ::"s"(x), "s"(n), "s"(pitch), "s"(span), "s"(step), "s"(by_xcd), "s"(gridDim.x));
   if (clear != nullptr && blockIdx.x == 0)                 // a later kernel's counters
     for (unsigned i = threadIdx.x; i < nclear; i += kThreads) clear[i] = 0u;
-  const size_t tid = (size_t)blockIdx.x * kThreads + threadIdx.x;
-  const size_t nthreads = (size_t)gridDim.x * kThreads;
   const size_t nvec = n / 4;
+  const unsigned block = block_of(by_xcd);
+  const size_t first = block * pitch;
+  const size_t end = first + span < nvec ? first + span : nvec;
   const float4* xv = reinterpret_cast<const float4*>(x);
   float m0 = 0.f;
   // kAbsmaxFlight loads in flight per thread (past the end: the last vector again, which changes nothing)
-  for (size_t i = tid; i < nvec; i += kAbsmaxFlight * nthreads) {
+  for (size_t i = first + threadIdx.x; i < end; i += kAbsmaxFlight * step) {
     float4 a[kAbsmaxFlight];
 #pragma unroll
-    for (int t = 0; t < kAbsmaxFlight; ++t) a[t] = xv[i + t * nthreads < nvec ? i + t * nthreads : nvec - 1];
+    for (int t = 0; t < kAbsmaxFlight; ++t) a[t] = xv[i + t * step < end ? i + t * step : end - 1];
 #pragma unroll
     for (int t = 0; t < kAbsmaxFlight; ++t)
       m0 = fmaxf(m0, fmaxf(fmaxf(fabsf(a[t].x), fabsf(a[t].y)), fmaxf(fabsf(a[t].z), fabsf(a[t].w))));
   }
-  for (size_t j = nvec * 4 + tid; j < n; j += nthreads) m0 = fmaxf(m0, fabsf(x[j]));
+  if (block == gridDim.x - 1 && nvec * 4 + threadIdx.x < n) m0 = fmaxf(m0, fabsf(x[nvec * 4 + threadIdx.x]));
   const float m = __uint_as_float(wave_max_u32(__float_as_uint(m0)));
   __shared__ float part[kThreads / kWave];
   const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
@@ -372,9 +388,11 @@ __global__ __launch_bounds__(W * kWave) void k_quantize_pack(const float* __rest
                                                             size_t cols, const float* __restrict__ scale,
                                                             uint8_t* __restrict__ packed, unsigned ksplit,
                                                             unsigned npartial, float* __restrict__ scale_out,
-                                                            unsigned* __restrict__ clear, unsigned nclear) {
-  // words a later kernel wants zero (spread over the grid: one workgroup walking through them is a serial tail)
+                                                            unsigned* __restrict__ clear, unsigned nclear, unsigned by_xcd) {
   constexpr unsigned kT = W * kWave;
+  // all arguments at once: the loop's condition would split their loads, a trip to memory each
+  asm volatile("" ::"s"(x), "s"(rows), "s"(cols), "s"(ksplit), "s"(by_xcd), "s"(gridDim.x));
+  // words a later kernel wants zero (spread over the grid: one workgroup walking through them is a serial tail)
   for (unsigned i = blockIdx.x * kT + threadIdx.x; i < nclear; i += gridDim.x * kT) clear[i] = 0u;
   const PackedDims d(BITS, rows, cols);
   const int lim = BITS == 8 ? 127 : 32767;
@@ -383,7 +401,7 @@ __global__ __launch_bounds__(W * kWave) void k_quantize_pack(const float* __rest
   // (indexes of fragments, row groups and items fit 32 bits: rows and columns are below 2^31, items below 2^29 x 16)
   const unsigned kfrags = (unsigned)d.kfrags, row_groups = (unsigned)(d.Np / 8);
   const unsigned wave_in = threadIdx.x / kWave;
-  const unsigned wave = blockIdx.x * W + wave_in;
+  const unsigned block = block_of(by_xcd), wave = block * W + wave_in;
   const unsigned nwaves = gridDim.x * W;
   const unsigned shift = 31 - __builtin_clz(ksplit);     // (a power of two)
   const unsigned per = (kfrags + ksplit - 1) >> shift;   // fragments along K per work item
@@ -391,7 +409,7 @@ __global__ __launch_bounds__(W * kWave) void k_quantize_pack(const float* __rest
   // flight of one wave per row group, which leaves a chip with a thousand row groups at four waves per compute
   // unit), and the rows' sums meet in LDS.  ksplit is the number of waves of the workgroup then (see pack_split).
   const bool shared_rows = BITS == 16 && ksplit > 1;
-  unsigned rg = shared_rows ? blockIdx.x : wave >> shift, part = shared_rows ? wave_in : wave & (ksplit - 1);
+  unsigned rg = shared_rows ? block : wave >> shift, part = shared_rows ? wave_in : wave & (ksplit - 1);
   const unsigned ncols = (unsigned)cols, nrows = (unsigned)rows;
   float4 v[kQuantFlight];
   auto load = [&](unsigned kb0) {
@@ -433,7 +451,7 @@ __global__ __launch_bounds__(W * kWave) void k_quantize_pack(const float* __rest
   if (shared_rows) {
     __shared__ int s_part[W][8];
     for (; rg < row_groups; rg += gridDim.x) {
-      if (rg != blockIdx.x) load(part * per);
+      if (rg != block) load(part * per);
       const int sum = convert();
       if (sub == 0) s_part[part][lane / 8] = sum;
       __syncthreads();
@@ -574,6 +592,14 @@ __global__ __launch_bounds__(512) void k_absmax_quantize_pack(const float* __res
 
 }  // namespace
 
+// What the launch before has read on the same XCD comes from its L2 (20 MB in 2.2 us instead of 4.4).  Abs-max, quantizer and
+// product in 8 bit: 8192 x 1024 x 1024 30.5 -> 28.5 us, 4000 x 512 x 2048 25.3 -> 23.7, in 16 bit 8192 x 512 x 512 23.0 -> 22.0.  16 bit above 48
+// MB, more than the L2s hold, keeps the other order (8192 x 1024 x 4096 165 us, in eighths 167), and so do inputs below 4 MB,
+// whose split-K products share rows between XCDs (8-bit block of 1001 rows, 512 / 2048, 17.7 and 17.9; first product of the 16-bit
+// block of 300 rows 6.6 and 7.4), and inputs some product has written, whose XCDs held columns as well (the 16-bit block of 3000
+// rows, 512 / 2048, 54.8 and 55.7).
+bool by_eighths(int bits, size_t n) { return n >= ((size_t)1 << 20) && (bits == 8 || n <= ((size_t)12 << 20)); }
+
 namespace {
 // How many waves share a row group along K and, for 16 bit, how many a workgroup has.  8 bit: split K so that even a 300-row
 // batch fills the chip.  16 bit: the rows' sums have to meet in one workgroup, rows of 512 elements or more are shared by its
@@ -599,9 +625,11 @@ PackSplit pack_split(int bits, const PackedDims& d) {
 }
 
 // FROM_PARTIALS: `scale` holds `npartial` partial maxima and scale_out receives the multiplier (see the kernel).
+// by_xcd: rows go to the XCDs in eighths (by_eighths), as k_absmax_partial deals them and the products' bands of tiles expect
+// them; otherwise row groups go round the XCDs.
 template <bool FROM_PARTIALS>
 int launch_pack(const float* x, size_t rows, size_t cols, int bits, const float* scale, unsigned npartial, float* scale_out,
-                void* packed, unsigned* clear, unsigned nclear, hipStream_t s) {
+                void* packed, unsigned* clear, unsigned nclear, bool by_xcd, hipStream_t s) {
   const PackedDims d(bits, rows, cols);
   const size_t row_groups = d.Np / 8;
   const PackSplit sp = pack_split(bits, d);
@@ -609,7 +637,7 @@ int launch_pack(const float* x, size_t rows, size_t cols, int bits, const float*
   const Cols kind = cols_kind(cols);
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3(grid), dim3(sp.waves * kWave), 0, s, x, rows, cols, scale, static_cast<uint8_t*>(packed),
-                       sp.ksplit, npartial, scale_out, clear, nclear);
+                       sp.ksplit, npartial, scale_out, clear, nclear, by_xcd ? ~0u : 0u);
   };
   auto by_kind = [&](auto bits_tag, auto waves_tag) {
     constexpr int B = decltype(bits_tag)::value, W = decltype(waves_tag)::value;
@@ -627,7 +655,7 @@ int launch_pack(const float* x, size_t rows, size_t cols, int bits, const float*
 
 int launch_quantize_pack(const float* x, size_t rows, size_t cols, int bits, const float* scale,
                          void* packed, hipStream_t s, unsigned* clear, unsigned nclear) {
-  return launch_pack<false>(x, rows, cols, bits, scale, 0u, nullptr, packed, clear, nclear, s);
+  return launch_pack<false>(x, rows, cols, bits, scale, 0u, nullptr, packed, clear, nclear, by_eighths(bits, rows * cols), s);
 }
 
 int launch_fill_pattern(void* p, size_t bytes, unsigned seed, hipStream_t s) {
@@ -648,7 +676,7 @@ int launch_clear_words(unsigned* p, unsigned n, hipStream_t s) {
 // maxima (one is enough: a single max|x| in device memory); scale_out[0] receives the multiplier.
 int launch_quantize_pack_partials(const float* x, size_t rows, size_t cols, int bits, const float* partials,
                                   unsigned npartials, float* scale_out, void* packed, hipStream_t s) {
-  return launch_pack<true>(x, rows, cols, bits, partials, npartials, scale_out, packed, nullptr, 0u, s);
+  return launch_pack<true>(x, rows, cols, bits, partials, npartials, scale_out, packed, nullptr, 0u, false, s);
 }
 
 namespace {
@@ -722,19 +750,25 @@ int launch_absmax_quantize_pack_fused(const float* x, size_t rows, size_t cols, 
 // partial maxima to `partials` (kAbsmaxPartials floats), then quantization with the multiplier
 // formed from them; scale_out[0] receives the multiplier.
 // Partial maxima of |x| only (at most kAbsmaxPartials of them); *count receives how many were written.
-int launch_absmax_partials(const float* x, size_t n, float* partials, unsigned* count, hipStream_t s) {
+namespace {
+unsigned launch_absmax_blocks(const float* x, size_t n, float* partials, unsigned* clear, unsigned nclear, bool by_xcd, hipStream_t s) {
   const unsigned g1 = grid_for(n, (size_t)kThreads * 8, kAbsmaxPartials);
-  hipLaunchKernelGGL(k_absmax_partial, dim3(g1), dim3(kThreads), 0, s, x, n, partials, (unsigned*)nullptr, 0u);
-  *count = g1;
+  const size_t share = (n / 4 + g1 - 1) / g1;
+  hipLaunchKernelGGL(k_absmax_partial, dim3(g1), dim3(kThreads), 0, s, x, n, by_xcd ? share : (size_t)kThreads, by_xcd ? share : n,
+                     by_xcd ? (size_t)kThreads : (size_t)kThreads * g1, partials, clear, nclear, by_xcd ? ~0u : 0u);
+  return g1;
+}
+}  // namespace
+int launch_absmax_partials(const float* x, size_t n, float* partials, unsigned* count, hipStream_t s) {
+  *count = launch_absmax_blocks(x, n, partials, nullptr, 0u, false, s);
   return check_hip(hipGetLastError());
 }
 
 int launch_absmax_quantize_pack(const float* x, size_t rows, size_t cols, int bits, float* partials,
                                 float* scale_out, void* packed, hipStream_t s, unsigned* clear, unsigned nclear) {
   const size_t n = rows * cols;
-  const unsigned g1 = grid_for(n, (size_t)kThreads * 8, kAbsmaxPartials);
-  hipLaunchKernelGGL(k_absmax_partial, dim3(g1), dim3(kThreads), 0, s, x, n, partials, clear, nclear);
-  return launch_quantize_pack_partials(x, rows, cols, bits, partials, g1, scale_out, packed, s);
+  const unsigned g1 = launch_absmax_blocks(x, n, partials, clear, nclear, by_eighths(bits, n), s);
+  return launch_pack<true>(x, rows, cols, bits, partials, g1, scale_out, packed, nullptr, 0u, by_eighths(bits, n), s);
 }
 
 }  // namespace mq
