@@ -252,31 +252,25 @@ int launch_quantize(const float* x, size_t rows, size_t cols, int bits, const fl
 namespace mq {
 namespace {
 
-// This workgroup's place in the order of the data: its index, or with by_xcd (all ones; else zero) the XCDs' shares one after the
-// other.  (By arithmetic: a branch splits the loads of the arguments, 0.15 us of a small quantizer.)
-__device__ __forceinline__ unsigned block_of(unsigned by_xcd) {
-  return blockIdx.x ^ ((xcd_remap(blockIdx.x, gridDim.x) ^ blockIdx.x) & by_xcd);
-}
-
 // Abs-max without atomics or initialisation: block b writes its maximum to partial[b];
 // the consumer reduces the few hundred values itself (block_max_of_partials).  The blocks walk through the tensor together, one
-// piece of 256 vectors after the other; where the quantizer takes its rows in eighths of the tensor (by_eighths), every block takes
-// one run and every XCD an eighth of the tensor.
+// piece of 256 vectors after the other; BY_XCD (see by_eighths) every block takes one run of `share` vectors and every XCD an
+// eighth of the tensor.  Instances of their own, here and in the quantizer: with the order as an argument and the runs' ends
+// formed by 64-bit products in front of the first load, calls that deal nothing were 0.4 - 1 % slower (captured, 1001 x 512 x 1536
+// in 16 bit 14.96 us, now 14.83; 700 x 1024 x 1024 in 8 bit 10.81, now 10.76; 300 x 512 x 512 6.01, now 5.97).
 constexpr int kAbsmaxFlight = 4;
-// (pitch, span, step: a block's vectors of four are pitch block .. + span - 1, looked at 256 at a time, step apart; from the
-// host: a 64-bit division in front of the loads is 0.1 us)
-__global__ __launch_bounds__(kThreads) void k_absmax_partial(const float* __restrict__ x, size_t n, size_t pitch,
-                                                             size_t span, size_t step,
+template <bool BY_XCD>
+__global__ __launch_bounds__(kThreads) void k_absmax_partial(const float* __restrict__ x, size_t n,
                                                              float* __restrict__ partial, unsigned* clear, unsigned nclear,
-                                                             unsigned by_xcd) {
-  // all arguments at once: the condition below would split their loads, a trip to memory each
-  asm volatile("" ::"s"(x), "s"(n), "s"(pitch), "s"(span), "s"(step), "s"(by_xcd), "s"(gridDim.x));
+                                                             size_t share) {
+  // (all arguments at once: the condition below would split their loads, a trip to memory each)
+  if constexpr (BY_XCD) asm volatile("" ::"s"(x), "s"(n), "s"(share), "s"(gridDim.x));
   if (clear != nullptr && blockIdx.x == 0)                 // a later kernel's counters
     for (unsigned i = threadIdx.x; i < nclear; i += kThreads) clear[i] = 0u;
   const size_t nvec = n / 4;
-  const unsigned block = block_of(by_xcd);
-  const size_t first = block * pitch;
-  const size_t end = first + span < nvec ? first + span : nvec;
+  const unsigned block = BY_XCD ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x;
+  const size_t first = block * (BY_XCD ? share : (size_t)kThreads), step = BY_XCD ? (size_t)kThreads : (size_t)gridDim.x * kThreads;
+  const size_t end = BY_XCD && first + share < nvec ? first + share : nvec;
   const float4* xv = reinterpret_cast<const float4*>(x);
   float m0 = 0.f;
   // kAbsmaxFlight loads in flight per thread (past the end: the last vector again, which changes nothing)
@@ -288,7 +282,7 @@ __global__ __launch_bounds__(kThreads) void k_absmax_partial(const float* __rest
     for (int t = 0; t < kAbsmaxFlight; ++t)
       m0 = fmaxf(m0, fmaxf(fmaxf(fabsf(a[t].x), fabsf(a[t].y)), fmaxf(fabsf(a[t].z), fabsf(a[t].w))));
   }
-  if (block == gridDim.x - 1 && nvec * 4 + threadIdx.x < n) m0 = fmaxf(m0, fabsf(x[nvec * 4 + threadIdx.x]));
+  if (blockIdx.x == 0 && nvec * 4 + threadIdx.x < n) m0 = fmaxf(m0, fabsf(x[nvec * 4 + threadIdx.x]));      // n % 4 elements
   const float m = __uint_as_float(wave_max_u32(__float_as_uint(m0)));
   __shared__ float part[kThreads / kWave];
   const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
@@ -383,15 +377,15 @@ __device__ __forceinline__ int store4(uint8_t* dst, float4 v, float s, int lim, 
 // A work item is `per` fragments along K of a group of eight rows, kQuantFlight of them loaded at a time; the first item's
 // first loads go out before the partial maxima are asked for, so that the two round trips to memory are one.
 constexpr int kQuantFlight = 4;
-template <int BITS, Cols COLS, bool FROM_PARTIALS, int W>
+template <int BITS, Cols COLS, bool FROM_PARTIALS, int W, bool BY_XCD>
 __global__ __launch_bounds__(W * kWave) void k_quantize_pack(const float* __restrict__ x, size_t rows,
                                                             size_t cols, const float* __restrict__ scale,
                                                             uint8_t* __restrict__ packed, unsigned ksplit,
                                                             unsigned npartial, float* __restrict__ scale_out,
-                                                            unsigned* __restrict__ clear, unsigned nclear, unsigned by_xcd) {
+                                                            unsigned* __restrict__ clear, unsigned nclear) {
   constexpr unsigned kT = W * kWave;
-  // all arguments at once: the loop's condition would split their loads, a trip to memory each
-  asm volatile("" ::"s"(x), "s"(rows), "s"(cols), "s"(ksplit), "s"(by_xcd), "s"(gridDim.x));
+  // (all arguments at once: the loop's condition would split their loads, a trip to memory each)
+  if constexpr (BY_XCD) asm volatile("" ::"s"(x), "s"(rows), "s"(cols), "s"(ksplit), "s"(gridDim.x));
   // words a later kernel wants zero (spread over the grid: one workgroup walking through them is a serial tail)
   for (unsigned i = blockIdx.x * kT + threadIdx.x; i < nclear; i += gridDim.x * kT) clear[i] = 0u;
   const PackedDims d(BITS, rows, cols);
@@ -401,7 +395,7 @@ __global__ __launch_bounds__(W * kWave) void k_quantize_pack(const float* __rest
   // (indexes of fragments, row groups and items fit 32 bits: rows and columns are below 2^31, items below 2^29 x 16)
   const unsigned kfrags = (unsigned)d.kfrags, row_groups = (unsigned)(d.Np / 8);
   const unsigned wave_in = threadIdx.x / kWave;
-  const unsigned block = block_of(by_xcd), wave = block * W + wave_in;
+  const unsigned block = BY_XCD ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x, wave = block * W + wave_in;
   const unsigned nwaves = gridDim.x * W;
   const unsigned shift = 31 - __builtin_clz(ksplit);     // (a power of two)
   const unsigned per = (kfrags + ksplit - 1) >> shift;   // fragments along K per work item
@@ -637,18 +631,22 @@ int launch_pack(const float* x, size_t rows, size_t cols, int bits, const float*
   const Cols kind = cols_kind(cols);
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3(grid), dim3(sp.waves * kWave), 0, s, x, rows, cols, scale, static_cast<uint8_t*>(packed),
-                       sp.ksplit, npartial, scale_out, clear, nclear, by_xcd ? ~0u : 0u);
+                       sp.ksplit, npartial, scale_out, clear, nclear);
   };
-  auto by_kind = [&](auto bits_tag, auto waves_tag) {
+  auto by_kind = [&](auto bits_tag, auto waves_tag, auto xcd_tag) {
     constexpr int B = decltype(bits_tag)::value, W = decltype(waves_tag)::value;
-    if (kind == kColsVec) go(k_quantize_pack<B, kColsVec, FROM_PARTIALS, W>);
-    else if (kind == kColsAny) go(k_quantize_pack<B, kColsAny, FROM_PARTIALS, W>);
-    else if constexpr (W == 4) go(k_quantize_pack<B, kColsFew, FROM_PARTIALS, W>);      // (two fragments along K)
+    constexpr bool X = decltype(xcd_tag)::value;
+    if (kind == kColsVec) go(k_quantize_pack<B, kColsVec, FROM_PARTIALS, W, X>);
+    else if (kind == kColsAny) go(k_quantize_pack<B, kColsAny, FROM_PARTIALS, W, X>);
+    else if constexpr (W == 4) go(k_quantize_pack<B, kColsFew, FROM_PARTIALS, W, X>);      // (two fragments along K)
   };
-  if (bits == 8) by_kind(std::integral_constant<int, 8>{}, std::integral_constant<int, 4>{});
-  else if (sp.waves == 4) by_kind(std::integral_constant<int, 16>{}, std::integral_constant<int, 4>{});
-  else if (sp.waves == 8) by_kind(std::integral_constant<int, 16>{}, std::integral_constant<int, 8>{});
-  else by_kind(std::integral_constant<int, 16>{}, std::integral_constant<int, 16>{});
+  auto by_waves = [&](auto xcd_tag) {
+    if (bits == 8) by_kind(std::integral_constant<int, 8>{}, std::integral_constant<int, 4>{}, xcd_tag);
+    else if (sp.waves == 4) by_kind(std::integral_constant<int, 16>{}, std::integral_constant<int, 4>{}, xcd_tag);
+    else if (sp.waves == 8) by_kind(std::integral_constant<int, 16>{}, std::integral_constant<int, 8>{}, xcd_tag);
+    else by_kind(std::integral_constant<int, 16>{}, std::integral_constant<int, 16>{}, xcd_tag);
+  };
+  by_xcd ? by_waves(std::true_type{}) : by_waves(std::false_type{});
   return check_hip(hipGetLastError());
 }
 }  // namespace
@@ -754,8 +752,8 @@ namespace {
 unsigned launch_absmax_blocks(const float* x, size_t n, float* partials, unsigned* clear, unsigned nclear, bool by_xcd, hipStream_t s) {
   const unsigned g1 = grid_for(n, (size_t)kThreads * 8, kAbsmaxPartials);
   const size_t share = (n / 4 + g1 - 1) / g1;
-  hipLaunchKernelGGL(k_absmax_partial, dim3(g1), dim3(kThreads), 0, s, x, n, by_xcd ? share : (size_t)kThreads, by_xcd ? share : n,
-                     by_xcd ? (size_t)kThreads : (size_t)kThreads * g1, partials, clear, nclear, by_xcd ? ~0u : 0u);
+  auto kern = by_xcd ? k_absmax_partial<true> : k_absmax_partial<false>;
+  hipLaunchKernelGGL(kern, dim3(g1), dim3(kThreads), 0, s, x, n, partials, clear, nclear, share);
   return g1;
 }
 }  // namespace
