@@ -159,8 +159,6 @@ int launch_argmax_init(unsigned long long* keys, size_t M, hipStream_t s);
 int launch_argmax_finish(const unsigned long long* keys, size_t M, const float* sA, const float* sW,
                          int32_t* tok, float* maxlogit, hipStream_t s);
 
-// Whether a tensor of n elements is quantized in eighths of its rows, one to an XCD (launch_quantize_pack and behind abs-max).
-bool by_eighths(int bits, size_t n);
 constexpr unsigned kAbsmaxPartials = 1024;   // floats of scratch launch_absmax_quantize_pack needs
 int launch_absmax_quantize_pack(const float* x, size_t rows, size_t cols, int bits, float* partials,
                                 float* scale_out, void* packed, hipStream_t s, unsigned* clear = nullptr,

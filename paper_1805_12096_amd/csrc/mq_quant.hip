@@ -586,13 +586,23 @@ __global__ __launch_bounds__(512) void k_absmax_quantize_pack(const float* __res
 
 }  // namespace
 
-// What the launch before has read on the same XCD comes from its L2 (20 MB in 2.2 us instead of 4.4).  Abs-max, quantizer and
-// product in 8 bit: 8192 x 1024 x 1024 30.5 -> 28.5 us, 4000 x 512 x 2048 25.3 -> 23.7, in 16 bit 8192 x 512 x 512 23.0 -> 22.0.  16 bit above 48
-// MB, more than the L2s hold, keeps the other order (8192 x 1024 x 4096 165 us, in eighths 167), and so do inputs below 4 MB,
-// whose split-K products share rows between XCDs (8-bit block of 1001 rows, 512 / 2048, 17.7 and 17.9; first product of the 16-bit
-// block of 300 rows 6.6 and 7.4), and inputs some product has written, whose XCDs held columns as well (the 16-bit block of 3000
-// rows, 512 / 2048, 54.8 and 55.7).
+namespace {
+// Whether abs-max and the quantizer behind it take a tensor in eighths, one to an XCD: what the abs-max launch has read on the
+// same XCD then comes from its L2 (20 MB in 2.2 us instead of 4.4).  Captured calls of mq_linear_f32 with abs-max, 300 to 4096
+// columns in and out, 600 to 8192 rows, eighths against row groups that go round the XCDs (mean, least and largest ratio by
+// millions of 2^20 elements):
+//   8 bit   below 1  0.986 (0.956 - 1.015)   1 - 2  0.974 (0.942 - 1.008)   2 - 4  0.961 (0.934 - 0.994)   4 - 12  0.947 (0.912 -
+//           0.987)   12 - 16  0.985 (0.950 - 1.045)   above  0.994 (0.952 - 1.013)
+//   16 bit  below 1  0.994 (0.982 - 1.012)   1 - 2  0.982 (0.951 - 0.995)   2 - 4  0.971 (0.938 - 0.993)   4 - 12  0.970 (0.945 -
+//           0.994)   12 - 16  0.993 (0.969 - 1.023)   above  1.003 (0.995 - 1.013)
+// (8192 x 1024 x 1024 in 8 bit 30.5 -> 28.5 us, 8192 x 512 x 512 in 16 bit 23.0 -> 22.0).  Below a million the gain is small and the
+// first products of the blocks lose (8-bit block of 1001 rows, 512 / 2048, 17.7 and 17.9; first product of the 16-bit block of 300
+// rows 6.6 and 7.4).  The products behind it matter less: those that split K and share rows between XCDs gain as well.
+// Only behind an abs-max launch: with the multiplier given nobody has read the tensor before (106 calls a width of 1 to 14
+// million elements: 8 bit 0.998, 0.940 - 1.029, 16 bit 1.002, 0.981 - 1.014), and an input that some product has written lies on
+// the XCDs that held its columns (the 16-bit block of 3000 rows, 512 / 2048, 54.8 and 55.7).
 bool by_eighths(int bits, size_t n) { return n >= ((size_t)1 << 20) && (bits == 8 || n <= ((size_t)12 << 20)); }
+}  // namespace
 
 namespace {
 // How many waves share a row group along K and, for 16 bit, how many a workgroup has.  8 bit: split K so that even a 300-row
@@ -619,8 +629,7 @@ PackSplit pack_split(int bits, const PackedDims& d) {
 }
 
 // FROM_PARTIALS: `scale` holds `npartial` partial maxima and scale_out receives the multiplier (see the kernel).
-// by_xcd: rows go to the XCDs in eighths (by_eighths), as k_absmax_partial deals them and the products' bands of tiles expect
-// them; otherwise row groups go round the XCDs.
+// by_xcd: rows go to the XCDs in eighths (by_eighths), as k_absmax_partial has dealt them; otherwise row groups go round the XCDs.
 template <bool FROM_PARTIALS>
 int launch_pack(const float* x, size_t rows, size_t cols, int bits, const float* scale, unsigned npartial, float* scale_out,
                 void* packed, unsigned* clear, unsigned nclear, bool by_xcd, hipStream_t s) {
@@ -646,14 +655,15 @@ int launch_pack(const float* x, size_t rows, size_t cols, int bits, const float*
     else if (sp.waves == 8) by_kind(std::integral_constant<int, 16>{}, std::integral_constant<int, 8>{}, xcd_tag);
     else by_kind(std::integral_constant<int, 16>{}, std::integral_constant<int, 16>{}, xcd_tag);
   };
-  by_xcd ? by_waves(std::true_type{}) : by_waves(std::false_type{});
+  if constexpr (FROM_PARTIALS) by_xcd ? by_waves(std::true_type{}) : by_waves(std::false_type{});
+  else by_waves(std::false_type{});
   return check_hip(hipGetLastError());
 }
 }  // namespace
 
 int launch_quantize_pack(const float* x, size_t rows, size_t cols, int bits, const float* scale,
                          void* packed, hipStream_t s, unsigned* clear, unsigned nclear) {
-  return launch_pack<false>(x, rows, cols, bits, scale, 0u, nullptr, packed, clear, nclear, by_eighths(bits, rows * cols), s);
+  return launch_pack<false>(x, rows, cols, bits, scale, 0u, nullptr, packed, clear, nclear, false, s);
 }
 
 int launch_fill_pattern(void* p, size_t bytes, unsigned seed, hipStream_t s) {
@@ -765,8 +775,9 @@ int launch_absmax_partials(const float* x, size_t n, float* partials, unsigned* 
 int launch_absmax_quantize_pack(const float* x, size_t rows, size_t cols, int bits, float* partials,
                                 float* scale_out, void* packed, hipStream_t s, unsigned* clear, unsigned nclear) {
   const size_t n = rows * cols;
-  const unsigned g1 = launch_absmax_blocks(x, n, partials, clear, nclear, by_eighths(bits, n), s);
-  return launch_pack<true>(x, rows, cols, bits, partials, g1, scale_out, packed, nullptr, 0u, by_eighths(bits, n), s);
+  const bool by_xcd = by_eighths(bits, n);
+  const unsigned g1 = launch_absmax_blocks(x, n, partials, clear, nclear, by_xcd, s);
+  return launch_pack<true>(x, rows, cols, bits, partials, g1, scale_out, packed, nullptr, 0u, by_xcd, s);
 }
 
 }  // namespace mq

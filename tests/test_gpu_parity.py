@@ -750,6 +750,50 @@ def test_quantizers_at_row_ends(bits, rows, cols):
         check(packed, oq)
 
 
+@pytest.mark.parametrize("bits,rows,cols", [
+    # a million elements and its neighbour; elements that fill no vector of four; both sides of twelve million; rows shared by 16
+    # waves and by 4, short ones and ones of three elements in more items than the grid has waves
+    (8, 1024, 1024), (16, 1024, 1024), (8, 1023, 1025), (16, 1023, 1025), (8, 2049, 2047), (16, 2049, 2047), (8, 6148, 2047),
+    (16, 6147, 2047), (16, 6148, 2047), (16, 515, 4099), (8, 270001, 5), (16, 270001, 5), (8, 350003, 3), (16, 350003, 3)])
+def test_absmax_and_quantizer_of_large_tensors(bits, rows, cols):
+    # Two launches, the tensor dealt to the XCDs in runs of one workgroup: the largest magnitude in turn at the ends of the tensor,
+    # of runs and of what fills no vector; the multiplier and, against the quantizer that is given it, every byte.
+    n = rows * cols
+    blocks = min((n + 2047) // 2048, 1024)
+    run = (n // 4 + blocks - 1) // blocks * 4
+    last = n // 4 * 4 // run * run
+    x = np.random.default_rng(n + bits).standard_normal((rows, cols), dtype=np.float32).clip(-4, 4)
+    xd, nb = dev(x), mq.mq_quantize_absmax_ws_bytes()
+    flat = xd.view(-1)
+    ws = torch.full((nb,), 0x6D, dtype=torch.uint8, device=DEV)
+    got = torch.empty(mq.mq_packed_bytes(bits, rows, cols), dtype=torch.uint8, device=DEV)
+    s, want = torch.empty(1, dtype=torch.float32, device=DEV), torch.empty_like(got)
+    given = torch.full((1,), np.float32(127 if bits == 8 else 32767) / np.float32(9.5), dtype=torch.float32, device=DEV)
+    try:
+        mq.mq_set_quantize_single_pass(0)
+        for at in sorted({0, 3, run - 1, run, blocks // 2 * run - 1, blocks // 2 * run, last - 1, last, n // 4 * 4 - 1, n // 4 * 4, n - 1}):
+            if not 0 <= at < n:
+                continue
+            was = flat[at].clone()
+            flat[at] = -9.5
+            got.fill_(0x5A)
+            mq.mq_quantize_absmax_pack_f32(xd, rows, cols, bits, got, s, ws, nb)
+            mq.mq_quantize_pack_f32(xd, rows, cols, bits, given, want)
+            assert torch.equal(s, given), at
+            assert torch.equal(got, want), at
+            flat[at] = was
+        mq.mq_quantize_absmax_pack_f32(xd, rows, cols, bits, got, s, ws, nb)
+    finally:
+        mq.mq_set_quantize_single_pass(1)
+    oq, os_ = oracle.quant_int_absmax(x, bits)
+    q = torch.empty((rows, cols), dtype=QT[bits], device=DEV)
+    mq.mq_unpack_weight(got, bits, rows, cols, q)
+    assert host(s)[0] == os_ and np.array_equal(host(q), oq)
+    if bits == 16:
+        sums = host(got)[-4 * ((rows + 31) // 32 * 32):].view(np.int32)
+        assert np.array_equal(sums[:rows], oq.sum(1, dtype=np.int32)) and not sums[rows:].any()
+
+
 @pytest.mark.parametrize("rows", [1017, 1025, 2048, 2049])
 @pytest.mark.parametrize("cols", [2047, 2052])
 def test_quantize_pack_16_bit_waves_per_row_group(rows, cols):
