@@ -791,11 +791,10 @@ int mq_ffn_i16_f32(const float* A, size_t M, size_t d, size_t f, const void* pac
   // otherwise two passes (partial maxima, then the quantizer), the first of which zeroes max|H|.
   unsigned* bar = reinterpret_cast<unsigned*>(base + L.off_bar);
   static_assert(sizeof(float) * 3 <= 256, "max|H| sits right in front of the agreement words");
-  // Few rows: quant_int(A) in the first product's operand fetch (unless the caller has forced or tuned a packed product); its
-  // workgroups' maxima of H go where the packed A would be.
-  const size_t wg = gemm_small_f32_partials(16, M, f, d);
-  const bool in_fetch = gemm_small_f32_supported(16, M, f, d) && !variant_named(16, M, f, d) && wg <= kAbsmaxPartials &&
-                        wg * sizeof(float) <= L.off_H - L.off_qA && !overlap(A, M * d, static_cast<const float*>(ws), L.total / 4);
+  // Few rows: quant_int(A) in the first product's operand fetch (unless the caller has forced or tuned a packed product); the
+  // maxima of H, one from each of its workgroups, of which there are at most 512, go where the packed A would be (4 KB or more).
+  const bool in_fetch = gemm_small_f32_supported(16, M, f, d) && !variant_named(16, M, f, d) &&
+                        !overlap(A, M * d, static_cast<const float*>(ws), L.total / 4);
   GemmArgs g1{};
   g1.packedW = packedW1; g1.bits = 16; g1.M = M; g1.N = f; g1.K = d;
   g1.sW = sW1; g1.bias = b1; g1.relu = 1; g1.Y = H;
@@ -807,7 +806,7 @@ int mq_ffn_i16_f32(const float* A, size_t M, size_t d, size_t f, const void* pac
     g1.partial = reinterpret_cast<float*>(qA);
     rc = launch_gemm_small_f32(A, part, np, nullptr, g1, s);
     if (rc != MQ_OK) return rc;
-    rc = launch_quantize_pack_partials(H, M, f, 16, g1.partial, (unsigned)wg, sH, qH, s);
+    rc = launch_quantize_pack_partials(H, M, f, 16, g1.partial, (unsigned)gemm_small_f32_partials(16, M, f, d), sH, qH, s);
     return rc != MQ_OK ? rc : second();
   }
   if (g_ffn_single_pass && M * d >= ((size_t)1 << 20)) {

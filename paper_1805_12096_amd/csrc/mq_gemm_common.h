@@ -19,7 +19,6 @@ struct Params {
   const uint8_t* packedW;
   unsigned M, N, K;
   unsigned tiles_m, tiles_n;
-  unsigned band;            // tile rows of a band, see tile_at (packed kernel only)
   int32_t* C;
   const float* sA;
   const float* sW;

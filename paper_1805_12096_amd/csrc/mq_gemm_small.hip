@@ -876,7 +876,7 @@ struct SmallF32Shape {
 };
 SmallF32Shape small_f32_shape(int bits, size_t M, size_t N, size_t K) {
   auto workgroups = [&](size_t blocks) { return row_blocks(M) * ((column_blocks(N) + blocks - 1) / blocks); };
-  if (bits == 16) return {K <= 512 || workgroups(1) <= kCUs ? 1 : 2, K <= 512 ? 4 : 8};
+  if (bits == 16) return K <= 512 ? SmallF32Shape{1, 4} : SmallF32Shape{workgroups(1) <= kCUs ? 1 : 2, 8};
   if (K <= 512) {
     if (workgroups(2) < 160) return {1, 4};
     return {workgroups(2) > kCUs && workgroups(3) <= kCUs ? 3 : 2, 4};
@@ -969,7 +969,8 @@ int launch_gemm_small_requant_agree(const GemmArgs& a, hipStream_t s) {
 // 512 x 512 10.7 and 9.6; 640 workgroups, 300 x 2048 x 512, 11.3 and 11.5; 1008, 2000 x 512 x 512, 13.4 and 14.6); K up to 1024 in
 // one round of up to two column blocks (500 x 1024 x 1024 12.6 and 10.8; 480 of them, 300 x 3072 x 1024, 16.0 and 16.1); K up to
 // 2048 in one round of one (300 x 512 x 2048 12.8 and 11.5; two blocks, 600 x 512 x 2048, with the multiplier given 12.6 and
-// 12.7).  K = 4096 with the multiplier given: 12.7 and 14.0.
+// 12.7).  K = 4096 with the multiplier given: 12.7 and 14.0.  max|y| in one word draws no line of its own: it adds 0.2 us with 512
+// workgroups as with 96 (1000 x 512 x 512 9.3 and 9.5 us, 10.7 and 11.0 in three launches; 500 x 1024 x 256 7.8 and 8.1, 9.8 and 13.2).
 bool gemm_small_f32_supported(int bits, size_t M, size_t N, size_t K) {
   if (bits == 16) {
     if (M < 1 || N < 1 || K < 32 || K % 32 != 0 || K > 2048) return false;
@@ -991,7 +992,7 @@ int launch_small_f32_any(SmallF32Params p, const GemmArgs& a, hipStream_t s) {
   p.partial_out = a.partial;
   const SmallF32Shape shape = small_f32_shape(a.bits, a.M, a.N, a.K);
   if (a.bits == 16) {
-    if (shape.waves == 4) return shape.blocks == 1 ? launch_small_f32<16, 1, 4>(p, s) : launch_small_f32<16, 2, 4>(p, s);
+    if (shape.waves == 4) return launch_small_f32<16, 1, 4>(p, s);
     return shape.blocks == 1 ? launch_small_f32<16, 1, 8>(p, s) : launch_small_f32<16, 2, 8>(p, s);
   }
   if (shape.waves == 4) {
