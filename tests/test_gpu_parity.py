@@ -1321,11 +1321,12 @@ def test_ffn_single_pass_and_two_pass_agree_with_oracle(M, d, f):
         mq.mq_set_ffn_single_pass(1)
 
 
-@pytest.mark.parametrize("bits,M,d,f", [(16, 70, 64, 600), (8, 700, 128, 600)])
+@pytest.mark.parametrize("bits,M,d,f", [(16, 70, 64, 600), (16, 70, 68, 600), (8, 700, 128, 600)])
 def test_a_variant_named_by_another_thread_changes_no_result(bits, M, d, f):
     # Calls in which more than one launch depends on the product's configuration, while another thread forces one and takes it
     # back: who leaves the maxima of the intermediate (16 bit: the split-K kernel one a workgroup, the tiles in words of their
-    # own) and how many there are (8 bit in two passes: one a tile) is settled once.
+    # own; widths that are no multiple of 32, as others may quantize in the product's operand fetch and then look at no
+    # configuration again) and how many there are (8 bit in two passes: one a tile) is settled once.
     import threading
     c = workloads.ffn(2 if bits == 8 else 4, M, d, f, 0.04, bits, seed_extra=M + f)
     W1, W2 = (mq.prepare_weight(dev(c[n]), bits) for n in ("W1t", "W2t"))
@@ -1377,6 +1378,39 @@ def test_ffn_int16_one_call_matches_oracle_chain(M, d, f):
         mq.mq_ffn_i16_f32(A, M, d, f, p1.packed, p1.scale, dev(c["b1"]), p2.packed, p2.scale, dev(c["b2"]), Y, ws,
                           nbytes)
         assert np.array_equal(host(Y), o2["Y"])
+
+
+@pytest.mark.parametrize("M,d,f,count", [
+    # quant_int in the first product's operand fetch (22 x 10 workgroups of the 256 allowed in the third); widths and numbers of
+    # workgroups (29 x 10) that refuse it; of these, inputs of a million elements that one kernel quantizes (the last two: ragged
+    # rows and columns)
+    (37, 64, 200, 4), (70, 64, 600, 4), (300, 256, 520, 4), (700, 1024, 600, 4), (37, 68, 200, 5), (70, 68, 600, 5), (300, 260, 520, 5),
+    (900, 1024, 600, 5), (1100, 500, 700, 5), (2100, 520, 96, 5), (3001, 512, 2048, 5)])
+def test_ffn_int16_launches_and_oracle_chain(M, d, f, count):
+    # which launches a call takes, with and without the kernels that wait, and the oracle's bits either way
+    c = workloads.ffn(4, M, d, f, 0.03, 16, seed_extra=M + d + 3 * f)
+    o1 = oracle.linear(c["A"], c["W1t"], 16, c["b1"], True)
+    s2 = oracle.scale_from_amax(oracle.absmax(o1["Y"]), 16)
+    o2 = oracle.linear(o1["Y"], c["W2t"], 16, c["b2"], False, sA=s2)
+    A, b1, b2 = dev(c["A"]), dev(c["b1"]), dev(c["b2"])
+    p1, p2 = (mq.prepare_weight(dev(c[n]), 16) for n in ("W1t", "W2t"))
+    nb = mq.mq_ffn_i16_ws_bytes(M, d, f)
+    ws, Y = torch.full((nb,), 0x3C, dtype=torch.uint8, device=DEV), torch.empty((M, d), dtype=torch.float32, device=DEV)
+
+    def call(stream):
+        mq.mq_ffn_i16_f32(A, M, d, f, p1.packed, p1.scale, b1, p2.packed, p2.scale, b2, Y, ws, nb, stream)
+
+    absmax = min((M * d + 2047) // 2048, 1024)         # workgroups of an abs-max launch; the other first launch clears a few words
+    try:
+        for single in (1, 0):
+            mq.mq_set_ffn_single_pass(single)
+            Y.fill_(-3.0)
+            grids = launched_grids(call)
+            assert len(grids) == count
+            assert (grids[0][0] != absmax) == (count == 5 and single == 1 and M * d >= 2 ** 20)
+            assert np.array_equal(host(Y), o2["Y"])
+    finally:
+        mq.mq_set_ffn_single_pass(1)
 
 
 def test_ffn_fused_full_size_equals_oracle_on_all_rows():
