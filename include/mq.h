@@ -404,8 +404,10 @@ size_t mq_linear_ws_bytes(int bits, size_t M, size_t K);
  * sA_or_null is not NULL), dot'_int, dequantize + bias (+ReLU), with the results
  * of mq_quantize_f32 + mq_gemm_dequant bit for bit.  Three launches on `stream`
  * with abs-max, two with a given multiplier; for 8-bit products with at most
- * 512 rows and K a multiple of 32 up to 1024 (a decode step) quant_int runs
- * inside the product kernel: two and one.  Up to 32 rows with K a multiple of 4
+ * 512 rows and K a multiple of 32 up to 1024 (a decode step), and for 16-bit
+ * ones with K a multiple of 32 up to 2048 whose result is at most 512 blocks
+ * of 32 x 32 (K above 512: 256 workgroups, above 1024 of one block each),
+ * quant_int runs inside the product kernel: two and one.  Up to 32 rows with K a multiple of 4
  * up to 2048 (8 bit and at most 16 rows: 4096) everything is ONE launch, with a
  * given multiplier only where that is the faster form; a shape that
  * mq_autotune_gemm or mq_set_gemm_variant has named a packed product for takes
@@ -469,7 +471,8 @@ int mq_ffn_i8_f32_prepared(const float* A, size_t M, size_t d, size_t f, const v
  * b1 + ReLU into a binary32 H kept in ws with max|H| as a by-product of the
  * epilogue, quant_int(H) straight into the packed layout with the multiplier
  * formed in that kernel, second product + b2.  (The input is read once where
- * it fits the one-kernel quantizer, see "Single-pass kernels" at the top.)  Five launches, no host
+ * it fits the one-kernel quantizer, see "Single-pass kernels" at the top.)  Five launches, four where
+ * the first product is within mq_linear_f32's limits for quant_int inside a 16-bit product; no host
  * synchronisation; packedW1 / packedW2 from mq_prepare_weight(bits = 16).
  * Results are identical to the call-by-call chain.  Arguments as
  * mq_ffn_i8_f32; ws: mq_ffn_i16_ws_bytes(M, d, f) bytes (it holds H). */

@@ -14,8 +14,8 @@
 //     plain per-lane registers and nothing crosses lanes until the very end;
 //   * the quantized hidden states (M x K, a few 100 KB) are loaded once per
 //     workgroup into REGISTERS as operand fragments, split over the eight waves
-//     by 16-sentence tile; more sentences than that go in chunks (the grid's y
-//     index) that share the compute units;
+//     by 16-sentence tile; more sentences than that go in chunks (of one launch,
+//     see chunk_of) that share the compute units;
 //   * the packed embedding streams through LDS with direct-to-LDS loads: each
 //     load instruction gathers, for one 64-element K group, the 16 rows of the
 //     unit out of two 32-row fragments, so that LDS receives exactly the
@@ -147,7 +147,8 @@ __device__ __forceinline__ void merge_sorted(unsigned long long (&top)[BEAM], co
 // 1200 rows, k = 4, 36 000 words, with the quantizer and the reduce kernel: 84.7 us with maximum / minimum pairs, a
 // rescaled sum and every chunk of 256 rows spread over all compute units; 52.3 us with the above and the chunks sharing
 // them (launch_topk_stream); 48.3 us with sorted lists merged instead of inserted one by one at the end (42 with what follows below).  240 rows:
-// 29.1 -> 26.2 us.  What is left per unit: 0.27 us of LDS reads and waits, 0.13 of matrix instructions, 0.21 of these.
+// 29.1 -> 26.2 us.  A unit then was 0.27 us of LDS reads and waits, 0.13 of matrix instructions and 0.21 of these; the refill below
+// took 6 us off the 45 units of a workgroup (1200 rows, k = 4, this kernel in the trace 42.4 -> 36.3 us).
 // Greedy, 36 000 words, kernels of a captured step (quantizer included): 300 sentences of width 512 17.6 -> 16.9 us (the
 // 19th of 24 tile slots' operands no longer fetched for nothing, reduce kernel), 600 sentences against 50 000 words 34.8
 // -> 24.9 us (chunks that share the compute units instead of one launch pair after the other), 300 sentences of width
@@ -861,11 +862,12 @@ bool argmax_stream_rows_supported(size_t N, size_t K) {
 // Plain rows: the streaming kernel or the tiled product with the arg-max in its epilogue.  The tiled one multiplies 128 x 128
 // tiles and wins where the matrix instructions are few (narrow widths, which the streaming kernel multiplies as 512 or 1024
 // elements all the same) or the rows many against the words; one atomic maximum per row and 128 words holds it back.  In
-// microseconds, kernels alone, fitted to 1771 timed calls (widths 16 to 1024, 300 to 50 000 words, 1 to 16 384 rows,
-// profiles/output_layer_form_timings.csv; 5 - 7 % off on average): choosing by these is 0.4 % slower than the faster form
-// of each call on average, at worst 29 %, and on 1944 others (200 to 80 000 words) never more than 14 % slower than the
-// tiled product; always streaming 6.7 % (8192 rows, width 128, 2500 words 20.1 for 14.8 us), never
-// streaming 14 % (300 rows, width 1024, 36 000 words 35.6 for 22.8 us).
+// microseconds, kernels alone, fitted to 1771 timed calls (widths 16 to 1024, 300 to 50 000 words, 1 to 16 384 rows;
+// 5 - 7 % off on average).  They were fitted to the streaming kernel before its refilling stages became up to 18 % faster.  With the
+// present one, on the same calls (profiles/output_layer_form_timings.csv): choosing by these is 0.8 % slower than the faster form
+// of each call on average, at worst 47 % (width 528, where the tiled product keeps 300 rows against 36 000 words, 26.8 for 18.2 us),
+// and on 600 others (200 to 80 000 words) 0.7 %, never more than 12 % slower than the tiled product; always streaming 5.0 %, never
+// streaming 17 %.
 bool argmax_stream_rows_ahead(size_t M, size_t N, size_t K) {
   const bool wide = K > 64 * kKG;
   const float k = (float)((K + 63) / 64);
@@ -1008,6 +1010,8 @@ int launch_topk_stream(const void* packedA, const void* packedW, size_t M, size_
   // Rows go up to 256 (two sentence tiles per wave) to a workgroup; all chunks run in ONE launch that shares the compute units (cut_stream), and one
   // reduce launch follows for all rows: a launch per chunk (ten for 1200 rows) cost more than the chunks' work.
   const StreamCut c = cut_stream(M, units, (size_t)kWaves * 16 * kBeamTPW, max_units_of(kKG));
+  // (65535 chunks: what chunk_of's reciprocals are good for.  The workgroups stay far below what a launch holds, 2^32 threads: the
+  // entry point takes 2^40 logits at most, which are 1.1 million workgroups of 256 rows and 255 units.)
   if (c.chunks > 65535u || (units + c.columns - 1) / c.columns > max_units_of(kKG)) return MQ_ERR_UNSUPPORTED;
   ArgmaxParams p{};
   p.packedA = static_cast<const uint8_t*>(packedA);
