@@ -754,10 +754,6 @@ int launch_absmax_quantize_pack_fused(const float* x, size_t rows, size_t cols, 
   return bits == 8 ? go(std::integral_constant<int, 8>{}) : go(std::integral_constant<int, 16>{});
 }
 
-// abs-max + quant_int into the packed layout in two launches, no atomics, no fill:
-// partial maxima to `partials` (kAbsmaxPartials floats), then quantization with the multiplier
-// formed from them; scale_out[0] receives the multiplier.
-// Partial maxima of |x| only (at most kAbsmaxPartials of them); *count receives how many were written.
 namespace {
 unsigned launch_absmax_blocks(const float* x, size_t n, float* partials, unsigned* clear, unsigned nclear, bool by_xcd, hipStream_t s) {
   const unsigned g1 = grid_for(n, (size_t)kThreads * 8, kAbsmaxPartials);
@@ -767,11 +763,15 @@ unsigned launch_absmax_blocks(const float* x, size_t n, float* partials, unsigne
   return g1;
 }
 }  // namespace
+// Partial maxima of |x| only (at most kAbsmaxPartials of them); *count receives how many were written.
 int launch_absmax_partials(const float* x, size_t n, float* partials, unsigned* count, hipStream_t s) {
   *count = launch_absmax_blocks(x, n, partials, nullptr, 0u, false, s);
   return check_hip(hipGetLastError());
 }
 
+// abs-max + quant_int into the packed layout in two launches, no atomics, no fill:
+// partial maxima to `partials` (kAbsmaxPartials floats), then quantization with the multiplier
+// formed from them; scale_out[0] receives the multiplier.
 int launch_absmax_quantize_pack(const float* x, size_t rows, size_t cols, int bits, float* partials,
                                 float* scale_out, void* packed, hipStream_t s, unsigned* clear, unsigned nclear) {
   const size_t n = rows * cols;
